@@ -345,6 +345,7 @@ struct State {
                                 // (IMM: of the previous odd stage)
   uint32_t pw0[QB][16];         // IMM only: P~^T of the previous even stage
   float m_run[QB], l_run[QB], mloc_tile[QB];
+  float mc_ref[QB];  // reference of the exponentials, times c: P~ = exp2(S c - mc_ref); trails m_run c by < kLazyLog2
   // IMM only: row sum of the tile in flight (added to l_run once the tile is known not to have fired), and the
   // rescale factor of the previous stage, which O^T has not seen yet because its PV product runs a stage later
   float l_pend[QB], alpha_prev[QB];
@@ -475,6 +476,7 @@ __device__ __forceinline__ bf16x8 load_frag(int k, const uint32_t (&kread)[8], c
   return *reinterpret_cast<LA_LDS const bf16x8*>(vread[cc] + (uint32_t)(kV + 4096 * db));
 }
 
+constexpr float kLazyLog2 = 8.f;
 constexpr int kPrefetch = 3;  // LDS fragments in flight ahead of the MFMA that consumes them
 constexpr int kDmaGap = 2;    // steps between two DMA issues of a stage
 
@@ -521,7 +523,9 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
   for (int k = 0; k < kPrefetch; ++k)
     if (!IMM || pv_on) frag[k] = load_frag<kKSrc, kVSrc>(k, ln.kread, ln.vread);
 
-  float pm[QB][4], mx[QB], m_new[QB], mc[QB], alpha[QB], lsum[QB], ta0[QB], ta1[QB], tb0[QB];
+  float pm[QB][4], mx[QB], alpha[QB], ta0[QB], ta1[QB], tb0[QB];
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) alpha[qb] = 1.f;
   bool ok = true, grew = false;
   // The ragged last tile of the sequence: its columns past the end leave the row maxima and sums (one scalar compare
   // and branch per stage, taken for one tile per row at most).  This lane's element r of block blk is column
@@ -582,6 +586,7 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
   auto vector_part = [&](auto kc, auto qbc) __attribute__((always_inline)) {
     constexpr int k = decltype(kc)::value;
     constexpr int qb = decltype(qbc)::value;
+    float& lsum = IMM ? st.l_pend[qb] : st.l_run[qb];  // the row sum this stage adds to
     // ---- vector ALU: slice k of the online softmax of stage s (raw dot products; 1/sqrt(d) folded into c) ----
     {
       if (k < 4) {  // m_local: partial row maxima over 8 of this lane's 32 scores
@@ -594,46 +599,45 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
         mx[qb] = other_half_max(fmaxf(fmaxf(pm[qb][0], pm[qb][1]), fmaxf(pm[qb][2], pm[qb][3])));
       } else if (k == 5) {  // m_ij = max(m_{i,j-1}, m_local) and the rescale factor of the earlier stages
         st.mloc_tile[qb] = H ? fmaxf(st.mloc_tile[qb], mx[qb]) : mx[qb];
-        m_new[qb] = fmaxf(st.m_run[qb], mx[qb]);
-        alpha[qb] = __builtin_amdgcn_exp2f((st.m_run[qb] - m_new[qb]) * ln.c);
-        grew = grew || (m_new[qb] > st.m_run[qb]);
-        st.m_run[qb] = m_new[qb];
-        mc[qb] = m_new[qb] * ln.c;
-        lsum[qb] = 0.f;
+        st.m_run[qb] = fmaxf(st.m_run[qb], mx[qb]);
+        // the exponent's reference follows the maximum only when some row of the wave has outgrown it by kLazyLog2
+        const float up = st.m_run[qb] * ln.c;
+        if (__any(up > st.mc_ref[qb] + kLazyLog2)) {
+          alpha[qb] = __builtin_amdgcn_exp2f(st.mc_ref[qb] - up);
+          st.l_run[qb] *= alpha[qb];
+          if (IMM && H) st.l_pend[qb] *= alpha[qb];
+          st.mc_ref[qb] = up;
+          grew = true;
+        }
+        if (IMM && !H) st.l_pend[qb] = 0.f;
       } else if (k < 30) {
         // P~ = exp(S - m_ij), packed to bf16: 16 pairs of scores over 24 steps, four vector instructions per step
         // (a cycle of three steps does two pairs: exp exp | pack+sum, exp | exp, pack+sum)
         const int t = k - 6, c = t / 3, ph = t % 3;
         const int eA = 2 * c, eB = 2 * c + 1;
         if (ph == 0) {
-          ta0[qb] = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[qb][eA >> 3][2 * (eA & 7)], ln.c, -mc[qb]));
-          ta1[qb] = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[qb][eA >> 3][2 * (eA & 7) + 1], ln.c, -mc[qb]));
+          ta0[qb] = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[qb][eA >> 3][2 * (eA & 7)], ln.c, -st.mc_ref[qb]));
+          ta1[qb] = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[qb][eA >> 3][2 * (eA & 7) + 1], ln.c, -st.mc_ref[qb]));
           // empty volatile asms pin every slice to its step: without them the compiler sinks all the exponentials
           // behind the last MFMA, where nothing overlaps them
           asm volatile("" : "+v"(ta0[qb]), "+v"(ta1[qb]));
         } else if (ph == 1) {
           uint32_t w = pack_bf16x2(ta0[qb], ta1[qb]);
           // the row sum adds the bf16-rounded weights, the same values the PV product uses
-          lsum[qb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, lsum[qb], false);
-          tb0[qb] = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[qb][eB >> 3][2 * (eB & 7)], ln.c, -mc[qb]));
-          asm volatile("" : "+v"(w), "+v"(lsum[qb]), "+v"(tb0[qb]));
+          lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, lsum, false);
+          tb0[qb] = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[qb][eB >> 3][2 * (eB & 7)], ln.c, -st.mc_ref[qb]));
+          asm volatile("" : "+v"(w), "+v"(lsum), "+v"(tb0[qb]));
           pwc[qb][eA] = w;  // word e belongs to chunk e/4, whose last reader was the MFMA of step 4*(e/4)+3 < k
         } else {
-          const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[qb][eB >> 3][2 * (eB & 7) + 1], ln.c, -mc[qb]));
+          const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[qb][eB >> 3][2 * (eB & 7) + 1], ln.c, -st.mc_ref[qb]));
           uint32_t w = pack_bf16x2(tb0[qb], p1);
-          lsum[qb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, lsum[qb], false);
-          asm volatile("" : "+v"(w), "+v"(lsum[qb]));
+          lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, lsum, false);
+          asm volatile("" : "+v"(w), "+v"(lsum));
           pwc[qb][eB] = w;
         }
       } else if (k == 30) {
-        if (IMM) {
-          st.l_run[qb] *= alpha[qb];
-          st.l_pend[qb] = H ? st.l_pend[qb] * alpha[qb] + lsum[qb] : lsum[qb];
-        } else {
-          st.l_run[qb] = st.l_run[qb] * alpha[qb] + lsum[qb];
-        }
         if (H) {  // skip predicate of the whole 128-column tile, once its second half is in (eq. sparge_cond)
-          const float g = (st.mloc_tile[qb] - m_new[qb]) * ln.scale;  // this row; max over rows = ballot below
+          const float g = (st.mloc_tile[qb] - st.m_run[qb]) * ln.scale;  // this row; max over rows = ballot below
           ok = ok && (!ln.qvalid[qb] || (g <= ln.thr));
         }
       }
@@ -658,7 +662,7 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
   // O^T of the earlier stages is rescaled after this stage's PV MFMAs (rare once the running max has settled).
   // IMM: O^T now holds the products up to stage s-2 and moves to the reference maximum of stage s-1, whose product
   // the next stage adds; this stage's own factor waits one stage.
-  if (IMM ? st.grew_prev : (bool)__any(grew)) {
+  if (IMM ? st.grew_prev : grew) {
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
@@ -667,7 +671,7 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
         for (int r = 0; r < 16; ++r) st.oacc[qb][db][r] *= IMM ? st.alpha_prev[qb] : alpha[qb];
   }
   if (IMM) {
-    st.grew_prev = __any(grew);
+    st.grew_prev = grew;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) st.alpha_prev[qb] = alpha[qb];
   }
@@ -762,6 +766,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
 #pragma unroll
     for (int e = 0; e < 16; ++e) st.pw[qb][e] = 0u;
     st.m_run[qb] = -INFINITY;  // running row max of the raw dot products (m_{i,j-1} * sqrt(d))
+    st.mc_ref[qb] = -INFINITY;
     st.l_run[qb] = 0.f;        // this lane's half of the row sum
     st.mloc_tile[qb] = -INFINITY;
   }
