@@ -71,7 +71,8 @@ typedef struct {
 
 /* Opaque handle: owns the device Skip-Mask ([B,H,Tq,ceil(Tk/64)] uint64, bit j%64 of word j/64 set = tile (i,j)
    skipped) and the statistics, and owns or borrows (lite_attn_init_mask_shared) the per-call scratch: Skip-List
-   buffers and a copy of V^T (same size as V).
+   buffers and a copy of V^T (same size as V) or, for layers of at most 512 Q-tile rows, partial results (at most
+   104 MiB).
    Tq = ceil(N/tile_q), Tk = ceil(N/tile_k). */
 typedef struct lite_attn_mask lite_attn_mask_t;
 

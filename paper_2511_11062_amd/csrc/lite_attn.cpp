@@ -52,49 +52,68 @@ int hip_fail(hipError_t e) {
   return e == hipErrorOutOfMemory ? LITE_ATTN_ENOMEM : LITE_ATTN_EHIP;
 }
 
-hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListLayout& ll, char* lists, uint16_t* vt,
-                       const void* q, const void* k, const void* v, void* out, uint64_t* bits,
-                       unsigned long long* stats3, float threshold, bool lists_ready, bool build_next,
-                       hipStream_t stream, hipEvent_t mid) {
+hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListLayout& ll, char* lists, char* scratch,
+                       const CallArgs& a, hipStream_t stream, hipEvent_t mid) {
   uint32_t* runs = reinterpret_cast<uint32_t*>(lists + ll.runs);
   uint32_t* nruns = reinterpret_cast<uint32_t*>(lists + ll.nruns);
   uint32_t* live_cnt = reinterpret_cast<uint32_t*>(lists + ll.live_cnt);
-  uint32_t* order = reinterpret_cast<uint32_t*>(lists + ll.order);
-  uint32_t* chunk_work = reinterpret_cast<uint32_t*>(lists + ll.chunk_work);
   uint32_t* slots = reinterpret_cast<uint32_t*>(lists + ll.slots);
   uint32_t* xcd_rows = reinterpret_cast<uint32_t*>(lists + ll.xcd_rows);
+  uint16_t* vt = reinterpret_cast<uint16_t*>(scratch);
   const int diagonal_first = (d.flags & LITE_ATTN_ORDER_DIAGONAL_FIRST) ? 1 : 0;
+  const bool few = g.nseg > 0;
   hipError_t e = hipSuccess;
-  if (!lists_ready) {
-    e = launch_compact(bits, (int)g.rows, g.Tq, g.Tk, g.W, diagonal_first, g.run_stride, runs, nruns, live_cnt, stream);
+  if (a.fresh && g.nseg <= 1)  // (with segments, the fused kernel clears the counters and the merge pass the mask)
+    e = launch_clear(a.bits, few ? 0 : (size_t)g.rows * g.W, a.stats_all, a.stat_words, stream);
+  if (e != hipSuccess) return e;
+  if (!few) {
+    uint32_t* order = reinterpret_cast<uint32_t*>(lists + ll.order);
+    uint32_t* chunk_work = reinterpret_cast<uint32_t*>(lists + ll.chunk_work);
+    if (!a.lists_ready) {
+      e = launch_compact(a.bits, (int)g.rows, g.Tq, g.Tk, g.W, diagonal_first, g.run_stride, runs, nruns, live_cnt,
+                         stream);
+      if (e != hipSuccess) return e;
+    }
+    // ranking a head's rows needs the counts of all of them, dealing the ranked chunks to the XCDs those of all heads:
+    // two small kernels of their own
+    e = launch_order_rows(live_cnt, g.BH, g.Tq, g.Tk, order, chunk_work, stream);
+    if (e != hipSuccess) return e;
+    e = launch_deal_rows(chunk_work, order, g.BH, g.Tq, g.chunks, g.per_xcd, slots, xcd_rows, stream);
+    if (e != hipSuccess) return e;
+    e = launch_transpose_v(static_cast<const uint16_t*>(a.v), vt, d.stride_b, d.stride_h, d.stride_n, g.BH, d.heads,
+                           d.seqlen, g.Tk, stream);
     if (e != hipSuccess) return e;
   }
-  // ranking a head's rows needs the counts of all of them, dealing the ranked chunks to the XCDs those of all heads:
-  // two small kernels of their own
-  e = launch_order_rows(live_cnt, g.BH, g.Tq, g.Tk, order, chunk_work, stream);
-  if (e != hipSuccess) return e;
-  e = launch_deal_rows(chunk_work, order, g.BH, g.Tq, g.chunks, g.per_xcd, slots, xcd_rows, stream);
-  if (e != hipSuccess) return e;
-  e = launch_transpose_v(static_cast<const uint16_t*>(v), vt, d.stride_b, d.stride_h, d.stride_n, g.BH, d.heads,
-                         d.seqlen, g.Tk, stream);
-  if (e != hipSuccess) return e;
   FwdParams p;
-  p.q = static_cast<const uint16_t*>(q);
-  p.k = static_cast<const uint16_t*>(k);
+  p.q = static_cast<const uint16_t*>(a.q);
+  p.k = static_cast<const uint16_t*>(a.k);
   p.vt = vt;
-  p.out = static_cast<uint16_t*>(out);
+  p.out = static_cast<uint16_t*>(a.out);
   p.stride_b = d.stride_b; p.stride_h = d.stride_h; p.stride_n = d.stride_n;
   p.H = d.heads; p.N = d.seqlen; p.Tq = g.Tq; p.Tk = g.Tk; p.W = g.W;
   p.runs = runs; p.run_stride = g.run_stride; p.nruns = nruns; p.live_cnt = live_cnt;
-  p.bits = bits;
-  p.stat_skipped_in = stats3; p.stat_newly = stats3 + 1; p.stat_runs = stats3 + 2;
-  p.thr = threshold;
+  p.bits = a.bits;
+  p.stat_skipped_in = a.stats3;
+  p.stat_newly = a.stats3 ? a.stats3 + 1 : nullptr;
+  p.stat_runs = a.stats3 ? a.stats3 + 2 : nullptr;
+  p.thr = a.threshold;
   p.scale = 1.0f / std::sqrt((float)d.head_dim);
   p.protect_start = d.protect_start; p.protect_len = d.protect_len;
   p.rows_total = (int)g.rows;
   p.slots = slots; p.per_xcd = g.per_xcd; p.xcd_rows = xcd_rows;
-  p.build_next = build_next ? 1 : 0;
+  p.build_next = a.build_next ? 1 : 0;
   p.diagonal_first = diagonal_first;
+  if (few) {
+    const ScratchLayout sl = scratch_layout(g);
+    p.nseg = g.nseg;
+    p.fresh = a.fresh ? 1 : 0;
+    p.v = static_cast<const uint16_t*>(a.v);
+    p.seg_o = reinterpret_cast<float*>(scratch + sl.seg_o);
+    p.seg_stat = reinterpret_cast<float*>(scratch + sl.seg_stat);
+    p.seg_mloc = reinterpret_cast<float*>(scratch + sl.seg_mloc);
+    p.stats_all = a.stats_all;
+    p.stat_words = (int)a.stat_words;
+  }
   if (mid) {
     e = hipEventRecord(mid, stream);
     if (e != hipSuccess) return e;
@@ -115,7 +134,7 @@ using la::hip_fail;
   } while (0)
 
 hipStream_t stream_of(const lite_attn_mask* m) { return m->ctx ? m->ctx->stream : m->stream; }
-uint16_t* vt_of(const lite_attn_mask* m) { return static_cast<uint16_t*>(m->ctx ? m->ctx->scratch.base : m->own.base); }
+char* scratch_of(const lite_attn_mask* m) { return static_cast<char*>(m->ctx ? m->ctx->scratch.base : m->own.base); }
 
 int grow(la_scratch* s, size_t bytes) {
   if (bytes <= s->bytes) return LITE_ATTN_OK;
@@ -147,15 +166,15 @@ int init_common(const lite_attn_desc_t* desc, lite_attn_ctx* ctx, lite_attn_mask
   m->d_bits = nullptr;
   m->d_stats = nullptr;
   const size_t words = (size_t)m->geo.rows * m->geo.W, nstats = 3 * (size_t)desc->max_steps;
-  const size_t vt = la::vt_bytes(m->geo);
+  const size_t need = la::scratch_layout(m->geo).total;
   hipStream_t st = ctx ? ctx->stream : nullptr;
   rc = LITE_ATTN_OK;
   if (ctx) {
     // every call made so far through this context has to finish before its scratch may move
-    hipError_t e = vt > ctx->scratch.bytes ? hipStreamSynchronize(ctx->stream) : hipSuccess;
-    rc = e != hipSuccess ? hip_fail(e) : grow(&ctx->scratch, vt);
+    hipError_t e = need > ctx->scratch.bytes ? hipStreamSynchronize(ctx->stream) : hipSuccess;
+    rc = e != hipSuccess ? hip_fail(e) : grow(&ctx->scratch, need);
   } else {
-    rc = grow(&m->own, vt);
+    rc = grow(&m->own, need);
   }
   if (rc == LITE_ATTN_OK) {
     hipError_t e = hipMalloc(&m->d_bits, sizeof(uint64_t) * words);
@@ -235,9 +254,6 @@ int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_a
   if (step != 0 && step != m->next_step) return LITE_ATTN_ESTEP;
   const lite_attn_desc_t& d = m->desc;
   hipStream_t stream = stream_of(m);
-  if (step == 0)
-    LA_HIP(la::launch_clear(m->d_bits, (size_t)m->geo.rows * m->geo.W, m->d_stats, 3 * (size_t)d.max_steps, stream));
-  unsigned long long* st = m->d_stats + 3 * (size_t)step;
   hipEvent_t* ev = (m->profile && m->events) ? m->events + 3 * (size_t)step : nullptr;
   if (m->timed) m->timed[step] = ev != nullptr;
   if (ev) LA_HIP(hipEventRecord(ev[0], stream));
@@ -245,9 +261,18 @@ int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_a
   // was just cleared) and not after an import.  This call's epilogue then leaves the lists of the next call.
   const bool ready = m->lists_valid && step != 0;
   m->lists_valid = false;
-  LA_HIP(la::launch_call(d, m->geo, m->ll, m->d_lists, vt_of(m), q, k, v, out, m->d_bits, st, threshold, ready, true,
-                         stream, ev ? ev[1] : nullptr));
-  m->lists_valid = true;
+  la::CallArgs a;
+  a.q = q; a.k = k; a.v = v; a.out = out;
+  a.threshold = threshold;
+  a.bits = m->d_bits;
+  a.stats3 = m->d_stats + 3 * (size_t)step;
+  a.fresh = step == 0;
+  a.stats_all = m->d_stats;
+  a.stat_words = 3 * (size_t)d.max_steps;
+  a.lists_ready = ready;
+  a.build_next = true;
+  LA_HIP(la::launch_call(d, m->geo, m->ll, m->d_lists, scratch_of(m), a, stream, ev ? ev[1] : nullptr));
+  m->lists_valid = m->geo.nseg == 0;  // (calls with few rows keep no lists)
   if (ev) LA_HIP(hipEventRecord(ev[2], stream));
   m->next_step = step + 1;
   return LITE_ATTN_OK;

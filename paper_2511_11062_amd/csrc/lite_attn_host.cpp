@@ -1,5 +1,6 @@
 // Pure host logic of the C ABI (no HIP call, no device code): descriptor and call checks, tile geometry, layout of
 // the per-call scratch.  Kept apart so that it also builds with a plain C++ compiler under the CPU sanitizers.
+#include <algorithm>
 #include <cmath>
 
 #include "lite_attn_kernels.h"
@@ -38,6 +39,42 @@ int check_call(const void* q, const void* k, const void* v, const void* out, flo
   return LITE_ATTN_OK;
 }
 
+namespace {
+size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// Partial results of rows cut into segments: what the fused kernel hands to the merge pass.
+size_t segment_bytes(const Geometry& g, int nseg) {
+  return nseg > 1 ? sizeof(float) * (size_t)g.rows * (nseg * (128 * 128 + 3 * 128) + (size_t)g.Tk * 128) : 0;
+}
+
+// How many segments (workgroups) a row is cut into when there are few rows.  The chip holds 512 workgroups, two per CU;
+// a whole row per workgroup leaves most of it idle.  Cutting costs a second launch, 64 KB of fp32 partials per segment
+// written and read again, and the walk over the tiles' row maxima in the merge pass.  Minimum of a cost in units of
+// 10 ns whose terms were measured on segments of 1..256 tiles: a tile takes 1.73 us on a CU of its own and 2.7 us with
+// two workgroups on the CU, a further round of workgroups 5 us, the merge 5 us + 22 ns per segment + 0.3 us per tile
+// of a segment.  us per call, whole rows -> segments: 32 rows of 16 tiles 34.4 -> 20.5 (8 segments), 72 x 12 29.0 ->
+// 24.9 (3), 64 x 64 117 -> 46.7 (8), 128 x 32 64.5 -> 46.5 (4), 128 x 128 228 -> 125 (4), 256 x 256 522 -> 432 (4);
+// 192 x 32 and 444 x 37 gain nothing and stay whole.  The immediate variant needs a tile's verdict before its PV
+// product, which a segment cannot know: whole rows.
+int segments(const Geometry& g, int flags) {
+  if (flags & LITE_ATTN_PV_SKIP_IMMEDIATE) return 1;
+  int best = 1;
+  int64_t best_cost = 0;
+  for (int s = 1; s <= kMaxSegments && s <= g.Tk; ++s) {
+    if (segment_bytes(g, s) > kMaxSegmentBytes) break;
+    const int64_t wgs = g.rows * s, tiles = (g.Tk + s - 1) / s, last = wgs % 512;
+    const int64_t full = wgs / 512;
+    int64_t cost = tiles * (270 * full + (last == 0 ? 0 : last <= 256 ? 173 : 270)) + 500 * (full + (last != 0));
+    if (s > 1) cost += 500 + (22 * wgs) / 10 + 30 * tiles;
+    if (s == 1 || cost < best_cost) {
+      best = s;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+}  // namespace
+
 Geometry geometry(const lite_attn_desc_t& d) {
   Geometry g;
   g.Tq = (d.seqlen + d.tile_q - 1) / d.tile_q;
@@ -47,13 +84,14 @@ Geometry geometry(const lite_attn_desc_t& d) {
   g.BH = d.batch * d.heads;
   g.rows = (int64_t)g.BH * g.Tq;
   g.chunks = g.BH * ((g.Tq + kChunkRows - 1) / kChunkRows);
+  g.nseg = 0;
   g.per_xcd = ((g.chunks + 7) / 8 + 1) * kChunkRows;
+  if (g.rows <= kFewRows && g.W <= 64) {
+    g.nseg = segments(g, d.flags);
+    g.per_xcd = (int)((g.rows * g.nseg + 7) / 8);
+  }
   return g;
 }
-
-namespace {
-size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
-}  // namespace
 
 ListLayout list_layout(const Geometry& g) {
   ListLayout l;
@@ -78,6 +116,13 @@ ListLayout list_layout(const Geometry& g) {
   return l;
 }
 
-size_t vt_bytes(const Geometry& g) { return up256(sizeof(uint16_t) * (size_t)g.BH * 128 * ((size_t)g.Tk * 128)); }
+ScratchLayout scratch_layout(const Geometry& g) {
+  ScratchLayout l;  // the segments lie over the V^T that calls with few rows do not make
+  l.seg_o = 0;
+  l.seg_stat = sizeof(float) * (size_t)g.rows * g.nseg * 128 * 128;
+  l.seg_mloc = l.seg_stat + sizeof(float) * (size_t)g.rows * g.nseg * 3 * 128;
+  l.total = up256(std::max(sizeof(uint16_t) * (size_t)g.BH * 128 * ((size_t)g.Tk * 128), segment_bytes(g, g.nseg)));
+  return l;
+}
 
 }  // namespace la

@@ -11,6 +11,12 @@ namespace la {
 // Rows of one head that an XCD runs side by side (2 workgroups x 32 CUs): the unit of the row schedule ("chunk").
 constexpr int kChunkRows = 64;
 
+// Calls with at most kFewRows Q-tile rows (all of whose workgroups fit the chip at once) take no lists and no row schedule
+// and may cut rows into segments; the partial results stay small enough for the static scratch array.
+constexpr int kFewRows = 512;
+constexpr int kMaxSegments = 16;
+constexpr size_t kMaxSegmentBytes = (size_t)104 << 20;
+
 struct FwdParams {
   const uint16_t* q;
   const uint16_t* k;
@@ -36,6 +42,16 @@ struct FwdParams {
   // build_next != 0: the epilogue rewrites runs / nruns / live_cnt for the NEXT call from the mask this call leaves;
   // diagonal_first: visiting order of the lists
   int build_next, diagonal_first;
+  // Few rows (nseg > 0, see Geometry): V read as it is, the row's live tiles found from its mask row, no lists and no
+  // schedule (per_xcd = workgroups per XCD); the row cut into nseg segments, one workgroup each.
+  int nseg = 0;
+  int fresh = 0;                         // step 0: the mask counts as empty and is overwritten
+  const uint16_t* v = nullptr;
+  float* seg_o = nullptr;                // [rows][nseg][128][128] O^T partials in accumulator order
+  float* seg_stat = nullptr;             // [rows][nseg][3][128]: exponent reference, row sum, row maximum
+  float* seg_mloc = nullptr;             // [rows][Tk][128]: row maxima of the visited tiles
+  unsigned long long* stats_all = nullptr;  // all counters of the handle (stat_words of them): zeroed at step 0, nseg > 1
+  int stat_words = 0;
 };
 
 // Tile geometry of a layer, derived from its descriptor.
@@ -46,6 +62,7 @@ struct Geometry {
   int BH;          // batch * heads
   int64_t rows;    // BH * Tq
   int chunks;      // BH * ceil(Tq / kChunkRows): units of the row schedule
+  int nseg;        // > 0: few rows, each cut into this many segments (one workgroup each); 0: rows scheduled whole
   int per_xcd;     // row slots per XCD in the schedule table: (ceil(chunks / 8) + 1) chunks
 };
 
@@ -68,17 +85,30 @@ int check_desc(const lite_attn_desc_t* d);  // LITE_ATTN_OK or the error the hea
 int check_call(const void* q, const void* k, const void* v, const void* out, float threshold);
 Geometry geometry(const lite_attn_desc_t& d);
 ListLayout list_layout(const Geometry& g);
-size_t vt_bytes(const Geometry& g);  // V^T scratch of one call: [BH][128][128*Tk] bf16, rounded up to 256 bytes
+// Scratch of one call: V^T ([BH][128][128*Tk] bf16), or, with few rows, the segments' partial results in its place.
+struct ScratchLayout {
+  size_t seg_o, seg_stat, seg_mloc, total;
+};
+ScratchLayout scratch_layout(const Geometry& g);
 
 // lite_attn.cpp: the launches of one attention call on `stream`.  lists_ready: the Skip-Lists in `lists` already
 // describe the mask (left by the previous call's epilogue); otherwise the compaction kernel builds them first.  Then
 // the row schedule, the V^T pre-pass into `vt` and the fused attention kernel, whose epilogue builds the next call's
 // lists if build_next.  `mid` (may be null) is recorded just before the attention kernel.
 // Allocates nothing.
-hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListLayout& ll, char* lists, uint16_t* vt,
-                       const void* q, const void* k, const void* v, void* out, uint64_t* bits,
-                       unsigned long long* stats3, float threshold, bool lists_ready, bool build_next,
-                       hipStream_t stream, hipEvent_t mid);
+struct CallArgs {
+  const void *q, *k, *v;
+  void* out;
+  float threshold;
+  uint64_t* bits;              // the Skip-Mask
+  unsigned long long* stats3;  // this step's counters, or null (nobody reads them)
+  bool fresh;                  // step 0: the mask counts as empty, whatever it holds, and all counters start at zero
+  unsigned long long* stats_all;
+  size_t stat_words;
+  bool lists_ready, build_next;
+};
+hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListLayout& ll, char* lists, char* scratch,
+                       const CallArgs& a, hipStream_t stream, hipEvent_t mid);
 int hip_fail(hipError_t e);  // remembers e for lite_attn_last_hip_error() and maps it to a lite_attn_error
 
 int fwd_lds_bytes();

@@ -28,6 +28,18 @@
 //   * IMM variant (Algorithm 2 taken literally: a tile that fires contributes nothing in the step that marks it):
 //     O += V(s-2) P(s-2) runs two stages behind instead of one, so that the verdict on a tile is known before the
 //     first of its two PV products is issued; a fired tile's PV MFMAs and row sums are then dropped.
+//
+// Calls with few rows (template argument FEW of the fused kernel; at most kFewRows = 512, which all fit the chip at once)
+// are bound by launches and by latency, not by the matrix cores: the tiny layer's step was 36 us of attention on 32 of
+// 256 CUs behind four to six launches of 4 us each.  They run in one or two launches:
+//   * no lists, no ranking, no schedule: a workgroup finds its live tiles from the mask row itself (LiveWalk);
+//   * no V^T: the V fragments come from V as it lies in memory through transposing LDS reads (ds_read_b64_tr_b16), 16 LDS
+//     instructions more per stage, the same LDS cycles (no bank conflicts): 1.8 % of the kernel's time on the 12-head
+//     N = 32760 dense step, against a launch and a pass over V;
+//   * a row may be cut into segments, one workgroup each (the rule and its measurements: segments() in
+//     lite_attn_host.cpp); merge_segments_kernel adds up the partial results.  The predicate stays exact: the
+//     segments record every tile's row maxima, and the merge pass judges them against the running maximum carried
+//     over the segments, the value a single pass would have had.
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <stdint.h>
@@ -312,6 +324,75 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(const uint16_t* __rest
   }
 }
 
+// The live K/V tiles of one Skip-Mask row in visiting order, walked from the mask words themselves (calls with few rows,
+// where a list built by an earlier kernel would cost more than it saves): lane w of the wave holds word w of the row's
+// live set, the position is scalar.  Rows of at most 64 words (4096 tiles).  Used by whole waves only.
+struct LiveWalk {
+  uint32_t lo, hi;   // this lane's word of the live set
+  int W, start;      // words of a row; tile the visit starts with (diagonal first: the diagonal tile)
+  int v;             // visit position: the words from the starting one on, cyclically (the starting one twice: its tiles
+                     // from `start` on first, those before it last)
+  uint64_t cur;      // tiles of the current word still to come
+
+  __device__ __forceinline__ void open(const uint64_t* mrow, bool empty_mask, int Tk, int W_, int start_) {
+    const int lane = threadIdx.x & 63;
+    W = W_;
+    start = start_;
+    uint64_t live = 0;
+    if (lane < W) {
+      live = empty_mask ? ~0ull : ~mrow[lane];
+      if (lane == W - 1 && (Tk & 63)) live &= (1ull << (Tk & 63)) - 1ull;
+    }
+    lo = (uint32_t)live;
+    hi = (uint32_t)(live >> 32);
+    rewind();
+  }
+  __device__ __forceinline__ int words() const { return start > 0 ? W + 1 : W; }
+  __device__ __forceinline__ int index(int at) const {  // word of visit position `at`
+    const int w = (start >> 6) + at;
+    return w >= W ? w - W : w;
+  }
+  __device__ __forceinline__ uint64_t word(int at) const {
+    const int w = index(at);
+    const uint64_t x =
+        (uint32_t)__builtin_amdgcn_readlane(lo, w) | ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi, w) << 32);
+    const uint64_t lead = ~0ull << (start & 63);
+    return at == 0 ? x & lead : at == W ? x & ~lead : x;
+  }
+  __device__ __forceinline__ void rewind() {
+    v = 0;
+    cur = word(0);
+  }
+  __device__ __forceinline__ void count(int& tiles, int& runs) const {  // of the whole row
+    tiles = 0;
+    runs = 0;
+    uint64_t prev = 0;
+    for (int at = 0; at < words(); ++at) {
+      const uint64_t x = word(at);
+      if (index(at) == 0) prev = 0;  // a run does not continue from the last tile to the first
+      tiles += __popcll(x);
+      runs += __popcll(x & ~((x << 1) | (prev >> 63)));
+      prev = x;
+    }
+  }
+  __device__ __forceinline__ void skip(int n) {  // n tiles ahead; n is less than the tiles left
+    while (v + 1 < words()) {
+      const int c = __popcll(cur);
+      if (c > n) break;
+      n -= c;
+      cur = word(++v);
+    }
+    for (; n > 0; --n) cur &= cur - 1;
+  }
+  __device__ __forceinline__ bool next(int& j) {  // the next tile; false (j unchanged) at the end
+    while (cur == 0 && v + 1 < words()) cur = word(++v);
+    if (cur == 0) return false;
+    j = 64 * index(v) + __builtin_ctzll(cur);
+    cur &= cur - 1;
+    return true;
+  }
+};
+
 // Geometry of the fused kernel: a wave owns QB blocks of 32 Q rows, a workgroup (one Q tile of 128 rows) has 4/QB waves.
 template <int QB>
 struct Geo {
@@ -443,15 +524,27 @@ __device__ __forceinline__ void mma_qk(f32x16 (&nxt)[QB][2], const bf16x8 (&qf)[
   }
 }
 
+// V fragment of 16 K/V positions x 32 features (column chunk cc, d-block db) from a V stage as it lies in memory ([kv][d]):
+// two transposing reads, rows 4h..4h+3 and 8+4h..8+4h+3 of the chunk for lane half h -- the order of the P~ values.
+__device__ __forceinline__ bf16x8 load_v_rows(uint32_t addr) {
+  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LA_LDS s16x4*)(addr));
+  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LA_LDS s16x4*)(addr + 8 * 256));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
 // O^T += V^T P~^T for one 64-column stage held in LDS at byte offset sV ([d][64 kv], 128-byte rows).
-template <int QB>
+template <int QB, bool VROWS>
 __device__ __forceinline__ void mma_pv(f32x16 (&oacc)[QB][4], const uint32_t (&pw)[QB][16], int sV,
                                        const uint32_t (&vread)[4]) {
 #pragma unroll
   for (int cc = 0; cc < 4; ++cc)
 #pragma unroll
     for (int db = 0; db < 4; ++db) {
-      const bf16x8 a = *reinterpret_cast<LA_LDS const bf16x8*>(vread[cc] + (uint32_t)(sV + 4096 * db));
+      bf16x8 a;
+      if constexpr (VROWS)
+        a = load_v_rows(vread[db] + (uint32_t)(sV + 4096 * cc));
+      else
+        a = *reinterpret_cast<LA_LDS const bf16x8*>(vread[cc] + (uint32_t)(sV + 4096 * db));
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb)
         oacc[qb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, p_operand(&pw[qb][4 * cc]), oacc[qb][db], 0, 0, 0);
@@ -469,13 +562,18 @@ __device__ __forceinline__ void mma_pv(f32x16 (&oacc)[QB][4], const uint32_t (&p
 __device__ __forceinline__ constexpr int qk_blk(int k) { return (k - 16) >> 3; }
 __device__ __forceinline__ constexpr int qk_kk(int k) { return k & 7; }
 
-template <int kK, int kV>
+template <bool VROWS, int kK, int kV>
 __device__ __forceinline__ bf16x8 load_frag(int k, const uint32_t (&kread)[8], const uint32_t (&vread)[4]) {
   if (k >= 16) return *reinterpret_cast<LA_LDS const bf16x8*>(kread[qk_kk(k)] + (uint32_t)(kK + 8192 * qk_blk(k)));
   const int cc = k >> 2, db = k & 3;
+  if constexpr (VROWS) return load_v_rows(vread[db] + (uint32_t)(kV + 4096 * cc));
   return *reinterpret_cast<LA_LDS const bf16x8*>(vread[cc] + (uint32_t)(kV + 4096 * db));
 }
 
+// How far (in powers of two) the running maximum may outgrow the reference of the exponentials before O^T and the row sum
+// are rescaled: weights up to 2^8 keep their relative precision in bf16 and fp32.  Following the maximum at every stage
+// cost 64 multiplies per lane wherever any of a wave's 32 rows found a new one: 1.5 % of the dense 12-head N = 32760
+// step (5571 -> 5489 us), 6 % of the tiny layer's.
 constexpr float kLazyLog2 = 8.f;
 constexpr int kPrefetch = 3;  // LDS fragments in flight ahead of the MFMA that consumes them
 constexpr int kDmaGap = 2;    // steps between two DMA issues of a stage
@@ -499,7 +597,7 @@ struct NoOp {
 // verdict_load / verdict_commit (first stage of a tile, deferred marking only): the combine of the PREVIOUS tile's four
 // per-wave predicate results, spread over this stage -- its LDS read is issued at step 0 and used at step 12, so that
 // the wave that does it never waits for it.
-template <int QB, int H, bool IMM, class VLoad = NoOp, class VCommit = NoOp>
+template <int QB, int H, bool IMM, bool VROWS, class VLoad = NoOp, class VCommit = NoOp>
 __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, char* smem, int j_cur, int j_nxt,
                                       int* flag_slot, int j_tail, int j_v = 0, bool pv_on = true,
                                       VLoad verdict_load = VLoad(), VCommit verdict_commit = VCommit()) {
@@ -511,8 +609,8 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
   // loads are issued one at a time between the steps below (kDmaGap steps apart) so that a full memory
   // instruction queue does not hold up the MFMAs behind it ----
   const u32x4 krs = rebase(ln.krsrc, (uint32_t)(j_nxt * kTile + H * kSub) * ln.stride2);
-  const u32x4 vrs =
-      rebase(ln.vrsrc, IMM ? (uint32_t)(j_v * kTile + (H ^ 1) * kSub) * 2u : (uint32_t)(j_cur * kTile + H * kSub) * 2u);
+  const u32x4 vrs = rebase(ln.vrsrc, (uint32_t)(IMM ? j_v * kTile + (H ^ 1) * kSub : j_cur * kTile + H * kSub) *
+                                         (VROWS ? ln.stride2 : 2u));
   constexpr int kVDst = kVOff + (IMM ? (H ^ 1) : H) * kStageBytes;  // V^T buffer the DMA of this stage fills
   constexpr int kC = Geo<QB>::kChunks;
 
@@ -521,7 +619,7 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
   bf16x8 frag[kPrefetch];
 #pragma unroll
   for (int k = 0; k < kPrefetch; ++k)
-    if (!IMM || pv_on) frag[k] = load_frag<kKSrc, kVSrc>(k, ln.kread, ln.vread);
+    if (!IMM || pv_on) frag[k] = load_frag<VROWS, kKSrc, kVSrc>(k, ln.kread, ln.vread);
 
   float pm[QB][4], mx[QB], alpha[QB], ta0[QB], ta1[QB], tb0[QB];
 #pragma unroll
@@ -572,7 +670,7 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
     constexpr int k = decltype(kc)::value;
     if (k + kPrefetch < 32) {
       if (!IMM || pv_on || k + kPrefetch >= 16)
-        frag[k % kPrefetch] = load_frag<kKSrc, kVSrc>(k + kPrefetch, ln.kread, ln.vread);
+        frag[k % kPrefetch] = load_frag<VROWS, kKSrc, kVSrc>(k + kPrefetch, ln.kread, ln.vread);
     }
     if (k % kDmaGap == 0 && k / kDmaGap < 2 * kC) {
       const int x = k / kDmaGap;
@@ -679,7 +777,7 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
   __syncthreads();
 }
 
-template <int QB, bool IMM>
+template <int QB, bool IMM, bool FEW>
 __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kernel(const FwdParams p) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   constexpr int kWaves = Geo<QB>::kWaves, kThreads = Geo<QB>::kThreads, kChunks = Geo<QB>::kChunks;
@@ -689,27 +787,51 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
   // Consecutive workgroup ids land on different XCDs (id % 8): workgroup `slot` of an XCD computes the row that the
   // schedule table names for it (deal_rows_kernel: chunks of kChunkRows rows of one head side by side, so that the
   // workgroups sharing one L2 stream the same K/V; equal work per XCD; long rows first).
+  // FEW: no table; the (head, segment, row) triples are numbered row-fastest and every XCD takes an eighth of them, so
+  // that the rows walking the same K/V tiles of a head share an L2.
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  if (slot >= (int)p.xcd_rows[xcd]) return;
-  const int row = (int)p.slots[(size_t)xcd * p.per_xcd + slot];
-  if (row < 0) return;  // an empty slot behind a chunk shorter than kChunkRows
+  int row, seg = 0;
+  if constexpr (FEW) {
+    const int unit = xcd * p.per_xcd + slot;
+    if (unit >= p.rows_total * p.nseg) return;
+    const int u = unit / p.Tq;
+    seg = u % p.nseg;
+    row = (u / p.nseg) * p.Tq + unit % p.Tq;
+  } else {
+    if (slot >= (int)p.xcd_rows[xcd]) return;
+    row = (int)p.slots[(size_t)xcd * p.per_xcd + slot];
+    if (row < 0) return;  // an empty slot behind a chunk shorter than kChunkRows
+  }
   const int i = row % p.Tq;
   const int bh = row / p.Tq;
   const int64_t base = (int64_t)(bh / p.H) * p.stride_b + (int64_t)(bh % p.H) * p.stride_h;
   const uint16_t* qb_ptr = p.q + base;
   uint16_t* ob = p.out + base;
   const int N = p.N;
-  const int cnt = (int)p.live_cnt[row];
+  const bool split = FEW && p.nseg > 1;
+  LiveWalk walk;
+  int cnt, nruns, t_lo = 0, t_hi;
+  if constexpr (FEW) {
+    walk.open(p.bits + (size_t)row * p.W, p.fresh, p.Tk, p.W, p.diagonal_first ? i : 0);
+    walk.count(cnt, nruns);
+    t_lo = (int)((int64_t)cnt * seg / p.nseg);
+    t_hi = (int)((int64_t)cnt * (seg + 1) / p.nseg);
+    if (split && p.fresh && blockIdx.x == 0)  // a new trajectory: the merge pass adds this step's counters afterwards
+      for (int x = tid; x < p.stat_words; x += kThreads) p.stats_all[x] = 0;
+  } else {
+    cnt = (int)p.live_cnt[row];
+    nruns = (int)p.nruns[row];
+    t_hi = cnt;
+  }
   // the Skip-List is read-only here: constant address space makes these wave-uniform reads scalar loads
   typedef const __attribute__((address_space(4))) uint32_t* const_u32_ptr;
   const_u32_ptr runs = (const_u32_ptr)(p.runs + (size_t)row * p.run_stride);
-  const int nruns = (int)p.nruns[row];
   int* flags = reinterpret_cast<int*>(smem + kFlagsOff);
   // mask bits set by this workgroup during the call (thread 0 writes them, wave 0 reads them in the epilogue)
   uint64_t* fired_bits = reinterpret_cast<uint64_t*>(smem + kFiredOff);
-  if (p.build_next)
+  if (!FEW && p.build_next)
     for (int w = tid; w < p.W; w += kThreads) fired_bits[w] = 0;
-  if (tid == 0) {  // statistics of the step: tiles skipped on entry, Skip-List entries read
+  if (tid == 0 && !split && p.stat_newly) {  // statistics of the step: tiles skipped on entry, Skip-List entries
     atomicAdd(p.stat_skipped_in, (unsigned long long)(p.Tk - cnt));
     atomicAdd(p.stat_runs, (unsigned long long)nruns);
   }
@@ -724,13 +846,18 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
   const uint32_t head_bytes = (uint32_t)(((int64_t)(N - 1) * p.stride_n + 128) * 2);
   ln.krsrc = make_rsrc(p.k + base, head_bytes);
   const uint32_t vt_row_bytes = (uint32_t)p.Tk * kTile * 2;  // one feature row of V^T: n_pad bf16
-  ln.vrsrc = make_rsrc(p.vt + (size_t)bh * 128 * ((size_t)p.Tk * kTile), 128u * vt_row_bytes);
+  ln.vrsrc = FEW ? make_rsrc(p.v + base, head_bytes)
+                 : make_rsrc(p.vt + (size_t)bh * 128 * ((size_t)p.Tk * kTile), 128u * vt_row_bytes);
   ln.lds_wave = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(LA_LDS char*)smem + 1024 * kChunks * wave);
 #pragma unroll
   for (int x = 0; x < kChunks; ++x) {
     const int r = 4 * (kChunks * wave + x) + (lane >> 4);  // row inside the stage that this lane's piece belongs to
     const int pc = lane & 15;                              // physical 16-byte chunk inside the 256-byte LDS row
     ln.kdma[x] = (uint32_t)r * ln.stride2 + 16 * (pc ^ (r & 15));
+    if constexpr (FEW) {  // V stage: 64 token rows x 256 bytes; four rows' 64-byte pieces of a d-block meet all banks
+      ln.vdma[x] = (uint32_t)r * ln.stride2 + 16 * (pc ^ (4 * (r & 3)));
+      continue;
+    }
     // V^T stage: 128 feature rows x 128 bytes; this lane's piece is row rv, physical 16-byte slot pv
     const int rv = 8 * (kChunks * wave + x) + (lane >> 3), pv = lane & 7;
     ln.vdma[x] = (uint32_t)rv * vt_row_bytes + 16 * (pv ^ ((rv >> 1) & 7));
@@ -739,7 +866,14 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
 #pragma unroll
   for (int kk = 0; kk < 8; ++kk) ln.kread[kk] = lds0 + lq * 256 + ((32 * kk) ^ (16 * (ln.hi ^ (lq & 15))));
 #pragma unroll
-  for (int cc = 0; cc < 4; ++cc) ln.vread[cc] = lds0 + lq * 128 + ((32 * cc + 16 * ln.hi) ^ (16 * ((lq >> 1) & 7)));
+  for (int cc = 0; cc < 4; ++cc) {
+    if constexpr (FEW) {  // d-block cc: row 4*hi + (lane>>2 & 3) of a chunk, 8-byte piece lane & 3 of its 16 features
+      const int r = 4 * ln.hi + ((lane >> 2) & 3), c = 4 * cc + 2 * ((lane >> 4) & 1) + ((lane >> 1) & 1);
+      ln.vread[cc] = lds0 + r * 256 + 16 * (c ^ (4 * (r & 3))) + 8 * (lane & 1);
+    } else {
+      ln.vread[cc] = lds0 + lq * 128 + ((32 * cc + 16 * ln.hi) ^ (16 * ((lq >> 1) & 7)));
+    }
+  }
   const bool q_pinned = p.protect_len > 0 && i * kTile < p.protect_start + p.protect_len &&
                         p.protect_start < min(N, (i + 1) * kTile);
 
@@ -776,17 +910,24 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
   int* flag_slot0 = lane == 0 ? flags + wave : flags + 8 + lane;
   int* flag_slot1 = lane == 0 ? flags + 4 + wave : flags + 8 + lane;
 
-  if (cnt > 0) {
+  // FEW: lane w of wave 0 collects the bits of mask word w that this call sets
+  uint64_t fired_word = 0;
+  if (t_hi > t_lo) {
     // Walk the run-length Skip-List with a cursor kept two tiles ahead of the tile being computed, so that the
     // scalar load of the next run entry is off the critical path.  At the end of the list the cursor stays put.
-    int c_run = 0, c_j, c_end;
-    {
+    int c_run = 0, c_j = 0, c_end = 0;
+    if constexpr (FEW) {
+      walk.skip(t_lo);
+      walk.next(c_j);
+    } else {
       const uint32_t e = runs[0];
       c_j = (int)(e & 0xffffu);
       c_end = (int)(e >> 16);
     }
     auto advance = [&]() {
-      if (c_j + 1 < c_end) {
+      if constexpr (FEW) {
+        walk.next(c_j);
+      } else if (c_j + 1 < c_end) {
         ++c_j;
       } else if (c_run + 1 < nruns) {
         ++c_run;
@@ -823,7 +964,9 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
       const bool k_pinned = p.protect_len > 0 && j * kTile < p.protect_start + p.protect_len &&
                             p.protect_start < min(N, (j + 1) * kTile);
       const bool fired = all && !q_pinned && !k_pinned;
-      if (tid == 0 && fired) {
+      if constexpr (FEW) {
+        if (fired && tid == (j >> 6)) fired_word |= 1ull << (j & 63);
+      } else if (tid == 0 && fired) {
         atomicOr(reinterpret_cast<unsigned long long*>(p.bits + (size_t)row * p.W + (j >> 6)), 1ull << (j & 63));
         fired_bits[j >> 6] |= 1ull << (j & 63);
         ++newly;
@@ -838,32 +981,43 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
     const int* v_slot = flags;  // LDS slot of the tile whose verdict is pending
     int v_j = -1;               // its K/V tile index (-1: none pending)
     auto mark_if_fired = [&](int all, int j) {
-      if (tid == 0 && all) {
+      if (tid == (FEW ? j >> 6 : 0) && all) {
         const bool k_pinned = p.protect_len > 0 && j * kTile < p.protect_start + p.protect_len &&
                               p.protect_start < min(N, (j + 1) * kTile);
         if (!q_pinned && !k_pinned) {
-          atomicOr(reinterpret_cast<unsigned long long*>(p.bits + (size_t)row * p.W + (j >> 6)), 1ull << (j & 63));
-          fired_bits[j >> 6] |= 1ull << (j & 63);
-          ++newly;
+          if constexpr (FEW) {
+            fired_word |= 1ull << (j & 63);
+          } else {
+            atomicOr(reinterpret_cast<unsigned long long*>(p.bits + (size_t)row * p.W + (j >> 6)), 1ull << (j & 63));
+            fired_bits[j >> 6] |= 1ull << (j & 63);
+            ++newly;
+          }
         }
       }
     };
+    // split rows: whether a tile fires depends on the segments before this one; its row maxima go to the merge pass
+    float* mloc_out = nullptr;
+    if constexpr (FEW) mloc_out = p.seg_mloc + (size_t)row * p.Tk * kTile + 32 * wave + lq;
     auto verdict_load = [&]() {
       static_assert(IMM || kWaves == 4, "four per-wave flags per tile");
+      if (split) {
+        if (v_j >= 0 && ln.hi == 0 && p.thr > -INFINITY) mloc_out[v_j * kTile] = st.mloc_tile[0];
+        return;
+      }
       if (wave0) vflags = *reinterpret_cast<const int4*>(v_slot);
     };
     auto verdict_commit = [&]() {
-      if (wave0 && v_j >= 0) mark_if_fired(vflags.x & vflags.y & vflags.z & vflags.w, v_j);
+      if (!split && wave0 && v_j >= 0) mark_if_fired(vflags.x & vflags.y & vflags.z & vflags.w, v_j);
     };
     bool pv_on = false;  // IMM: the previous tile did not fire, its PV products are due
     int j_prev = j_cur;
-    for (int t = 0; t < cnt; ++t) {
+    for (int t = t_lo; t < t_hi; ++t) {
       advance();
       const int j_nn = c_j;  // needed one tile from now
       int* fs = (t & 1) ? flag_slot1 : flag_slot0;
       if constexpr (IMM) {
-        stage<QB, 0, true>(st, ln, smem, j_cur, j_nxt, fs, j_tail, j_prev, pv_on);
-        stage<QB, 1, true>(st, ln, smem, j_cur, j_nxt, fs, j_tail, j_cur, pv_on);
+        stage<QB, 0, true, FEW>(st, ln, smem, j_cur, j_nxt, fs, j_tail, j_prev, pv_on);
+        stage<QB, 1, true, FEW>(st, ln, smem, j_cur, j_nxt, fs, j_tail, j_cur, pv_on);
         pv_on = !finish_tile_imm(t, j_cur);
         if (pv_on) {
 #pragma unroll
@@ -871,8 +1025,8 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
         }
         j_prev = j_cur;
       } else {
-        stage<QB, 0, false>(st, ln, smem, j_cur, j_nxt, fs, j_tail, 0, true, verdict_load, verdict_commit);
-        stage<QB, 1, false>(st, ln, smem, j_cur, j_nxt, fs, j_tail);
+        stage<QB, 0, false, FEW>(st, ln, smem, j_cur, j_nxt, fs, j_tail, 0, true, verdict_load, verdict_commit);
+        stage<QB, 1, false, FEW>(st, ln, smem, j_cur, j_nxt, fs, j_tail);
         v_slot = flags + (t & 1) * 4;
         v_j = j_cur;
       }
@@ -882,10 +1036,10 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
     if constexpr (IMM) {
       // drain: the second V^T stage of the last tile is still to be loaded; then both of its PV products, the
       // rescale factor of its second stage in between
-      dma_stage<QB, kVOff + kStageBytes>(ln.vrsrc, ln.vdma, (uint32_t)(j_prev * kTile + kSub) * 2u, ln.lds_wave);
+      dma_stage<QB, kVOff + kStageBytes>(ln.vrsrc, ln.vdma, (uint32_t)(j_prev * kTile + kSub) * (FEW ? ln.stride2 : 2u), ln.lds_wave);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
-      if (pv_on) mma_pv<QB>(st.oacc, st.pw0, kVOff, ln.vread);
+      if (pv_on) mma_pv<QB, FEW>(st.oacc, st.pw0, kVOff, ln.vread);
       if (st.grew_prev) {
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb)
@@ -894,16 +1048,53 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
 #pragma unroll
             for (int r = 0; r < 16; ++r) st.oacc[qb][db][r] *= st.alpha_prev[qb];
       }
-      if (pv_on) mma_pv<QB>(st.oacc, st.pw, kVOff + kStageBytes, ln.vread);
+      if (pv_on) mma_pv<QB, FEW>(st.oacc, st.pw, kVOff + kStageBytes, ln.vread);
     } else {
       // drain: O^T += V^T P~^T of the last stage (odd parity buffer), and the verdict on the last tile
-      mma_pv<QB>(st.oacc, st.pw, kVOff + kStageBytes, ln.vread);
+      mma_pv<QB, FEW>(st.oacc, st.pw, kVOff + kStageBytes, ln.vread);
       verdict_load();
       verdict_commit();
     }
     __syncthreads();
   }
-  if (tid == 0 && newly) atomicAdd(p.stat_newly, (unsigned long long)newly);
+  // (the kernel arguments used from here on are read again from the argument segment instead of being kept in scalar
+  // registers across the main loop)
+  typedef const __attribute__((address_space(4))) FwdParams* const_params_ptr;
+  const_params_ptr e = (const_params_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(e));
+  if constexpr (FEW) {
+    if (split) {
+      // partial result of this segment, to be merged: O^T accumulators as the lanes hold them (1 KB per store), the
+      // reference of the exponentials, the row sums and the row maxima
+      const size_t s = (size_t)row * e->nseg + seg;
+      static_assert(QB == 1, "one Q block per wave");
+      float* po = e->seg_o + (s * 4 + wave) * 4096 + 4 * lane;
+      if (t_hi > t_lo)
+#pragma unroll
+        for (int g = 0; g < 16; ++g) {
+          const f32x16& a = st.oacc[0][g >> 2];
+          const int r = 4 * (g & 3);
+          *reinterpret_cast<float4*>(po + 256 * g) = float4{a[r], a[r + 1], a[r + 2], a[r + 3]};
+        }
+      const float l = other_half_sum(st.l_run[0]);
+      if (ln.hi == 0) {
+        float* ps = e->seg_stat + s * 3 * kTile + 32 * wave + lq;
+        ps[0] = st.mc_ref[0];
+        ps[kTile] = l;
+        ps[2 * kTile] = st.m_run[0];
+      }
+      return;
+    }
+    if (wave == 0) {
+      if (lane < e->W && (e->fresh || fired_word)) {
+        uint64_t* word = e->bits + (size_t)row * e->W + lane;
+        *word = (e->fresh ? 0ull : *word) | fired_word;
+      }
+      if (fired_word && e->stat_newly) atomicAdd(e->stat_newly, (unsigned long long)__popcll(fired_word));
+    }
+  } else {
+    if (tid == 0 && newly && e->stat_newly) atomicAdd(e->stat_newly, (unsigned long long)newly);
+  }
 
   // ---- epilogue: O = acc / l, transposed through LDS so that global stores are 16 B and row-contiguous ----
   char* sO = smem;
@@ -931,14 +1122,11 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
           *reinterpret_cast<const uint4*>(sO + r * kORow + 16 * (tid & 15));
   }
 
+  if constexpr (FEW) return;
   // ---- second epilogue: the Skip-List this row will walk in the NEXT call, compacted from the mask row as this call
   // leaves it: the row as it was on entry (nobody else writes it) OR the bits this workgroup set, which it kept in
   // LDS, so that nothing depends on when its own atomics become visible to its loads.  The row's list is private to
-  // this workgroup: it is overwritten in place, after its last read.  (The kernel arguments used here are read
-  // again from the argument segment instead of being kept in scalar registers across the main loop.) ----
-  typedef const __attribute__((address_space(4))) FwdParams* const_params_ptr;
-  const_params_ptr e = (const_params_ptr)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(e));
+  // this workgroup: it is overwritten in place, after its last read. ----
   if (e->build_next && wave == 0) {
     uint32_t ns, n;
     compact_row(e->bits + (size_t)row * e->W, [&](int w) { return fired_bits[w]; }, i, e->Tk, e->W, e->diagonal_first,
@@ -947,6 +1135,123 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
       e->nruns[row] = ns;
       e->live_cnt[row] = n;
     }
+  }
+}
+
+// Bound by latency and by the partials' way through memory (64 KB per segment; 16 MB for 256 segments): loads of four
+// segments, or of eight tiles' maxima, in flight together (call of 32 rows x 4 segments of 4 tiles 22.0 -> 20.7
+// us, of 128 rows x 2 segments of 64 tiles 163 -> 147 us, against one load at a time).
+// Rows that were cut into segments (FEW, nseg > 1): merges the segments' partial results and judges the tiles.
+// Workgroups 0 .. 4*rows-1: 32 Q rows each, one thread per (row, 8 features): O = sum_s 2^(m_s - M) O_s / sum_s ... .
+// Workgroups 4*rows .. 5*rows-1: one Skip-Mask row each; two waves per segment walk its tiles with the running maximum
+// carried over from the segments before it (exactly the maximum a single pass would have), set the row's mask bits and
+// add the step's counters.
+constexpr int kMergeThreads = 512;
+__global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const FwdParams p) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int nseg = p.nseg;
+  if ((int)blockIdx.x < 4 * p.rows_total) {
+    const int row = blockIdx.x >> 2, wave = blockIdx.x & 3;
+    const int i = row % p.Tq, bh = row / p.Tq;
+    const int lq = tid & 31, e = tid >> 5;  // e = 4 * d-block + group of four accumulator registers
+    const int qrow = i * kTile + 32 * wave + lq;
+    const float* ps = p.seg_stat + (size_t)row * nseg * 3 * kTile + 32 * wave + lq;
+    const float* po = p.seg_o + ((size_t)row * nseg * 4 + wave) * 4096 + 256 * e + 4 * lq;
+    float top = -INFINITY, l = 0.f;
+    for (int s = 0; s < nseg; ++s) top = fmaxf(top, ps[s * 3 * kTile]);
+    float4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
+    constexpr int kAhead = 4;  // segments whose loads are in flight together
+    for (int s0 = 0; s0 < nseg; s0 += kAhead) {
+      float m[kAhead], ls[kAhead];
+      float4 x[kAhead], y[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int s = min(s0 + u, nseg - 1);
+        m[u] = ps[s * 3 * kTile];
+        ls[u] = ps[s * 3 * kTile + kTile];
+        x[u] = *reinterpret_cast<const float4*>(po + (size_t)s * 4 * 4096);
+        y[u] = *reinterpret_cast<const float4*>(po + (size_t)s * 4 * 4096 + 128);
+      }
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        if (s0 + u >= nseg || m[u] == -INFINITY) continue;  // a segment without tiles has written no O
+        const float f = __builtin_amdgcn_exp2f(m[u] - top);
+        l += f * ls[u];
+        a.x += f * x[u].x; a.y += f * x[u].y; a.z += f * x[u].z; a.w += f * x[u].w;
+        b.x += f * y[u].x; b.y += f * y[u].y; b.z += f * y[u].z; b.w += f * y[u].w;
+      }
+    }
+    if (qrow >= p.N) return;
+    const float inv = l > 0.f ? 1.f / l : 0.f;
+    uint4 o;
+    o.x = pack_bf16x2(a.x * inv, a.y * inv);
+    o.y = pack_bf16x2(a.z * inv, a.w * inv);
+    o.z = pack_bf16x2(b.x * inv, b.y * inv);
+    o.w = pack_bf16x2(b.z * inv, b.w * inv);
+    uint16_t* out = p.out + (int64_t)(bh / p.H) * p.stride_b + (int64_t)(bh % p.H) * p.stride_h;
+    *reinterpret_cast<uint4*>(out + (int64_t)qrow * p.stride_n + 8 * e) = o;
+    return;
+  }
+  constexpr int kPairs = kMergeThreads / 128;
+  __shared__ uint64_t fired[2 * kPairs][64];  // per wave (half of a segment's Q rows): tiles that fire for its rows
+  const int row = blockIdx.x - 4 * p.rows_total;
+  const int i = row % p.Tq;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = tid & 127, pair = wave >> 1;
+  LiveWalk walk;
+  int cnt, nruns;
+  walk.open(p.bits + (size_t)row * p.W, p.fresh, p.Tk, p.W, p.diagonal_first ? i : 0);
+  walk.count(cnt, nruns);
+  const bool q_pinned = p.protect_len > 0 && i * kTile < p.protect_start + p.protect_len &&
+                        p.protect_start < min(p.N, (i + 1) * kTile);
+  uint64_t mine = 0;  // lane w: bits of mask word w
+  if (p.thr > -INFINITY && !q_pinned) {
+    const bool qvalid = i * kTile + r < p.N;
+    const float* ps = p.seg_stat + (size_t)row * nseg * 3 * kTile + 2 * kTile + r;
+    const float* mloc = p.seg_mloc + (size_t)row * p.Tk * kTile + r;
+    for (int s = pair; s < nseg; s += kPairs) {
+      const int t0 = (int)((int64_t)cnt * s / nseg), t1 = (int)((int64_t)cnt * (s + 1) / nseg);
+      if (t0 == t1) continue;
+      float run = -INFINITY;
+      for (int x = 0; x < s; ++x) run = fmaxf(run, ps[x * 3 * kTile]);
+      walk.rewind();
+      walk.skip(t0);
+      constexpr int kAhead = 8;  // tiles whose loads are in flight together
+      for (int t = t0; t < t1; t += kAhead) {
+        int j[kAhead];
+        float m[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+          j[u] = u > 0 ? j[u - 1] : 0;
+          walk.next(j[u]);
+          m[u] = mloc[(size_t)j[u] * kTile];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+          if (t + u >= t1) break;
+          run = fmaxf(run, m[u]);
+          if (__all(!qvalid || (m[u] - run) * p.scale <= p.thr) && lane == (j[u] >> 6)) {
+            const bool k_pinned = p.protect_len > 0 && j[u] * kTile < p.protect_start + p.protect_len &&
+                                  p.protect_start < min(p.N, (j[u] + 1) * kTile);
+            if (!k_pinned) mine |= 1ull << (j[u] & 63);
+          }
+        }
+      }
+    }
+  }
+  fired[wave][lane] = mine;
+  __syncthreads();
+  if (tid < p.W) {
+    uint64_t f = 0;
+#pragma unroll
+    for (int x = 0; x < kPairs; ++x) f |= fired[2 * x][tid] & fired[2 * x + 1][tid];
+    uint64_t* word = p.bits + (size_t)row * p.W + tid;
+    if (p.fresh || f) *word = (p.fresh ? 0ull : *word) | f;
+    if (f && p.stat_newly) atomicAdd(p.stat_newly, (unsigned long long)__popcll(f));
+  }
+  if (tid == 0 && p.stat_newly) {
+    atomicAdd(p.stat_skipped_in, (unsigned long long)(p.Tk - cnt));
+    atomicAdd(p.stat_runs, (unsigned long long)nruns);
   }
 }
 
@@ -983,12 +1288,14 @@ static size_t order_lds_bytes(int Tq, int Tk) {
 }
 
 hipError_t prepare_fwd() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(lite_attn_fwd_kernel<kQB, false>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, fwd_lds_bytes());
-  if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(lite_attn_fwd_kernel<1, true>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, fwd_lds_bytes());
-  if (e != hipSuccess) return e;
+  const void* fused[] = {reinterpret_cast<const void*>(lite_attn_fwd_kernel<kQB, false, false>),
+                         reinterpret_cast<const void*>(lite_attn_fwd_kernel<1, true, false>),
+                         reinterpret_cast<const void*>(lite_attn_fwd_kernel<1, false, true>),
+                         reinterpret_cast<const void*>(lite_attn_fwd_kernel<1, true, true>)};
+  for (const void* f : fused) {
+    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, fwd_lds_bytes());
+    if (e != hipSuccess) return e;
+  }
   return hipFuncSetAttribute(reinterpret_cast<const void*>(order_rows_kernel),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)order_lds_bytes(16383, 16383));
 }
@@ -1011,13 +1318,24 @@ hipError_t launch_deal_rows(const uint32_t* chunk_work, const uint32_t* order, i
 }
 
 hipError_t launch_fwd(const FwdParams& p, bool immediate, hipStream_t st) {
-  // one workgroup per slot of the schedule table; those past an XCD's last row return at once
+  // one workgroup per slot of the schedule table (FEW: per segment); those past an XCD's last row return at once
+  const dim3 grid(8 * p.per_xcd), block(Geo<kQB>::kThreads);
+  if (p.nseg == 0) {
+    if (immediate)
+      hipLaunchKernelGGL((lite_attn_fwd_kernel<1, true, false>), grid, block, fwd_lds_bytes(), st, p);
+    else
+      hipLaunchKernelGGL((lite_attn_fwd_kernel<kQB, false, false>), grid, block, fwd_lds_bytes(), st, p);
+    return hipGetLastError();
+  }
   if (immediate)
-    hipLaunchKernelGGL((lite_attn_fwd_kernel<1, true>), dim3(8 * p.per_xcd), dim3(Geo<1>::kThreads), fwd_lds_bytes(),
-                       st, p);
+    hipLaunchKernelGGL((lite_attn_fwd_kernel<1, true, true>), grid, block, fwd_lds_bytes(), st, p);
   else
-    hipLaunchKernelGGL((lite_attn_fwd_kernel<kQB, false>), dim3(8 * p.per_xcd), dim3(Geo<kQB>::kThreads),
-                       fwd_lds_bytes(), st, p);
+    hipLaunchKernelGGL((lite_attn_fwd_kernel<1, false, true>), grid, block, fwd_lds_bytes(), st, p);
+  if (p.nseg > 1) {
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(merge_segments_kernel, dim3(5 * p.rows_total), dim3(kMergeThreads), 0, st, p);
+  }
   return hipGetLastError();
 }
 

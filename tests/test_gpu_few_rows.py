@@ -1,0 +1,67 @@
+"""Calls with few Q-tile rows: rows cut into segments (one workgroup each) whose partial results a second kernel merges,
+and rows kept whole, both finding their tiles from the mask row itself.  Sizes at which that can go wrong: one tile, fewer
+live tiles than segments, segment lengths with a remainder, mask rows of one, exactly one and more than one 64-bit word,
+the last size with few rows and the first without."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2511_11062_amd import inputs
+import parity
+
+pytestmark = pytest.mark.gpu
+
+
+def layer(heads, tokens, text=0, batch=1, seed=71):
+    return inputs.Workload("few", batch, heads, (1, 1, tokens - text), text_tokens=text, steps=3, seed=seed)
+
+
+@pytest.mark.parametrize("diagonal_first", [False, True])
+@pytest.mark.parametrize("heads,tokens,text", [(1, 128 * 5 - 1, 0), (2, 128 * 17 + 3, 40), (1, 128 * 63 + 5, 0),
+                                               (1, 128 * 64, 0), (1, 128 * 65 + 7, 130), (7, 128 * 9 + 64, 0)])
+def test_marking_across_segments(heads, tokens, text, diagonal_first):
+    """Three steps against the oracle, deferred marking: the tiles of a later segment are judged against the maximum
+    carried over from the earlier ones; then with the literal PV skip, whose rows stay whole."""
+    thr = [-3.0, -1.5, -0.7]
+    reps = parity.run_sequence_check(layer(heads, tokens, text), steps=3, thresholds=thr, diagonal_first=diagonal_first)
+    assert reps[-1]["skipped_out"] > 0.02
+    parity.run_sequence_check(layer(heads, tokens, text), steps=2, thresholds=thr, diagonal_first=diagonal_first,
+                              immediate=True)
+
+
+@pytest.mark.parametrize("heads,tiles", [(1, 5), (2, 16), (1, 65), (3, 100), (4, 128), (1, 513), (27, 19)])
+@pytest.mark.parametrize("live", [0.02, 0.5])
+def test_every_row_under_sparse_masks(heads, tiles, live):
+    """Random imported masks, many rows with fewer live tiles than segments and some with none, every row against
+    block-masked softmax attention in fp32; 512 rows is the last and 513 the first size of the two paths."""
+    from paper_2511_11062_amd import lite_attn as la
+    n = 128 * tiles - 3
+    g = torch.Generator(device="cuda").manual_seed(1000 * heads + tiles)
+    q, k, v = (torch.randn(1, heads, n, 128, device="cuda", generator=g).to(torch.bfloat16) for _ in range(3))
+    rng = np.random.default_rng(tiles)
+    skip = rng.random((heads, tiles, tiles)) >= live
+    h = la.lite_attn_init_mask(1, heads, n, max_steps=2)
+    out = torch.full_like(q, float("nan"))
+    try:
+        la.lite_attn_set_stream(h, torch.cuda.current_stream().cuda_stream)
+        la.lite_attn_mask_import(h, parity.pack_mask(skip.astype(np.uint8)), 1)
+        la.lite_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), h, -float("inf"), 1)
+        st = la.lite_attn_skip_stats(h, 1)
+        bits = la.lite_attn_mask_export(h)
+    finally:
+        la.lite_attn_free_mask(h)
+    assert st.tiles_skipped_in == int(skip.sum()) and st.tiles_newly_marked == 0
+    assert st.live_list_bytes == 4 * int((~skip & np.pad(skip, ((0, 0), (0, 0), (1, 0)), constant_values=True)[..., :-1]).sum())
+    assert np.array_equal(bits, parity.pack_mask(skip.astype(np.uint8)).ravel())
+    dead = torch.from_numpy(skip).cuda()
+    for x in range(heads):
+        kf, vf = k[0, x].float().t().contiguous(), v[0, x].float()
+        for i0 in range(0, tiles, 32):
+            r0, r1 = 128 * i0, min(n, 128 * (i0 + 32))
+            s = (q[0, x, r0:r1].float() @ kf) * 128 ** -0.5
+            cols = dead[x, i0:i0 + 32].repeat_interleave(128, 0)[:r1 - r0].repeat_interleave(128, 1)[:, :n]
+            ref = torch.nan_to_num(torch.softmax(s.masked_fill_(cols, -float("inf")), dim=1), nan=0.0) @ vf
+            d = (out[0, x, r0:r1].float() - ref).abs()
+            assert torch.isfinite(out[0, x, r0:r1]).all()
+            # weights and result are rounded to bf16 (2^-9 each) of values up to max|O|
+            assert d.max().item() <= 1e-2 * ref.abs().max().clamp(min=1e-3).item(), (x, i0)
