@@ -113,6 +113,14 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     p.seg_mloc = reinterpret_cast<float*>(scratch + sl.seg_mloc);
     p.stats_all = a.stats_all;
     p.stat_words = (int)a.stat_words;
+    // all workgroups start together, or all rows are equally long: nothing to schedule
+    if (g.rows > kFewRows && g.rows <= kSchedRows && !a.fresh) {
+      p.scheduled = 1;
+      p.schedule_only = true;
+      e = launch_fwd(p, false, stream);
+      if (e != hipSuccess) return e;
+      p.schedule_only = false;
+    }
   }
   if (mid) {
     e = hipEventRecord(mid, stream);

@@ -86,9 +86,10 @@ Geometry geometry(const lite_attn_desc_t& d) {
   g.chunks = g.BH * ((g.Tq + kChunkRows - 1) / kChunkRows);
   g.nseg = 0;
   g.per_xcd = ((g.chunks + 7) / 8 + 1) * kChunkRows;
-  if (g.rows <= kFewRows && g.W <= 64) {
-    g.nseg = segments(g, d.flags);
+  if (g.rows <= kFewRows || g.Tk <= kShortTiles) {
+    g.nseg = g.rows <= kFewRows ? segments(g, d.flags) : 1;
     g.per_xcd = (int)((g.rows * g.nseg + 7) / 8);
+    if (g.rows > kFewRows) g.per_xcd += g.per_xcd / 2;  // room for an XCD whose rows are short
   }
   return g;
 }

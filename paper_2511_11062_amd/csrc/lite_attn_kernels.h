@@ -11,9 +11,14 @@ namespace la {
 // Rows of one head that an XCD runs side by side (2 workgroups x 32 CUs): the unit of the row schedule ("chunk").
 constexpr int kChunkRows = 64;
 
-// Calls with at most kFewRows Q-tile rows (all of whose workgroups fit the chip at once) take no lists and no row schedule
-// and may cut rows into segments; the partial results stay small enough for the static scratch array.
+// Calls with few rows or short rows take no Skip-Lists and no V^T (kernel argument FEW; measurements at
+// schedule_rows_kernel): at most kFewRows Q-tile rows -- all of whose workgroups fit the chip at once; they need no schedule
+// and may be cut into segments, whose partial results stay small enough for the static scratch array -- or at most
+// kShortTiles tiles a row.  Beyond kSchedRows rows there are so many rounds of workgroups that the order of the rows
+// does not matter.
 constexpr int kFewRows = 512;
+constexpr int kShortTiles = 192;
+constexpr int kSchedRows = 32768;
 constexpr int kMaxSegments = 16;
 constexpr size_t kMaxSegmentBytes = (size_t)104 << 20;
 
@@ -45,6 +50,10 @@ struct FwdParams {
   // Few rows (nseg > 0, see Geometry): V read as it is, the row's live tiles found from its mask row, no lists and no
   // schedule (per_xcd = workgroups per XCD); the row cut into nseg segments, one workgroup each.
   int nseg = 0;
+  // Not scheduled: the (head, segment, row) triples in order, an eighth of them to each XCD.  schedule_only: launch_fwd
+  // makes the table (slots, xcd_rows) of such a call instead of running it.
+  int scheduled = 0;
+  bool schedule_only = false;
   int fresh = 0;                         // step 0: the mask counts as empty and is overwritten
   const uint16_t* v = nullptr;
   float* seg_o = nullptr;                // [rows][nseg][128][128] O^T partials in accumulator order

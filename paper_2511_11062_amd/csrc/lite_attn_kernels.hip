@@ -286,6 +286,123 @@ __global__ __launch_bounds__(256) void deal_rows_kernel(const uint32_t* __restri
   }
 }
 
+// Row schedule of a call with short rows (FEW, kFewRows < rows <= kSchedRows), from the mask itself, in one launch:
+// workgroup x names the rows of XCD x.  Rows are numbered (head, Q tile); an XCD takes a contiguous range of them -- its
+// workgroups share the K/V of a few heads in its L2 -- such that all ranges hold the same work (live tiles +
+// kRowOverhead per row), bent where it would exceed per_xcd rows.  Within its range the longest rows come first, in
+// kLengthClasses classes, heads and Q tiles in order inside a class (rows of one head and similar length run side by
+// side).  Every workgroup counts the live tiles of all rows (at most three words each).
+// Bound by latency: a dozen dependent steps.  With the V^T pass gone it replaces three launches (ranking, dealing,
+// transposing; 31 us beside 210-305 us of attention for 888 rows of 37 tiles): three steps of that layer 750 -> 627 us,
+// two of 2440 rows x 61 tiles 3850 -> 3661, four of 1320 x 110 (diagonal first) 2262 -> 2165, three of 5120 x 128
+// 10040 -> 9918.  At 256 tiles and more the V^T pass is the better bargain again (its cost goes with the tiles, the
+// transposing reads' with their square): 3072 x 256 dense 5664 -> 5699, 6000 x 300 20.23 -> 20.53 ms, 2400 x 400 10.98
+// -> 11.24 ms.
+constexpr int kLengthClasses = 32;
+constexpr int kSchedThreads = 1024;
+__global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint64_t* __restrict__ bits, int rows,
+                                                                       int Tk, int W, int per_xcd,
+                                                                       uint32_t* __restrict__ slots,
+                                                                       uint32_t* __restrict__ xcd_rows) {
+  constexpr int kWaves = kSchedThreads / 64;
+  __shared__ uint32_t part[kSchedThreads];  // work before each thread's piece of the rows
+  __shared__ uint32_t wave_sum[kWaves];
+  __shared__ uint32_t table[kLengthClasses * kWaves];
+  __shared__ uint32_t class_base[kLengthClasses];
+  __shared__ int first_row[9];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, xcd = blockIdx.x;
+  auto live_tiles = [&](int row) -> uint32_t {
+    uint32_t n = 0;
+    for (int w = 0; w < W; ++w) {
+      uint64_t m = ~bits[(size_t)row * W + w];
+      if (w == W - 1 && (Tk & 63)) m &= (1ull << (Tk & 63)) - 1ull;
+      n += (uint32_t)__popcll(m);
+    }
+    return n;
+  };
+  // work before each row: this thread's contiguous piece, then a scan over the threads
+  const int piece = (rows + kSchedThreads - 1) / kSchedThreads;
+  const int lo = min(rows, tid * piece), hi = min(rows, lo + piece);
+  uint32_t sum = 0;
+  for (int r = lo; r < hi; ++r) sum += live_tiles(r) + kRowOverhead;
+  uint32_t scan = sum;
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t o = __shfl_up(scan, d, 64);
+    if (lane >= d) scan += o;
+  }
+  if (lane == 63) wave_sum[wave] = scan;
+  __syncthreads();
+  uint32_t before = 0, total = 0;
+  for (int x = 0; x < kWaves; ++x) {
+    if (x < wave) before += wave_sum[x];
+    total += wave_sum[x];
+  }
+  part[tid] = before + scan - sum;
+  __syncthreads();
+  // boundaries: XCD y starts at the first row with at least y/8 of the work before it
+  if (tid < 9) {
+    int b = rows;
+    if (tid < 8) {
+      const uint64_t goal = (uint64_t)total * tid;  // in eighths
+      int t = 0;
+      for (int step = kSchedThreads / 2; step > 0; step >>= 1)  // last thread whose piece starts below the goal
+        if (8ull * part[t + step] < goal) t += step;
+      b = min(rows, t * piece);
+      uint64_t work = part[t];
+      while (b < rows && 8 * work < goal) work += live_tiles(b++) + kRowOverhead;
+    }
+    first_row[tid] = b;
+  }
+  for (int x = tid; x < kLengthClasses; x += kSchedThreads) class_base[x] = 0;
+  __syncthreads();
+  // no XCD takes more than per_xcd rows (8 * per_xcd >= rows): bend the boundaries from the first to the last
+  int r0 = 0, r1 = 0;
+  for (int x = 1; x <= xcd + 1; ++x) {
+    r0 = r1;
+    r1 = max(rows - (8 - x) * per_xcd, min(first_row[x], r0 + per_xcd));
+  }
+  const int n = r1 - r0;
+  auto length_class = [&](uint32_t live) -> int { return (int)((uint32_t)(Tk - live) * kLengthClasses / (uint32_t)(Tk + 1)); };
+  // class sizes -> first position of each class
+  for (int x = tid; x < n; x += kSchedThreads) atomicAdd(&class_base[length_class(live_tiles(r0 + x))], 1u);
+  __syncthreads();
+  if (tid == 0) {
+    uint32_t run = 0;
+    for (int x = 0; x < kLengthClasses; ++x) {
+      const uint32_t c = class_base[x];
+      class_base[x] = run;
+      run += c;
+    }
+  }
+  __syncthreads();
+  // positions inside the classes, in row order: kSchedThreads rows at a time
+  for (int x0 = 0; x0 < n; x0 += kSchedThreads) {
+    const int x = x0 + tid;
+    const int mine = x < n ? length_class(live_tiles(r0 + x)) : -1;
+    uint32_t rank = 0;
+#pragma unroll 4
+    for (int y = 0; y < kLengthClasses; ++y) {
+      const uint64_t same = __ballot(mine == y);
+      if (mine == y) rank = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+      if (lane == 0) table[y * kWaves + wave] = (uint32_t)__popcll(same);
+    }
+    __syncthreads();
+    if (mine >= 0) {
+      uint32_t pos = class_base[mine] + rank;
+      for (int y = 0; y < wave; ++y) pos += table[mine * kWaves + y];
+      slots[(size_t)xcd * per_xcd + pos] = (uint32_t)(r0 + x);
+    }
+    __syncthreads();
+    if (tid < kLengthClasses) {
+      uint32_t c = 0;
+      for (int y = 0; y < kWaves; ++y) c += table[tid * kWaves + y];
+      class_base[tid] += c;
+    }
+    __syncthreads();
+  }
+  if (tid == 0) xcd_rows[xcd] = (uint32_t)n;
+}
+
 // V -> V^T pre-pass.  The PV product contracts over the K/V index, so the matrix cores want, per lane, 8 V values
 // of ONE feature d at 8 K/V positions: a 16-byte read from a [d][kv] layout, but a strided gather from V's [kv][d].
 // (gfx950's transposing LDS read, ds_read_b64_tr_b16, delivers only 8 bytes per lane and measured at a third of the
@@ -792,11 +909,17 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   int row, seg = 0;
   if constexpr (FEW) {
-    const int unit = xcd * p.per_xcd + slot;
-    if (unit >= p.rows_total * p.nseg) return;
-    const int u = unit / p.Tq;
-    seg = u % p.nseg;
-    row = (u / p.nseg) * p.Tq + unit % p.Tq;
+    if (p.scheduled) {
+      if (slot >= (int)p.xcd_rows[xcd]) return;
+      row = (int)p.slots[(size_t)xcd * p.per_xcd + slot];
+    } else {
+      const int units = p.rows_total * p.nseg, share = (units + 7) / 8;
+      const int unit = xcd * share + slot;
+      if (slot >= share || unit >= units) return;
+      const int u = unit / p.Tq;
+      seg = u % p.nseg;
+      row = (u / p.nseg) * p.Tq + unit % p.Tq;
+    }
   } else {
     if (slot >= (int)p.xcd_rows[xcd]) return;
     row = (int)p.slots[(size_t)xcd * p.per_xcd + slot];
@@ -1318,6 +1441,11 @@ hipError_t launch_deal_rows(const uint32_t* chunk_work, const uint32_t* order, i
 }
 
 hipError_t launch_fwd(const FwdParams& p, bool immediate, hipStream_t st) {
+  if (p.schedule_only) {
+    hipLaunchKernelGGL(schedule_rows_kernel, dim3(8), dim3(kSchedThreads), 0, st, p.bits, p.rows_total, p.Tk, p.W,
+                       p.per_xcd, const_cast<uint32_t*>(p.slots), const_cast<uint32_t*>(p.xcd_rows));
+    return hipGetLastError();
+  }
   // one workgroup per slot of the schedule table (FEW: per segment); those past an XCD's last row return at once
   const dim3 grid(8 * p.per_xcd), block(Geo<kQB>::kThreads);
   if (p.nseg == 0) {
