@@ -106,6 +106,7 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
   if (few) {
     const ScratchLayout sl = scratch_layout(g);
     p.nseg = g.nseg;
+    p.pair = g.pair;
     p.fresh = a.fresh ? 1 : 0;
     p.v = static_cast<const uint16_t*>(a.v);
     p.seg_o = reinterpret_cast<float*>(scratch + sl.seg_o);

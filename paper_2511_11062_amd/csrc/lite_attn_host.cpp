@@ -47,31 +47,32 @@ size_t segment_bytes(const Geometry& g, int nseg) {
   return nseg > 1 ? sizeof(float) * (size_t)g.rows * (nseg * (128 * 128 + 3 * 128) + (size_t)g.Tk * 128) : 0;
 }
 
-// How many segments (workgroups) a row is cut into when there are few rows.  The chip holds 512 workgroups, two per CU;
-// a whole row per workgroup leaves most of it idle.  Cutting costs a second launch, 64 KB of fp32 partials per segment
-// written and read again, and the walk over the tiles' row maxima in the merge pass.  Minimum of a cost in units of
-// 10 ns whose terms were measured on segments of 1..256 tiles: a tile takes 1.73 us on a CU of its own and 2.7 us with
-// two workgroups on the CU, a further round of workgroups 5 us, the merge 5 us + 22 ns per segment + 0.3 us per tile
-// of a segment.  us per call, whole rows -> segments: 32 rows of 16 tiles 34.4 -> 20.5 (8 segments), 72 x 12 29.0 ->
-// 24.9 (3), 64 x 64 117 -> 46.7 (8), 128 x 32 64.5 -> 46.5 (4), 128 x 128 228 -> 125 (4), 256 x 256 522 -> 432 (4);
-// 192 x 32 and 444 x 37 gain nothing and stay whole.  The immediate variant needs a tile's verdict before its PV
-// product, which a segment cannot know: whole rows.
-int segments(const Geometry& g, int flags) {
-  if (flags & LITE_ATTN_PV_SKIP_IMMEDIATE) return 1;
-  int best = 1;
-  int64_t best_cost = 0;
-  for (int s = 1; s <= kMaxSegments && s <= g.Tk; ++s) {
-    if (segment_bytes(g, s) > kMaxSegmentBytes) break;
-    const int64_t wgs = g.rows * s, tiles = (g.Tk + s - 1) / s, last = wgs % 512;
-    const int64_t full = wgs / 512;
-    int64_t cost = tiles * (270 * full + (last == 0 ? 0 : last <= 256 ? 173 : 270)) + 500 * (full + (last != 0));
-    if (s > 1) cost += 500 + (22 * wgs) / 10 + 30 * tiles;
-    if (s == 1 || cost < best_cost) {
-      best = s;
-      best_cost = cost;
+// How few rows share the chip: how many segments (workgroups) a row is cut into, and whether a workgroup is a pair of
+// groups of four waves that take a column half of every tile each.  The chip holds 512 workgroups of four waves, two
+// per CU, or 256 pairs.  A CU with a single wave per SIMD takes 1.69 us for a tile (a wave's instructions issue one after
+// the other: 2050 cycles for a stage of 1024 matrix cycles), a pair 1.36 us and 2.7 us more per row for its merge in
+// LDS, two workgroups on a CU 2.7 us for a tile each.  Cutting a row costs a second launch, 64 KB of fp32 partials per
+// segment written and read again, and the walk over the tiles' row maxima in the merge pass.  Minimum of a cost in
+// units of 10 ns made of these measurements.  us per call, whole rows -> segments: 32 rows of 16 tiles 33.6 -> 20.4 (8
+// segments), 72 x 12 28.5 -> 24.9 (3), 128 x 128 223 -> 125 (4); -> pairs: 192 x 32 64.3 -> 56.8, 256 x 32 69.1 -> 64.4,
+// 155 x 31 with the immediate variant 77.5 -> 60.4; -> both: 64 x 64 115 -> 46.4 (4), 128 x 32 63.0 -> 45.9 (2).  The
+// immediate variant needs a tile's verdict before its PV product, which a segment cannot know: never cut.
+void share_chip(Geometry& g, int flags) {
+  const int most = (flags & LITE_ATTN_PV_SKIP_IMMEDIATE) ? 1 : std::min(kMaxSegments, g.Tk);
+  int64_t best = -1;
+  for (int s = 1; s <= most && (s == 1 || segment_bytes(g, s) <= kMaxSegmentBytes); ++s) {
+    const int64_t wgs = g.rows * s, tiles = (g.Tk + s - 1) / s, full = wgs / 512, last = wgs % 512;
+    const int64_t merge = s > 1 ? 400 + 22 * wgs / 10 + 15 * tiles : 0;
+    for (int pair = 0; pair < (wgs <= kPairWorkgroups ? 2 : 1); ++pair) {
+      const int64_t tile = pair ? 136 : 270 * full + (last == 0 ? 0 : last <= 256 ? 169 : 270);
+      const int64_t cost = merge + tiles * tile + (pair ? 270 : 500 * (full + (last != 0) - 1));
+      if (best < 0 || cost < best) {
+        best = cost;
+        g.nseg = s;
+        g.pair = pair;
+      }
     }
   }
-  return best;
 }
 }  // namespace
 
@@ -85,9 +86,11 @@ Geometry geometry(const lite_attn_desc_t& d) {
   g.rows = (int64_t)g.BH * g.Tq;
   g.chunks = g.BH * ((g.Tq + kChunkRows - 1) / kChunkRows);
   g.nseg = 0;
+  g.pair = 0;
   g.per_xcd = ((g.chunks + 7) / 8 + 1) * kChunkRows;
   if (g.rows <= kFewRows || g.Tk <= kShortTiles) {
-    g.nseg = g.rows <= kFewRows ? segments(g, d.flags) : 1;
+    g.nseg = 1;
+    if (g.rows <= kFewRows) share_chip(g, d.flags);
     g.per_xcd = (int)((g.rows * g.nseg + 7) / 8);
     if (g.rows > kFewRows) g.per_xcd += g.per_xcd / 2;  // room for an XCD whose rows are short
   }

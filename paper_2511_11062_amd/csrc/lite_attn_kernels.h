@@ -19,6 +19,7 @@ constexpr int kChunkRows = 64;
 constexpr int kFewRows = 512;
 constexpr int kShortTiles = 192;
 constexpr int kSchedRows = 32768;
+constexpr int kPairWorkgroups = 256;
 constexpr int kMaxSegments = 16;
 constexpr size_t kMaxSegmentBytes = (size_t)104 << 20;
 
@@ -50,6 +51,7 @@ struct FwdParams {
   // Few rows (nseg > 0, see Geometry): V read as it is, the row's live tiles found from its mask row, no lists and no
   // schedule (per_xcd = workgroups per XCD); the row cut into nseg segments, one workgroup each.
   int nseg = 0;
+  int pair = 0;
   // Not scheduled: the (head, segment, row) triples in order, an eighth of them to each XCD.  schedule_only: launch_fwd
   // makes the table (slots, xcd_rows) of such a call instead of running it.
   int scheduled = 0;
@@ -71,6 +73,7 @@ struct Geometry {
   int BH;          // batch * heads
   int64_t rows;    // BH * Tq
   int chunks;      // BH * ceil(Tq / kChunkRows): units of the row schedule
+  int pair;        // workgroups of two groups of four waves (at most kPairWorkgroups of them)
   int nseg;        // > 0: few rows, each cut into this many segments (one workgroup each); 0: rows scheduled whole
   int per_xcd;     // row slots per XCD in the schedule table: (ceil(chunks / 8) + 1) chunks
 };

@@ -36,7 +36,10 @@
 //   * no V^T: the V fragments come from V as it lies in memory through transposing LDS reads (ds_read_b64_tr_b16), 16 LDS
 //     instructions more per stage, the same LDS cycles (no bank conflicts): 1.8 % of the kernel's time on the 12-head
 //     N = 32760 dense step, against a launch and a pass over V;
-//   * a row may be cut into segments, one workgroup each (the rule and its measurements: segments() in
+//   * a workgroup may be a PAIR of groups of four waves, each with its own stage buffers and one 64-column half of every
+//     tile (a CU with one wave per SIMD issues too slowly to keep the matrix cores busy); the groups' results meet in LDS
+//     at the end, their row maxima once per tile, for the predicate;
+//   * a row may be cut into segments, one workgroup each (the rule and its measurements: share_chip() in
 //     lite_attn_host.cpp); merge_segments_kernel adds up the partial results.  The predicate stays exact: the
 //     segments record every tile's row maxima, and the merge pass judges them against the running maximum carried
 //     over the segments, the value a single pass would have had.
@@ -76,6 +79,10 @@ constexpr int kFlagsOff = 4 * kStageBytes;  // 8 ints [tile parity][wave] + 64 d
 constexpr int kFiredOff = kFlagsOff + 8 * 4 + 64 * 4;  // W uint64: mask bits this workgroup set during the call
 constexpr int kMaxMaskWords = 256;                     // ceil(16383 / 64)
 constexpr int kLdsBytes = kFiredOff + 8 * kMaxMaskWords;
+// PAIR: two sets of stage buffers, then the flags, then group 1's row maxima [tile parity][128]
+constexpr int kPairFlagsOff = 8 * kStageBytes;
+constexpr int kPairXchOff = kPairFlagsOff + 8 * 4 + 64 * 4;
+constexpr int kPairLdsBytes = kPairXchOff + 2 * kTile * 4;
 constexpr int kORow = 272;        // bytes per O row in the epilogue staging (reuses the stage buffers)
 
 constexpr int kRowsPerWave = 8;  // Q-tile rows compacted by one wave of compact_skiplist
@@ -528,6 +535,7 @@ struct Lane {
   uint32_t lds_wave;  // LDS address of this wave's first DMA piece inside stage buffer 0 (wave-uniform)
   uint32_t stride2;   // stride_n * 2 (bytes per token row)
   int hi;
+  int col;            // PAIR: first column of this group's half of a tile (wave-uniform)
   bool qvalid[QB];
   float c;            // scale * log2(e)
   float scale, thr;
@@ -546,8 +554,12 @@ struct State {
   float mc_ref[QB];  // reference of the exponentials, times c: P~ = exp2(S c - mc_ref); trails m_run c by < kLazyLog2
   // IMM only: row sum of the tile in flight (added to l_run once the tile is known not to have fired), and the
   // rescale factor of the previous stage, which O^T has not seen yet because its PV product runs a stage later
-  float l_pend[QB], alpha_prev[QB];
+  // (PAIR: of the two tiles in flight, by parity)
+  float l_pend[QB][2], alpha_prev[QB];
   bool grew_prev;
+  // PAIR only: this wave's row maxima of the previous tile (its half of the columns), and the running row maximum over
+  // both halves
+  float mloc_prev, m_all;
 };
 
 // Buffer descriptor (V#) of a raw buffer of `bytes` bytes at `ptr`: loads at offsets >= bytes return zero.
@@ -692,6 +704,8 @@ __device__ __forceinline__ bf16x8 load_frag(int k, const uint32_t (&kread)[8], c
 // cost 64 multiplies per lane wherever any of a wave's 32 rows found a new one: 1.5 % of the dense 12-head N = 32760
 // step (5571 -> 5489 us), 6 % of the tiny layer's.
 constexpr float kLazyLog2 = 8.f;
+constexpr float kNoRef = -1e38f;  // reference before the first tile; finite, so that a column half without valid columns
+                                  // weighs exp2(-inf + 1e38) = 0
 constexpr int kPrefetch = 3;  // LDS fragments in flight ahead of the MFMA that consumes them
 constexpr int kDmaGap = 2;    // steps between two DMA issues of a stage
 
@@ -708,16 +722,20 @@ constexpr int kDmaGap = 2;    // steps between two DMA issues of a stage
 // H), issued only if pv_on (wave-uniform: the tile it belongs to did not fire); the V^T stage loaded here is that of
 // stage s-1 (tile j_v, the other half), into the buffer of the other parity.
 struct NoOp {
-  __device__ __forceinline__ void operator()() const {}
+  template <class... A>
+  __device__ __forceinline__ void operator()(A...) const {}
 };
 
 // verdict_load / verdict_commit (first stage of a tile, deferred marking only): the combine of the PREVIOUS tile's four
 // per-wave predicate results, spread over this stage -- its LDS read is issued at step 0 and used at step 12, so that
 // the wave that does it never waits for it.
-template <int QB, int H, bool IMM, bool VROWS, class VLoad = NoOp, class VCommit = NoOp>
+// PAIR: a stage is this group's half of a whole tile (H = parity of the tile, j_nxt = the tile two ahead, j_v the
+// previous one); verdict_end receives the half's row maxima at the end of the stage.
+template <int QB, int H, bool IMM, bool VROWS, bool PAIR, class VLoad = NoOp, class VCommit = NoOp, class VEnd = NoOp>
 __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, char* smem, int j_cur, int j_nxt,
                                       int* flag_slot, int j_tail, int j_v = 0, bool pv_on = true,
-                                      VLoad verdict_load = VLoad(), VCommit verdict_commit = VCommit()) {
+                                      VLoad verdict_load = VLoad(), VCommit verdict_commit = VCommit(),
+                                      VEnd verdict_end = VEnd()) {
   f32x16(&cur)[QB][2] = H ? st.sB : st.sA;
   f32x16(&nxt)[QB][2] = H ? st.sA : st.sB;
   uint32_t(&pwc)[QB][16] = (IMM && !H) ? st.pw0 : st.pw;
@@ -725,9 +743,9 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
   // ---- DMA: K of stage s+2 (next tile, same half) and V of this stage go into the buffers of parity H; the
   // loads are issued one at a time between the steps below (kDmaGap steps apart) so that a full memory
   // instruction queue does not hold up the MFMAs behind it ----
-  const u32x4 krs = rebase(ln.krsrc, (uint32_t)(j_nxt * kTile + H * kSub) * ln.stride2);
-  const u32x4 vrs = rebase(ln.vrsrc, (uint32_t)(IMM ? j_v * kTile + (H ^ 1) * kSub : j_cur * kTile + H * kSub) *
-                                         (VROWS ? ln.stride2 : 2u));
+  const int col = PAIR ? ln.col : H * kSub, col_v = PAIR ? ln.col : IMM ? (H ^ 1) * kSub : H * kSub;
+  const u32x4 krs = rebase(ln.krsrc, (uint32_t)(j_nxt * kTile + col) * ln.stride2);
+  const u32x4 vrs = rebase(ln.vrsrc, (uint32_t)((IMM ? j_v : j_cur) * kTile + col_v) * (VROWS ? ln.stride2 : 2u));
   constexpr int kVDst = kVOff + (IMM ? (H ^ 1) : H) * kStageBytes;  // V^T buffer the DMA of this stage fills
   constexpr int kC = Geo<QB>::kChunks;
 
@@ -746,7 +764,7 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
   // and branch per stage, taken for one tile per row at most).  This lane's element r of block blk is column
   // 32*blk + 8*(r>>2) + (r&3) + 4*hi of the stage: the lane-independent part is compared with one per-lane limit.
   if (j_cur == j_tail) {
-    int lim = ln.N - (j_cur * kTile + H * kSub) - 4 * ln.hi;
+    int lim = ln.N - (j_cur * kTile + col) - 4 * ln.hi;
     asm volatile("" : "+v"(lim));  // keeps the compares inside this branch (else their lane masks are formed ahead of
                                    // time, for every stage, and held in scalar registers)
 #pragma unroll
@@ -801,7 +819,8 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
   auto vector_part = [&](auto kc, auto qbc) __attribute__((always_inline)) {
     constexpr int k = decltype(kc)::value;
     constexpr int qb = decltype(qbc)::value;
-    float& lsum = IMM ? st.l_pend[qb] : st.l_run[qb];  // the row sum this stage adds to
+    constexpr int pend = PAIR ? H : 0;
+    float& lsum = IMM ? st.l_pend[qb][pend] : st.l_run[qb];  // the row sum this stage adds to
     // ---- vector ALU: slice k of the online softmax of stage s (raw dot products; 1/sqrt(d) folded into c) ----
     {
       if (k < 4) {  // m_local: partial row maxima over 8 of this lane's 32 scores
@@ -813,18 +832,19 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
       } else if (k == 4) {
         mx[qb] = other_half_max(fmaxf(fmaxf(pm[qb][0], pm[qb][1]), fmaxf(pm[qb][2], pm[qb][3])));
       } else if (k == 5) {  // m_ij = max(m_{i,j-1}, m_local) and the rescale factor of the earlier stages
-        st.mloc_tile[qb] = H ? fmaxf(st.mloc_tile[qb], mx[qb]) : mx[qb];
+        if (!PAIR) st.mloc_tile[qb] = H ? fmaxf(st.mloc_tile[qb], mx[qb]) : mx[qb];
         st.m_run[qb] = fmaxf(st.m_run[qb], mx[qb]);
         // the exponent's reference follows the maximum only when some row of the wave has outgrown it by kLazyLog2
         const float up = st.m_run[qb] * ln.c;
         if (__any(up > st.mc_ref[qb] + kLazyLog2)) {
           alpha[qb] = __builtin_amdgcn_exp2f(st.mc_ref[qb] - up);
           st.l_run[qb] *= alpha[qb];
-          if (IMM && H) st.l_pend[qb] *= alpha[qb];
+          if (IMM && PAIR) st.l_pend[qb][H ^ 1] *= alpha[qb];
+          if (IMM && !PAIR && H) st.l_pend[qb][0] *= alpha[qb];
           st.mc_ref[qb] = up;
           grew = true;
         }
-        if (IMM && !H) st.l_pend[qb] = 0.f;
+        if (IMM && (PAIR || !H)) st.l_pend[qb][pend] = 0.f;
       } else if (k < 30) {
         // P~ = exp(S - m_ij), packed to bf16: 16 pairs of scores over 24 steps, four vector instructions per step
         // (a cycle of three steps does two pairs: exp exp | pack+sum, exp | exp, pack+sum)
@@ -851,13 +871,14 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
           pwc[qb][eB] = w;
         }
       } else if (k == 30) {
-        if (H) {  // skip predicate of the whole 128-column tile, once its second half is in (eq. sparge_cond)
+        if (!PAIR && H) {  // skip predicate of the whole 128-column tile, once its second half is in (eq. sparge_cond)
           const float g = (st.mloc_tile[qb] - st.m_run[qb]) * ln.scale;  // this row; max over rows = ballot below
           ok = ok && (!ln.qvalid[qb] || (g <= ln.thr));
         }
       }
     }
-    if (H && k == 31 && qb == QB - 1)
+    if (PAIR && k == 30) verdict_end(mx[qb]);
+    if (!PAIR && H && k == 31 && qb == QB - 1)
       *flag_slot = __all(ok) ? 1 : 0;  // lane 0: the wave's slot; other lanes: a dummy word each
     if (k == 12 && qb == QB - 1) verdict_commit();
   };
@@ -894,11 +915,14 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
   __syncthreads();
 }
 
-template <int QB, bool IMM, bool FEW>
-__global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kernel(const FwdParams p) {
+template <int QB, bool IMM, bool FEW, bool PAIR>
+__global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void lite_attn_fwd_kernel(const FwdParams p) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  constexpr int kWaves = Geo<QB>::kWaves, kThreads = Geo<QB>::kThreads, kChunks = Geo<QB>::kChunks;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  static_assert(!PAIR || (FEW && QB == 1), "two groups of four waves: only with few rows");
+  constexpr int kWaves = Geo<QB>::kWaves, kChunks = Geo<QB>::kChunks;
+  constexpr int kThreads = Geo<QB>::kThreads * (PAIR ? 2 : 1);
+  const int tid = threadIdx.x, lane = tid & 63, wave = (tid >> 6) & (kWaves - 1);
+  const int grp = PAIR ? __builtin_amdgcn_readfirstlane(tid >> 8) : 0;  // PAIR: which half of every tile's columns
   const int lq = lane & 31;
 
   // Consecutive workgroup ids land on different XCDs (id % 8): workgroup `slot` of an XCD computes the row that the
@@ -949,7 +973,9 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
   // the Skip-List is read-only here: constant address space makes these wave-uniform reads scalar loads
   typedef const __attribute__((address_space(4))) uint32_t* const_u32_ptr;
   const_u32_ptr runs = (const_u32_ptr)(p.runs + (size_t)row * p.run_stride);
-  int* flags = reinterpret_cast<int*>(smem + kFlagsOff);
+  int* flags = reinterpret_cast<int*>(smem + (PAIR ? kPairFlagsOff : kFlagsOff));
+  float* xch = reinterpret_cast<float*>(smem + kPairXchOff);  // PAIR: group 1's row maxima, by parity of the tile
+  char* const stages = smem + (PAIR ? grp * 4 * kStageBytes : 0);  // this group's stage buffers
   // mask bits set by this workgroup during the call (thread 0 writes them, wave 0 reads them in the epilogue)
   uint64_t* fired_bits = reinterpret_cast<uint64_t*>(smem + kFiredOff);
   if (!FEW && p.build_next)
@@ -971,7 +997,8 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
   const uint32_t vt_row_bytes = (uint32_t)p.Tk * kTile * 2;  // one feature row of V^T: n_pad bf16
   ln.vrsrc = FEW ? make_rsrc(p.v + base, head_bytes)
                  : make_rsrc(p.vt + (size_t)bh * 128 * ((size_t)p.Tk * kTile), 128u * vt_row_bytes);
-  ln.lds_wave = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(LA_LDS char*)smem + 1024 * kChunks * wave);
+  ln.lds_wave = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(LA_LDS char*)stages + 1024 * kChunks * wave);
+  ln.col = grp * kSub;
 #pragma unroll
   for (int x = 0; x < kChunks; ++x) {
     const int r = 4 * (kChunks * wave + x) + (lane >> 4);  // row inside the stage that this lane's piece belongs to
@@ -985,7 +1012,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
     const int rv = 8 * (kChunks * wave + x) + (lane >> 3), pv = lane & 7;
     ln.vdma[x] = (uint32_t)rv * vt_row_bytes + 16 * (pv ^ ((rv >> 1) & 7));
   }
-  const uint32_t lds0 = (uint32_t)(size_t)(LA_LDS char*)smem;
+  const uint32_t lds0 = (uint32_t)(size_t)(LA_LDS char*)stages;
 #pragma unroll
   for (int kk = 0; kk < 8; ++kk) ln.kread[kk] = lds0 + lq * 256 + ((32 * kk) ^ (16 * (ln.hi ^ (lq & 15))));
 #pragma unroll
@@ -1000,11 +1027,21 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
   const bool q_pinned = p.protect_len > 0 && i * kTile < p.protect_start + p.protect_len &&
                         p.protect_start < min(N, (i + 1) * kTile);
 
+  // whether tile (i, j) meets the pinned token range; FEW: asked only of tiles that would fire, with the kernel arguments
+  // read again (scalar registers are short in the main loop)
+  typedef const __attribute__((address_space(4))) FwdParams* const_params_ptr;
+  auto pinned = [&](int j) -> bool {
+    const_params_ptr a = (const_params_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(a));
+    const int lo = a->protect_start, hi = lo + a->protect_len, n = a->N;
+    return hi > lo && ((i * kTile < hi && lo < min(n, (i + 1) * kTile)) || (j * kTile < hi && lo < min(n, (j + 1) * kTile)));
+  };
+
   State<QB, IMM> st;
   st.grew_prev = false;
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
-    st.l_pend[qb] = 0.f;
+    st.l_pend[qb][0] = st.l_pend[qb][1] = 0.f;
     st.alpha_prev[qb] = 1.f;
     const int qrow = i * kTile + 32 * (QB * wave + qb) + lq;
     ln.qvalid[qb] = qrow < N;
@@ -1023,10 +1060,11 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
 #pragma unroll
     for (int e = 0; e < 16; ++e) st.pw[qb][e] = 0u;
     st.m_run[qb] = -INFINITY;  // running row max of the raw dot products (m_{i,j-1} * sqrt(d))
-    st.mc_ref[qb] = -INFINITY;
+    st.mc_ref[qb] = kNoRef;
     st.l_run[qb] = 0.f;        // this lane's half of the row sum
     st.mloc_tile[qb] = -INFINITY;
   }
+  st.mloc_prev = st.m_all = -INFINITY;
   unsigned newly = 0;
 
   // lane 0 writes the wave's predicate flag, every other lane a private dummy word (keeps the stage branch-free)
@@ -1069,10 +1107,11 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
     // prologue: the odd V^T buffer is read (times P~ = 0) before it is first filled: make it finite; K of
     // stages 0 and 1; then S^T(0)
     if (!IMM)
-      for (int x = tid; x < kStageBytes / 16; x += kThreads)
-        *reinterpret_cast<uint4*>(smem + kVOff + kStageBytes + 16 * x) = uint4{0u, 0u, 0u, 0u};
-    dma_stage<QB, kKOff>(ln.krsrc, ln.kdma, (uint32_t)(j_cur * kTile) * ln.stride2, ln.lds_wave);
-    dma_stage<QB, kKOff + kStageBytes>(ln.krsrc, ln.kdma, (uint32_t)(j_cur * kTile + kSub) * ln.stride2, ln.lds_wave);
+      for (int x = tid & (64 * kWaves - 1); x < kStageBytes / 16; x += 64 * kWaves)
+        *reinterpret_cast<uint4*>(stages + kVOff + kStageBytes + 16 * x) = uint4{0u, 0u, 0u, 0u};
+    dma_stage<QB, kKOff>(ln.krsrc, ln.kdma, (uint32_t)(j_cur * kTile + ln.col) * ln.stride2, ln.lds_wave);
+    dma_stage<QB, kKOff + kStageBytes>(
+        ln.krsrc, ln.kdma, (uint32_t)(PAIR ? j_nxt * kTile + ln.col : j_cur * kTile + kSub) * ln.stride2, ln.lds_wave);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     mma_qk<QB>(st.sA, st.qf, kKOff, ln.kread);
@@ -1084,9 +1123,14 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
       const int4 f = *reinterpret_cast<const int4*>(flags + (t & 1) * 4);
       static_assert(!IMM || kWaves == 4, "four per-wave flags per tile");
       const int all = __builtin_amdgcn_readfirstlane(f.x & f.y & f.z & f.w);
-      const bool k_pinned = p.protect_len > 0 && j * kTile < p.protect_start + p.protect_len &&
-                            p.protect_start < min(N, (j + 1) * kTile);
-      const bool fired = all && !q_pinned && !k_pinned;
+      bool fired;
+      if constexpr (FEW) {
+        fired = all && !pinned(j);
+      } else {
+        const bool k_pinned = p.protect_len > 0 && j * kTile < p.protect_start + p.protect_len &&
+                              p.protect_start < min(N, (j + 1) * kTile);
+        fired = all && !q_pinned && !k_pinned;
+      }
       if constexpr (FEW) {
         if (fired && tid == (j >> 6)) fired_word |= 1ull << (j & 63);
       } else if (tid == 0 && fired) {
@@ -1099,22 +1143,20 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
     // Deferred marking: the per-wave results of a finished tile meet in LDS; wave 0 combines them and updates the
     // mask, not at the barrier that ends the tile (it would be late for the next stage by the latency of an LDS read,
     // and the other three waves would wait for it at the next barrier) but during the first stage of the next tile.
-    const bool wave0 = __builtin_amdgcn_readfirstlane(wave) == 0;
+    const bool wave0 = __builtin_amdgcn_readfirstlane(tid >> 6) == 0;
     int4 vflags = {0, 0, 0, 0};
     const int* v_slot = flags;  // LDS slot of the tile whose verdict is pending
     int v_j = -1;               // its K/V tile index (-1: none pending)
     auto mark_if_fired = [&](int all, int j) {
-      if (tid == (FEW ? j >> 6 : 0) && all) {
+      if constexpr (FEW) {
+        if (__builtin_amdgcn_readfirstlane(all) && !pinned(j) && tid == (j >> 6)) fired_word |= 1ull << (j & 63);
+      } else if (tid == 0 && all) {
         const bool k_pinned = p.protect_len > 0 && j * kTile < p.protect_start + p.protect_len &&
                               p.protect_start < min(N, (j + 1) * kTile);
         if (!q_pinned && !k_pinned) {
-          if constexpr (FEW) {
-            fired_word |= 1ull << (j & 63);
-          } else {
-            atomicOr(reinterpret_cast<unsigned long long*>(p.bits + (size_t)row * p.W + (j >> 6)), 1ull << (j & 63));
-            fired_bits[j >> 6] |= 1ull << (j & 63);
-            ++newly;
-          }
+          atomicOr(reinterpret_cast<unsigned long long*>(p.bits + (size_t)row * p.W + (j >> 6)), 1ull << (j & 63));
+          fired_bits[j >> 6] |= 1ull << (j & 63);
+          ++newly;
         }
       }
     };
@@ -1124,7 +1166,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
     auto verdict_load = [&]() {
       static_assert(IMM || kWaves == 4, "four per-wave flags per tile");
       if (split) {
-        if (v_j >= 0 && ln.hi == 0 && p.thr > -INFINITY) mloc_out[v_j * kTile] = st.mloc_tile[0];
+        if (v_j >= 0 && ln.hi == 0 && ln.thr > -INFINITY) mloc_out[v_j * kTile] = st.mloc_tile[0];
         return;
       }
       if (wave0) vflags = *reinterpret_cast<const int4*>(v_slot);
@@ -1134,29 +1176,167 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
     };
     bool pv_on = false;  // IMM: the previous tile did not fire, its PV products are due
     int j_prev = j_cur;
-    for (int t = t_lo; t < t_hi; ++t) {
+    if constexpr (PAIR) {
+      // One stage per tile.  Tile t's verdict: group 1's row maxima reach LDS at the end of stage t; during stage t+1
+      // group 0 joins them with its own, judges the tile and puts the four per-wave results into the flags (split
+      // rows: stores the joint maxima for the merge pass instead); during stage t+2 wave 0 updates the mask (IMM: all
+      // waves read the verdict before stage t+2, which holds the tile's PV product).
+      int j_pp = -1;  // the tile before the previous one
+      j_prev = -1;
+      float other = 0.f;
+      auto join = [&](int parity) {  // group 0: the previous tile's maxima over all columns, and its judgement
+        if (grp != 0) return;
+        const float mloc = fmaxf(st.mloc_prev, other);
+        st.m_all = fmaxf(st.m_all, mloc);
+        if (split) {
+          if (ln.hi == 0 && ln.thr > -INFINITY) mloc_out[j_prev * kTile] = mloc;
+        } else {
+          const bool ok = __all(!ln.qvalid[0] || (mloc - st.m_all) * ln.scale <= ln.thr);
+          *(lane == 0 ? flags + 4 * parity + wave : flags + 8 + lane) = ok ? 1 : 0;
+        }
+      };
+      auto imm_verdict = [&](int parity, float pend) {  // of tile j_pp: marks it, or adds its row sums
+        pv_on = false;
+        if (j_pp < 0) return;
+        const int4 f = *reinterpret_cast<const int4*>(flags + 4 * parity);
+        const int all = __builtin_amdgcn_readfirstlane(f.x & f.y & f.z & f.w);
+        pv_on = !(all && !pinned(j_pp));
+        if (pv_on)
+          st.l_run[0] += pend;
+        else if (tid == (j_pp >> 6))
+          fired_word |= 1ull << (j_pp & 63);
+      };
+      auto one = [&](auto par) __attribute__((always_inline)) {
+        constexpr int H = decltype(par)::value;
+        advance();
+        const int j_nn = c_j;
+        if constexpr (IMM) imm_verdict(H, st.l_pend[0][H]);
+        auto load = [&]() {
+          if (grp == 0 && j_prev >= 0) other = xch[(H ^ 1) * kTile + 32 * wave + lq];
+          if (!IMM && !split && wave0) vflags = *reinterpret_cast<const int4*>(flags + 4 * H);
+        };
+        auto commit = [&]() {
+          if (j_prev >= 0) join(H ^ 1);
+          if (!IMM && !split && wave0 && j_pp >= 0) mark_if_fired(vflags.x & vflags.y & vflags.z & vflags.w, j_pp);
+        };
+        auto end = [&](float mx) {
+          st.mloc_prev = mx;
+          if (grp == 1 && ln.hi == 0) xch[H * kTile + 32 * wave + lq] = mx;
+        };
+        stage<QB, H, IMM, true, true>(st, ln, smem, j_cur, j_nn, flags, j_tail, max(j_prev, 0), !IMM || pv_on, load,
+                                      commit, end);
+        j_pp = j_prev;
+        j_prev = j_cur;
+        j_cur = j_nxt;
+        j_nxt = j_nn;
+      };
+      int last = 0;  // parity of the last tile
+      for (int t = t_lo;;) {
+        last = 0;
+        one(std::integral_constant<int, 0>{});
+        if (++t >= t_hi) break;
+        last = 1;
+        one(std::integral_constant<int, 1>{});
+        if (++t >= t_hi) break;
+      }
+      // drain: the last tile's PV product (IMM: the last two tiles'), its verdict and that of the tile before it
+      if (IMM)
+        dma_stage<QB, kVOff>(ln.vrsrc, ln.vdma, (uint32_t)(j_prev * kTile + ln.col) * ln.stride2,
+                             ln.lds_wave + (uint32_t)last * kStageBytes);
+      if (grp == 0) other = xch[last * kTile + 32 * wave + lq];
+      if constexpr (IMM) {
+        imm_verdict(last ^ 1, last ? st.l_pend[0][0] : st.l_pend[0][1]);
+      } else if (!split && wave0 && j_pp >= 0) {
+        vflags = *reinterpret_cast<const int4*>(flags + 4 * (last ^ 1));
+        mark_if_fired(vflags.x & vflags.y & vflags.z & vflags.w, j_pp);
+      }
+      join(last);
+      if (!IMM) mma_pv<QB, true>(st.oacc, st.pw, kVOff + last * kStageBytes, ln.vread);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      j_pp = j_prev;
+      if constexpr (IMM) {
+        auto drain = [&](const uint32_t (&p_prev)[QB][16], const uint32_t (&p_last)[QB][16]) {
+          if (pv_on) mma_pv<QB, true>(st.oacc, p_prev, kVOff + (last ^ 1) * kStageBytes, ln.vread);
+          if (st.grew_prev) {
+#pragma unroll
+            for (int db = 0; db < 4; ++db)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) st.oacc[0][db][r] *= st.alpha_prev[0];
+          }
+          imm_verdict(last, last ? st.l_pend[0][1] : st.l_pend[0][0]);
+          if (pv_on) mma_pv<QB, true>(st.oacc, p_last, kVOff + last * kStageBytes, ln.vread);
+        };
+        if (last)
+          drain(st.pw0, st.pw);
+        else
+          drain(st.pw, st.pw0);
+      } else if (!split && wave0) {
+        vflags = *reinterpret_cast<const int4*>(flags + 4 * last);
+        mark_if_fired(vflags.x & vflags.y & vflags.z & vflags.w, j_prev);
+      }
+      __syncthreads();
+      // group 1's share joins group 0's: accumulators as the lanes hold them, through group 1's stage buffers
+      float4* hand = reinterpret_cast<float4*>(smem + 4 * kStageBytes) + (size_t)wave * 1024 + lane;
+      float* hand_stat = xch;  // [reference, row sum][128]
+      const float l_half = other_half_sum(st.l_run[0]);
+      if (grp == 1) {
+#pragma unroll
+        for (int g = 0; g < 16; ++g) {
+          const f32x16& a = st.oacc[0][g >> 2];
+          const int r = 4 * (g & 3);
+          hand[64 * g] = float4{a[r], a[r + 1], a[r + 2], a[r + 3]};
+        }
+        if (ln.hi == 0) {
+          hand_stat[32 * wave + lq] = st.mc_ref[0];
+          hand_stat[kTile + 32 * wave + lq] = l_half;
+        }
+      }
+      __syncthreads();
+      if (grp == 0) {
+        const float m1 = hand_stat[32 * wave + lq], l1 = hand_stat[kTile + 32 * wave + lq];
+        const float top = fmaxf(st.mc_ref[0], m1);
+        const float f0 = __builtin_amdgcn_exp2f(st.mc_ref[0] - top), f1 = __builtin_amdgcn_exp2f(m1 - top);
+        st.mc_ref[0] = top;
+        st.l_run[0] = 0.5f * (f0 * l_half + f1 * l1);  // (each half of the wave: half of the row sum)
+        st.m_run[0] = st.m_all;
+#pragma unroll
+        for (int g = 0; g < 16; ++g) {
+          f32x16& a = st.oacc[0][g >> 2];
+          const int r = 4 * (g & 3);
+          const float4 b = hand[64 * g];
+          a[r] = f0 * a[r] + f1 * b.x;
+          a[r + 1] = f0 * a[r + 1] + f1 * b.y;
+          a[r + 2] = f0 * a[r + 2] + f1 * b.z;
+          a[r + 3] = f0 * a[r + 3] + f1 * b.w;
+        }
+      }
+    }
+    for (int t = t_lo; !PAIR && t < t_hi; ++t) {
       advance();
       const int j_nn = c_j;  // needed one tile from now
       int* fs = (t & 1) ? flag_slot1 : flag_slot0;
-      if constexpr (IMM) {
-        stage<QB, 0, true, FEW>(st, ln, smem, j_cur, j_nxt, fs, j_tail, j_prev, pv_on);
-        stage<QB, 1, true, FEW>(st, ln, smem, j_cur, j_nxt, fs, j_tail, j_cur, pv_on);
+      if constexpr (PAIR) {
+      } else if constexpr (IMM) {
+        stage<QB, 0, true, FEW, false>(st, ln, smem, j_cur, j_nxt, fs, j_tail, j_prev, pv_on);
+        stage<QB, 1, true, FEW, false>(st, ln, smem, j_cur, j_nxt, fs, j_tail, j_cur, pv_on);
         pv_on = !finish_tile_imm(t, j_cur);
         if (pv_on) {
 #pragma unroll
-          for (int qb = 0; qb < QB; ++qb) st.l_run[qb] += st.l_pend[qb];
+          for (int qb = 0; qb < QB; ++qb) st.l_run[qb] += st.l_pend[qb][0];
         }
         j_prev = j_cur;
       } else {
-        stage<QB, 0, false, FEW>(st, ln, smem, j_cur, j_nxt, fs, j_tail, 0, true, verdict_load, verdict_commit);
-        stage<QB, 1, false, FEW>(st, ln, smem, j_cur, j_nxt, fs, j_tail);
+        stage<QB, 0, false, FEW, false>(st, ln, smem, j_cur, j_nxt, fs, j_tail, 0, true, verdict_load, verdict_commit);
+        stage<QB, 1, false, FEW, false>(st, ln, smem, j_cur, j_nxt, fs, j_tail);
         v_slot = flags + (t & 1) * 4;
         v_j = j_cur;
       }
       j_cur = j_nxt;
       j_nxt = j_nn;
     }
-    if constexpr (IMM) {
+    if constexpr (PAIR) {
+    } else if constexpr (IMM) {
       // drain: the second V^T stage of the last tile is still to be loaded; then both of its PV products, the
       // rescale factor of its second stage in between
       dma_stage<QB, kVOff + kStageBytes>(ln.vrsrc, ln.vdma, (uint32_t)(j_prev * kTile + kSub) * (FEW ? ln.stride2 : 2u), ln.lds_wave);
@@ -1182,7 +1362,6 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
   }
   // (the kernel arguments used from here on are read again from the argument segment instead of being kept in scalar
   // registers across the main loop)
-  typedef const __attribute__((address_space(4))) FwdParams* const_params_ptr;
   const_params_ptr e = (const_params_ptr)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(e));
   if constexpr (FEW) {
@@ -1192,6 +1371,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
       const size_t s = (size_t)row * e->nseg + seg;
       static_assert(QB == 1, "one Q block per wave");
       float* po = e->seg_o + (s * 4 + wave) * 4096 + 4 * lane;
+      if (grp != 0) return;
       if (t_hi > t_lo)
 #pragma unroll
         for (int g = 0; g < 16; ++g) {
@@ -1208,7 +1388,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
       }
       return;
     }
-    if (wave == 0) {
+    if (tid < 64) {
       if (lane < e->W && (e->fresh || fired_word)) {
         uint64_t* word = e->bits + (size_t)row * e->W + lane;
         *word = (e->fresh ? 0ull : *word) | fired_word;
@@ -1223,6 +1403,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads, 2 / QB) void lite_attn_fwd_kerne
   char* sO = smem;
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
+    if (grp != 0) break;
     const float l = other_half_sum(st.l_run[qb]);
     const float inv = (l > 0.f) ? 1.f / l : 0.f;
 #pragma unroll
@@ -1297,7 +1478,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const Fwd
       }
 #pragma unroll
       for (int u = 0; u < kAhead; ++u) {
-        if (s0 + u >= nseg || m[u] == -INFINITY) continue;  // a segment without tiles has written no O
+        if (s0 + u >= nseg || m[u] == kNoRef) continue;  // a segment without tiles has written no O
         const float f = __builtin_amdgcn_exp2f(m[u] - top);
         l += f * ls[u];
         a.x += f * x[u].x; a.y += f * x[u].y; a.z += f * x[u].z; a.w += f * x[u].w;
@@ -1411,12 +1592,15 @@ static size_t order_lds_bytes(int Tq, int Tk) {
 }
 
 hipError_t prepare_fwd() {
-  const void* fused[] = {reinterpret_cast<const void*>(lite_attn_fwd_kernel<kQB, false, false>),
-                         reinterpret_cast<const void*>(lite_attn_fwd_kernel<1, true, false>),
-                         reinterpret_cast<const void*>(lite_attn_fwd_kernel<1, false, true>),
-                         reinterpret_cast<const void*>(lite_attn_fwd_kernel<1, true, true>)};
+  const void* fused[] = {reinterpret_cast<const void*>(lite_attn_fwd_kernel<kQB, false, false, false>),
+                         reinterpret_cast<const void*>(lite_attn_fwd_kernel<1, true, false, false>),
+                         reinterpret_cast<const void*>(lite_attn_fwd_kernel<1, false, true, false>),
+                         reinterpret_cast<const void*>(lite_attn_fwd_kernel<1, true, true, false>),
+                         reinterpret_cast<const void*>(lite_attn_fwd_kernel<1, false, true, true>),
+                         reinterpret_cast<const void*>(lite_attn_fwd_kernel<1, true, true, true>)};
   for (const void* f : fused) {
-    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, fwd_lds_bytes());
+    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       std::max(kLdsBytes, kPairLdsBytes));
     if (e != hipSuccess) return e;
   }
   return hipFuncSetAttribute(reinterpret_cast<const void*>(order_rows_kernel),
@@ -1450,15 +1634,21 @@ hipError_t launch_fwd(const FwdParams& p, bool immediate, hipStream_t st) {
   const dim3 grid(8 * p.per_xcd), block(Geo<kQB>::kThreads);
   if (p.nseg == 0) {
     if (immediate)
-      hipLaunchKernelGGL((lite_attn_fwd_kernel<1, true, false>), grid, block, fwd_lds_bytes(), st, p);
+      hipLaunchKernelGGL((lite_attn_fwd_kernel<1, true, false, false>), grid, block, kLdsBytes, st, p);
     else
-      hipLaunchKernelGGL((lite_attn_fwd_kernel<kQB, false, false>), grid, block, fwd_lds_bytes(), st, p);
+      hipLaunchKernelGGL((lite_attn_fwd_kernel<kQB, false, false, false>), grid, block, kLdsBytes, st, p);
     return hipGetLastError();
   }
-  if (immediate)
-    hipLaunchKernelGGL((lite_attn_fwd_kernel<1, true, true>), grid, block, fwd_lds_bytes(), st, p);
-  else
-    hipLaunchKernelGGL((lite_attn_fwd_kernel<1, false, true>), grid, block, fwd_lds_bytes(), st, p);
+  if (p.pair) {
+    if (immediate)
+      hipLaunchKernelGGL((lite_attn_fwd_kernel<1, true, true, true>), grid, dim3(512), kPairLdsBytes, st, p);
+    else
+      hipLaunchKernelGGL((lite_attn_fwd_kernel<1, false, true, true>), grid, dim3(512), kPairLdsBytes, st, p);
+  } else if (immediate) {
+    hipLaunchKernelGGL((lite_attn_fwd_kernel<1, true, true, false>), grid, block, kLdsBytes, st, p);
+  } else {
+    hipLaunchKernelGGL((lite_attn_fwd_kernel<1, false, true, false>), grid, block, kLdsBytes, st, p);
+  }
   if (p.nseg > 1) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
