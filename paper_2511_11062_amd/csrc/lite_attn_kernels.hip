@@ -87,6 +87,17 @@ constexpr int kORow = 272;        // bytes per O row in the epilogue staging (re
 
 constexpr int kRowsPerWave = 8;  // Q-tile rows compacted by one wave of compact_skiplist
 
+// Brings the kernel's arguments into the scalar cache, all lines at once: they come from host memory, and left to the
+// places of their first use a workgroup would wait for one line after the other.
+__device__ __forceinline__ void touch_arguments(size_t bytes) {
+  typedef const __attribute__((address_space(4))) uint32_t* words;
+  const words a = (words)__builtin_amdgcn_kernarg_segment_ptr();
+  const int last = (int)bytes / 4 - 1;
+  static_assert(sizeof(FwdParams) > 256 && sizeof(FwdParams) <= 384, "six lines of 64 bytes");
+  const uint32_t x0 = a[0], x1 = a[16], x2 = a[32], x3 = a[48], x4 = a[64], x5 = a[last];
+  asm volatile("" ::"s"(x0), "s"(x1), "s"(x2), "s"(x3), "s"(x4), "s"(x5));
+}
+
 __global__ void clear_state_kernel(uint64_t* bits, size_t words, unsigned long long* stats, size_t nstats) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -458,13 +469,17 @@ struct LiveWalk {
                      // from `start` on first, those before it last)
   uint64_t cur;      // tiles of the current word still to come
 
-  __device__ __forceinline__ void open(const uint64_t* mrow, bool empty_mask, int Tk, int W_, int start_) {
+  static __device__ __forceinline__ uint64_t load(const uint64_t* mrow, bool empty_mask, int words) {
+    const int lane = threadIdx.x & 63;
+    return !empty_mask && lane < words ? mrow[lane] : 0ull;
+  }
+  __device__ __forceinline__ void open(uint64_t skipped, int Tk, int W_, int start_) {
     const int lane = threadIdx.x & 63;
     W = W_;
     start = start_;
     uint64_t live = 0;
     if (lane < W) {
-      live = empty_mask ? ~0ull : ~mrow[lane];
+      live = ~skipped;
       if (lane == W - 1 && (Tk & 63)) live &= (1ull << (Tk & 63)) - 1ull;
     }
     lo = (uint32_t)live;
@@ -915,12 +930,24 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
   __syncthreads();
 }
 
+// a / b of small wave-uniform numbers (0 <= a < 2^24, b >= 1): the rounded reciprocal's product is off by one at most
+__device__ __forceinline__ int quotient(int a, int b) {
+  int q = (int)((float)a * __builtin_amdgcn_rcpf((float)b));
+  q -= q * b > a;
+  q += (q + 1) * b <= a;
+  return __builtin_amdgcn_readfirstlane(q);
+}
+
+// First visiting position of segment s of a row with cnt live tiles.
+__device__ __forceinline__ int segment_start(int cnt, int s, int nseg) { return nseg == 1 ? cnt * s : quotient(cnt * s, nseg); }
+
 template <int QB, bool IMM, bool FEW, bool PAIR>
 __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void lite_attn_fwd_kernel(const FwdParams p) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   static_assert(!PAIR || (FEW && QB == 1), "two groups of four waves: only with few rows");
   constexpr int kWaves = Geo<QB>::kWaves, kChunks = Geo<QB>::kChunks;
   constexpr int kThreads = Geo<QB>::kThreads * (PAIR ? 2 : 1);
+  if constexpr (FEW) touch_arguments(sizeof(FwdParams));
   const int tid = threadIdx.x, lane = tid & 63, wave = (tid >> 6) & (kWaves - 1);
   const int grp = PAIR ? __builtin_amdgcn_readfirstlane(tid >> 8) : 0;  // PAIR: which half of every tile's columns
   const int lq = lane & 31;
@@ -931,38 +958,72 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   // FEW: no table; the (head, segment, row) triples are numbered row-fastest and every XCD takes an eighth of them, so
   // that the rows walking the same K/V tiles of a head share an L2.
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  int row, seg = 0;
+  int row, i, bh, seg = 0;
   if constexpr (FEW) {
     if (p.scheduled) {
       if (slot >= (int)p.xcd_rows[xcd]) return;
       row = (int)p.slots[(size_t)xcd * p.per_xcd + slot];
+      bh = quotient(row, p.Tq);
+      i = row - bh * p.Tq;
     } else {
       const int units = p.rows_total * p.nseg, share = (units + 7) / 8;
       const int unit = xcd * share + slot;
       if (slot >= share || unit >= units) return;
-      const int u = unit / p.Tq;
-      seg = u % p.nseg;
-      row = (u / p.nseg) * p.Tq + unit % p.Tq;
+      const int u = quotient(unit, p.Tq);
+      bh = quotient(u, p.nseg);
+      seg = u - bh * p.nseg;
+      i = unit - u * p.Tq;
+      row = bh * p.Tq + i;
     }
   } else {
     if (slot >= (int)p.xcd_rows[xcd]) return;
     row = (int)p.slots[(size_t)xcd * p.per_xcd + slot];
     if (row < 0) return;  // an empty slot behind a chunk shorter than kChunkRows
+    i = row % p.Tq;
+    bh = row / p.Tq;
   }
-  const int i = row % p.Tq;
-  const int bh = row / p.Tq;
-  const int64_t base = (int64_t)(bh / p.H) * p.stride_b + (int64_t)(bh % p.H) * p.stride_h;
-  const uint16_t* qb_ptr = p.q + base;
+  const int b = FEW ? quotient(bh, p.H) : bh / p.H;
+  const int64_t base = (int64_t)b * p.stride_b + (int64_t)(bh - b * p.H) * p.stride_h;
   uint16_t* ob = p.out + base;
   const int N = p.N;
   const bool split = FEW && p.nseg > 1;
+  Lane<QB> ln;
+  State<QB, IMM> st;
+  ln.hi = lane >> 5;
+  const uint32_t head_bytes = (uint32_t)(((int64_t)(N - 1) * p.stride_n + 128) * 2);
+  auto load_q = [&]() {  // Q^T fragments: B operand of S^T = K Q^T, kept for the whole row
+    const auto qr = __builtin_amdgcn_make_buffer_rsrc((void*)(p.q + base), 0, head_bytes, 0x00020000);
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      const int qrow = i * kTile + 32 * (QB * wave + qb) + lq;
+      ln.qvalid[qb] = qrow < N;
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) {
+        if constexpr (FEW) {  // rows past the end of the sequence read as zeros: no branch per load
+          st.qf[qb][kk] = __builtin_bit_cast(
+              bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                          qr, (int)((uint32_t)qrow * (uint32_t)(p.stride_n * 2) + 16 * ln.hi), 32 * kk, 0));
+        } else {
+          uint4 raw = {0u, 0u, 0u, 0u};
+          if (ln.qvalid[qb])
+            raw = *reinterpret_cast<const uint4*>(p.q + base + (int64_t)qrow * p.stride_n + 16 * kk + 8 * ln.hi);
+          st.qf[qb][kk] = *reinterpret_cast<bf16x8*>(&raw);
+        }
+      }
+    }
+  };
   LiveWalk walk;
   int cnt, nruns, t_lo = 0, t_hi;
   if constexpr (FEW) {
-    walk.open(p.bits + (size_t)row * p.W, p.fresh, p.Tk, p.W, p.diagonal_first ? i : 0);
+    // the mask row first, then Q, all in flight together.  With the arguments brought in at once and the divisions in
+    // a few instructions: tiny layer's step 20.1 -> 19.3 us, options clip's 60.6 -> 59.1 (loading a word of K and V here
+    // too, to have their pages mapped early, was slower: 20.3)
+    const uint64_t skipped = LiveWalk::load(p.bits + (size_t)row * p.W, p.fresh, p.W);
+    load_q();
+    walk.open(skipped, p.Tk, p.W, p.diagonal_first ? i : 0);
     walk.count(cnt, nruns);
-    t_lo = (int)((int64_t)cnt * seg / p.nseg);
-    t_hi = (int)((int64_t)cnt * (seg + 1) / p.nseg);
+    t_lo = segment_start(cnt, seg, p.nseg);
+    t_hi = segment_start(cnt, seg + 1, p.nseg);
     if (split && p.fresh && blockIdx.x == 0)  // a new trajectory: the merge pass adds this step's counters afterwards
       for (int x = tid; x < p.stat_words; x += kThreads) p.stats_all[x] = 0;
   } else {
@@ -985,14 +1046,11 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
     atomicAdd(p.stat_runs, (unsigned long long)nruns);
   }
 
-  Lane<QB> ln;
-  ln.hi = lane >> 5;
   ln.N = N;
   ln.scale = p.scale;
   ln.thr = p.thr;
   ln.c = p.scale * 1.4426950408889634f;
   ln.stride2 = (uint32_t)(p.stride_n * 2);
-  const uint32_t head_bytes = (uint32_t)(((int64_t)(N - 1) * p.stride_n + 128) * 2);
   ln.krsrc = make_rsrc(p.k + base, head_bytes);
   const uint32_t vt_row_bytes = (uint32_t)p.Tk * kTile * 2;  // one feature row of V^T: n_pad bf16
   ln.vrsrc = FEW ? make_rsrc(p.v + base, head_bytes)
@@ -1037,22 +1095,12 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
     return hi > lo && ((i * kTile < hi && lo < min(n, (i + 1) * kTile)) || (j * kTile < hi && lo < min(n, (j + 1) * kTile)));
   };
 
-  State<QB, IMM> st;
+  if constexpr (!FEW) load_q();
   st.grew_prev = false;
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     st.l_pend[qb][0] = st.l_pend[qb][1] = 0.f;
     st.alpha_prev[qb] = 1.f;
-    const int qrow = i * kTile + 32 * (QB * wave + qb) + lq;
-    ln.qvalid[qb] = qrow < N;
-    // Q^T fragments: B operand of S^T = K Q^T, kept for the whole row.
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-      uint4 raw = {0u, 0u, 0u, 0u};
-      if (ln.qvalid[qb])
-        raw = *reinterpret_cast<const uint4*>(qb_ptr + (int64_t)qrow * p.stride_n + 16 * kk + 8 * ln.hi);
-      st.qf[qb][kk] = *reinterpret_cast<bf16x8*>(&raw);
-    }
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -1452,6 +1500,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
 // add the step's counters.
 constexpr int kMergeThreads = 512;
 __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const FwdParams p) {
+  touch_arguments(sizeof(FwdParams));
   const int tid = threadIdx.x, lane = tid & 63;
   const int nseg = p.nseg;
   if ((int)blockIdx.x < 4 * p.rows_total) {
@@ -1504,7 +1553,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const Fwd
   const int r = tid & 127, pair = wave >> 1;
   LiveWalk walk;
   int cnt, nruns;
-  walk.open(p.bits + (size_t)row * p.W, p.fresh, p.Tk, p.W, p.diagonal_first ? i : 0);
+  walk.open(LiveWalk::load(p.bits + (size_t)row * p.W, p.fresh, p.W), p.Tk, p.W, p.diagonal_first ? i : 0);
   walk.count(cnt, nruns);
   const bool q_pinned = p.protect_len > 0 && i * kTile < p.protect_start + p.protect_len &&
                         p.protect_start < min(p.N, (i + 1) * kTile);
@@ -1514,7 +1563,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const Fwd
     const float* ps = p.seg_stat + (size_t)row * nseg * 3 * kTile + 2 * kTile + r;
     const float* mloc = p.seg_mloc + (size_t)row * p.Tk * kTile + r;
     for (int s = pair; s < nseg; s += kPairs) {
-      const int t0 = (int)((int64_t)cnt * s / nseg), t1 = (int)((int64_t)cnt * (s + 1) / nseg);
+      const int t0 = segment_start(cnt, s, nseg), t1 = segment_start(cnt, s + 1, nseg);
       if (t0 == t1) continue;
       float run = -INFINITY;
       for (int x = 0; x < s; ++x) run = fmaxf(run, ps[x * 3 * kTile]);
