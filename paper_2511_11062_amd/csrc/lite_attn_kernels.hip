@@ -771,7 +771,8 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
   for (int k = 0; k < kPrefetch; ++k)
     if (!IMM || pv_on) frag[k] = load_frag<VROWS, kKSrc, kVSrc>(k, ln.kread, ln.vread);
 
-  float pm[QB][4], mx[QB], alpha[QB], ta0[QB], ta1[QB], tb0[QB];
+  float pm[QB][4], mx[QB], alpha[QB], ta0[QB], ta1[QB], tb0[QB], tb1[QB];
+  uint32_t wb[QB];  // (kPackLate) packed pair whose sum is still to be taken
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) alpha[qb] = 1.f;
   bool ok = true, grew = false;
@@ -792,6 +793,9 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
           asm volatile("" : "+v"(cur[qb][blk][r]));  // one lane mask alive at a time
         }
   }
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) wb[qb] = 0u;
+  constexpr bool kPackLate = VROWS && !IMM;
   const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 
   auto mfma_part = [&](auto kc, auto qbc) __attribute__((always_inline)) {
@@ -862,10 +866,36 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
         if (IMM && (PAIR || !H)) st.l_pend[qb][pend] = 0.f;
       } else if (k < 30) {
         // P~ = exp(S - m_ij), packed to bf16: 16 pairs of scores over 24 steps, four vector instructions per step
-        // (a cycle of three steps does two pairs: exp exp | pack+sum, exp | exp, pack+sum)
+        // (a cycle of three steps does two pairs: exp exp | pack+sum, exp | exp, pack+sum).  kPackLate: the second pair
+        // is packed in the next cycle (exp, pack | exp, sum, exp | pack, exp, sum), so that no instruction directly
+        // follows the exponential it uses, which costs a wait state: 0.6 % of the short clip's, the two-layer and the
+        // diagonal-first sequence; the kernel for long rows, whose clock is limited by power, ran up to 0.45 % slower
+        // with it, the immediate pair 0.2 %.
         const int t = k - 6, c = t / 3, ph = t % 3;
         const int eA = 2 * c, eB = 2 * c + 1;
-        if (ph == 0) {
+        if (kPackLate) {
+          auto exponent = [&](int e, int half) {
+            return __builtin_fmaf(cur[qb][e >> 3][2 * (e & 7) + half], ln.c, -st.mc_ref[qb]);
+          };
+          if (ph == 0) {
+            ta0[qb] = __builtin_amdgcn_exp2f(exponent(eA, 0));
+            ta1[qb] = exponent(eA, 1);
+            if (c > 0) wb[qb] = pack_bf16x2(tb0[qb], tb1[qb]);
+            asm volatile("" : "+v"(ta0[qb]), "+v"(ta1[qb]), "+v"(wb[qb]));
+            if (c > 0) pwc[qb][eA - 1] = wb[qb];
+          } else if (ph == 1) {
+            ta1[qb] = __builtin_amdgcn_exp2f(ta1[qb]);
+            if (c > 0) lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, wb[qb]), ones, lsum, false);
+            tb0[qb] = __builtin_amdgcn_exp2f(exponent(eB, 0));
+            asm volatile("" : "+v"(ta1[qb]), "+v"(lsum), "+v"(tb0[qb]));
+          } else {
+            uint32_t w = pack_bf16x2(ta0[qb], ta1[qb]);
+            tb1[qb] = __builtin_amdgcn_exp2f(exponent(eB, 1));
+            lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, lsum, false);
+            asm volatile("" : "+v"(w), "+v"(lsum), "+v"(tb1[qb]));
+            pwc[qb][eA] = w;
+          }
+        } else if (ph == 0) {
           ta0[qb] = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[qb][eA >> 3][2 * (eA & 7)], ln.c, -st.mc_ref[qb]));
           ta1[qb] = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[qb][eA >> 3][2 * (eA & 7) + 1], ln.c, -st.mc_ref[qb]));
           // empty volatile asms pin every slice to its step: without them the compiler sinks all the exponentials
@@ -886,6 +916,12 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
           pwc[qb][eB] = w;
         }
       } else if (k == 30) {
+        if (kPackLate) {
+          wb[qb] = pack_bf16x2(tb0[qb], tb1[qb]);
+          lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, wb[qb]), ones, lsum, false);
+          asm volatile("" : "+v"(wb[qb]), "+v"(lsum));
+          pwc[qb][15] = wb[qb];
+        }
         if (!PAIR && H) {  // skip predicate of the whole 128-column tile, once its second half is in (eq. sparge_cond)
           const float g = (st.mloc_tile[qb] - st.m_run[qb]) * ln.scale;  // this row; max over rows = ballot below
           ok = ok && (!ln.qvalid[qb] || (g <= ln.thr));
