@@ -1589,20 +1589,27 @@ __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const Fwd
   const int r = tid & 127, pair = wave >> 1;
   LiveWalk walk;
   int cnt, nruns;
-  walk.open(LiveWalk::load(p.bits + (size_t)row * p.W, p.fresh, p.W), p.Tk, p.W, p.diagonal_first ? i : 0);
+  // the mask row and the segments' row maxima, all in flight together
+  const uint64_t skipped = LiveWalk::load(p.bits + (size_t)row * p.W, p.fresh, p.W);
+  float seg_max[kMaxSegments];
+#pragma unroll
+  for (int x = 0; x < kMaxSegments; ++x)
+    if (x < 4 || nseg > 4)
+      seg_max[x] = p.seg_stat[((size_t)row * nseg + min(x, nseg - 1)) * 3 * kTile + 2 * kTile + r];
+  walk.open(skipped, p.Tk, p.W, p.diagonal_first ? i : 0);
   walk.count(cnt, nruns);
   const bool q_pinned = p.protect_len > 0 && i * kTile < p.protect_start + p.protect_len &&
                         p.protect_start < min(p.N, (i + 1) * kTile);
   uint64_t mine = 0;  // lane w: bits of mask word w
   if (p.thr > -INFINITY && !q_pinned) {
     const bool qvalid = i * kTile + r < p.N;
-    const float* ps = p.seg_stat + (size_t)row * nseg * 3 * kTile + 2 * kTile + r;
     const float* mloc = p.seg_mloc + (size_t)row * p.Tk * kTile + r;
     for (int s = pair; s < nseg; s += kPairs) {
       const int t0 = segment_start(cnt, s, nseg), t1 = segment_start(cnt, s + 1, nseg);
       if (t0 == t1) continue;
       float run = -INFINITY;
-      for (int x = 0; x < s; ++x) run = fmaxf(run, ps[x * 3 * kTile]);
+#pragma unroll
+      for (int x = 0; x < kMaxSegments; ++x) run = x < s ? fmaxf(run, seg_max[x]) : run;
       walk.rewind();
       walk.skip(t0);
       constexpr int kAhead = 8;  // tiles whose loads are in flight together
@@ -1635,7 +1642,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const Fwd
 #pragma unroll
     for (int x = 0; x < kPairs; ++x) f |= fired[2 * x][tid] & fired[2 * x + 1][tid];
     uint64_t* word = p.bits + (size_t)row * p.W + tid;
-    if (p.fresh || f) *word = (p.fresh ? 0ull : *word) | f;
+    if (p.fresh || f) *word = skipped | f;  // (tid < W: the lane's own word)
     if (f && p.stat_newly) atomicAdd(p.stat_newly, (unsigned long long)__popcll(f));
   }
   if (tid == 0 && p.stat_newly) {
