@@ -52,17 +52,19 @@ size_t segment_bytes(const Geometry& g, int nseg) {
 // per CU, or 256 pairs.  A CU with a single wave per SIMD takes 1.69 us for a tile (a wave's instructions issue one after
 // the other: 2050 cycles for a stage of 1024 matrix cycles), a pair 1.36 us and 2.7 us more per row for its merge in
 // LDS, two workgroups on a CU 2.7 us for a tile each.  Cutting a row costs a second launch, 64 KB of fp32 partials per
-// segment written and read again, and the walk over the tiles' row maxima in the merge pass.  Minimum of a cost in
-// units of 10 ns made of these measurements.  us per call, whole rows -> segments: 32 rows of 16 tiles 33.6 -> 20.4 (8
-// segments), 72 x 12 28.5 -> 24.9 (3), 128 x 128 223 -> 125 (4); -> pairs: 192 x 32 64.3 -> 56.8, 256 x 32 69.1 -> 64.4,
-// 155 x 31 with the immediate variant 77.5 -> 60.4; -> both: 64 x 64 115 -> 46.4 (4), 128 x 32 63.0 -> 45.9 (2).  The
-// immediate variant needs a tile's verdict before its PV product, which a segment cannot know: never cut.
+// segment written and read again, and the walk over the tiles' row maxima in the merge pass (3 us, 0.8 us per four
+// segments, 18 ns per segment, 30 ns per row and 0.15 us per tile of a segment fit calls of 3..300 rows).  Minimum of a
+// cost in units of 10 ns made of these measurements; over fifteen shapes between 3 x 3 and 300 x 30 the choice is the best
+// one or within 5 % of it.  us per call, whole rows -> segments: 32 rows of 16 tiles 33.6 -> 19.2 (8 segments), 72 x 12
+// 28.5 -> 23.8 (3), 128 x 128 223 -> 125 (4); -> pairs: 192 x 32 64.3 -> 56.8, 256 x 32 69.1 -> 64.4, 155 x 31 with the
+// immediate variant 77.5 -> 60.4; -> both: 64 x 64 115 -> 46.4 (4), 128 x 32 63.0 -> 45.9 (2).  The immediate variant
+// needs a tile's verdict before its PV product, which a segment cannot know: never cut.
 void share_chip(Geometry& g, int flags) {
   const int most = (flags & LITE_ATTN_PV_SKIP_IMMEDIATE) ? 1 : std::min(kMaxSegments, g.Tk);
   int64_t best = -1;
   for (int s = 1; s <= most && (s == 1 || segment_bytes(g, s) <= kMaxSegmentBytes); ++s) {
     const int64_t wgs = g.rows * s, tiles = (g.Tk + s - 1) / s, full = wgs / 512, last = wgs % 512;
-    const int64_t merge = s > 1 ? 400 + 22 * wgs / 10 + 15 * tiles : 0;
+    const int64_t merge = s > 1 ? 300 + 80 * ((s + 3) / 4) + 18 * wgs / 10 + 3 * g.rows + 15 * tiles : 0;
     for (int pair = 0; pair < (wgs <= kPairWorkgroups ? 2 : 1); ++pair) {
       const int64_t tile = pair ? 136 : 270 * full + (last == 0 ? 0 : last <= 256 ? 169 : 270);
       const int64_t cost = merge + tiles * tile + (pair ? 270 : 500 * (full + (last != 0) - 1));
