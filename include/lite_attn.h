@@ -98,7 +98,8 @@ int lite_attn_set_stream(lite_attn_mask_t* mask, void* hip_stream);
 
 /* Scratch shared by the layers of a model (this library's own arrangement, nothing of the paper's).
    A call needs device scratch that nothing reads after the call has finished: the Skip-List, the row schedule and
-   a transposed copy of V, together about the size of V.  A handle made by lite_attn_init_mask owns its own; a model
+   a transposed copy of V, together about the size of V (layers of at most 512 Q-tile rows: or partial results of rows cut
+   into segments, at most 104 MiB).  A handle made by lite_attn_init_mask owns its own; a model
    with one handle per layer would hold that once per layer.  Handles made by lite_attn_init_mask_shared borrow the
    scratch of a context instead: one buffer on the context's device, grown to the largest layer attached so far.
    Sharing is safe because all handles of a context run on the context's ONE stream, where calls are serial:
@@ -121,7 +122,7 @@ int lite_attn_ctx_free(lite_attn_ctx_t* ctx);
      q, k, v   device bf16, layout given by the handle's strides; borrowed, not modified; values must be finite
                (the kernels are built with the assumption that no NaN occurs)
      out       device bf16, same layout; every valid row is written
-     skip_mask handle; its mask is read (via the Skip-List built from it at the start of the call) and updated
+     skip_mask handle; its mask as it stands at the start of the call is read and then updated
      threshold signed -eps of eq. (sparge_cond) in natural-log units of S = QK^T/sqrt(d), must be < 0;
                -INFINITY never marks anything (with an empty mask the result is dense attention)
      step      0 clears the mask and the statistics first (new denoising trajectory); otherwise must be the
@@ -136,8 +137,8 @@ int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_a
 /* The same attention call for callers that cannot allocate device memory at all -- code running under HIP graph
    capture, serving loops and harnesses that forbid hipMalloc -- and therefore cannot create a handle.  It allocates
    nothing and frees nothing: no hipMalloc, no hipFree, no allocating library routine.  Everything the other entry
-   points keep in allocated device memory besides the Skip-Mask (Skip-List, row schedule, V^T, the call's counters)
-   lives in ONE static device array of LITE_ATTN_STATIC_SCRATCH_BYTES that the library's code object brings along on
+   points keep in allocated device memory besides the Skip-Mask (Skip-List, row schedule, V^T or partial results; no
+   counters, which nobody could ask for) lives in ONE static device array of LITE_ATTN_STATIC_SCRATCH_BYTES that the library's code object brings along on
    every GPU it is loaded on and holds until the process ends.
      q, k, v, out, threshold   as for lite_attn_fwd
      desc            shape, strides, protected range and flags of the layer, as for lite_attn_init_mask (max_steps
@@ -151,8 +152,8 @@ int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_a
    layer; the larger benchmark shapes need a handle.  The first call on a GPU looks up the array's address there and
    sets the attention kernel's function attributes (no allocation, but not work to record into a graph: make the first
    call on a GPU outside stream capture).
-   Every call on a GPU uses that GPU's one array, which keeps the previous call's contents (what has to start at
-   zero is cleared by the call itself): calls that overlap in time on one GPU -- two streams, two threads -- race;
+   Every call on a GPU uses that GPU's one array, which keeps the previous call's contents (a call writes what it
+   reads there): calls that overlap in time on one GPU -- two streams, two threads -- race;
    calls on one stream are safe. */
 #define LITE_ATTN_STATIC_SCRATCH_BYTES (128u << 20)
 int lite_attn_fwd_static(const void* q, const void* k, const void* v, void* out, const lite_attn_desc_t* desc,
@@ -164,8 +165,9 @@ int lite_attn_skip_stats(lite_attn_mask_t* mask, int step, lite_attn_stats_t* ho
 
 /* Per-phase timing for benchmarks.  enable != 0 makes every later lite_attn_fwd record HIP events on the handle's
    stream around its two phases (events are created on the first enabled call; a few microseconds per call).
-   lite_attn_kernel_times returns the durations of a completed step in milliseconds -- host_prep_ms: Skip-List
-   compaction plus the V transposition pre-pass; host_fwd_ms: the fused attention kernel -- it synchronises the
+   lite_attn_kernel_times returns the durations of a completed step in milliseconds -- host_prep_ms: what runs
+   before the attention kernel (clearing, Skip-List compaction, row schedule, V transposition, as far as the call has
+   them); host_fwd_ms: the fused attention kernel and, for rows cut into segments, the pass that merges them -- it synchronises the
    stream and fails with LITE_ATTN_ESTEP if that step was not run with profiling enabled. */
 int lite_attn_profile(lite_attn_mask_t* mask, int enable);
 int lite_attn_kernel_times(lite_attn_mask_t* mask, int step, float* host_prep_ms, float* host_fwd_ms);

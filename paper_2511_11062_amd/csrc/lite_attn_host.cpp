@@ -109,9 +109,9 @@ ListLayout list_layout(const Geometry& g) {
   l.live_cnt = at;
   at += up256(sizeof(uint32_t) * (size_t)g.rows);
   l.order = at;
-  at += up256(sizeof(uint32_t) * (size_t)g.rows);
+  if (g.nseg == 0) at += up256(sizeof(uint32_t) * (size_t)g.rows);
   l.chunk_work = at;
-  at += up256(sizeof(uint32_t) * (size_t)g.chunks);
+  if (g.nseg == 0) at += up256(sizeof(uint32_t) * (size_t)g.chunks);
   l.slots = at;
   at += up256(sizeof(uint32_t) * 8 * (size_t)g.per_xcd);
   l.xcd_rows = at;

@@ -84,7 +84,7 @@ struct ListLayout {
   size_t stats;     // 3 uint64 counters for callers without a handle (handles keep per-step counters of their own)
   size_t nruns;     // [rows] uint32 runs per row
   size_t live_cnt;  // [rows] uint32 live tiles per row
-  size_t order;     // [BH][Tq] uint32 row ranking
+  size_t order;     // [BH][Tq] uint32 row ranking (none with few or short rows)
   size_t chunk_work;  // [chunks] uint32 work of each chunk (live tiles + a per-row constant)
   size_t slots;     // [8][per_xcd] uint32 schedule table
   size_t xcd_rows;  // [8] uint32
@@ -105,9 +105,10 @@ ScratchLayout scratch_layout(const Geometry& g);
 
 // lite_attn.cpp: the launches of one attention call on `stream`.  lists_ready: the Skip-Lists in `lists` already
 // describe the mask (left by the previous call's epilogue); otherwise the compaction kernel builds them first.  Then
-// the row schedule, the V^T pre-pass into `vt` and the fused attention kernel, whose epilogue builds the next call's
-// lists if build_next.  `mid` (may be null) is recorded just before the attention kernel.
-// Allocates nothing.
+// the row schedule, the V^T pre-pass into `scratch` and the fused attention kernel, whose epilogue builds the next call's
+// lists if build_next.  With few or short rows (Geometry::nseg > 0) there are no lists and no V^T: at most a schedule, the
+// fused kernel and, for rows cut into segments, the merge pass.  `mid` (may be null) is recorded just before the
+// attention kernel.  Allocates nothing.
 struct CallArgs {
   const void *q, *k, *v;
   void* out;
