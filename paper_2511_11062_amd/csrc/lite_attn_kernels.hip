@@ -427,7 +427,10 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
 // 16-byte read bandwidth, which made LDS the bound of the fused kernel.)  This kernel writes, once per call,
 // vt[bh][d][n_pad] with n_pad = 128 * Tk, zero beyond the sequence, with the K/V index permuted inside every
 // group of 16: position 8*h + t holds K/V offset 4*h + t + 4*(t >= 4) -- the order in which a lane of the fused
-// kernel holds its P~ values.  One workgroup transposes one 128 x 128 tile through LDS.
+// kernel holds its P~ values.  One workgroup transposes one 128 x 128 tile through LDS, twice: once with
+// transposing reads, once to regroup, because a wave that stores the transposed pieces as it reads them writes 64
+// separate 16-byte pieces.  Bound by memory: 55 -> 39 us for 12 heads x 32760 tokens (3.7 -> 5.1 TB/s; a large copy
+// reaches 4.9).
 __global__ __launch_bounds__(256) void transpose_v_kernel(const uint16_t* __restrict__ v, uint16_t* __restrict__ vt,
                                                            int64_t stride_b, int64_t stride_h, int64_t stride_n,
                                                            int H, int N, int Tk) {
@@ -446,6 +449,7 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(const uint16_t* __rest
   __syncthreads();
   const int g = lane >> 4, i16 = lane & 15, r_src = i16 >> 2, c_src = lane & 3;
   uint16_t* out = vt + (int64_t)bh * 128 * (128 * (int64_t)Tk) + (int64_t)j * 128;
+  s16x8 o[8];
 #pragma unroll
   for (int x = 0; x < 8; ++x) {
     const int q = 8 * wave + x;                    // 32 (16-group, half, d-half) combinations per tile
@@ -453,9 +457,21 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(const uint16_t* __rest
     const char* src = tile + (16 * c16 + 4 * hh + r_src) * kRow + 2 * (64 * dhalf + 16 * g + 4 * c_src);
     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LA_LDS s16x4*)(src));
     const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LA_LDS s16x4*)(src + 8 * kRow));
-    const s16x8 o = __builtin_shufflevector(lo, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
-    const int d = 64 * dhalf + 16 * g + i16;
-    *reinterpret_cast<s16x8*>(out + (int64_t)d * (128 * (int64_t)Tk) + 16 * c16 + 8 * hh) = o;
+    o[x] = __builtin_shufflevector(lo, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
+  }
+  __syncthreads();
+  // back through LDS as [d][kv], so that 16 lanes store a whole 256-byte piece of a feature row
+#pragma unroll
+  for (int x = 0; x < 8; ++x) {
+    const int q = 8 * wave + x, d = 64 * (q & 1) + 16 * g + i16;
+    *reinterpret_cast<s16x8*>(tile + d * kRow + 32 * (q >> 2) + 16 * ((q >> 1) & 1)) = o[x];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    const int d = (tid >> 4) + 16 * t;
+    *reinterpret_cast<uint4*>(out + (int64_t)d * (128 * (int64_t)Tk) + 8 * (tid & 15)) =
+        *reinterpret_cast<const uint4*>(tile + d * kRow + 16 * (tid & 15));
   }
 }
 
