@@ -5,6 +5,9 @@
 //                          (Implementation, "Producer and Skip-List Optimization"); only at the start of a trajectory
 //                          or after a mask import: the fused kernel's epilogue builds the next call's Skip-Lists
 //   order_rows_kernel    : per head, Q-tile rows ranked by Skip-List length (the launch order of the fused kernel)
+//   deal_rows_kernel     : the ranked rows dealt to the XCDs
+//   schedule_rows_kernel : the row schedule of layers with short rows, from the mask itself
+//   merge_segments_kernel: partial results of rows that were cut into segments -> O, mask bits, statistics
 //   transpose_v_kernel   : V -> V^T scratch, so that the PV operand is read from LDS like the QK operand
 //   lite_attn_fwd_kernel : fused tiled forward over the live tiles with the skip predicate
 //                          (Algorithm 2; eq. sparge_cond; tile recurrences of the Preliminaries)
