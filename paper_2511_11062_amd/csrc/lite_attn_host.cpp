@@ -44,7 +44,7 @@ size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Partial results of rows cut into segments: what the fused kernel hands to the merge pass.
 size_t segment_bytes(const Geometry& g, int nseg) {
-  return nseg > 1 ? sizeof(float) * (size_t)g.rows * (nseg * (128 * 128 + 3 * 128) + (size_t)g.Tk * 128) : 0;
+  return nseg > 1 ? sizeof(float) * (size_t)g.rows * (nseg * (128 * 128 + 2 * 128) + (size_t)g.Tk * 128) : 0;
 }
 
 // How few rows share the chip: how many segments (workgroups) a row is cut into, and whether a workgroup is a pair of
@@ -126,7 +126,7 @@ ScratchLayout scratch_layout(const Geometry& g) {
   ScratchLayout l;  // the segments lie over the V^T that calls with few rows do not make
   l.seg_o = 0;
   l.seg_stat = sizeof(float) * (size_t)g.rows * g.nseg * 128 * 128;
-  l.seg_mloc = l.seg_stat + sizeof(float) * (size_t)g.rows * g.nseg * 3 * 128;
+  l.seg_mloc = l.seg_stat + sizeof(float) * (size_t)g.rows * g.nseg * 2 * 128;
   l.total = up256(std::max(sizeof(uint16_t) * (size_t)g.BH * 128 * ((size_t)g.Tk * 128), segment_bytes(g, g.nseg)));
   return l;
 }

@@ -59,7 +59,7 @@ struct FwdParams {
   int fresh = 0;                         // step 0: the mask counts as empty and is overwritten
   const uint16_t* v = nullptr;
   float* seg_o = nullptr;                // [rows][nseg][128][128] O^T partials in accumulator order
-  float* seg_stat = nullptr;             // [rows][nseg][3][128]: exponent reference, row sum, row maximum
+  float* seg_stat = nullptr;             // [rows][nseg][2][128]: row maximum (the exponents' reference), row sum
   float* seg_mloc = nullptr;             // [rows][Tk][128]: row maxima of the visited tiles
   unsigned long long* stats_all = nullptr;  // all counters of the handle (stat_words of them): zeroed at step 0, nseg > 1
   int stat_words = 0;

@@ -585,7 +585,6 @@ struct State {
                                 // (IMM: of the previous odd stage)
   uint32_t pw0[QB][16];         // IMM only: P~^T of the previous even stage
   float m_run[QB], l_run[QB], mloc_tile[QB];
-  float mc_ref[QB];  // reference of the exponentials, times c: P~ = exp2(S c - mc_ref); trails m_run c by < kLazyLog2
   // IMM only: row sum of the tile in flight (added to l_run once the tile is known not to have fired), and the
   // rescale factor of the previous stage, which O^T has not seen yet because its PV product runs a stage later
   // (PAIR: of the two tiles in flight, by parity)
@@ -733,13 +732,9 @@ __device__ __forceinline__ bf16x8 load_frag(int k, const uint32_t (&kread)[8], c
   return *reinterpret_cast<LA_LDS const bf16x8*>(vread[cc] + (uint32_t)(kV + 4096 * db));
 }
 
-// How far (in powers of two) the running maximum may outgrow the reference of the exponentials before O^T and the row sum
-// are rescaled: weights up to 2^8 keep their relative precision in bf16 and fp32.  Following the maximum at every stage
-// cost 64 multiplies per lane wherever any of a wave's 32 rows found a new one: 1.5 % of the dense 12-head N = 32760
-// step (5571 -> 5489 us), 6 % of the tiny layer's.
-constexpr float kLazyLog2 = 8.f;
-constexpr float kNoRef = -1e38f;  // reference before the first tile; finite, so that a column half without valid columns
-                                  // weighs exp2(-inf + 1e38) = 0
+// Row maximum before the first tile: below every score of finite operands, and finite itself, so that a column half without
+// valid columns weighs exp2(-inf - kNoMax c) = 0.
+constexpr float kNoMax = -3.402823466e38f;
 constexpr int kPrefetch = 3;  // LDS fragments in flight ahead of the MFMA that consumes them
 constexpr int kDmaGap = 2;    // steps between two DMA issues of a stage
 
@@ -790,10 +785,8 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
   for (int k = 0; k < kPrefetch; ++k)
     if (!IMM || pv_on) frag[k] = load_frag<VROWS, kKSrc, kVSrc>(k, ln.kread, ln.vread);
 
-  float pm[QB][4], mx[QB], alpha[QB], ta0[QB], ta1[QB], tb0[QB], tb1[QB];
+  float pm[QB][4], mx[QB], m_new[QB], mc[QB], alpha[QB], lsum[QB], ta0[QB], ta1[QB], tb0[QB], tb1[QB];
   uint32_t wb[QB];  // (kPackLate) packed pair whose sum is still to be taken
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) alpha[qb] = 1.f;
   bool ok = true, grew = false;
   // The ragged last tile of the sequence: its columns past the end leave the row maxima and sums (one scalar compare
   // and branch per stage, taken for one tile per row at most).  This lane's element r of block blk is column
@@ -858,7 +851,6 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
     constexpr int k = decltype(kc)::value;
     constexpr int qb = decltype(qbc)::value;
     constexpr int pend = PAIR ? H : 0;
-    float& lsum = IMM ? st.l_pend[qb][pend] : st.l_run[qb];  // the row sum this stage adds to
     // ---- vector ALU: slice k of the online softmax of stage s (raw dot products; 1/sqrt(d) folded into c) ----
     {
       if (k < 4) {  // m_local: partial row maxima over 8 of this lane's 32 scores
@@ -871,18 +863,15 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
         mx[qb] = other_half_max(fmaxf(fmaxf(pm[qb][0], pm[qb][1]), fmaxf(pm[qb][2], pm[qb][3])));
       } else if (k == 5) {  // m_ij = max(m_{i,j-1}, m_local) and the rescale factor of the earlier stages
         if (!PAIR) st.mloc_tile[qb] = H ? fmaxf(st.mloc_tile[qb], mx[qb]) : mx[qb];
-        st.m_run[qb] = fmaxf(st.m_run[qb], mx[qb]);
-        // the exponent's reference follows the maximum only when some row of the wave has outgrown it by kLazyLog2
-        const float up = st.m_run[qb] * ln.c;
-        if (__any(up > st.mc_ref[qb] + kLazyLog2)) {
-          alpha[qb] = __builtin_amdgcn_exp2f(st.mc_ref[qb] - up);
-          st.l_run[qb] *= alpha[qb];
-          if (IMM && PAIR) st.l_pend[qb][H ^ 1] *= alpha[qb];
-          if (IMM && !PAIR && H) st.l_pend[qb][0] *= alpha[qb];
-          st.mc_ref[qb] = up;
-          grew = true;
-        }
-        if (IMM && (PAIR || !H)) st.l_pend[qb][pend] = 0.f;
+        // the reference of the exponentials is the running maximum itself, at every stage: a row's largest weight is then
+        // exactly 1, which bf16 holds without error (a reference trailing the maximum saved 1.5 % of the dense 12-head
+        // step and let that rounding error in: up to 9e-3 of the values where large terms cancel)
+        m_new[qb] = fmaxf(st.m_run[qb], mx[qb]);
+        alpha[qb] = __builtin_amdgcn_exp2f((st.m_run[qb] - m_new[qb]) * ln.c);
+        grew = grew || (m_new[qb] > st.m_run[qb]);
+        st.m_run[qb] = m_new[qb];
+        mc[qb] = m_new[qb] * ln.c;
+        lsum[qb] = 0.f;
       } else if (k < 30) {
         // P~ = exp(S - m_ij), packed to bf16: 16 pairs of scores over 24 steps, four vector instructions per step
         // (a cycle of three steps does two pairs: exp exp | pack+sum, exp | exp, pack+sum).  kPackLate: the second pair
@@ -894,7 +883,7 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
         const int eA = 2 * c, eB = 2 * c + 1;
         if (kPackLate) {
           auto exponent = [&](int e, int half) {
-            return __builtin_fmaf(cur[qb][e >> 3][2 * (e & 7) + half], ln.c, -st.mc_ref[qb]);
+            return __builtin_fmaf(cur[qb][e >> 3][2 * (e & 7) + half], ln.c, -mc[qb]);
           };
           if (ph == 0) {
             ta0[qb] = __builtin_amdgcn_exp2f(exponent(eA, 0));
@@ -904,45 +893,52 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
             if (c > 0) pwc[qb][eA - 1] = wb[qb];
           } else if (ph == 1) {
             ta1[qb] = __builtin_amdgcn_exp2f(ta1[qb]);
-            if (c > 0) lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, wb[qb]), ones, lsum, false);
+            if (c > 0) lsum[qb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, wb[qb]), ones, lsum[qb], false);
             tb0[qb] = __builtin_amdgcn_exp2f(exponent(eB, 0));
-            asm volatile("" : "+v"(ta1[qb]), "+v"(lsum), "+v"(tb0[qb]));
+            asm volatile("" : "+v"(ta1[qb]), "+v"(lsum[qb]), "+v"(tb0[qb]));
           } else {
             uint32_t w = pack_bf16x2(ta0[qb], ta1[qb]);
             tb1[qb] = __builtin_amdgcn_exp2f(exponent(eB, 1));
-            lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, lsum, false);
-            asm volatile("" : "+v"(w), "+v"(lsum), "+v"(tb1[qb]));
+            lsum[qb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, lsum[qb], false);
+            asm volatile("" : "+v"(w), "+v"(lsum[qb]), "+v"(tb1[qb]));
             pwc[qb][eA] = w;
           }
         } else if (ph == 0) {
-          ta0[qb] = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[qb][eA >> 3][2 * (eA & 7)], ln.c, -st.mc_ref[qb]));
-          ta1[qb] = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[qb][eA >> 3][2 * (eA & 7) + 1], ln.c, -st.mc_ref[qb]));
+          ta0[qb] = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[qb][eA >> 3][2 * (eA & 7)], ln.c, -mc[qb]));
+          ta1[qb] = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[qb][eA >> 3][2 * (eA & 7) + 1], ln.c, -mc[qb]));
           // empty volatile asms pin every slice to its step: without them the compiler sinks all the exponentials
           // behind the last MFMA, where nothing overlaps them
           asm volatile("" : "+v"(ta0[qb]), "+v"(ta1[qb]));
         } else if (ph == 1) {
           uint32_t w = pack_bf16x2(ta0[qb], ta1[qb]);
           // the row sum adds the bf16-rounded weights, the same values the PV product uses
-          lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, lsum, false);
-          tb0[qb] = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[qb][eB >> 3][2 * (eB & 7)], ln.c, -st.mc_ref[qb]));
-          asm volatile("" : "+v"(w), "+v"(lsum), "+v"(tb0[qb]));
+          lsum[qb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, lsum[qb], false);
+          tb0[qb] = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[qb][eB >> 3][2 * (eB & 7)], ln.c, -mc[qb]));
+          asm volatile("" : "+v"(w), "+v"(lsum[qb]), "+v"(tb0[qb]));
           pwc[qb][eA] = w;  // word e belongs to chunk e/4, whose last reader was the MFMA of step 4*(e/4)+3 < k
         } else {
-          const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[qb][eB >> 3][2 * (eB & 7) + 1], ln.c, -st.mc_ref[qb]));
+          const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[qb][eB >> 3][2 * (eB & 7) + 1], ln.c, -mc[qb]));
           uint32_t w = pack_bf16x2(tb0[qb], p1);
-          lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, lsum, false);
-          asm volatile("" : "+v"(w), "+v"(lsum));
+          lsum[qb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, lsum[qb], false);
+          asm volatile("" : "+v"(w), "+v"(lsum[qb]));
           pwc[qb][eB] = w;
         }
       } else if (k == 30) {
         if (kPackLate) {
           wb[qb] = pack_bf16x2(tb0[qb], tb1[qb]);
-          lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, wb[qb]), ones, lsum, false);
-          asm volatile("" : "+v"(wb[qb]), "+v"(lsum));
+          lsum[qb] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, wb[qb]), ones, lsum[qb], false);
+          asm volatile("" : "+v"(wb[qb]), "+v"(lsum[qb]));
           pwc[qb][15] = wb[qb];
         }
+        if (!IMM) {
+          st.l_run[qb] = st.l_run[qb] * alpha[qb] + lsum[qb];
+        } else {
+          st.l_run[qb] *= alpha[qb];
+          if (PAIR) st.l_pend[qb][H ^ 1] *= alpha[qb];
+          st.l_pend[qb][pend] = (!PAIR && H) ? st.l_pend[qb][0] * alpha[qb] + lsum[qb] : lsum[qb];
+        }
         if (!PAIR && H) {  // skip predicate of the whole 128-column tile, once its second half is in (eq. sparge_cond)
-          const float g = (st.mloc_tile[qb] - st.m_run[qb]) * ln.scale;  // this row; max over rows = ballot below
+          const float g = (st.mloc_tile[qb] - m_new[qb]) * ln.scale;  // this row; max over rows = ballot below
           ok = ok && (!ln.qvalid[qb] || (g <= ln.thr));
         }
       }
@@ -968,7 +964,7 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
   // O^T of the earlier stages is rescaled after this stage's PV MFMAs (rare once the running max has settled).
   // IMM: O^T now holds the products up to stage s-2 and moves to the reference maximum of stage s-1, whose product
   // the next stage adds; this stage's own factor waits one stage.
-  if (IMM ? st.grew_prev : grew) {
+  if (IMM ? st.grew_prev : (bool)__any(grew)) {
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
@@ -977,7 +973,7 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
         for (int r = 0; r < 16; ++r) st.oacc[qb][db][r] *= IMM ? st.alpha_prev[qb] : alpha[qb];
   }
   if (IMM) {
-    st.grew_prev = grew;
+    st.grew_prev = __any(grew);
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) st.alpha_prev[qb] = alpha[qb];
   }
@@ -1162,8 +1158,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
       for (int r = 0; r < 16; ++r) st.oacc[qb][db][r] = 0.f;
 #pragma unroll
     for (int e = 0; e < 16; ++e) st.pw[qb][e] = 0u;
-    st.m_run[qb] = -INFINITY;  // running row max of the raw dot products (m_{i,j-1} * sqrt(d))
-    st.mc_ref[qb] = kNoRef;
+    st.m_run[qb] = kNoMax;     // running row max of the raw dot products (m_{i,j-1} * sqrt(d))
     st.l_run[qb] = 0.f;        // this lane's half of the row sum
     st.mloc_tile[qb] = -INFINITY;
   }
@@ -1381,7 +1376,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
       __syncthreads();
       // group 1's share joins group 0's: accumulators as the lanes hold them, through group 1's stage buffers
       float4* hand = reinterpret_cast<float4*>(smem + 4 * kStageBytes) + (size_t)wave * 1024 + lane;
-      float* hand_stat = xch;  // [reference, row sum][128]
+      float* hand_stat = xch;  // [row maximum, row sum][128]
       const float l_half = other_half_sum(st.l_run[0]);
       if (grp == 1) {
 #pragma unroll
@@ -1391,18 +1386,17 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
           hand[64 * g] = float4{a[r], a[r + 1], a[r + 2], a[r + 3]};
         }
         if (ln.hi == 0) {
-          hand_stat[32 * wave + lq] = st.mc_ref[0];
+          hand_stat[32 * wave + lq] = st.m_run[0];
           hand_stat[kTile + 32 * wave + lq] = l_half;
         }
       }
       __syncthreads();
       if (grp == 0) {
         const float m1 = hand_stat[32 * wave + lq], l1 = hand_stat[kTile + 32 * wave + lq];
-        const float top = fmaxf(st.mc_ref[0], m1);
-        const float f0 = __builtin_amdgcn_exp2f(st.mc_ref[0] - top), f1 = __builtin_amdgcn_exp2f(m1 - top);
-        st.mc_ref[0] = top;
+        const float top = fmaxf(st.m_run[0], m1);
+        const float f0 = __builtin_amdgcn_exp2f((st.m_run[0] - top) * ln.c), f1 = __builtin_amdgcn_exp2f((m1 - top) * ln.c);
+        st.m_run[0] = top;
         st.l_run[0] = 0.5f * (f0 * l_half + f1 * l1);  // (each half of the wave: half of the row sum)
-        st.m_run[0] = st.m_all;
 #pragma unroll
         for (int g = 0; g < 16; ++g) {
           f32x16& a = st.oacc[0][g >> 2];
@@ -1470,7 +1464,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   if constexpr (FEW) {
     if (split) {
       // partial result of this segment, to be merged: O^T accumulators as the lanes hold them (1 KB per store), the
-      // reference of the exponentials, the row sums and the row maxima
+      // row maxima (reference of the exponentials) and the row sums
       const size_t s = (size_t)row * e->nseg + seg;
       static_assert(QB == 1, "one Q block per wave");
       float* po = e->seg_o + (s * 4 + wave) * 4096 + 4 * lane;
@@ -1484,10 +1478,9 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
         }
       const float l = other_half_sum(st.l_run[0]);
       if (ln.hi == 0) {
-        float* ps = e->seg_stat + s * 3 * kTile + 32 * wave + lq;
-        ps[0] = st.mc_ref[0];
+        float* ps = e->seg_stat + s * 2 * kTile + 32 * wave + lq;
+        ps[0] = st.m_run[0];
         ps[kTile] = l;
-        ps[2 * kTile] = st.m_run[0];
       }
       return;
     }
@@ -1549,7 +1542,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
 // segments, or of eight tiles' maxima, in flight together (call of 32 rows x 4 segments of 4 tiles 22.0 -> 20.7
 // us, of 128 rows x 2 segments of 64 tiles 163 -> 147 us, against one load at a time).
 // Rows that were cut into segments (FEW, nseg > 1): merges the segments' partial results and judges the tiles.
-// Workgroups 0 .. 4*rows-1: 32 Q rows each, one thread per (row, 8 features): O = sum_s 2^(m_s - M) O_s / sum_s ... .
+// Workgroups 0 .. 4*rows-1: 32 Q rows each, one thread per (row, 8 features): O = sum_s 2^(c (m_s - M)) O_s / sum_s ... .
 // Workgroups 4*rows .. 5*rows-1: one Skip-Mask row each; two waves per segment walk its tiles with the running maximum
 // carried over from the segments before it (exactly the maximum a single pass would have), set the row's mask bits and
 // add the step's counters.
@@ -1563,10 +1556,11 @@ __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const Fwd
     const int i = row % p.Tq, bh = row / p.Tq;
     const int lq = tid & 31, e = tid >> 5;  // e = 4 * d-block + group of four accumulator registers
     const int qrow = i * kTile + 32 * wave + lq;
-    const float* ps = p.seg_stat + (size_t)row * nseg * 3 * kTile + 32 * wave + lq;
+    const float* ps = p.seg_stat + (size_t)row * nseg * 2 * kTile + 32 * wave + lq;
     const float* po = p.seg_o + ((size_t)row * nseg * 4 + wave) * 4096 + 256 * e + 4 * lq;
-    float top = -INFINITY, l = 0.f;
-    for (int s = 0; s < nseg; ++s) top = fmaxf(top, ps[s * 3 * kTile]);
+    const float c = p.scale * 1.4426950408889634f;
+    float top = kNoMax, l = 0.f;
+    for (int s = 0; s < nseg; ++s) top = fmaxf(top, ps[s * 2 * kTile]);
     float4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
     constexpr int kAhead = 4;  // segments whose loads are in flight together
     for (int s0 = 0; s0 < nseg; s0 += kAhead) {
@@ -1575,15 +1569,15 @@ __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const Fwd
 #pragma unroll
       for (int u = 0; u < kAhead; ++u) {
         const int s = min(s0 + u, nseg - 1);
-        m[u] = ps[s * 3 * kTile];
-        ls[u] = ps[s * 3 * kTile + kTile];
+        m[u] = ps[s * 2 * kTile];
+        ls[u] = ps[s * 2 * kTile + kTile];
         x[u] = *reinterpret_cast<const float4*>(po + (size_t)s * 4 * 4096);
         y[u] = *reinterpret_cast<const float4*>(po + (size_t)s * 4 * 4096 + 128);
       }
 #pragma unroll
       for (int u = 0; u < kAhead; ++u) {
-        if (s0 + u >= nseg || m[u] == kNoRef) continue;  // a segment without tiles has written no O
-        const float f = __builtin_amdgcn_exp2f(m[u] - top);
+        if (s0 + u >= nseg || m[u] == kNoMax) continue;  // a segment without tiles has written no O
+        const float f = __builtin_amdgcn_exp2f((m[u] - top) * c);
         l += f * ls[u];
         a.x += f * x[u].x; a.y += f * x[u].y; a.z += f * x[u].z; a.w += f * x[u].w;
         b.x += f * y[u].x; b.y += f * y[u].y; b.z += f * y[u].z; b.w += f * y[u].w;
@@ -1614,7 +1608,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const Fwd
 #pragma unroll
   for (int x = 0; x < kMaxSegments; ++x)
     if (x < 4 || nseg > 4)
-      seg_max[x] = p.seg_stat[((size_t)row * nseg + min(x, nseg - 1)) * 3 * kTile + 2 * kTile + r];
+      seg_max[x] = p.seg_stat[((size_t)row * nseg + min(x, nseg - 1)) * 2 * kTile + r];
   walk.open(skipped, p.Tk, p.W, p.diagonal_first ? i : 0);
   walk.count(cnt, nruns);
   const bool q_pinned = p.protect_len > 0 && i * kTile < p.protect_start + p.protect_len &&
