@@ -117,10 +117,8 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     // all workgroups start together, or all rows are equally long: nothing to schedule
     if (g.rows > kFewRows && g.rows <= kSchedRows && !a.fresh) {
       p.scheduled = 1;
-      p.schedule_only = true;
-      e = launch_fwd(p, false, stream);
+      e = launch_schedule_rows(a.bits, (int)g.rows, g.Tk, g.W, g.per_xcd, slots, xcd_rows, stream);
       if (e != hipSuccess) return e;
-      p.schedule_only = false;
     }
   }
   if (mid) {

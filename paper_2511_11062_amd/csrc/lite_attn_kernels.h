@@ -52,10 +52,8 @@ struct FwdParams {
   // schedule (per_xcd = workgroups per XCD); the row cut into nseg segments, one workgroup each.
   int nseg = 0;
   int pair = 0;
-  // Not scheduled: the (head, segment, row) triples in order, an eighth of them to each XCD.  schedule_only: launch_fwd
-  // makes the table (slots, xcd_rows) of such a call instead of running it.
+  // Not scheduled: the (head, segment, row) triples in order, an eighth of them to each XCD.
   int scheduled = 0;
-  bool schedule_only = false;
   int fresh = 0;                         // step 0: the mask counts as empty and is overwritten
   const uint16_t* v = nullptr;
   float* seg_o = nullptr;                // [rows][nseg][128][128] O^T partials in accumulator order
@@ -124,7 +122,6 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
                        const CallArgs& a, hipStream_t stream, hipEvent_t mid);
 int hip_fail(hipError_t e);  // remembers e for lite_attn_last_hip_error() and maps it to a lite_attn_error
 
-int fwd_lds_bytes();
 hipError_t prepare_fwd();
 hipError_t launch_clear(uint64_t* bits, size_t words, unsigned long long* stats, size_t nstats, hipStream_t st);
 hipError_t launch_compact(const uint64_t* bits, int rows, int Tq, int Tk, int W, int diagonal_first, int run_stride,
@@ -135,6 +132,8 @@ hipError_t launch_order_rows(const uint32_t* live_cnt, int BH, int Tq, int Tk, u
                              hipStream_t st);
 hipError_t launch_deal_rows(const uint32_t* chunk_work, const uint32_t* order, int BH, int Tq, int chunks, int per_xcd,
                             uint32_t* slots, uint32_t* xcd_rows, hipStream_t st);
+hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int Tk, int W, int per_xcd, uint32_t* slots,
+                                uint32_t* xcd_rows, hipStream_t st);
 hipError_t launch_fwd(const FwdParams& p, bool immediate, hipStream_t st);
 
 }  // namespace la

@@ -1664,8 +1664,6 @@ __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const Fwd
   }
 }
 
-int fwd_lds_bytes() { return kLdsBytes; }
-
 hipError_t launch_clear(uint64_t* bits, size_t words, unsigned long long* stats, size_t nstats, hipStream_t st) {
   size_t n = words > nstats ? words : nstats;
   int blocks = (int)((n + 255) / 256);
@@ -1729,12 +1727,13 @@ hipError_t launch_deal_rows(const uint32_t* chunk_work, const uint32_t* order, i
   return hipGetLastError();
 }
 
+hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int Tk, int W, int per_xcd, uint32_t* slots,
+                                uint32_t* xcd_rows, hipStream_t st) {
+  hipLaunchKernelGGL(schedule_rows_kernel, dim3(8), dim3(kSchedThreads), 0, st, bits, rows, Tk, W, per_xcd, slots, xcd_rows);
+  return hipGetLastError();
+}
+
 hipError_t launch_fwd(const FwdParams& p, bool immediate, hipStream_t st) {
-  if (p.schedule_only) {
-    hipLaunchKernelGGL(schedule_rows_kernel, dim3(8), dim3(kSchedThreads), 0, st, p.bits, p.rows_total, p.Tk, p.W,
-                       p.per_xcd, const_cast<uint32_t*>(p.slots), const_cast<uint32_t*>(p.xcd_rows));
-    return hipGetLastError();
-  }
   // one workgroup per slot of the schedule table (FEW: per segment); those past an XCD's last row return at once
   const dim3 grid(8 * p.per_xcd), block(Geo<kQB>::kThreads);
   if (p.nseg == 0) {

@@ -7,7 +7,6 @@
 
 namespace la {
 
-int fwd_lds_bytes() { return 0; }
 hipError_t prepare_fwd() { return hipSuccess; }
 
 hipError_t launch_clear(uint64_t* bits, size_t words, unsigned long long* stats, size_t nstats, hipStream_t) {
@@ -49,6 +48,15 @@ hipError_t launch_deal_rows(const uint32_t* chunk_work, const uint32_t* order, i
 hipError_t launch_transpose_v(const uint16_t*, uint16_t* vt, int64_t, int64_t, int64_t, int BH, int, int, int Tk,
                               hipStream_t) {
   memset(vt, 0, sizeof(uint16_t) * (size_t)BH * 128 * ((size_t)Tk * 128));
+  return hipSuccess;
+}
+
+hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int, int W, int per_xcd, uint32_t* slots,
+                                uint32_t* xcd_rows, hipStream_t) {
+  volatile uint64_t sink = bits[0] + bits[(size_t)rows * W - 1];
+  (void)sink;
+  memset(slots, 0, sizeof(uint32_t) * 8 * (size_t)per_xcd);
+  for (int x = 0; x < 8; ++x) xcd_rows[x] = 0;
   return hipSuccess;
 }
 
