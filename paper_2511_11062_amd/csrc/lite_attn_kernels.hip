@@ -310,9 +310,15 @@ __global__ __launch_bounds__(256) void deal_rows_kernel(const uint32_t* __restri
 // Row schedule of a call with short rows (FEW, kFewRows < rows <= kSchedRows), from the mask itself, in one launch:
 // workgroup x names the rows of XCD x.  Rows are numbered (head, Q tile); an XCD takes a contiguous range of them -- its
 // workgroups share the K/V of a few heads in its L2 -- such that all ranges hold the same work (live tiles +
-// kRowOverhead per row), bent where it would exceed per_xcd rows.  Within its range the longest rows come first, in
-// kLengthClasses classes, heads and Q tiles in order inside a class (rows of one head and similar length run side by
-// side).  Every workgroup counts the live tiles of all rows (at most three words each).
+// kRowOverhead per row).  Where heads differ so much that a range would exceed per_xcd rows, an XCD takes two ranges: an
+// eighth, by number, of the rows with at most the mean work, and of the longer ones as many as bring it to an eighth of all
+// work (there is always room for some: the first kind holds less than an eighth).  At most 1.9 times its share of
+// rows then; should that still be too many, an eighth of the rows in order.  Busiest XCD's work over the mean, from the
+// table: 40 heads x 61 tiles, half of the heads 70 % live, half 20 %, 1.32 with the overflow handed to the next XCD,
+// 1.005 with two ranges; 90 / 15 % 1.84 -> 1.003; one dense head of eight 2.8 -> 1.03.
+// Within its range the longest rows come first, in kLengthClasses classes, heads and Q tiles in order inside a class
+// (rows of one head and similar length run side by side).  Every workgroup counts the live tiles of all rows (at most
+// three words each).
 // Bound by latency: a dozen dependent steps.  With the V^T pass gone it replaces three launches (ranking, dealing,
 // transposing; 31 us beside 210-305 us of attention for 888 rows of 37 tiles): three steps of that layer 750 -> 627 us,
 // two of 2440 rows x 61 tiles 3850 -> 3661, four of 1320 x 110 (diagonal first) 2262 -> 2165, three of 5120 x 128
@@ -326,11 +332,14 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
                                                                        uint32_t* __restrict__ slots,
                                                                        uint32_t* __restrict__ xcd_rows) {
   constexpr int kWaves = kSchedThreads / 64;
-  __shared__ uint32_t part[kSchedThreads];  // work before each thread's piece of the rows
-  __shared__ uint32_t wave_sum[kWaves];
+  // before each thread's piece of the rows: work of the long rows | work of the others << 24 | number of the others << 48
+  __shared__ uint64_t part[kSchedThreads];
+  static_assert((uint64_t)kSchedRows * (kShortTiles + kRowOverhead) < 1u << 24 && kSchedRows < 1 << 16, "fields of `part`");
+  __shared__ uint64_t wave_sum[kWaves];
   __shared__ uint32_t table[kLengthClasses * kWaves];
   __shared__ uint32_t class_base[kLengthClasses];
-  __shared__ int first_row[9];
+  // where XCD y's ranges start (9: where the last one ends): row, and rows of the kind before it
+  __shared__ int first_long[9], longs_before[9], first_other[9], others_before[9];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, xcd = blockIdx.x;
   auto live_tiles = [&](int row) -> uint32_t {
     uint32_t n = 0;
@@ -341,51 +350,111 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
     }
     return n;
   };
-  // work before each row: this thread's contiguous piece, then a scan over the threads
   const int piece = (rows + kSchedThreads - 1) / kSchedThreads;
   const int lo = min(rows, tid * piece), hi = min(rows, lo + piece);
-  uint32_t sum = 0;
-  for (int r = lo; r < hi; ++r) sum += live_tiles(r) + kRowOverhead;
-  uint32_t scan = sum;
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t o = __shfl_up(scan, d, 64);
-    if (lane >= d) scan += o;
-  }
-  if (lane == 63) wave_sum[wave] = scan;
-  __syncthreads();
-  uint32_t before = 0, total = 0;
-  for (int x = 0; x < kWaves; ++x) {
-    if (x < wave) before += wave_sum[x];
-    total += wave_sum[x];
-  }
-  part[tid] = before + scan - sum;
-  __syncthreads();
-  // boundaries: XCD y starts at the first row with at least y/8 of the work before it
-  if (tid < 9) {
-    int b = rows;
-    if (tid < 8) {
-      const uint64_t goal = (uint64_t)total * tid;  // in eighths
-      int t = 0;
-      for (int step = kSchedThreads / 2; step > 0; step >>= 1)  // last thread whose piece starts below the goal
-        if (8ull * part[t + step] < goal) t += step;
-      b = min(rows, t * piece);
-      uint64_t work = part[t];
-      while (b < rows && 8 * work < goal) work += live_tiles(b++) + kRowOverhead;
+  uint32_t total = 0;
+  uint32_t bar = 0;  // rows of more than bar / rows work count as long: all of them, those above the mean, none
+  auto is_long = [&](uint32_t work) { return work * (uint32_t)rows > bar; };
+  int l0, l1, o0, o1;  // this XCD's ranges: long rows of [l0, l1), others of [o0, o1)
+  for (int attempt = 0;; ++attempt) {
+    // this thread's contiguous piece, then a scan over the threads
+    uint64_t sum = 0;
+    for (int r = lo; r < hi; ++r) {
+      const uint32_t work = live_tiles(r) + kRowOverhead;
+      sum += is_long(work) ? (uint64_t)work : ((uint64_t)work << 24) | (1ull << 48);
     }
-    first_row[tid] = b;
+    uint64_t scan = sum;
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint64_t o = __shfl_up((unsigned long long)scan, d, 64);
+      if (lane >= d) scan += o;
+    }
+    if (lane == 63) wave_sum[wave] = scan;
+    __syncthreads();
+    uint64_t before = 0, all = 0;
+    for (int x = 0; x < kWaves; ++x) {
+      if (x < wave) before += wave_sum[x];
+      all += wave_sum[x];
+    }
+    part[tid] = before + scan - sum;
+    total = (uint32_t)(all & 0xffffffu) + (uint32_t)((all >> 24) & 0xffffffu);
+    const int others = (int)(all >> 48);
+    __syncthreads();
+    // boundaries: y/8 of the others before the one, of the long rows what completes y/8 of the work before the other
+    if (tid < 9) {
+      int b = 0, left = others * tid / 8;
+      others_before[tid] = left;
+      uint32_t other_work = 0;
+      if (left > 0) {
+        int t = 0;
+        for (int step = kSchedThreads / 2; step > 0; step >>= 1)  // last thread with fewer than that before its piece
+          if ((int)(part[t + step] >> 48) < left) t += step;
+        b = min(rows, t * piece);
+        left -= (int)(part[t] >> 48);
+        other_work = (uint32_t)(part[t] >> 24) & 0xffffffu;
+        for (; b < rows && left > 0; ++b) {
+          const uint32_t work = live_tiles(b) + kRowOverhead;
+          if (!is_long(work)) {
+            other_work += work;
+            --left;
+          }
+        }
+      }
+      first_other[tid] = b;
+      b = rows;
+      int longs = rows - others;
+      if (tid < 8) {
+        const int64_t goal = (int64_t)total * tid - 8 * (int64_t)other_work;  // in eighths
+        int t = 0;
+        for (int step = kSchedThreads / 2; step > 0; step >>= 1)  // last thread whose piece starts below the goal
+          if (8 * (int64_t)(part[t + step] & 0xffffffu) < goal) t += step;
+        b = min(rows, t * piece);
+        longs = b - (int)(part[t] >> 48);
+        int64_t work = (int64_t)(part[t] & 0xffffffu);
+        for (; b < rows && 8 * work < goal; ++b) {
+          const uint32_t w = live_tiles(b) + kRowOverhead;
+          if (is_long(w)) {
+            work += w;
+            ++longs;
+          }
+        }
+      }
+      first_long[tid] = b;
+      longs_before[tid] = longs;
+    }
+    for (int x = tid; x < kLengthClasses; x += kSchedThreads) class_base[x] = 0;
+    __syncthreads();
+    bool fits = true;
+    int start = 0, count = 0;  // (goals a row apart may come out in the other order)
+    l0 = l1 = 0;
+    for (int y = 1; y <= 8; ++y) {
+      const int s = max(start, first_long[y]), c = max(count, longs_before[y]);
+      fits = fits && c - count + others_before[y] - others_before[y - 1] <= per_xcd;
+      if (y == xcd + 1) {
+        l0 = start;
+        l1 = s;
+      }
+      start = s;
+      count = c;
+    }
+    o0 = first_other[xcd];
+    o1 = first_other[xcd + 1];
+    if (fits || attempt == 2) break;  // (an eighth of the rows, by number, always fits: 8 * per_xcd >= rows)
+    bar = attempt == 0 ? total : 0xffffffffu;
+    __syncthreads();
   }
-  for (int x = tid; x < kLengthClasses; x += kSchedThreads) class_base[x] = 0;
-  __syncthreads();
-  // no XCD takes more than per_xcd rows (8 * per_xcd >= rows): bend the boundaries from the first to the last
-  int r0 = 0, r1 = 0;
-  for (int x = 1; x <= xcd + 1; ++x) {
-    r0 = r1;
-    r1 = max(rows - (8 - x) * per_xcd, min(first_row[x], r0 + per_xcd));
-  }
-  const int n = r1 - r0;
-  auto length_class = [&](uint32_t live) -> int { return (int)((uint32_t)(Tk - live) * kLengthClasses / (uint32_t)(Tk + 1)); };
+  const int span = l1 - l0, n = span + o1 - o0;  // rows to look at; those of the other kind are passed over
+  auto row_at = [&](int x) { return x < span ? l0 + x : o0 + x - span; };
+  auto length_class = [&](int x) -> int {
+    if (x >= n) return -1;
+    const uint32_t live = live_tiles(row_at(x));
+    if (is_long(live + kRowOverhead) != (x < span)) return -1;
+    return (int)((uint32_t)(Tk - live) * kLengthClasses / (uint32_t)(Tk + 1));
+  };
   // class sizes -> first position of each class
-  for (int x = tid; x < n; x += kSchedThreads) atomicAdd(&class_base[length_class(live_tiles(r0 + x))], 1u);
+  for (int x = tid; x < n; x += kSchedThreads) {
+    const int c = length_class(x);
+    if (c >= 0) atomicAdd(&class_base[c], 1u);
+  }
   __syncthreads();
   if (tid == 0) {
     uint32_t run = 0;
@@ -394,12 +463,12 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
       class_base[x] = run;
       run += c;
     }
+    xcd_rows[xcd] = run;
   }
   __syncthreads();
   // positions inside the classes, in row order: kSchedThreads rows at a time
   for (int x0 = 0; x0 < n; x0 += kSchedThreads) {
-    const int x = x0 + tid;
-    const int mine = x < n ? length_class(live_tiles(r0 + x)) : -1;
+    const int mine = length_class(x0 + tid);
     uint32_t rank = 0;
 #pragma unroll 4
     for (int y = 0; y < kLengthClasses; ++y) {
@@ -411,7 +480,7 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
     if (mine >= 0) {
       uint32_t pos = class_base[mine] + rank;
       for (int y = 0; y < wave; ++y) pos += table[mine * kWaves + y];
-      slots[(size_t)xcd * per_xcd + pos] = (uint32_t)(r0 + x);
+      slots[(size_t)xcd * per_xcd + pos] = (uint32_t)row_at(x0 + tid);
     }
     __syncthreads();
     if (tid < kLengthClasses) {
@@ -421,7 +490,6 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
     }
     __syncthreads();
   }
-  if (tid == 0) xcd_rows[xcd] = (uint32_t)n;
 }
 
 // V -> V^T pre-pass.  The PV product contracts over the K/V index, so the matrix cores want, per lane, 8 V values

@@ -8,6 +8,8 @@ bf16 bytes and are compared:
   * exit mask: bit-exact, except tiles whose oracle predicate value lies within 1e-3 of the threshold.
 Rows (b,h,i) are independent, so large shapes are compared on a sample of rows.
 """
+import ctypes
+
 import numpy as np
 import torch
 
@@ -17,6 +19,24 @@ from oracle.lite_attn_oracle import oracle_step
 MAX_REL = 1e-2     # max|dO| <= MAX_REL * max|O|
 MEAN_ABS = 1e-3    # mean|dO| <= MEAN_ABS
 G_BAND = 1e-3      # |g - thr| <= G_BAND excuses a mask bit
+
+
+class Path(ctypes.Structure):
+    """la::Geometry (csrc/lite_attn_kernels.h): which way through the library a shape takes.  nseg 0: Skip-Lists, row
+    ranking and V^T; 1: whole rows found from the mask; more: rows cut into segments.  pair: workgroups of two groups."""
+    _fields_ = [("Tq", ctypes.c_int), ("Tk", ctypes.c_int), ("W", ctypes.c_int), ("run_stride", ctypes.c_int),
+                ("BH", ctypes.c_int), ("rows", ctypes.c_int64), ("chunks", ctypes.c_int), ("pair", ctypes.c_int),
+                ("nseg", ctypes.c_int), ("per_xcd", ctypes.c_int)]
+
+
+def path_of(batch, heads, seqlen, flags=0) -> Path:
+    """What the library itself decides for a layer, so that a test can say which kernels it is about."""
+    from paper_2511_11062_amd import lite_attn as la
+    f = la._lib._ZN2la8geometryERK16lite_attn_desc_t
+    f.restype, f.argtypes = Path, [ctypes.POINTER(la.Desc)]
+    p = f(ctypes.byref(la.make_desc(batch, heads, seqlen, flags=flags)))
+    assert (p.Tk, p.BH, p.rows) == (-(-seqlen // 128), batch * heads, batch * heads * -(-seqlen // 128))
+    return p
 
 
 def pack_mask(mask_bytes: np.ndarray) -> np.ndarray:
