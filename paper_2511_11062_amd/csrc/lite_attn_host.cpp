@@ -94,7 +94,10 @@ Geometry geometry(const lite_attn_desc_t& d) {
     g.nseg = 1;
     if (g.rows <= kFewRows) share_chip(g, d.flags);
     g.per_xcd = (int)((g.rows * g.nseg + 7) / 8);
-    if (g.rows > kFewRows) g.per_xcd += g.per_xcd / 2;  // room for an XCD whose rows are short
+    if (g.rows > kSchedRows)
+      g.per_xcd = (int)((g.rows + 8 * kDealtRows - 1) / (8 * kDealtRows)) * kDealtRows;
+    else if (g.rows > kFewRows)
+      g.per_xcd += g.per_xcd / 2;  // room for an XCD whose rows are short
   }
   return g;
 }

@@ -11,17 +11,23 @@ namespace la {
 // Rows of one head that an XCD runs side by side (2 workgroups x 32 CUs): the unit of the row schedule ("chunk").
 constexpr int kChunkRows = 64;
 
-// Calls with few rows or short rows take no Skip-Lists and no V^T (kernel argument FEW; measurements at
+// Calls with few rows or short rows take no Skip-Lists and no V^T (template argument FEW; measurements at
 // schedule_rows_kernel): at most kFewRows Q-tile rows -- all of whose workgroups fit the chip at once; they need no schedule
 // and may be cut into segments, whose partial results stay small enough for the static scratch array -- or at most
-// kShortTiles tiles a row.  Beyond kSchedRows rows there are so many rounds of workgroups that the order of the rows
-// does not matter.
+// kShortTiles tiles a row.  Beyond kSchedRows rows there are so many rounds of workgroups that the order of the rows inside
+// an XCD does not matter and no table is made: chunks of kDealtRows rows go to the XCDs in turn (dealt_chunk).
 constexpr int kFewRows = 512;
 constexpr int kShortTiles = 192;
 constexpr int kSchedRows = 32768;
+constexpr int kDealtRows = kChunkRows;
 constexpr int kPairWorkgroups = 256;
 constexpr int kMaxSegments = 16;
 constexpr size_t kMaxSegmentBytes = (size_t)104 << 20;
+
+// The chunk of rows that XCD `xcd` takes of the `group`-th eight chunks.  The assignment turns from group to group, in
+// three periods, so that heads that differ with a period of their own (the heads of a layer, batch entry after batch entry)
+// do not all fall to one XCD.
+constexpr int dealt_chunk(int group, int xcd) { return 8 * group + ((xcd - group - group / 8 - group / 64) & 7); }
 
 struct FwdParams {
   const uint16_t* q;
@@ -52,7 +58,7 @@ struct FwdParams {
   // schedule (per_xcd = workgroups per XCD); the row cut into nseg segments, one workgroup each.
   int nseg = 0;
   int pair = 0;
-  // Not scheduled: the (head, segment, row) triples in order, an eighth of them to each XCD.
+  // Not scheduled: the (head, segment, row) triples in order, an eighth of them to each XCD; beyond kSchedRows rows chunks.
   int scheduled = 0;
   int fresh = 0;                         // step 0: the mask counts as empty and is overwritten
   const uint16_t* v = nullptr;

@@ -1074,14 +1074,24 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   // Consecutive workgroup ids land on different XCDs (id % 8): workgroup `slot` of an XCD computes the row that the
   // schedule table names for it (deal_rows_kernel: chunks of kChunkRows rows of one head side by side, so that the
   // workgroups sharing one L2 stream the same K/V; equal work per XCD; long rows first).
-  // FEW: no table; the (head, segment, row) triples are numbered row-fastest and every XCD takes an eighth of them, so
-  // that the rows walking the same K/V tiles of a head share an L2.
+  // FEW: the table of schedule_rows_kernel if the call has one; else the (head, segment, row) triples, numbered
+  // row-fastest, an eighth to every XCD, so that the rows walking the same K/V tiles of a head share an L2; beyond kSchedRows
+  // rows, where the XCDs' shares would be whole heads, chunks of rows dealt to the XCDs in turn.  Over 200 seeded sets of
+  // head densities (260-1000 heads, alike to 0.05 against 0.95, with and without a period) the busiest XCD has 1.035 times
+  // the mean work, at worst 1.18; eighths give 4.4 where an eighth of the heads is dense and the others 10 % live.  320
+  // heads x 128 tiles, ms: that mask 30.6 -> 9.3, half the heads 90 % and half 15 % live 34.8 -> 21.7, all 45 % 19.6 both
+  // ways (chunks of 32 rows 19.7, of 128 19.6).
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   int row, i, bh, seg = 0;
   if constexpr (FEW) {
     if (p.scheduled) {
       if (slot >= (int)p.xcd_rows[xcd]) return;
       row = (int)p.slots[(size_t)xcd * p.per_xcd + slot];
+      bh = quotient(row, p.Tq);
+      i = row - bh * p.Tq;
+    } else if (p.rows_total > kSchedRows) {
+      row = dealt_chunk(slot / kDealtRows, xcd) * kDealtRows + slot % kDealtRows;
+      if (row >= p.rows_total) return;
       bh = quotient(row, p.Tq);
       i = row - bh * p.Tq;
     } else {
@@ -1802,8 +1812,10 @@ hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int Tk, int W, i
 }
 
 hipError_t launch_fwd(const FwdParams& p, bool immediate, hipStream_t st) {
-  // one workgroup per slot of the schedule table (FEW: per segment); those past an XCD's last row return at once
-  const dim3 grid(8 * p.per_xcd), block(Geo<kQB>::kThreads);
+  // one workgroup per slot of the schedule table (FEW without a table: per segment or row); those past an XCD's last row
+  // return at once
+  const bool in_order = p.nseg > 0 && !p.scheduled && p.rows_total <= kSchedRows;
+  const dim3 grid(8 * (in_order ? (p.rows_total * p.nseg + 7) / 8 : p.per_xcd)), block(Geo<kQB>::kThreads);
   if (p.nseg == 0) {
     if (immediate)
       hipLaunchKernelGGL((lite_attn_fwd_kernel<1, true, false, false>), grid, block, kLdsBytes, st, p);

@@ -30,12 +30,12 @@ def test_marking_across_segments(heads, tokens, text, diagonal_first):
 
 
 @pytest.mark.parametrize("heads,tiles", [(1, 5), (2, 16), (1, 65), (3, 100), (4, 128), (1, 513), (27, 19),
-                                         (3, 192), (8, 193), (520, 2), (33000, 1)])
+                                         (3, 192), (8, 193), (520, 2), (33000, 1), (3301, 10)])
 @pytest.mark.parametrize("live", [0.02, 0.5, "uneven"])
 def test_every_row_under_sparse_masks(heads, tiles, live):
     """Random imported masks, many rows with fewer live tiles than segments and some with none, every row against
     block-masked softmax attention in fp32; 512 and 513 rows, 192 and 193 tiles a row and 32768 rows are where the path changes
-    (no schedule / rows scheduled / lists and V^T; the last, rows in order)."""
+    (no schedule / rows scheduled / lists and V^T; beyond 32768 rows, chunks of rows dealt in turn)."""
     from paper_2511_11062_amd import lite_attn as la
     n = 128 * tiles - 3
     g = torch.Generator(device="cuda").manual_seed(1000 * heads + tiles)
