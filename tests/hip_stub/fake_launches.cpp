@@ -5,6 +5,13 @@
 
 #include "lite_attn_kernels.h"
 
+namespace {
+
+// Pieces of one allocation that must not run into the piece behind them (AddressSanitizer sees only the allocation's end).
+bool before(const void* end, const void* next) { return (uintptr_t)end <= (uintptr_t)next; }
+
+}  // namespace
+
 namespace la {
 
 hipError_t prepare_fwd() { return hipSuccess; }
@@ -40,6 +47,7 @@ hipError_t launch_deal_rows(const uint32_t* chunk_work, const uint32_t* order, i
                             uint32_t* slots, uint32_t* xcd_rows, hipStream_t) {
   volatile uint32_t sink = chunk_work[chunks - 1] + order[(size_t)BH * Tq - 1];
   (void)sink;
+  if (!before(slots + 8 * (size_t)per_xcd, xcd_rows)) return hipErrorInvalidValue;
   memset(slots, 0, sizeof(uint32_t) * 8 * (size_t)per_xcd);   // the whole table may be written
   for (int x = 0; x < 8; ++x) xcd_rows[x] = 0;
   return hipSuccess;
@@ -55,30 +63,60 @@ hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int, int W, int 
                                 uint32_t* xcd_rows, hipStream_t) {
   volatile uint64_t sink = bits[0] + bits[(size_t)rows * W - 1];
   (void)sink;
+  if (!before(slots + 8 * (size_t)per_xcd, xcd_rows)) return hipErrorInvalidValue;
   memset(slots, 0, sizeof(uint32_t) * 8 * (size_t)per_xcd);
   for (int x = 0; x < 8; ++x) xcd_rows[x] = 0;
   return hipSuccess;
 }
 
-hipError_t launch_fwd(const FwdParams& p, bool, hipStream_t) {
-  // touches the first and last element of everything the kernel reads or writes besides q, k, v, out
+namespace {
+
+// Few or short rows: no lists and no V^T.  Rows cut into segments leave partial results in the scratch, for the merge pass
+// behind the fused kernel; at step 0 the mask is overwritten and, with segments, all counters are cleared.
+hipError_t fwd_without_lists(const FwdParams& p) {
   const size_t rows = (size_t)p.rows_total;
-  volatile uint32_t sink = p.runs[0] + p.runs[rows * p.run_stride - 1] + p.nruns[rows - 1] + p.live_cnt[rows - 1] +
-                           p.slots[8 * (size_t)p.per_xcd - 1] + p.xcd_rows[7] + p.vt[(size_t)(rows / p.Tq) * 128 * ((size_t)p.Tk * 128) - 1];
+  volatile uint32_t sink = 0;
+  if (p.scheduled) sink = p.slots[8 * (size_t)p.per_xcd - 1] + p.xcd_rows[7];
   (void)sink;
-  p.bits[0] |= 0;
-  p.bits[rows * p.W - 1] |= 0;
+  if (p.nseg > 1) {
+    if (!before(p.seg_o + rows * p.nseg * 128 * 128, p.seg_stat) || !before(p.seg_stat + rows * p.nseg * 2 * 128, p.seg_mloc))
+      return hipErrorInvalidValue;
+    memset(p.seg_o, 0, sizeof(float) * rows * p.nseg * 128 * 128);
+    memset(p.seg_stat, 0, sizeof(float) * rows * p.nseg * 2 * 128);
+    memset(p.seg_mloc, 0, sizeof(float) * rows * p.Tk * 128);
+    if (p.fresh) memset(p.stats_all, 0, sizeof(unsigned long long) * (size_t)p.stat_words);
+  }
+  for (size_t x = 0; x < rows * p.W; ++x) p.bits[x] = p.fresh ? 0 : p.bits[x];
+  return hipSuccess;
+}
+
+}  // namespace
+
+hipError_t launch_fwd(const FwdParams& p, bool, hipStream_t) {
+  const size_t rows = (size_t)p.rows_total;
+  if (p.nseg > 0) {
+    const hipError_t e = fwd_without_lists(p);
+    if (e != hipSuccess) return e;
+  } else {
+    // the first and last element of everything the kernel reads or writes besides q, k, v, out
+    volatile uint32_t sink = p.runs[0] + p.runs[rows * p.run_stride - 1] + p.nruns[rows - 1] + p.live_cnt[rows - 1] +
+                             p.slots[8 * (size_t)p.per_xcd - 1] + p.xcd_rows[7] +
+                             p.vt[(size_t)(rows / p.Tq) * 128 * ((size_t)p.Tk * 128) - 1];
+    (void)sink;
+    p.bits[0] |= 0;
+    p.bits[rows * p.W - 1] |= 0;
+    if (p.build_next) {  // the epilogue rewrites the lists in full
+      memset(p.runs, 0, sizeof(uint32_t) * rows * p.run_stride);
+      for (size_t r = 0; r < rows; ++r) {
+        p.runs[r * p.run_stride] = (uint32_t)p.Tk << 16;
+        p.nruns[r] = 1;
+        p.live_cnt[r] = (uint32_t)p.Tk;
+      }
+    }
+  }
   *p.stat_skipped_in += 0;
   *p.stat_newly += 0;
   *p.stat_runs += (unsigned long long)rows;
-  if (p.build_next) {  // the epilogue rewrites the lists in full
-    memset(p.runs, 0, sizeof(uint32_t) * rows * p.run_stride);
-    for (size_t r = 0; r < rows; ++r) {
-      p.runs[r * p.run_stride] = (uint32_t)p.Tk << 16;
-      p.nruns[r] = 1;
-      p.live_cnt[r] = (uint32_t)p.Tk;
-    }
-  }
   return hipSuccess;
 }
 

@@ -45,6 +45,23 @@ lib.lite_attn_ctx_set_stream.argtypes = [H, ctypes.c_void_p]
 lib.lite_attn_ctx_free.argtypes = [H]
 
 
+class Path(ctypes.Structure):                    # la::Geometry
+    _fields_ = [("Tq", ctypes.c_int), ("Tk", ctypes.c_int), ("W", ctypes.c_int), ("run_stride", ctypes.c_int),
+                ("BH", ctypes.c_int), ("rows", ctypes.c_int64), ("chunks", ctypes.c_int), ("pair", ctypes.c_int),
+                ("nseg", ctypes.c_int), ("per_xcd", ctypes.c_int)]
+
+
+geometry = lib._ZN2la8geometryERK16lite_attn_desc_t
+geometry.restype, geometry.argtypes = Path, [ctypes.POINTER(Desc)]
+
+
+def path(heads, n, flags=0):
+    p = geometry(ctypes.byref(desc(heads, n, flags=flags)))
+    assert (p.BH, p.rows) == (heads, heads * -(-n // 128))
+    return "lists" if p.nseg == 0 else "segments" if p.nseg > 1 else "in order" if p.rows <= 512 else \
+        "schedule" if p.rows <= 32768 else "dealt"
+
+
 def desc(heads, n, steps=3, flags=0, protect=(0, 0)):
     return Desc(1, heads, n, 128, 128, 128, heads * n * 128, n * 128, 128, protect[0], protect[1], flags, steps)
 
@@ -88,8 +105,10 @@ def exercise(h, heads, n, steps):
     assert (cnt == tk).all() and (idx == np.arange(tk, dtype=np.uint16)).all()
 
 
-for heads, n in ((1, 1), (2, 300), (3, 128 * 65 + 7)):
+for heads, n, way in ((1, 1, "in order"), (2, 300, None), (3, 128 * 65 + 7, "in order"), (2, 2048, "segments"),
+                      (16, 128 * 40 - 9, "schedule"), (3, 128 * 193, "lists"), (33000, 3, "dealt")):
     for flags in (0, 1, 2, 3):
+        assert way is None or flags & 1 or path(heads, n, flags) == way, (heads, n, path(heads, n, flags))
         h = H()
         d = desc(heads, n, flags=flags, protect=(0, min(n, 5)))
         assert lib.lite_attn_init_mask(ctypes.byref(d), ctypes.byref(h)) == 0
@@ -101,7 +120,8 @@ ctx = H()
 assert lib.lite_attn_ctx_create(ctypes.byref(ctx)) == 0
 assert lib.lite_attn_ctx_set_stream(ctx, ctypes.c_void_p(64)) == 0
 hs = []
-for heads, n in ((2, 300), (1, 128 * 9), (4, 2000), (1, 50)):       # the shared scratch grows twice
+# the shared scratch grows from layer to layer, the last but one apart: few rows, segments, schedule, lists and V^T
+for heads, n in ((2, 300), (1, 128 * 9), (4, 2000), (16, 128 * 40), (3, 128 * 193), (1, 50)):
     h = H()
     d = desc(heads, n)
     assert lib.lite_attn_init_mask_shared(ctypes.byref(d), ctx, ctypes.byref(h)) == 0
