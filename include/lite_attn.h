@@ -70,9 +70,9 @@ typedef struct {
 } lite_attn_desc_t;
 
 /* Opaque handle: owns the device Skip-Mask ([B,H,Tq,ceil(Tk/64)] uint64, bit j%64 of word j/64 set = tile (i,j)
-   skipped) and the statistics, and owns or borrows (lite_attn_init_mask_shared) the per-call scratch: Skip-List
-   buffers and a copy of V^T (same size as V) or, for layers of at most 512 Q-tile rows, partial results (at most
-   104 MiB).
+   skipped) and the statistics, the Skip-List buffers, and owns or borrows (lite_attn_init_mask_shared) the per-call
+   scratch: a copy of V^T (same size as V), or, for layers of at most 512 Q-tile rows, partial results (at most
+   104 MiB); other layers of at most 192 K/V tiles need none.
    Tq = ceil(N/tile_q), Tk = ceil(N/tile_k). */
 typedef struct lite_attn_mask lite_attn_mask_t;
 
@@ -98,8 +98,8 @@ int lite_attn_set_stream(lite_attn_mask_t* mask, void* hip_stream);
 
 /* Scratch shared by the layers of a model (this library's own arrangement, nothing of the paper's).
    A call needs device scratch that nothing reads after the call has finished: the Skip-List, the row schedule and
-   a transposed copy of V, together about the size of V (layers of at most 512 Q-tile rows: or partial results of rows cut
-   into segments, at most 104 MiB).  A handle made by lite_attn_init_mask owns its own; a model
+   a transposed copy of V, together about the size of V (in place of that copy, layers of at most 512 Q-tile rows may need
+   partial results of rows cut into segments, at most 104 MiB; other layers of at most 192 K/V tiles need nothing).  A handle made by lite_attn_init_mask owns its own; a model
    with one handle per layer would hold that once per layer.  Handles made by lite_attn_init_mask_shared borrow the
    scratch of a context instead: one buffer on the context's device, grown to the largest layer attached so far.
    Sharing is safe because all handles of a context run on the context's ONE stream, where calls are serial:
@@ -121,7 +121,7 @@ int lite_attn_ctx_free(lite_attn_ctx_t* ctx);
    immediate variant and the visiting order).
      q, k, v   device bf16, layout given by the handle's strides; borrowed, not modified; values must be finite
                (the kernels are built with the assumption that no NaN occurs)
-     out       device bf16, same layout; every valid row is written
+     out       device bf16, same layout; every valid row is written; must not overlap q, k or v
      skip_mask handle; its mask as it stands at the start of the call is read and then updated
      threshold signed -eps of eq. (sparge_cond) in natural-log units of S = QK^T/sqrt(d), must be < 0;
                -INFINITY never marks anything (with an empty mask the result is dense attention)
@@ -138,8 +138,8 @@ int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_a
    capture, serving loops and harnesses that forbid hipMalloc -- and therefore cannot create a handle.  It allocates
    nothing and frees nothing: no hipMalloc, no hipFree, no allocating library routine.  Everything the other entry
    points keep in allocated device memory besides the Skip-Mask (Skip-List, row schedule, V^T or partial results; no
-   counters, which nobody could ask for) lives in ONE static device array of LITE_ATTN_STATIC_SCRATCH_BYTES that the library's code object brings along on
-   every GPU it is loaded on and holds until the process ends.
+   counters, which nobody could ask for) lives in ONE static device array of LITE_ATTN_STATIC_SCRATCH_BYTES that the
+   library's code object brings along on every GPU it is loaded on and holds until the process ends.
      q, k, v, out, threshold   as for lite_attn_fwd
      desc            shape, strides, protected range and flags of the layer, as for lite_attn_init_mask (max_steps
                      must be >= 1 and is otherwise unused)
@@ -147,9 +147,9 @@ int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_a
                      handle's layout (bit j%64 of word j/64 of row (b*H+h)*Tq+i set = tile (i,j) skipped).  Input and
                      output: the caller owns it, keeps it between timesteps, and zeroes it to start a new trajectory
      hip_stream      hipStream_t on which the call's kernels are enqueued (asynchronous)
-   A shape whose scratch (about the size of V plus 2*Tk+12 bytes per Q-tile row) exceeds the array is refused with
-   LITE_ATTN_ESCRATCH before anything is launched: B*H*ceil(N/128) up to about 4000, e.g. the 12-head N=32760
-   layer; the larger benchmark shapes need a handle.  The first call on a GPU looks up the array's address there and
+   A shape whose scratch (about the size of V plus 2*Tk+16 bytes per Q-tile row; without the V of that, if Tk <= 192)
+   exceeds the array is refused with LITE_ATTN_ESCRATCH before anything is launched: B*H*ceil(N/128) up to about 4000,
+   e.g. the 12-head N=32760 layer (300000 with Tk <= 192); the larger benchmark shapes need a handle.  The first call on a GPU looks up the array's address there and
    sets the attention kernel's function attributes (no allocation, but not work to record into a graph: make the first
    call on a GPU outside stream capture).
    Every call on a GPU uses that GPU's one array, which keeps the previous call's contents (a call writes what it

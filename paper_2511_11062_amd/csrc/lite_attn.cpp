@@ -10,8 +10,8 @@
 
 #include "lite_attn_kernels.h"
 
-// Device memory that every call rewrites before reading it (nothing in it outlives a call): V^T.  A handle either
-// owns one or borrows its context's.
+// Device memory that every call rewrites before reading it (nothing in it outlives a call): V^T or partial results.  A
+// handle either owns one or borrows its context's; empty if no layer needs any.
 struct la_scratch {
   void* base = nullptr;
   size_t bytes = 0;
@@ -104,14 +104,16 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
   p.build_next = a.build_next ? 1 : 0;
   p.diagonal_first = diagonal_first;
   if (few) {
-    const ScratchLayout sl = scratch_layout(g);
     p.nseg = g.nseg;
     p.pair = g.pair;
     p.fresh = a.fresh ? 1 : 0;
     p.v = static_cast<const uint16_t*>(a.v);
-    p.seg_o = reinterpret_cast<float*>(scratch + sl.seg_o);
-    p.seg_stat = reinterpret_cast<float*>(scratch + sl.seg_stat);
-    p.seg_mloc = reinterpret_cast<float*>(scratch + sl.seg_mloc);
+    if (g.nseg > 1) {
+      const ScratchLayout sl = scratch_layout(g);
+      p.seg_o = reinterpret_cast<float*>(scratch + sl.seg_o);
+      p.seg_stat = reinterpret_cast<float*>(scratch + sl.seg_stat);
+      p.seg_mloc = reinterpret_cast<float*>(scratch + sl.seg_mloc);
+    }
     p.stats_all = a.stats_all;
     p.stat_words = (int)a.stat_words;
     // all workgroups start together, or all rows are equally long: nothing to schedule
@@ -279,7 +281,7 @@ int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_a
   a.lists_ready = ready;
   a.build_next = true;
   LA_HIP(la::launch_call(d, m->geo, m->ll, m->d_lists, scratch_of(m), a, stream, ev ? ev[1] : nullptr));
-  m->lists_valid = m->geo.nseg == 0;  // (calls with few rows keep no lists)
+  m->lists_valid = m->geo.nseg == 0;  // (calls with few or short rows keep no lists)
   if (ev) LA_HIP(hipEventRecord(ev[2], stream));
   m->next_step = step + 1;
   return LITE_ATTN_OK;

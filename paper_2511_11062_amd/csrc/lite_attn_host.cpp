@@ -90,7 +90,7 @@ Geometry geometry(const lite_attn_desc_t& d) {
   g.nseg = 0;
   g.pair = 0;
   g.per_xcd = ((g.chunks + 7) / 8 + 1) * kChunkRows;
-  if (g.rows <= kFewRows || g.Tk <= kShortTiles) {
+  if (g.rows <= kFewRows || (g.Tk <= kShortTiles && g.rows <= kMaxListless)) {
     g.nseg = 1;
     if (g.rows <= kFewRows) share_chip(g, d.flags);
     g.per_xcd = (int)((g.rows * g.nseg + 7) / 8);
@@ -105,8 +105,6 @@ Geometry geometry(const lite_attn_desc_t& d) {
 ListLayout list_layout(const Geometry& g) {
   ListLayout l;
   size_t at = 0;
-  l.stats = at;
-  at += up256(3 * sizeof(unsigned long long));
   l.nruns = at;
   at += up256(sizeof(uint32_t) * (size_t)g.rows);
   l.live_cnt = at;
@@ -126,11 +124,11 @@ ListLayout list_layout(const Geometry& g) {
 }
 
 ScratchLayout scratch_layout(const Geometry& g) {
-  ScratchLayout l;  // the segments lie over the V^T that calls with few rows do not make
+  ScratchLayout l;
   l.seg_o = 0;
   l.seg_stat = sizeof(float) * (size_t)g.rows * g.nseg * 128 * 128;
   l.seg_mloc = l.seg_stat + sizeof(float) * (size_t)g.rows * g.nseg * 2 * 128;
-  l.total = up256(std::max(sizeof(uint16_t) * (size_t)g.BH * 128 * ((size_t)g.Tk * 128), segment_bytes(g, g.nseg)));
+  l.total = up256(g.nseg > 0 ? segment_bytes(g, g.nseg) : sizeof(uint16_t) * (size_t)g.BH * 128 * ((size_t)g.Tk * 128));
   return l;
 }
 

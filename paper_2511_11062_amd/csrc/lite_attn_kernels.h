@@ -18,6 +18,7 @@ constexpr int kChunkRows = 64;
 // an XCD does not matter and no table is made: chunks of kDealtRows rows go to the XCDs in turn (dealt_chunk).
 constexpr int kFewRows = 512;
 constexpr int kShortTiles = 192;
+constexpr int kMaxListless = 1 << 23;  // rows; the kernel's short division and its grid hold for that many
 constexpr int kSchedRows = 32768;
 constexpr int kDealtRows = kChunkRows;
 constexpr int kPairWorkgroups = 256;
@@ -85,7 +86,6 @@ struct Geometry {
 // Byte offsets of the Skip-List buffers inside one allocation (256-byte aligned pieces).  Handles keep them between
 // calls (a call's epilogue leaves the next call's lists there); the handle-free entry point rebuilds them per call.
 struct ListLayout {
-  size_t stats;     // 3 uint64 counters for callers without a handle (handles keep per-step counters of their own)
   size_t nruns;     // [rows] uint32 runs per row
   size_t live_cnt;  // [rows] uint32 live tiles per row
   size_t order;     // [BH][Tq] uint32 row ranking (none with few or short rows)
@@ -101,7 +101,8 @@ int check_desc(const lite_attn_desc_t* d);  // LITE_ATTN_OK or the error the hea
 int check_call(const void* q, const void* k, const void* v, const void* out, float threshold);
 Geometry geometry(const lite_attn_desc_t& d);
 ListLayout list_layout(const Geometry& g);
-// Scratch of one call: V^T ([BH][128][128*Tk] bf16), or, with few rows, the segments' partial results in its place.
+// Scratch of one call: V^T ([BH][128][128*Tk] bf16), or the partial results of rows cut into segments; rows that stay
+// whole and take no lists need neither (total 0).
 struct ScratchLayout {
   size_t seg_o, seg_stat, seg_mloc, total;
 };

@@ -1049,7 +1049,7 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
   __syncthreads();
 }
 
-// a / b of small wave-uniform numbers (0 <= a < 2^24, b >= 1): the rounded reciprocal's product is off by one at most
+// a / b of small wave-uniform numbers (0 <= a <= 2^23, b >= 1): the rounded reciprocal's product is off by one at most
 __device__ __forceinline__ int quotient(int a, int b) {
   int q = (int)((float)a * __builtin_amdgcn_rcpf((float)b));
   q -= q * b > a;

@@ -1,6 +1,6 @@
 // The allocation-free entry point of the C ABI (include/lite_attn.h: lite_attn_fwd_static) and the static device array
 // that stands in for everything the other entry points keep in allocated device memory besides the Skip-Mask: the
-// Skip-List, the row schedule, V^T and the statistics counters of the call.
+// Skip-List, the row schedule, V^T or partial results.
 #include <hip/hip_runtime.h>
 
 #include <mutex>

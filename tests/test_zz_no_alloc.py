@@ -53,6 +53,33 @@ def test_static_entry_point_matches_the_handle_path():
             assert torch.equal(o, ref[t][0]), "%s step %d: output differs" % (wl.name, t)
 
 
+def test_static_entry_point_takes_short_rows_whatever_the_size_of_v():
+    """5120 rows of 128 tiles: V alone is larger than the static array, but such a call needs no copy of it.  A dense step
+    and one that skips, bit for bit what a handle gives."""
+    heads, n = 40, 128 * 128
+    desc = la.make_desc(1, heads, n, max_steps=1)
+    assert heads * n * 256 > 128 << 20
+    g = torch.Generator(device="cuda").manual_seed(53)
+    q, k, v = (torch.randn(1, heads, n, 128, device="cuda", generator=g).to(torch.bfloat16) for _ in range(3))
+    q.mul_(3.0)                                                # peaked rows: some tiles fire at the threshold below
+    stream = torch.cuda.current_stream().cuda_stream
+    mask = torch.zeros(la.static_mask_words(desc), dtype=torch.int64, device="cuda")
+    out, ref = torch.empty_like(q), torch.empty_like(q)
+    h = la.lite_attn_init_mask(1, heads, n, max_steps=2)
+    la.lite_attn_set_stream(h, stream)
+    try:
+        for t in range(2):
+            la.lite_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), ref.data_ptr(), h, -0.3, t)
+            la.lite_attn_fwd_static(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.fill_(float("nan")).data_ptr(), desc,
+                                    mask.data_ptr(), -0.3, stream)
+            torch.cuda.synchronize()
+            assert torch.equal(out, ref), "step %d" % t
+            got = mask.cpu().numpy().view(np.uint64)
+            assert np.array_equal(got, la.lite_attn_mask_export(h)) and got.any()
+    finally:
+        la.lite_attn_free_mask(h)
+
+
 def test_static_entry_point_refuses_what_does_not_fit():
     wl = inputs.WORKLOADS["wan14b"]
     desc = la.make_desc(1, wl.heads, wl.seqlen)
