@@ -29,6 +29,48 @@ def test_marking_across_segments(heads, tokens, text, diagonal_first):
                               immediate=True)
 
 
+@pytest.mark.parametrize("flags", [0, 1, 2, 3])
+@pytest.mark.parametrize("batch,heads,tokens,text", [(2, 12, 128 * 37 - 51, 0), (1, 8, 128 * 65 + 7, 130),
+                                                     (1, 5, 128 * 128, 0), (1, 3, 128 * 192 - 1, 0)])
+def test_marking_beyond_one_round_of_workgroups(batch, heads, tokens, text, flags):
+    """More rows than run side by side, at most 192 tiles a row: a step 0 without a schedule, whose marks the scheduled steps
+    read (one to three mask words a row), thresholds that rise, protected text, either order, deferred and literal PV skip;
+    sampled rows against the oracle.  Then the trajectory on its own: the counters of every step against the masks."""
+    from paper_2511_11062_amd import lite_attn as la
+    wl = layer(heads, tokens, text, batch=batch)
+    path = parity.path_of(batch, heads, tokens, flags)
+    assert path.nseg == 1 and 512 < path.rows <= 32768
+    thr = [-3.0, -1.5, -0.7]
+    reps = parity.run_sequence_check(wl, steps=3, thresholds=thr, sample_rows=16, seed=flags, immediate=bool(flags & 1),
+                                     diagonal_first=bool(flags & 2))
+    assert reps[-1]["skipped_out"] > 0.02
+    seq = inputs.DriftSequence(wl, "cuda:0")
+    h = la.lite_attn_init_mask(batch, heads, tokens, protect=wl.protect, max_steps=3, flags=flags)
+    try:
+        la.lite_attn_set_stream(h, torch.cuda.current_stream().cuda_stream)
+        before = np.zeros((path.rows, path.Tk), dtype=bool)
+        for t in range(3):
+            q, k, v = (x.contiguous() for x in next(seq))
+            out = torch.full_like(q, float("nan"))
+            la.lite_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), h, thr[t], t)
+            st = la.lite_attn_skip_stats(h, t)
+            after = parity.unpack_mask(la.lite_attn_mask_export(h).reshape(path.rows, path.W), path.Tk) != 0
+            assert torch.isfinite(out).all() and not (before & ~after).any()
+            assert st.tiles_skipped_in == int(before.sum()) and st.tiles_newly_marked == int((after & ~before).sum())
+            # entries of the list the row would have: maximal runs of live tiles, a wrap-around run counted twice
+            starts = ~before & np.pad(before, ((0, 0), (1, 0)), constant_values=True)[:, :-1]
+            runs = int(starts.sum())
+            if flags & 2:                                       # diagonal first: a run across the diagonal is cut there
+                i = np.tile(np.arange(path.Tq), path.BH)
+                r = np.arange(path.rows)
+                runs += int((~before[r, i] & ~before[r, np.maximum(i - 1, 0)] & (i > 0)).sum())
+            assert st.live_list_bytes == 4 * runs
+            before = after
+        assert before.any()
+    finally:
+        la.lite_attn_free_mask(h)
+
+
 @pytest.mark.parametrize("heads,tiles", [(1, 5), (2, 16), (1, 65), (3, 100), (4, 128), (1, 513), (27, 19),
                                          (3, 192), (8, 193), (520, 2), (33000, 1), (3301, 10)])
 @pytest.mark.parametrize("live", [0.02, 0.5, "uneven"])

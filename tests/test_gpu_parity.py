@@ -14,6 +14,26 @@ def small(name, heads, grid, steps, text=0, batch=1, seed=5):
     return inputs.Workload(name, batch, heads, grid, text_tokens=text, steps=steps, seed=seed)
 
 
+# One layer for each way through the library (parity.path_of): rows cut into segments; whole rows in order; rows scheduled
+# from the mask; Skip-Lists, row ranking and V^T.  All ragged.
+WAYS = {"segments": (2, (2, 24, 31), 0), "in order": (5, (3, 31, 41), 100), "schedule": (16, (3, 40, 42), 60),
+        "lists": (3, (5, 60, 82), 99)}
+
+
+def layer_of(way, steps, seed, batch=1):
+    heads, grid, text = WAYS[way]
+    wl = small(way.replace(" ", "_"), heads, grid, steps, text=text, batch=batch, seed=seed)
+    p = parity.path_of(batch, heads, wl.seqlen)
+    got = "lists" if p.nseg == 0 else "segments" if p.nseg > 1 else "in order" if p.rows <= 512 else "schedule"
+    assert got == way, "this layer now takes another way (%s): choose another shape" % got
+    return wl
+
+
+def on_gpu(wl, steps):
+    seq = inputs.DriftSequence(wl, "cuda:0")
+    return [tuple(x.contiguous() for x in next(seq)) for _ in range(steps)]
+
+
 def test_tiny_config_full_parity_four_steps():
     """Benchmark config 1: B=1,H=2,N=2048,d=128, 4 steps, fixed threshold, every row compared."""
     reps = parity.run_sequence_check("tiny", steps=4, threshold=-2.0, verbose=True)
@@ -234,17 +254,22 @@ def test_threshold_schedule_checked_against_the_oracle():
     assert not parted.any()         # (deterministic inputs: no tile of this sequence sits inside the band)
 
 
+@pytest.mark.parametrize("way", [None, "lists"])
 @pytest.mark.parametrize("flags", [0, 1, 2, 3])
-def test_lists_built_in_the_epilogue_equal_recompacted_lists(flags):
-    """From the second call of a trajectory on, the Skip-Lists and the row ranking a call walks were left by the
-    previous call's epilogue.  Run a sequence twice: once as it is, once with the mask exported and imported again
-    between the calls, which makes every call rebuild its lists with the compaction and ranking kernels.  Outputs,
-    masks and the per-step statistics (tiles skipped on entry, Skip-List entries read) must be identical.  Every output
-    buffer starts as NaN, so a row that the ranking lost would show."""
+def test_lists_built_in_the_epilogue_equal_recompacted_lists(flags, way):
+    """Where a call walks Skip-Lists, they were left by the previous call's epilogue from the second call of a trajectory
+    on.  Run a sequence twice: once as it is, once with the mask exported and imported again between the calls, which
+    makes every call rebuild its lists with the compaction kernel.  Outputs, masks and the per-step statistics (tiles
+    skipped on entry, Skip-List entries read) must be identical.  Every output buffer starts as NaN, so a row that the
+    ranking lost would show.  (None: a layer whose calls find their tiles from the mask and must not miss an import either.)"""
     from paper_2511_11062_amd import lite_attn as la
-    wl = small("epi", 5, (3, 31, 41), 5, text=100, seed=61)               # 5 heads, N = 3913: 31 tiles, ragged
-    seq = inputs.DriftSequence(wl, "cpu")
-    data = [tuple(x.cuda().contiguous() for x in next(seq)) for _ in range(5)]
+    if way:
+        wl = layer_of(way, 5, seed=62)
+        data = on_gpu(wl, 5)
+    else:
+        wl = small("epi", 5, (3, 31, 41), 5, text=100, seed=61)           # 5 heads, N = 3913: 31 tiles, ragged
+        seq = inputs.DriftSequence(wl, "cpu")
+        data = [tuple(x.cuda().contiguous() for x in next(seq)) for _ in range(5)]
     thr = [-3.5, -3.0, -2.5, -1.5, -1.0]
 
     def run(reimport):
@@ -269,6 +294,47 @@ def test_lists_built_in_the_epilogue_equal_recompacted_lists(flags):
         assert torch.isfinite(a[t][0]).all() and torch.equal(a[t][0], b[t][0]), "step %d" % t
         assert np.array_equal(a[t][1], b[t][1]) and a[t][2] == b[t][2], "step %d: %s vs %s" % (t, a[t][2], b[t][2])
     assert a[4][2][0] > a[1][2][0] > 0                                    # the mask grew along the sequence
+
+
+@pytest.mark.parametrize("ways", [("segments", "lists"), ("lists", "segments"), ("schedule", "lists")])
+def test_shared_scratch_context_across_ways(ways):
+    """Layers that use a context's scratch for different things (partial results, V^T, nothing), called in turn: what
+    handles with scratch of their own give, bit for bit."""
+    from paper_2511_11062_amd import lite_attn as la
+    wls = [layer_of(w, 3, seed=45 + n) for n, w in enumerate(ways)]
+    data = [on_gpu(wl, 3) for wl in wls]
+    thr = [-3.0, -2.0, -1.5]
+    stream = torch.cuda.current_stream()
+
+    def run(handles):
+        outs = [[torch.full_like(d[0], float("nan")) for d in layer] for layer in data]
+        for t in range(3):
+            for n, h in enumerate(handles):
+                q, k, v = data[n][t]
+                la.lite_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), outs[n][t].data_ptr(), h, thr[t], t)
+        stream.synchronize()
+        return [o for layer in outs for o in layer], [la.lite_attn_mask_export(h).copy() for h in handles]
+
+    kw = [dict(max_steps=3, protect=w.protect) for w in wls]
+    own = [la.lite_attn_init_mask(w.batch, w.heads, w.seqlen, **kw[n]) for n, w in enumerate(wls)]
+    ctx = la.lite_attn_ctx_create()
+    shared = []
+    try:
+        for h in own:
+            la.lite_attn_set_stream(h, stream.cuda_stream)
+        la.lite_attn_ctx_set_stream(ctx, stream.cuda_stream)
+        for n, w in enumerate(wls):
+            shared.append(la.lite_attn_init_mask_shared(ctx, w.batch, w.heads, w.seqlen, **kw[n]))
+        ref_o, ref_m = run(own)
+        got_o, got_m = run(shared)
+        for a, b in zip(ref_o, got_o):
+            assert torch.isfinite(a).all() and torch.equal(a, b)
+        for a, b in zip(ref_m, got_m):
+            assert np.array_equal(a, b) and a.any()
+    finally:
+        for h in own + shared:
+            la.lite_attn_free_mask(h)
+        la.lite_attn_ctx_free(ctx)
 
 
 def test_shared_scratch_context():
@@ -371,16 +437,17 @@ def test_free_running_trajectories_stay_together():
     print("diverged rows per step:", [r["diverged_rows"] for r in reps], "bits:", [r["diverged_bits"] for r in reps])
 
 
-def test_hip_graph_capture_and_replay():
+@pytest.mark.parametrize("way", [None, "in order", "schedule", "lists"])
+def test_hip_graph_capture_and_replay(way):
     """lite_attn_fwd only launches kernels on the handle's stream (the step-0 clear is a fill kernel too), so a
     sequence of calls can be captured in a HIP graph.  Three steps are captured once and replayed three times, with
     eager work and synchronisations in between; every replay must reproduce the eager outputs and the eager mask
     bit for bit (step 0 clears the mask, so each replay starts a fresh trajectory)."""
     from paper_2511_11062_amd import lite_attn as la
-    wl = small("graph", 2, (2, 20, 31), 3, seed=9)              # N = 1240: ragged tail
+    wl = layer_of(way, 3, seed=9) if way else small("graph", 2, (2, 20, 31), 3, seed=9)      # N = 1240: ragged tail
     B, H, N = wl.batch, wl.heads, wl.seqlen
     dev = torch.device("cuda:0")
-    seq = inputs.DriftSequence(wl, "cpu")
+    seq = inputs.DriftSequence(wl, dev if way else "cpu")
     data = [tuple(x.to(dev).contiguous() for x in next(seq)) for _ in range(3)]
     thr = [-3.0, -2.0, -1.0]
 
@@ -536,16 +603,20 @@ def test_arbitrary_imported_masks(density, diagonal_first):
 
 
 @pytest.mark.parametrize("heads,tiles", [(1, 1), (5, 2), (9, 63), (8, 64), (17, 65), (3, 127), (40, 3), (2, 129), (7, 191),
-                                         (65, 8), (513, 1), (261, 65)])
+                                         (65, 8), (513, 1), (261, 65), (3, 193), (4, 200), (2, 320), (9, 255),
+                                         (129, 193)])
 def test_row_schedule_covers_every_row(heads, tiles):
-    """Property check of the row schedule (rows ranked by Skip-List length, cut into chunks of 64, the chunks dealt to
-    the XCDs by work -- or round-robin when there are more than 512 of them, the last two cases): for head
-    counts and row counts around the chunk and XCD boundaries, with random imported masks (so that the ranking is a
-    real permutation), EVERY row of every head must come out right.  The reference here is block-masked softmax
+    """Property check of the row schedules.  The last five shapes have lists: rows ranked by Skip-List length, cut into
+    chunks of 64, the chunks dealt to the XCDs by work -- or round-robin when there are more than 512 of them, the last.
+    The others are in order (up to 512 rows) or scheduled from the mask.  For head counts and row counts around the chunk
+    and XCD boundaries, with random imported masks (so that the ranking is a real permutation), EVERY row of every head
+    must come out right.  The reference here is block-masked softmax
     attention computed with PyTorch fp32 matmuls on the GPU -- a definition check on all rows, which the sampled-row
     oracle comparison cannot give at these sizes; the oracle stays the parity gate elsewhere."""
     from paper_2511_11062_amd import lite_attn as la
     N = 128 * tiles - 3
+    path = parity.path_of(1, heads, N)
+    assert (path.nseg == 0) == (tiles > 192) and (path.chunks > 512) == ((heads, tiles) in [(513, 1), (261, 65), (129, 193)])
     g = torch.Generator(device="cuda").manual_seed(1000 * heads + tiles)
     q, k, v = (torch.randn(1, heads, N, 128, device="cuda", generator=g).to(torch.bfloat16) for _ in range(3))
     rng = np.random.default_rng(heads * 7 + tiles)
@@ -573,15 +644,20 @@ def test_row_schedule_covers_every_row(heads, tiles):
     assert worst <= parity.MAX_REL, worst
 
 
-def test_two_handles_on_two_streams():
+@pytest.mark.parametrize("ways", [None, ("lists", "lists"), ("schedule", "lists")])
+def test_two_handles_on_two_streams(ways):
     """Two layers' handles driven on two streams at the same time give what each gives alone (the library keeps no
     state outside the handle)."""
     from paper_2511_11062_amd import lite_attn as la
-    wls = [small("layer_a", 3, (3, 20, 33), 3, seed=41), small("layer_b", 2, (2, 31, 47), 3, seed=42)]
-    data = []
-    for wl in wls:
-        seq = inputs.DriftSequence(wl, "cpu")
-        data.append([tuple(x.cuda().contiguous() for x in next(seq)) for _ in range(3)])
+    if ways:
+        wls = [layer_of(w, 3, seed=41 + n) for n, w in enumerate(ways)]
+        data = [on_gpu(wl, 3) for wl in wls]
+    else:
+        wls = [small("layer_a", 3, (3, 20, 33), 3, seed=41), small("layer_b", 2, (2, 31, 47), 3, seed=42)]
+        data = []
+        for wl in wls:
+            seq = inputs.DriftSequence(wl, "cpu")
+            data.append([tuple(x.cuda().contiguous() for x in next(seq)) for _ in range(3)])
     thr = [-3.0, -2.0, -1.0]
 
     def run_all(streams):
@@ -610,6 +686,18 @@ def test_two_handles_on_two_streams():
         assert np.array_equal(serial_m[n], par_m[n]) and serial_m[n].any()
         for t in range(3):
             assert torch.equal(serial_o[n][t], par_o[n][t])
+
+
+@pytest.mark.parametrize("layout", ["padded", "bnhd"])
+@pytest.mark.parametrize("way", ["schedule", "lists"])
+def test_strided_layouts_of_larger_layers(way, layout):
+    """Batch of two in the two strided memory orders (NaN in the gaps of the padded one), three steps with skipping, then both
+    flags: the V^T pass, the lists and the scheduled rows at strides other than the packed ones."""
+    wl = layer_of(way, 3, seed=29, batch=2)
+    reps = parity.run_sequence_check(wl, steps=3, thresholds=[-3.0, -2.0, -1.0], layout=layout, sample_rows=10)
+    assert reps[-1]["skipped_out"] > 0.05
+    parity.run_sequence_check(wl, steps=2, thresholds=[-2.0, -1.0], layout=layout, diagonal_first=True, immediate=True,
+                              sample_rows=10, seed=1)
 
 
 def test_padded_strides_multi_step():

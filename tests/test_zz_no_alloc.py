@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 import torch
 
+import parity
 from paper_2511_11062_amd import inputs
 from paper_2511_11062_amd import lite_attn as la
 
@@ -16,14 +17,16 @@ def _layer(name, heads, grid, seed, text=0):
 
 
 def test_static_entry_point_matches_the_handle_path():
-    """lite_attn_fwd_static on two layers in a row, the second smaller than the first (so the static array still holds
-    the first one's Skip-List, row schedule and V^T beyond what the second overwrites), two timesteps each with the
+    """lite_attn_fwd_static on layers in a row, each smaller than the one before (so the static array still holds
+    that one's Skip-List, row schedule, V^T or partial results beyond what the next overwrites), two timesteps each with the
     caller-owned Skip-Mask carried from the first to the second: outputs and masks must equal what lite_attn_fwd
     gives with a handle -- the same kernels on the same inputs, so bit for bit, which is inside every tolerance."""
     stream = torch.cuda.current_stream().cuda_stream
     thr = [-3.0, -2.0]
-    layers = [_layer("na_big", 3, (2, 24, 31), 51, text=40), _layer("na_small", 2, (1, 12, 25), 52)]   # N = 1528, 300
-    assert layers[1][0].seqlen < layers[0][0].seqlen
+    # Skip-Lists and V^T, rows scheduled from the mask, segments: N = 24699, 5100, 1528, 300
+    layers = [_layer("na_lists", 3, (5, 60, 82), 54, text=99), _layer("na_schedule", 16, (3, 40, 42), 55, text=60),
+              _layer("na_big", 3, (2, 24, 31), 51, text=40), _layer("na_small", 2, (1, 12, 25), 52)]
+    assert [parity.path_of(1, wl.heads, wl.seqlen).nseg > 0 for wl, _ in layers] == [False, True, True, True]
     for wl, data in layers:
         H, N = wl.heads, wl.seqlen
         h = la.lite_attn_init_mask(1, H, N, protect=wl.protect, max_steps=2)
