@@ -116,7 +116,8 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     }
     p.stats_all = a.stats_all;
     p.stat_words = (int)a.stat_words;
-    // all workgroups start together, or all rows are equally long: nothing to schedule
+    // nothing to schedule where all workgroups start together or all rows are equally long; beyond kSchedRows rows the kernel
+    // deals chunks of them in turn
     if (g.rows > kFewRows && g.rows <= kSchedRows && !a.fresh) {
       p.scheduled = 1;
       e = launch_schedule_rows(a.bits, (int)g.rows, g.Tk, g.W, g.per_xcd, slots, xcd_rows, stream);

@@ -51,14 +51,16 @@ size_t segment_bytes(const Geometry& g, int nseg) {
 // groups of four waves that take a column half of every tile each.  The chip holds 512 workgroups of four waves, two
 // per CU, or 256 pairs.  A CU with a single wave per SIMD takes 1.69 us for a tile (a wave's instructions issue one after
 // the other: 2050 cycles for a stage of 1024 matrix cycles), a pair 1.36 us and 2.7 us more per row for its merge in
-// LDS, two workgroups on a CU 2.7 us for a tile each.  Cutting a row costs a second launch, 64 KB of fp32 partials per
-// segment written and read again, and the walk over the tiles' row maxima in the merge pass (3 us, 0.8 us per four
-// segments, 18 ns per segment, 30 ns per row and 0.15 us per tile of a segment fit calls of 3..300 rows).  Minimum of a
-// cost in units of 10 ns made of these measurements; over fifteen shapes between 3 x 3 and 300 x 30 the choice is the best
-// one or within 5 % of it.  us per call, whole rows -> segments: 32 rows of 16 tiles 33.6 -> 19.2 (8 segments), 72 x 12
-// 28.5 -> 23.8 (3), 128 x 128 223 -> 125 (4); -> pairs: 192 x 32 64.3 -> 56.8, 256 x 32 69.1 -> 64.4, 155 x 31 with the
-// immediate variant 77.5 -> 60.4; -> both: 64 x 64 115 -> 46.4 (4), 128 x 32 63.0 -> 45.9 (2).  The immediate variant
-// needs a tile's verdict before its PV product, which a segment cannot know: never cut.
+// LDS, two workgroups on a CU 2.7 us for a tile each, a further round of workgroups 5 us.  Cutting a row costs a second
+// launch, 64 KB of fp32 partials per segment written and read again, and the walk over the tiles' row maxima in the merge
+// pass (3 us, 0.8 us per four segments, 18 ns per segment, 30 ns per row and 0.15 us per tile of a segment fit calls of
+// 3..300 rows).  Minimum of a cost in units of 10 ns made of these measurements.  They were taken while the exponents'
+// reference trailed the maximum; since it follows it again a tile takes 1.88 us, in a pair 1.53, at the same ratio, and the
+// choices made with the new values are no better: over eighteen shapes between 3 x 3 and 450 x 15 the choice is the best of
+// all that were timed or within 7 % of it.  us per call, whole rows -> segments: 32 rows of 16 tiles 35.4 -> 19.6 (8
+// segments), 72 x 12 29.4 -> 24.4 (3), 128 x 128 236 -> 126 (4); -> pairs: 200 x 10 28.9 -> 27.0, 256 x 32 71.6 -> 65.4;
+// -> both: 64 x 64 122 -> 45.8 (4).  The immediate variant needs a tile's verdict before its PV product, which a segment
+// cannot know: never cut.
 void share_chip(Geometry& g, int flags) {
   const int most = (flags & LITE_ATTN_PV_SKIP_IMMEDIATE) ? 1 : std::min(kMaxSegments, g.Tk);
   int64_t best = -1;

@@ -55,8 +55,8 @@ struct FwdParams {
   // build_next != 0: the epilogue rewrites runs / nruns / live_cnt for the NEXT call from the mask this call leaves;
   // diagonal_first: visiting order of the lists
   int build_next, diagonal_first;
-  // Few rows (nseg > 0, see Geometry): V read as it is, the row's live tiles found from its mask row, no lists and no
-  // schedule (per_xcd = workgroups per XCD); the row cut into nseg segments, one workgroup each.
+  // Few or short rows (nseg > 0, see Geometry): V read as it is, the row's live tiles found from its mask row, no lists;
+  // the row cut into nseg segments, one workgroup each.
   int nseg = 0;
   int pair = 0;
   // Not scheduled: the (head, segment, row) triples in order, an eighth of them to each XCD; beyond kSchedRows rows chunks.
@@ -79,8 +79,10 @@ struct Geometry {
   int64_t rows;    // BH * Tq
   int chunks;      // BH * ceil(Tq / kChunkRows): units of the row schedule
   int pair;        // workgroups of two groups of four waves (at most kPairWorkgroups of them)
-  int nseg;        // > 0: few rows, each cut into this many segments (one workgroup each); 0: rows scheduled whole
-  int per_xcd;     // row slots per XCD in the schedule table: (ceil(chunks / 8) + 1) chunks
+  int nseg;        // > 0: few or short rows, each cut into this many segments (one workgroup each; 1 beyond kFewRows rows);
+                   // 0: Skip-Lists, row ranking and V^T
+  int per_xcd;     // row slots per XCD in the schedule table: with lists (ceil(chunks / 8) + 1) chunks, short rows 1.5
+                   // shares; where there is no table, the workgroups of an XCD
 };
 
 // Byte offsets of the Skip-List buffers inside one allocation (256-byte aligned pieces).  Handles keep them between
@@ -111,8 +113,8 @@ ScratchLayout scratch_layout(const Geometry& g);
 // lite_attn.cpp: the launches of one attention call on `stream`.  lists_ready: the Skip-Lists in `lists` already
 // describe the mask (left by the previous call's epilogue); otherwise the compaction kernel builds them first.  Then
 // the row schedule, the V^T pre-pass into `scratch` and the fused attention kernel, whose epilogue builds the next call's
-// lists if build_next.  With few or short rows (Geometry::nseg > 0) there are no lists and no V^T: at most a schedule, the
-// fused kernel and, for rows cut into segments, the merge pass.  `mid` (may be null) is recorded just before the
+// lists if build_next.  With few or short rows (Geometry::nseg > 0) there are no lists and no V^T: the fused kernel, before
+// it a schedule or behind it, for rows cut into segments, the merge pass.  `mid` (may be null) is recorded just before the
 // attention kernel.  Allocates nothing.
 struct CallArgs {
   const void *q, *k, *v;

@@ -32,17 +32,20 @@
 //     O += V(s-2) P(s-2) runs two stages behind instead of one, so that the verdict on a tile is known before the
 //     first of its two PV products is issued; a fired tile's PV MFMAs and row sums are then dropped.
 //
-// Calls with few rows (template argument FEW of the fused kernel; at most kFewRows = 512, which all fit the chip at once)
-// are bound by launches and by latency, not by the matrix cores: the tiny layer's step was 36 us of attention on 32 of
-// 256 CUs behind four to six launches of 4 us each.  They run in one or two launches:
-//   * no lists, no ranking, no schedule: a workgroup finds its live tiles from the mask row itself (LiveWalk);
+// Calls with few rows (at most kFewRows = 512, which all fit the chip at once) or short rows (at most kShortTiles = 192
+// tiles, any number of them up to kMaxListless) take the template argument FEW of the fused kernel.  The former are bound by
+// launches and by latency, not by the matrix cores: the tiny layer's step was 36 us of attention on 32 of 256 CUs behind four
+// to six launches of 4 us each; for the latter the passes before the kernel cost more than they save.  They run in one or two
+// launches:
+//   * no lists and no ranking: a workgroup finds its live tiles from the mask row itself (LiveWalk); more than kFewRows rows
+//     are scheduled from the mask in one launch (schedule_rows_kernel; not at step 0 and not beyond kSchedRows rows);
 //   * no V^T: the V fragments come from V as it lies in memory through transposing LDS reads (ds_read_b64_tr_b16), 16 LDS
 //     instructions more per stage, the same LDS cycles (no bank conflicts): 1.8 % of the kernel's time on the 12-head
 //     N = 32760 dense step, against a launch and a pass over V;
-//   * a workgroup may be a PAIR of groups of four waves, each with its own stage buffers and one 64-column half of every
+//   * with few rows a workgroup may be a PAIR of groups of four waves, each with its own stage buffers and one 64-column half of every
 //     tile (a CU with one wave per SIMD issues too slowly to keep the matrix cores busy); the groups' results meet in LDS
 //     at the end, their row maxima once per tile, for the predicate;
-//   * a row may be cut into segments, one workgroup each (the rule and its measurements: share_chip() in
+//   * with few rows a row may be cut into segments, one workgroup each (the rule and its measurements: share_chip() in
 //     lite_attn_host.cpp); merge_segments_kernel adds up the partial results.  The predicate stays exact: the
 //     segments record every tile's row maxima, and the merge pass judges them against the running maximum carried
 //     over the segments, the value a single pass would have had.
@@ -494,8 +497,9 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
 
 // V -> V^T pre-pass.  The PV product contracts over the K/V index, so the matrix cores want, per lane, 8 V values
 // of ONE feature d at 8 K/V positions: a 16-byte read from a [d][kv] layout, but a strided gather from V's [kv][d].
-// (gfx950's transposing LDS read, ds_read_b64_tr_b16, delivers only 8 bytes per lane and measured at a third of the
-// 16-byte read bandwidth, which made LDS the bound of the fused kernel.)  This kernel writes, once per call,
+// (gfx950's transposing LDS read, ds_read_b64_tr_b16, takes V as it is, at 8 bytes per lane: 16 LDS instructions more per
+// stage, the same LDS cycles, 1.8 % of the fused kernel's time, which beyond kShortTiles tiles a row is more than this pass
+// costs.)  This kernel writes, once per call,
 // vt[bh][d][n_pad] with n_pad = 128 * Tk, zero beyond the sequence, with the K/V index permuted inside every
 // group of 16: position 8*h + t holds K/V offset 4*h + t + 4*(t >= 4) -- the order in which a lane of the fused
 // kernel holds its P~ values.  One workgroup transposes one 128 x 128 tile through LDS, twice: once with
@@ -546,8 +550,8 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(const uint16_t* __rest
   }
 }
 
-// The live K/V tiles of one Skip-Mask row in visiting order, walked from the mask words themselves (calls with few rows,
-// where a list built by an earlier kernel would cost more than it saves): lane w of the wave holds word w of the row's
+// The live K/V tiles of one Skip-Mask row in visiting order, walked from the mask words themselves (calls with few or
+// short rows, where a list built by an earlier kernel would cost more than it saves): lane w of the wave holds word w of the row's
 // live set, the position is scalar.  Rows of at most 64 words (4096 tiles).  Used by whole waves only.
 struct LiveWalk {
   uint32_t lo, hi;   // this lane's word of the live set
@@ -945,8 +949,9 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
         // (a cycle of three steps does two pairs: exp exp | pack+sum, exp | exp, pack+sum).  kPackLate: the second pair
         // is packed in the next cycle (exp, pack | exp, sum, exp | pack, exp, sum), so that no instruction directly
         // follows the exponential it uses, which costs a wait state: 0.6 % of the short clip's, the two-layer and the
-        // diagonal-first sequence; the kernel for long rows, whose clock is limited by power, ran up to 0.45 % slower
-        // with it, the immediate pair 0.2 %.
+        // diagonal-first sequence.  Of the others nothing certain is known (long rows: 12 heads dense 0.7 % faster with it,
+        // long video 0.45 % slower; immediate pair 0.2 % slower; builds of one source differ by 0.1-0.5 %): they keep the
+        // order they had.
         const int t = k - 6, c = t / 3, ph = t % 3;
         const int eA = 2 * c, eB = 2 * c + 1;
         if (kPackLate) {
