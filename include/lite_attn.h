@@ -98,9 +98,9 @@ int lite_attn_set_stream(lite_attn_mask_t* mask, void* hip_stream);
 
 /* Scratch shared by the layers of a model (this library's own arrangement, nothing of the paper's).
    A call needs device scratch that nothing reads after the call has finished: the Skip-List, the row schedule and
-   a transposed copy of V, together about the size of V (in place of that copy, layers of at most 512 Q-tile rows may need
-   partial results of rows cut into segments, at most 104 MiB; other layers of at most 192 K/V tiles need nothing).  A handle made by lite_attn_init_mask owns its own; a model
-   with one handle per layer would hold that once per layer.  Handles made by lite_attn_init_mask_shared borrow the
+   a transposed copy of V, together about the size of V (in place of that copy, layers of at most 512 Q-tile rows may
+   need partial results of rows cut into segments, at most 104 MiB; other layers of at most 192 K/V tiles need nothing).
+   A handle made by lite_attn_init_mask owns its own; a model with one handle per layer would hold that once per layer.  Handles made by lite_attn_init_mask_shared borrow the
    scratch of a context instead: one buffer on the context's device, grown to the largest layer attached so far.
    Sharing is safe because all handles of a context run on the context's ONE stream, where calls are serial:
      lite_attn_ctx_create       context on the current HIP device, null stream, no scratch yet
@@ -149,9 +149,9 @@ int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_a
      hip_stream      hipStream_t on which the call's kernels are enqueued (asynchronous)
    A shape whose scratch (about the size of V plus 2*Tk+16 bytes per Q-tile row; without the V of that, if Tk <= 192)
    exceeds the array is refused with LITE_ATTN_ESCRATCH before anything is launched: B*H*ceil(N/128) up to about 4000,
-   e.g. the 12-head N=32760 layer (300000 with Tk <= 192); the larger benchmark shapes need a handle.  The first call on a GPU looks up the array's address there and
-   sets the attention kernel's function attributes (no allocation, but not work to record into a graph: make the first
-   call on a GPU outside stream capture).
+   e.g. the 12-head N=32760 layer (300000 with Tk <= 192); the larger benchmark shapes need a handle.
+   The first call on a GPU looks up the array's address there and sets the attention kernel's function attributes (no
+   allocation, but not work to record into a graph: make the first call on a GPU outside stream capture).
    Every call on a GPU uses that GPU's one array, which keeps the previous call's contents (a call writes what it
    reads there): calls that overlap in time on one GPU -- two streams, two threads -- race;
    calls on one stream are safe. */

@@ -42,9 +42,9 @@
 //   * no V^T: the V fragments come from V as it lies in memory through transposing LDS reads (ds_read_b64_tr_b16), 16 LDS
 //     instructions more per stage, the same LDS cycles (no bank conflicts): 1.8 % of the kernel's time on the 12-head
 //     N = 32760 dense step, against a launch and a pass over V;
-//   * with few rows a workgroup may be a PAIR of groups of four waves, each with its own stage buffers and one 64-column half of every
-//     tile (a CU with one wave per SIMD issues too slowly to keep the matrix cores busy); the groups' results meet in LDS
-//     at the end, their row maxima once per tile, for the predicate;
+//   * with few rows a workgroup may be a PAIR of groups of four waves, each with its own stage buffers and one 64-column half
+//     of every tile (a CU with one wave per SIMD issues too slowly to keep the matrix cores busy); the groups' results meet
+//     in LDS at the end, their row maxima once per tile, for the predicate;
 //   * with few rows a row may be cut into segments, one workgroup each (the rule and its measurements: share_chip() in
 //     lite_attn_host.cpp); merge_segments_kernel adds up the partial results.  The predicate stays exact: the
 //     segments record every tile's row maxima, and the merge pass judges them against the running maximum carried

@@ -79,7 +79,8 @@ hipError_t fwd_without_lists(const FwdParams& p) {
   if (p.scheduled) sink = p.slots[8 * (size_t)p.per_xcd - 1] + p.xcd_rows[7];
   (void)sink;
   if (p.nseg > 1) {
-    if (!before(p.seg_o + rows * p.nseg * 128 * 128, p.seg_stat) || !before(p.seg_stat + rows * p.nseg * 2 * 128, p.seg_mloc))
+    if (!before(p.seg_o + rows * p.nseg * 128 * 128, p.seg_stat) ||
+        !before(p.seg_stat + rows * p.nseg * 2 * 128, p.seg_mloc))
       return hipErrorInvalidValue;
     memset(p.seg_o, 0, sizeof(float) * rows * p.nseg * 128 * 128);
     memset(p.seg_stat, 0, sizeof(float) * rows * p.nseg * 2 * 128);

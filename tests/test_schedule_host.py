@@ -50,13 +50,15 @@ def xcd_of_rows(lib, heads, tiles):
 
 def shares(kind, heads):
     h = np.arange(heads)
-    return {"alike": np.full(heads, 0.5), "eighth": np.where(h < heads // 8, 1.0, 0.1), "halves": np.where(h < heads // 2, 0.9, 0.15),
-            "every second": np.where(h % 2, 0.9, 0.15), "every fourth": np.where(h % 4, 0.1, 1.0), "every eighth": np.where(h % 8, 0.1, 1.0),
+    return {"alike": np.full(heads, 0.5), "eighth": np.where(h < heads // 8, 1.0, 0.1),
+            "halves": np.where(h < heads // 2, 0.9, 0.15), "every second": np.where(h % 2, 0.9, 0.15),
+            "every fourth": np.where(h % 4, 0.1, 1.0), "every eighth": np.where(h % 8, 0.1, 1.0),
             "five of forty": np.where(h % 40 < 5, 1.0, 0.1)}[kind]
 
 
 @pytest.mark.parametrize("heads,tiles", [(320, 128), (640, 64), (257, 128), (1000, 40), (33000, 1), (190, 191)])
-@pytest.mark.parametrize("kind", ["alike", "eighth", "halves", "every second", "every fourth", "every eighth", "five of forty"])
+@pytest.mark.parametrize("kind", ["alike", "eighth", "halves", "every second", "every fourth", "every eighth",
+                                  "five of forty"])
 def test_rows_dealt_in_chunks_share_the_work(lib, heads, tiles, kind):
     owner = xcd_of_rows(lib, heads, tiles)
     work = np.repeat(shares(kind, heads) * tiles + 2.0, tiles)               # live tiles + what a row costs besides them
