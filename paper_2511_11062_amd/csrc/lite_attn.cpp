@@ -63,8 +63,16 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
   const int diagonal_first = (d.flags & LITE_ATTN_ORDER_DIAGONAL_FIRST) ? 1 : 0;
   const bool few = g.nseg > 0;
   hipError_t e = hipSuccess;
-  if (a.fresh && g.nseg <= 1)  // (with segments, the fused kernel clears the counters and the merge pass the mask)
-    e = launch_clear(a.bits, few ? 0 : (size_t)g.rows * g.W, a.stats_all, a.stat_words, stream);
+  // a table of rows comes with its ticket counters cleared; calls without one keep theirs where the table would be
+  const bool table = !few || (g.rows > kFewRows && g.rows <= kSchedRows && !a.fresh);
+  const bool tickets = g.rows > kFewRows;
+  if (!few && a.fresh) {
+    e = launch_clear(a.bits, (size_t)g.rows * g.W, a.stats_all, a.stat_words, stream);
+  } else if (few && ((a.fresh && g.nseg <= 1) || (tickets && !table))) {
+    // (with segments, the fused kernel clears the counters and the merge pass the mask)
+    e = launch_clear(reinterpret_cast<uint64_t*>(slots), tickets && !table ? 8 * kTicketWords / 2 : 0, a.stats_all,
+                     a.fresh ? a.stat_words : 0, stream);
+  }
   if (e != hipSuccess) return e;
   if (!few) {
     uint32_t* order = reinterpret_cast<uint32_t*>(lists + ll.order);
@@ -101,6 +109,8 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
   p.protect_start = d.protect_start; p.protect_len = d.protect_len;
   p.rows_total = (int)g.rows;
   p.slots = slots; p.per_xcd = g.per_xcd; p.xcd_rows = xcd_rows;
+  p.tickets = !tickets ? nullptr : table ? slots + g.per_xcd - 1 : slots;
+  p.ticket_stride = table ? g.per_xcd : kTicketWords;
   p.build_next = a.build_next ? 1 : 0;
   p.diagonal_first = diagonal_first;
   if (few) {
@@ -118,7 +128,7 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     p.stat_words = (int)a.stat_words;
     // nothing to schedule where all workgroups start together or all rows are equally long; beyond kSchedRows rows the kernel
     // deals chunks of them in turn
-    if (g.rows > kFewRows && g.rows <= kSchedRows && !a.fresh) {
+    if (table) {
       p.scheduled = 1;
       e = launch_schedule_rows(a.bits, (int)g.rows, g.Tk, g.W, g.per_xcd, slots, xcd_rows, stream);
       if (e != hipSuccess) return e;

@@ -91,7 +91,7 @@ Geometry geometry(const lite_attn_desc_t& d) {
   g.chunks = g.BH * ((g.Tq + kChunkRows - 1) / kChunkRows);
   g.nseg = 0;
   g.pair = 0;
-  g.per_xcd = ((g.chunks + 7) / 8 + 1) * kChunkRows;
+  g.per_xcd = ((g.chunks + 7) / 8 + 1) * kChunkRows + 1;
   if (g.rows <= kFewRows || (g.Tk <= kShortTiles && g.rows <= kMaxListless)) {
     g.nseg = 1;
     if (g.rows <= kFewRows) share_chip(g, d.flags);
@@ -99,7 +99,7 @@ Geometry geometry(const lite_attn_desc_t& d) {
     if (g.rows > kSchedRows)
       g.per_xcd = (int)((g.rows + 8 * kDealtRows - 1) / (8 * kDealtRows)) * kDealtRows;
     else if (g.rows > kFewRows)
-      g.per_xcd += g.per_xcd / 2;  // room for an XCD whose rows are short
+      g.per_xcd += g.per_xcd / 2 + 1;  // room for an XCD whose rows are short
   }
   return g;
 }

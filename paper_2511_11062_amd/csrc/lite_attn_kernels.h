@@ -21,6 +21,10 @@ constexpr int kShortTiles = 192;
 constexpr int kMaxListless = 1 << 23;  // rows; the kernel's short division and its grid hold for that many
 constexpr int kSchedRows = 32768;
 constexpr int kDealtRows = kChunkRows;
+// Workgroups that an XCD holds at once (two per CU): the first round takes the rows that its place in the grid names, later
+// workgroups draw theirs (FwdParams::tickets).
+constexpr int kResident = 64;
+constexpr int kTicketWords = 32;  // distance of the counters of an unscheduled call, a cache line
 constexpr int kPairWorkgroups = 256;
 constexpr int kMaxSegments = 16;
 constexpr size_t kMaxSegmentBytes = (size_t)104 << 20;
@@ -52,6 +56,8 @@ struct FwdParams {
   const uint32_t* slots;                 // [8][per_xcd]: the row (index into [B*H][Tq]) that workgroup `slot` of an
   int per_xcd;                           //   XCD computes, written by launch_deal_rows; entries >= xcd_rows[xcd] unused
   const uint32_t* xcd_rows;              // [8] rows dealt to each XCD
+  uint32_t* tickets;                     // [8] at ticket_stride: rows drawn so far from each XCD's list beyond the first
+  int ticket_stride;                     //   kResident; null: one round of workgroups, each has its place
   // build_next != 0: the epilogue rewrites runs / nruns / live_cnt for the NEXT call from the mask this call leaves;
   // diagonal_first: visiting order of the lists
   int build_next, diagonal_first;
@@ -81,8 +87,8 @@ struct Geometry {
   int pair;        // workgroups of two groups of four waves (at most kPairWorkgroups of them)
   int nseg;        // > 0: few or short rows, each cut into this many segments (one workgroup each; 1 beyond kFewRows rows);
                    // 0: Skip-Lists, row ranking and V^T
-  int per_xcd;     // row slots per XCD in the schedule table: with lists (ceil(chunks / 8) + 1) chunks, short rows 1.5
-                   // shares; where there is no table, the workgroups of an XCD
+  int per_xcd;     // entries per XCD in the schedule table: row slots, with lists (ceil(chunks / 8) + 1) chunks, short rows
+                   // 1.5 shares, and the ticket counter; where there is no table, the workgroups of an XCD
 };
 
 // Byte offsets of the Skip-List buffers inside one allocation (256-byte aligned pieces).  Handles keep them between

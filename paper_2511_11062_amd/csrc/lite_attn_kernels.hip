@@ -270,7 +270,8 @@ __global__ __launch_bounds__(256) void deal_rows_kernel(const uint32_t* __restri
   __shared__ uint32_t dest[kDealMax];  // xcd << 29 | first slot of chunk u
   const int tid = threadIdx.x, lane = tid & 63;
   const int ranks = (Tq + kChunkRows - 1) / kChunkRows;
-  const uint32_t cap = (uint32_t)(per_xcd / kChunkRows);
+  const uint32_t cap = (uint32_t)(per_xcd / kChunkRows);  // (the last entry of an XCD's share of the table is its ticket)
+  if (blockIdx.x == 0 && tid < 8) slots[(size_t)tid * per_xcd + per_xcd - 1] = 0;
   const bool greedy = chunks <= kDealMax;
   if (greedy) {
     for (int u = tid; u < chunks; u += 256) work[u] = chunk_work[u];
@@ -431,7 +432,7 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
     l0 = l1 = 0;
     for (int y = 1; y <= 8; ++y) {
       const int s = max(start, first_long[y]), c = max(count, longs_before[y]);
-      fits = fits && c - count + others_before[y] - others_before[y - 1] <= per_xcd;
+      fits = fits && c - count + others_before[y] - others_before[y - 1] < per_xcd;
       if (y == xcd + 1) {
         l0 = start;
         l1 = s;
@@ -441,7 +442,7 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
     }
     o0 = first_other[xcd];
     o1 = first_other[xcd + 1];
-    if (fits || attempt == 2) break;  // (an eighth of the rows, by number, always fits: 8 * per_xcd >= rows)
+    if (fits || attempt == 2) break;  // (an eighth of the rows, by number, always fits: 8 * (per_xcd - 1) >= rows)
     bar = attempt == 0 ? total : 0xffffffffu;
     __syncthreads();
   }
@@ -467,6 +468,7 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
       run += c;
     }
     xcd_rows[xcd] = run;
+    slots[(size_t)xcd * per_xcd + per_xcd - 1] = 0;  // this XCD's ticket
   }
   __syncthreads();
   // positions inside the classes, in row order: kSchedThreads rows at a time
@@ -1065,6 +1067,57 @@ __device__ __forceinline__ int quotient(int a, int b) {
 // First visiting position of segment s of a row with cnt live tiles.
 __device__ __forceinline__ int segment_start(int cnt, int s, int nseg) { return nseg == 1 ? cnt * s : quotient(cnt * s, nseg); }
 
+// How many places XCD x's list of rows has, and the row at place t of it (-1: none).
+template <bool FEW>
+__device__ __forceinline__ int places_of(const FwdParams& p, int x) {
+  if (!FEW || p.scheduled) return (int)p.xcd_rows[x];
+  if (p.rows_total > kSchedRows) return p.per_xcd;
+  const int share = (p.rows_total + 7) / 8;
+  return max(0, min(share, p.rows_total - x * share));
+}
+template <bool FEW>
+__device__ __forceinline__ int row_at_place(const FwdParams& p, int x, int t) {
+  if (t >= places_of<FEW>(p, x)) return -1;
+  if (!FEW || p.scheduled) return (int)p.slots[(size_t)x * p.per_xcd + t];  // (-1 behind a chunk of fewer than kChunkRows)
+  if (p.rows_total > kSchedRows) {
+    const int row = dealt_chunk(t / kDealtRows, x) * kDealtRows + t % kDealtRows;
+    return row < p.rows_total ? row : -1;
+  }
+  return x * ((p.rows_total + 7) / 8) + t;
+}
+
+// The next row for a workgroup that starts on XCD `home` after the first round, by one thread: the next place of its own
+// XCD's list; if that list is used up, of the one with most places left; -1 if there are none.  Places below kResident
+// belong to the first round's workgroups, which need no counter.  Ends: a draw that fails has found its list used up, which
+// it then stays.  Why: workgroups go to XCDs by id, but equal lists do not end together, because the XCDs' clocks differ (a
+// tile took 3.2 us on the fastest, 3.6 on the slowest, the same ones in every kernel of a session; lists of the 12-head
+// dense step ended between 5.14 and 5.68 ms).  A row drawn costs a counter's round trip (0.35 us).  Lists by place -> drawn:
+// 40 heads x 591 tiles, dense + sparse step, 170.7 -> 164.8 ms; 24 x 931 253.8 -> 245.4; a sparse step of 12 x 256 2379 ->
+// 2331 us; 12 x 110, diagonal first, four steps 2128 -> 2102; no gain where few rounds of equally long rows leave nothing to
+// draw (12 x 256 dense, six rounds).
+template <bool FEW>
+__device__ __forceinline__ int draw_row(const FwdParams& p, int home) {
+  for (int from = home;;) {
+    const int t = kResident + (int)atomicAdd(p.tickets + (size_t)from * p.ticket_stride, 1u);
+    if (t < places_of<FEW>(p, from)) {
+      const int row = row_at_place<FEW>(p, from, t);
+      if (row >= 0) return row;
+      continue;
+    }
+    int most = 0;
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      const int left = places_of<FEW>(p, x) - kResident -
+                       (int)__hip_atomic_load(p.tickets + (size_t)x * p.ticket_stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (left > most) {
+        most = left;
+        from = x;
+      }
+    }
+    if (most == 0) return -1;
+  }
+}
+
 template <int QB, bool IMM, bool FEW, bool PAIR>
 __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void lite_attn_fwd_kernel(const FwdParams p) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -1076,9 +1129,10 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   const int grp = PAIR ? __builtin_amdgcn_readfirstlane(tid >> 8) : 0;  // PAIR: which half of every tile's columns
   const int lq = lane & 31;
 
-  // Consecutive workgroup ids land on different XCDs (id % 8): workgroup `slot` of an XCD computes the row that the
-  // schedule table names for it (deal_rows_kernel: chunks of kChunkRows rows of one head side by side, so that the
-  // workgroups sharing one L2 stream the same K/V; equal work per XCD; long rows first).
+  // Consecutive workgroup ids land on different XCDs (id % 8): workgroup `slot` of an XCD computes the row at that place of
+  // the XCD's list in the schedule table (deal_rows_kernel: chunks of kChunkRows rows of one head side by side, so that the
+  // workgroups sharing one L2 stream the same K/V; equal work per XCD; long rows first) or, after the first round, the one
+  // that it draws (draw_row).
   // FEW: the table of schedule_rows_kernel if the call has one; else the (head, segment, row) triples, numbered
   // row-fastest, an eighth to every XCD, so that the rows walking the same K/V tiles of a head share an L2; beyond kSchedRows
   // rows, where the XCDs' shares would be whole heads, chunks of rows dealt to the XCDs in turn.  Over 200 seeded sets of
@@ -1087,34 +1141,28 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   // heads x 128 tiles, ms: that mask 30.6 -> 9.3, half the heads 90 % and half 15 % live 34.8 -> 21.7, all 45 % 19.6 both
   // ways (chunks of 32 rows 19.7, of 128 19.6).
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  int row, i, bh, seg = 0;
-  if constexpr (FEW) {
-    if (p.scheduled) {
-      if (slot >= (int)p.xcd_rows[xcd]) return;
-      row = (int)p.slots[(size_t)xcd * p.per_xcd + slot];
-      bh = quotient(row, p.Tq);
-      i = row - bh * p.Tq;
-    } else if (p.rows_total > kSchedRows) {
-      row = dealt_chunk(slot / kDealtRows, xcd) * kDealtRows + slot % kDealtRows;
-      if (row >= p.rows_total) return;
-      bh = quotient(row, p.Tq);
-      i = row - bh * p.Tq;
-    } else {
-      const int units = p.rows_total * p.nseg, share = (units + 7) / 8;
-      const int unit = xcd * share + slot;
-      if (slot >= share || unit >= units) return;
-      const int u = quotient(unit, p.Tq);
-      bh = quotient(u, p.nseg);
-      seg = u - bh * p.nseg;
-      i = unit - u * p.Tq;
-      row = bh * p.Tq + i;
-    }
+  int row = -1, i, bh, seg = 0;
+  if (FEW && !p.tickets) {
+    const int units = p.rows_total * p.nseg, share = (units + 7) / 8;
+    const int unit = xcd * share + slot;
+    if (slot >= share || unit >= units) return;
+    const int u = quotient(unit, p.Tq);
+    bh = quotient(u, p.nseg);
+    seg = u - bh * p.nseg;
+    i = unit - u * p.Tq;
+    row = bh * p.Tq + i;
   } else {
-    if (slot >= (int)p.xcd_rows[xcd]) return;
-    row = (int)p.slots[(size_t)xcd * p.per_xcd + slot];
-    if (row < 0) return;  // an empty slot behind a chunk shorter than kChunkRows
-    i = row % p.Tq;
-    bh = row / p.Tq;
+    if (slot < kResident) row = row_at_place<FEW>(p, xcd, slot);
+    if (row < 0) {
+      int* told = reinterpret_cast<int*>(smem + (PAIR ? kPairFlagsOff : kFlagsOff));
+      if (tid == 0) *told = draw_row<FEW>(p, xcd);
+      __syncthreads();
+      row = __builtin_amdgcn_readfirstlane(*told);
+      if (row < 0) return;
+      __syncthreads();  // (the flags are this word's next user)
+    }
+    bh = FEW ? quotient(row, p.Tq) : row / p.Tq;
+    i = row - bh * p.Tq;
   }
   const int b = FEW ? quotient(bh, p.H) : bh / p.H;
   const int64_t base = (int64_t)b * p.stride_b + (int64_t)(bh - b * p.H) * p.stride_h;
@@ -1820,7 +1868,9 @@ hipError_t launch_fwd(const FwdParams& p, bool immediate, hipStream_t st) {
   // one workgroup per slot of the schedule table (FEW without a table: per segment or row); those past an XCD's last row
   // return at once
   const bool in_order = p.nseg > 0 && !p.scheduled && p.rows_total <= kSchedRows;
-  const dim3 grid(8 * (in_order ? (p.rows_total * p.nseg + 7) / 8 : p.per_xcd)), block(Geo<kQB>::kThreads);
+  const int places = in_order ? (p.rows_total * p.nseg + 7) / 8 : p.per_xcd;
+  // with tickets an XCD may come to more rows than its list has
+  const dim3 grid(8 * (p.tickets && !(p.nseg > 0 && p.scheduled) ? places + places / 8 + 8 : places)), block(Geo<kQB>::kThreads);
   if (p.nseg == 0) {
     if (immediate)
       hipLaunchKernelGGL((lite_attn_fwd_kernel<1, true, false, false>), grid, block, kLdsBytes, st, p);
