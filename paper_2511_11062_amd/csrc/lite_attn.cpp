@@ -32,6 +32,7 @@ struct lite_attn_mask {
   char* d_lists;      // Skip-Lists and row ranking (layout ll); kept between calls
   bool lists_valid;   // the lists describe the mask as it stands (left by the previous call's epilogue)
   unsigned long long* d_stats;  // [max_steps][3]: skipped on entry, newly marked, Skip-List runs
+  uint32_t* d_newly;            // few rows: [kFewRows] tiles that step 0 marked, per row (part of step 0's newly marked)
   la_scratch own;               // used when ctx == nullptr
   lite_attn_ctx* ctx;           // shared scratch + stream, or nullptr
   hipStream_t stream;           // used when ctx == nullptr
@@ -68,10 +69,8 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
   const bool tickets = g.rows > kFewRows;
   if (!few && a.fresh) {
     e = launch_clear(a.bits, (size_t)g.rows * g.W, a.stats_all, a.stat_words, stream);
-  } else if (few && ((a.fresh && g.nseg <= 1) || (tickets && !table))) {
-    // (with segments, the fused kernel clears the counters and the merge pass the mask)
-    e = launch_clear(reinterpret_cast<uint64_t*>(slots), tickets && !table ? 8 * kTicketWords / 2 : 0, a.stats_all,
-                     a.fresh ? a.stat_words : 0, stream);
+  } else if (tickets && !table) {  // (the mask is overwritten; few rows: the fused kernel clears the counters)
+    e = launch_clear(reinterpret_cast<uint64_t*>(slots), 8 * kTicketWords / 2, a.stats_all, a.fresh ? a.stat_words : 0, stream);
   }
   if (e != hipSuccess) return e;
   if (!few) {
@@ -125,6 +124,7 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
       p.seg_mloc = reinterpret_cast<float*>(scratch + sl.seg_mloc);
     }
     p.stats_all = a.stats_all;
+    p.newly_rows = a.newly_rows;
     p.stat_words = (int)a.stat_words;
     // nothing to schedule where all workgroups start together or all rows are equally long; beyond kSchedRows rows the kernel
     // deals chunks of them in turn
@@ -185,6 +185,7 @@ int init_common(const lite_attn_desc_t* desc, lite_attn_ctx* ctx, lite_attn_mask
   m->timed = nullptr;
   m->d_bits = nullptr;
   m->d_stats = nullptr;
+  m->d_newly = nullptr;
   const size_t words = (size_t)m->geo.rows * m->geo.W, nstats = 3 * (size_t)desc->max_steps;
   const size_t need = la::scratch_layout(m->geo).total;
   hipStream_t st = ctx ? ctx->stream : nullptr;
@@ -202,6 +203,10 @@ int init_common(const lite_attn_desc_t* desc, lite_attn_ctx* ctx, lite_attn_mask
     if (e == hipSuccess) e = hipMalloc(&m->d_lists, m->ll.total);
     if (e == hipSuccess) e = la::prepare_fwd();
     if (e == hipSuccess) e = la::launch_clear(m->d_bits, words, m->d_stats, nstats, st);
+    if (e == hipSuccess && m->geo.rows <= la::kFewRows) {
+      e = hipMalloc(&m->d_newly, sizeof(uint32_t) * la::kFewRows);
+      if (e == hipSuccess) e = la::launch_clear(reinterpret_cast<uint64_t*>(m->d_newly), la::kFewRows / 2, m->d_stats, 0, st);
+    }
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) rc = hip_fail(e);
   }
@@ -289,6 +294,7 @@ int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_a
   a.fresh = step == 0;
   a.stats_all = m->d_stats;
   a.stat_words = 3 * (size_t)d.max_steps;
+  a.newly_rows = m->d_newly;
   a.lists_ready = ready;
   a.build_next = true;
   LA_HIP(la::launch_call(d, m->geo, m->ll, m->d_lists, scratch_of(m), a, stream, ev ? ev[1] : nullptr));
@@ -303,7 +309,11 @@ int lite_attn_skip_stats(lite_attn_mask_t* m, int step, lite_attn_stats_t* host_
   if (step < 0 || step >= m->next_step || step >= m->desc.max_steps) return LITE_ATTN_ESTEP;
   unsigned long long raw[3];
   LA_HIP(hipMemcpyAsync(raw, m->d_stats + 3 * (size_t)step, sizeof raw, hipMemcpyDeviceToHost, stream_of(m)));
+  uint32_t newly[la::kFewRows] = {};
+  if (step == 0 && m->d_newly)
+    LA_HIP(hipMemcpyAsync(newly, m->d_newly, sizeof newly, hipMemcpyDeviceToHost, stream_of(m)));
   LA_HIP(hipStreamSynchronize(stream_of(m)));
+  for (const uint32_t n : newly) raw[1] += n;
   host_out->step = step;
   host_out->tiles_total = (uint64_t)m->geo.rows * (uint64_t)m->geo.Tk;
   host_out->tiles_skipped_in = raw[0];
@@ -417,6 +427,7 @@ void lite_attn_free_mask(lite_attn_mask_t* m) {
   }
   if (m->d_bits) (void)hipFree(m->d_bits);
   if (m->d_stats) (void)hipFree(m->d_stats);
+  if (m->d_newly) (void)hipFree(m->d_newly);
   if (m->d_lists) (void)hipFree(m->d_lists);
   if (m->own.base) (void)hipFree(m->own.base);
   if (m->events) {

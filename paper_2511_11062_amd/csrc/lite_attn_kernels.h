@@ -72,8 +72,9 @@ struct FwdParams {
   float* seg_o = nullptr;                // [rows][nseg][128][128] O^T partials in accumulator order
   float* seg_stat = nullptr;             // [rows][nseg][2][128]: row maximum (the exponents' reference), row sum
   float* seg_mloc = nullptr;             // [rows][Tk][128]: row maxima of the visited tiles
-  unsigned long long* stats_all = nullptr;  // all counters of the handle (stat_words of them): zeroed at step 0, nseg > 1
+  unsigned long long* stats_all = nullptr;  // all counters of the handle (stat_words of them)
   int stat_words = 0;
+  uint32_t* newly_rows = nullptr;        // few rows: [rows] tiles that step 0 marks, per row (the kernel clears the counters)
 };
 
 // Tile geometry of a layer, derived from its descriptor.
@@ -131,6 +132,7 @@ struct CallArgs {
   bool fresh;                  // step 0: the mask counts as empty, whatever it holds, and all counters start at zero
   unsigned long long* stats_all;
   size_t stat_words;
+  uint32_t* newly_rows;        // few rows: marks of step 0, per row; null elsewhere
   bool lists_ready, build_next;
 };
 hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListLayout& ll, char* lists, char* scratch,

@@ -1118,6 +1118,32 @@ __device__ __forceinline__ int draw_row(const FwdParams& p, int home) {
   }
 }
 
+typedef const __attribute__((address_space(4))) FwdParams* const_params_ptr;
+typedef const __attribute__((address_space(4))) FwdParams& ParamsRef;
+
+// Step 0 of a call with few rows, by one workgroup: nothing was skipped on entry, a row is one run (two, if its visit starts at
+// a diagonal tile that is not the first), what the rows mark goes to newly_rows; the later steps' counters start at zero.  The
+// launch that cleared them before the kernel cost 1.5-3.4 us (one call of 2 rows x 1 tile 8.1 -> 6.7 us, 32 x 4 14.7 -> 12.5,
+// 120 x 2 12.8 -> 9.4).
+__device__ __forceinline__ void clear_counters(const FwdParams& p, int tid, int threads) {
+  for (int x = tid; x < p.stat_words; x += threads)
+    p.stats_all[x] = x == 2 ? (unsigned long long)(p.rows_total + (p.diagonal_first ? p.rows_total - p.rows_total / p.Tq : 0)) : 0ull;
+}
+
+// The end of a row without lists, by one wave: the tiles that fired (lane w: word w) join the Skip-Mask row as it was on entry
+// (`skipped`; only of interest where something fired), the step's counter moves.
+__device__ __forceinline__ void finish_mask_row(ParamsRef p, int row, int lane, uint64_t skipped, uint64_t fired) {
+  if (lane < p.W && (p.fresh || fired)) p.bits[(size_t)row * p.W + lane] = skipped | fired;
+  if (!p.stat_newly) return;
+  if (!p.fresh || !p.newly_rows) {
+    if (fired) atomicAdd(p.stat_newly, (unsigned long long)__popcll(fired));
+    return;
+  }
+  int n = __popcll(fired);
+  for (int d = 1; d < p.W; d <<= 1) n += __shfl_xor(n, d, 64);
+  if (lane == 0) p.newly_rows[row] = (uint32_t)n;
+}
+
 template <int QB, bool IMM, bool FEW, bool PAIR>
 __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void lite_attn_fwd_kernel(const FwdParams p) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -1206,8 +1232,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
     walk.count(cnt, nruns);
     t_lo = segment_start(cnt, seg, p.nseg);
     t_hi = segment_start(cnt, seg + 1, p.nseg);
-    if (split && p.fresh && blockIdx.x == 0)  // a new trajectory: the merge pass adds this step's counters afterwards
-      for (int x = tid; x < p.stat_words; x += kThreads) p.stats_all[x] = 0;
+    if (p.fresh && p.newly_rows && blockIdx.x == 0) clear_counters(p, tid, kThreads);
   } else {
     cnt = (int)p.live_cnt[row];
     nruns = (int)p.nruns[row];
@@ -1223,7 +1248,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   uint64_t* fired_bits = reinterpret_cast<uint64_t*>(smem + kFiredOff);
   if (!FEW && p.build_next)
     for (int w = tid; w < p.W; w += kThreads) fired_bits[w] = 0;
-  if (tid == 0 && !split && p.stat_newly) {  // statistics of the step: tiles skipped on entry, Skip-List entries
+  if (tid == 0 && !split && p.stat_newly && !(FEW && p.fresh && p.newly_rows)) {  // statistics of the step: tiles skipped on entry, Skip-List entries
     atomicAdd(p.stat_skipped_in, (unsigned long long)(p.Tk - cnt));
     atomicAdd(p.stat_runs, (unsigned long long)nruns);
   }
@@ -1269,7 +1294,6 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
 
   // whether tile (i, j) meets the pinned token range; FEW: asked only of tiles that would fire, with the kernel arguments
   // read again (scalar registers are short in the main loop)
-  typedef const __attribute__((address_space(4))) FwdParams* const_params_ptr;
   auto pinned = [&](int j) -> bool {
     const_params_ptr a = (const_params_ptr)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(a));
@@ -1616,11 +1640,8 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
       return;
     }
     if (tid < 64) {
-      if (lane < e->W && (e->fresh || fired_word)) {
-        uint64_t* word = e->bits + (size_t)row * e->W + lane;
-        *word = (e->fresh ? 0ull : *word) | fired_word;
-      }
-      if (fired_word && e->stat_newly) atomicAdd(e->stat_newly, (unsigned long long)__popcll(fired_word));
+      const uint64_t skipped = fired_word && !e->fresh ? e->bits[(size_t)row * e->W + lane] : 0ull;
+      finish_mask_row(*e, row, lane, skipped, fired_word);
     }
   } else {
     if (tid == 0 && newly && e->stat_newly) atomicAdd(e->stat_newly, (unsigned long long)newly);
@@ -1781,15 +1802,13 @@ __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const Fwd
   }
   fired[wave][lane] = mine;
   __syncthreads();
-  if (tid < p.W) {
+  if (wave == 0) {
     uint64_t f = 0;
 #pragma unroll
-    for (int x = 0; x < kPairs; ++x) f |= fired[2 * x][tid] & fired[2 * x + 1][tid];
-    uint64_t* word = p.bits + (size_t)row * p.W + tid;
-    if (p.fresh || f) *word = skipped | f;  // (tid < W: the lane's own word)
-    if (f && p.stat_newly) atomicAdd(p.stat_newly, (unsigned long long)__popcll(f));
+    for (int x = 0; x < kPairs; ++x) f |= fired[2 * x][lane] & fired[2 * x + 1][lane];
+    finish_mask_row(*(const_params_ptr)__builtin_amdgcn_kernarg_segment_ptr(), row, lane, skipped, f);
   }
-  if (tid == 0 && p.stat_newly) {
+  if (tid == 0 && p.stat_newly && !p.fresh) {
     atomicAdd(p.stat_skipped_in, (unsigned long long)(p.Tk - cnt));
     atomicAdd(p.stat_runs, (unsigned long long)nruns);
   }
