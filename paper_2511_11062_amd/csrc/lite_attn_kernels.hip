@@ -63,6 +63,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -74,6 +75,14 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 template <int... Ks, class F>
 __device__ __forceinline__ void static_for(std::integer_sequence<int, Ks...>, F&& f) {
   (f(std::integral_constant<int, Ks>{}), ...);
+}
+
+// Stores past the XCD's L2 (scope bit sc1, the agent scope), for what the next launch reads: a line left in the L2 is written
+// back at the end of the kernel, and that launch waits for it (5 us behind a call that leaves 16 MB of partial results, 2 us
+// behind one without).
+constexpr int kStoreThrough = 16;  // cache policy of a buffer store
+__device__ __forceinline__ void store_through(float* at, float x) {
+  __hip_atomic_store(at, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 constexpr int kTile = 128;        // Skip-Mask tile: 128 Q rows x 128 K/V columns
@@ -1419,7 +1428,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
     auto verdict_load = [&]() {
       static_assert(IMM || kWaves == 4, "four per-wave flags per tile");
       if (split) {
-        if (v_j >= 0 && ln.hi == 0 && ln.thr > -INFINITY) mloc_out[v_j * kTile] = st.mloc_tile[0];
+        if (v_j >= 0 && ln.hi == 0 && ln.thr > -INFINITY) store_through(mloc_out + v_j * kTile, st.mloc_tile[0]);
         return;
       }
       if (wave0) vflags = *reinterpret_cast<const int4*>(v_slot);
@@ -1442,7 +1451,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
         const float mloc = fmaxf(st.mloc_prev, other);
         st.m_all = fmaxf(st.m_all, mloc);
         if (split) {
-          if (ln.hi == 0 && ln.thr > -INFINITY) mloc_out[j_prev * kTile] = mloc;
+          if (ln.hi == 0 && ln.thr > -INFINITY) store_through(mloc_out + j_prev * kTile, mloc);
         } else {
           const bool ok = __all(!ln.qvalid[0] || (mloc - st.m_all) * ln.scale <= ln.thr);
           *(lane == 0 ? flags + 4 * parity + wave : flags + 8 + lane) = ok ? 1 : 0;
@@ -1622,20 +1631,21 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
       // row maxima (reference of the exponentials) and the row sums
       const size_t s = (size_t)row * e->nseg + seg;
       static_assert(QB == 1, "one Q block per wave");
-      float* po = e->seg_o + (s * 4 + wave) * 4096 + 4 * lane;
+      const auto po = __builtin_amdgcn_make_buffer_rsrc((void*)(e->seg_o + (s * 4 + wave) * 4096), 0, 4 * 4096, 0x00020000);
       if (grp != 0) return;
       if (t_hi > t_lo)
 #pragma unroll
         for (int g = 0; g < 16; ++g) {
           const f32x16& a = st.oacc[0][g >> 2];
           const int r = 4 * (g & 3);
-          *reinterpret_cast<float4*>(po + 256 * g) = float4{a[r], a[r + 1], a[r + 2], a[r + 3]};
+          const f32x4 o = {a[r], a[r + 1], a[r + 2], a[r + 3]};
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), po, 16 * lane, 1024 * g, kStoreThrough);
         }
       const float l = other_half_sum(st.l_run[0]);
       if (ln.hi == 0) {
         float* ps = e->seg_stat + s * 2 * kTile + 32 * wave + lq;
-        ps[0] = st.m_run[0];
-        ps[kTile] = l;
+        store_through(ps, st.m_run[0]);
+        store_through(ps + kTile, l);
       }
       return;
     }
@@ -1669,9 +1679,12 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   for (int t = 0; t < 2048 / kThreads; ++t) {
     const int r = (tid >> 4) + (kThreads / 16) * t;
     const int grow = i * kTile + r;
-    if (grow < N)
-      *reinterpret_cast<uint4*>(ob + (int64_t)grow * p.stride_n + 8 * (tid & 15)) =
-          *reinterpret_cast<const uint4*>(sO + r * kORow + 16 * (tid & 15));
+    const u32x4 o = *reinterpret_cast<const u32x4*>(sO + r * kORow + 16 * (tid & 15));
+    if constexpr (FEW)  // (rows past the end of the sequence lie past the end of the buffer)
+      __builtin_amdgcn_raw_buffer_store_b128(o, __builtin_amdgcn_make_buffer_rsrc((void*)ob, 0, head_bytes, 0x00020000),
+                                             (int)((uint32_t)grow * ln.stride2 + 16 * (tid & 15)), 0, kStoreThrough);
+    else if (grow < N)
+      *reinterpret_cast<u32x4*>(ob + (int64_t)grow * p.stride_n + 8 * (tid & 15)) = o;
   }
 
   if constexpr (FEW) return;
@@ -1692,7 +1705,9 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
 
 // Bound by latency and by the partials' way through memory (64 KB per segment; 16 MB for 256 segments): loads of four
 // segments, or of eight tiles' maxima, in flight together (call of 32 rows x 4 segments of 4 tiles 22.0 -> 20.7
-// us, of 128 rows x 2 segments of 64 tiles 163 -> 147 us, against one load at a time).
+// us, of 128 rows x 2 segments of 64 tiles 163 -> 147 us, against one load at a time); written past the L2 and read without
+// leaving a trace there (a step of 32 rows x 16 tiles 18.8 -> 16.5 us, of 72 x 12 24.1 -> 19.5, of 100 x 25 36.1 -> 34.6; the
+// stores alone give a third of it, nt in place of sc1 half).  All segments' loads at once: no faster with 8, slower with 2-4.
 // Rows that were cut into segments (FEW, nseg > 1): merges the segments' partial results and judges the tiles.
 // Workgroups 0 .. 4*rows-1: 32 Q rows each, one thread per (row, 8 features): O = sum_s 2^(c (m_s - M)) O_s / sum_s ... .
 // Workgroups 4*rows .. 5*rows-1: one Skip-Mask row each; two waves per segment walk its tiles with the running maximum
@@ -1717,14 +1732,14 @@ __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const Fwd
     constexpr int kAhead = 4;  // segments whose loads are in flight together
     for (int s0 = 0; s0 < nseg; s0 += kAhead) {
       float m[kAhead], ls[kAhead];
-      float4 x[kAhead], y[kAhead];
+      f32x4 x[kAhead], y[kAhead];
 #pragma unroll
       for (int u = 0; u < kAhead; ++u) {
         const int s = min(s0 + u, nseg - 1);
         m[u] = ps[s * 2 * kTile];
         ls[u] = ps[s * 2 * kTile + kTile];
-        x[u] = *reinterpret_cast<const float4*>(po + (size_t)s * 4 * 4096);
-        y[u] = *reinterpret_cast<const float4*>(po + (size_t)s * 4 * 4096 + 128);
+        x[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(po + (size_t)s * 4 * 4096));
+        y[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(po + (size_t)s * 4 * 4096 + 128));
       }
 #pragma unroll
       for (int u = 0; u < kAhead; ++u) {
