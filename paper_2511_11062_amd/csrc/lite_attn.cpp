@@ -32,7 +32,8 @@ struct lite_attn_mask {
   char* d_lists;      // Skip-Lists and row ranking (layout ll); kept between calls
   bool lists_valid;   // the lists describe the mask as it stands (left by the previous call's epilogue)
   unsigned long long* d_stats;  // [max_steps][3]: skipped on entry, newly marked, Skip-List runs
-  uint32_t* d_newly;            // few rows: [kFewRows] tiles that step 0 marked, per row (part of step 0's newly marked)
+  uint32_t* d_newly;            // few rows: [kFewRows] tiles that step 0 marked, per row (part of step 0's newly marked);
+                                // [kFewRows] arrivals of rows cut into pieces, zero between calls
   la_scratch own;               // used when ctx == nullptr
   lite_attn_ctx* ctx;           // shared scratch + stream, or nullptr
   hipStream_t stream;           // used when ctx == nullptr
@@ -117,8 +118,20 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     p.pair = g.pair;
     p.fresh = a.fresh ? 1 : 0;
     p.v = static_cast<const uint16_t*>(a.v);
-    if (g.nseg > 1) {
-      const ScratchLayout sl = scratch_layout(g);
+    // (a call that marks nothing is one of dense attention in all likelihood: its rows are alike)
+    if (g.pieces > 0 && !a.fresh && a.threshold > -INFINITY) {
+      p.nseg = 1;
+      p.pair = g.pieces == kPairWorkgroups ? 1 : 0;
+      p.piece_units = g.pieces;
+      p.arrive = a.arrive;
+      if (!p.arrive) {  // (where the table would be)
+        p.arrive = slots;
+        e = launch_clear(reinterpret_cast<uint64_t*>(slots), (size_t)(g.rows + 1) / 2, nullptr, 0, stream);
+        if (e != hipSuccess) return e;
+      }
+    }
+    if (p.nseg > 1 || p.piece_units > 0) {
+      const ScratchLayout sl = scratch_layout(g, p.piece_units > 0);
       p.seg_o = reinterpret_cast<float*>(scratch + sl.seg_o);
       p.seg_stat = reinterpret_cast<float*>(scratch + sl.seg_stat);
       p.seg_mloc = reinterpret_cast<float*>(scratch + sl.seg_mloc);
@@ -204,8 +217,8 @@ int init_common(const lite_attn_desc_t* desc, lite_attn_ctx* ctx, lite_attn_mask
     if (e == hipSuccess) e = la::prepare_fwd();
     if (e == hipSuccess) e = la::launch_clear(m->d_bits, words, m->d_stats, nstats, st);
     if (e == hipSuccess && m->geo.rows <= la::kFewRows) {
-      e = hipMalloc(&m->d_newly, sizeof(uint32_t) * la::kFewRows);
-      if (e == hipSuccess) e = la::launch_clear(reinterpret_cast<uint64_t*>(m->d_newly), la::kFewRows / 2, m->d_stats, 0, st);
+      e = hipMalloc(&m->d_newly, sizeof(uint32_t) * 2 * la::kFewRows);
+      if (e == hipSuccess) e = la::launch_clear(reinterpret_cast<uint64_t*>(m->d_newly), la::kFewRows, m->d_stats, 0, st);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) rc = hip_fail(e);
@@ -295,6 +308,7 @@ int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_a
   a.stats_all = m->d_stats;
   a.stat_words = 3 * (size_t)d.max_steps;
   a.newly_rows = m->d_newly;
+  a.arrive = m->d_newly ? m->d_newly + la::kFewRows : nullptr;
   a.lists_ready = ready;
   a.build_next = true;
   LA_HIP(la::launch_call(d, m->geo, m->ll, m->d_lists, scratch_of(m), a, stream, ev ? ev[1] : nullptr));

@@ -78,6 +78,31 @@ void share_chip(Geometry& g, int flags) {
     }
   }
 }
+
+// Partial results and row maxima of rows cut into pieces.
+size_t piece_bytes(const Geometry& g) {
+  return g.pieces > 0 ? sizeof(float) * ((size_t)g.pieces * (128 * 128 + 2 * 128) + (size_t)g.rows * g.Tk * 128) : 0;
+}
+
+// Few rows: whether the steps after step 0, which know a mask, cut the rows by their live tiles (pick_piece() in
+// lite_attn_kernels.hip) instead of all alike: into at most as many pieces as the chip runs side by side, pairs or, with more
+// rows, single groups.  us per call of a sequence of 3-4 steps (the first is dense), alike -> by live tiles: whole rows, 135 x
+// 15 tiles 31.8 -> 28.7, 155 x 31 56 -> 46.6, 290 x 29 90.9 -> 71.5, 300 x 10 38.3 -> 36.3; segments and merge pass, 100 x 25
+// 34.0 -> 30.8, 128 x 64 66.4 -> 62.2, 99 x 99 80.6 -> 73.7, 300 x 60 137.5 -> 124.1.  Not where the room is taken by the rows
+// themselves (184 of 256 -3 %, 250 -2 %), nor where a row has so few tiles that finding the pieces (1-2 us) costs what it saves
+// (128 x 8 -11 %, 72 x 12 in segments -10 %) or so many segments that more than kMaxPieces would be needed (64 x 32 -1 %).  The
+// literal PV skip can only cut rows of protected tokens, whose tiles need no verdict; diagonal first they are the only long ones
+// (155 x 31, 10 of them protected, four steps 247 -> 155 us; in ascending order -2 %).
+void allow_pieces(Geometry& g, const lite_attn_desc_t& d) {
+  const bool immediate = (d.flags & LITE_ATTN_PV_SKIP_IMMEDIATE) != 0;
+  if (immediate && (d.protect_len == 0 || !(d.flags & LITE_ATTN_ORDER_DIAGONAL_FIRST))) return;
+  if (g.nseg > 1 ? g.Tk < 16 || g.rows < 80 : g.Tk < 10) return;
+  const bool pairs = g.nseg > 1 ? 10 * g.rows <= 7 * kPairWorkgroups : g.pair != 0;
+  const int room = pairs ? kPairWorkgroups : kFewRows;
+  if (10 * g.rows > 7 * room) return;
+  g.pieces = room;
+  if (piece_bytes(g) > kMaxSegmentBytes) g.pieces = 0;
+}
 }  // namespace
 
 Geometry geometry(const lite_attn_desc_t& d) {
@@ -91,10 +116,14 @@ Geometry geometry(const lite_attn_desc_t& d) {
   g.chunks = g.BH * ((g.Tq + kChunkRows - 1) / kChunkRows);
   g.nseg = 0;
   g.pair = 0;
+  g.pieces = 0;
   g.per_xcd = ((g.chunks + 7) / 8 + 1) * kChunkRows + 1;
   if (g.rows <= kFewRows || (g.Tk <= kShortTiles && g.rows <= kMaxListless)) {
     g.nseg = 1;
-    if (g.rows <= kFewRows) share_chip(g, d.flags);
+    if (g.rows <= kFewRows) {
+      share_chip(g, d.flags);
+      allow_pieces(g, d);
+    }
     g.per_xcd = (int)((g.rows * g.nseg + 7) / 8);
     if (g.rows > kSchedRows)
       g.per_xcd = (int)((g.rows + 8 * kDealtRows - 1) / (8 * kDealtRows)) * kDealtRows;
@@ -125,12 +154,14 @@ ListLayout list_layout(const Geometry& g) {
   return l;
 }
 
-ScratchLayout scratch_layout(const Geometry& g) {
+ScratchLayout scratch_layout(const Geometry& g, bool pieces) {
+  const size_t parts = pieces ? (size_t)g.pieces : (size_t)g.rows * g.nseg;
   ScratchLayout l;
   l.seg_o = 0;
-  l.seg_stat = sizeof(float) * (size_t)g.rows * g.nseg * 128 * 128;
-  l.seg_mloc = l.seg_stat + sizeof(float) * (size_t)g.rows * g.nseg * 2 * 128;
-  l.total = up256(g.nseg > 0 ? segment_bytes(g, g.nseg) : sizeof(uint16_t) * (size_t)g.BH * 128 * ((size_t)g.Tk * 128));
+  l.seg_stat = sizeof(float) * parts * 128 * 128;
+  l.seg_mloc = l.seg_stat + sizeof(float) * parts * 2 * 128;
+  l.total = up256(g.nseg > 0 ? std::max(segment_bytes(g, g.nseg), piece_bytes(g))
+                             : sizeof(uint16_t) * (size_t)g.BH * 128 * ((size_t)g.Tk * 128));
   return l;
 }
 

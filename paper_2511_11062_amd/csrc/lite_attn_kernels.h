@@ -27,6 +27,7 @@ constexpr int kResident = 64;
 constexpr int kTicketWords = 32;  // distance of the counters of an unscheduled call, a cache line
 constexpr int kPairWorkgroups = 256;
 constexpr int kMaxSegments = 16;
+constexpr int kMaxPieces = 4;
 constexpr size_t kMaxSegmentBytes = (size_t)104 << 20;
 
 // The chunk of rows that XCD `xcd` takes of the `group`-th eight chunks.  The assignment turns from group to group, in
@@ -74,6 +75,10 @@ struct FwdParams {
   float* seg_mloc = nullptr;             // [rows][Tk][128]: row maxima of the visited tiles
   unsigned long long* stats_all = nullptr;  // all counters of the handle (stat_words of them)
   int stat_words = 0;
+  // > 0: the rows are cut into pieces by their live tiles, at most this many altogether (pick_piece).  Their partial results are
+  // in seg_o and seg_stat, by piece, the row maxima in seg_mloc.
+  int piece_units = 0;
+  uint32_t* arrive = nullptr;            // [rows] pieces that have arrived; zero between calls
   uint32_t* newly_rows = nullptr;        // few rows: [rows] tiles that step 0 marks, per row (the kernel clears the counters)
 };
 
@@ -83,6 +88,8 @@ struct Geometry {
   int run_stride;  // capacity of one row's run-length Skip-List: floor(Tk/2) + 1 runs (ascending order needs at most
                    // ceil(Tk/2); diagonal first can split one more run at the wrap-around)
   int BH;          // batch * heads
+  int pieces;      // > 0: few rows, cut by their live tiles where there is a mask, into at most this many pieces (workgroups;
+                   // pairs, if it is kPairWorkgroups); nseg and pair are for step 0 then
   int64_t rows;    // BH * Tq
   int chunks;      // BH * ceil(Tq / kChunkRows): units of the row schedule
   int pair;        // workgroups of two groups of four waves (at most kPairWorkgroups of them)
@@ -110,12 +117,12 @@ int check_desc(const lite_attn_desc_t* d);  // LITE_ATTN_OK or the error the hea
 int check_call(const void* q, const void* k, const void* v, const void* out, float threshold);
 Geometry geometry(const lite_attn_desc_t& d);
 ListLayout list_layout(const Geometry& g);
-// Scratch of one call: V^T ([BH][128][128*Tk] bf16), or the partial results of rows cut into segments; rows that stay
-// whole and take no lists need neither (total 0).
+// Scratch of one call: V^T ([BH][128][128*Tk] bf16), or the partial results of rows cut into segments or pieces; rows that
+// stay whole and take no lists need neither (total 0).
 struct ScratchLayout {
   size_t seg_o, seg_stat, seg_mloc, total;
 };
-ScratchLayout scratch_layout(const Geometry& g);
+ScratchLayout scratch_layout(const Geometry& g, bool pieces = false);
 
 // lite_attn.cpp: the launches of one attention call on `stream`.  lists_ready: the Skip-Lists in `lists` already
 // describe the mask (left by the previous call's epilogue); otherwise the compaction kernel builds them first.  Then
@@ -133,6 +140,7 @@ struct CallArgs {
   unsigned long long* stats_all;
   size_t stat_words;
   uint32_t* newly_rows;        // few rows: marks of step 0, per row; null elsewhere
+  uint32_t* arrive;            // few rows: kFewRows counters that are zero between calls; null: to be cleared by the call
   bool lists_ready, build_next;
 };
 hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListLayout& ll, char* lists, char* scratch,

@@ -48,7 +48,9 @@
 //   * with few rows a row may be cut into segments, one workgroup each (the rule and its measurements: share_chip() in
 //     lite_attn_host.cpp); merge_segments_kernel adds up the partial results.  The predicate stays exact: the
 //     segments record every tile's row maxima, and the merge pass judges them against the running maximum carried
-//     over the segments, the value a single pass would have had.
+//     over the segments, the value a single pass would have had;
+//   * where rows stay whole at step 0, a sparse step cuts the long ones into pieces of about equal length (pick_piece), merged by
+//     the workgroup that finishes last.
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <stdint.h>
@@ -1153,6 +1155,190 @@ __device__ __forceinline__ void finish_mask_row(ParamsRef p, int row, int lane, 
   if (lane == 0) p.newly_rows[row] = (uint32_t)n;
 }
 
+// Adds up the partial results of a row's pieces, in their order whichever arrived last, into what the end of the kernel expects
+// of a whole row.  Loads have agent scope, like the stores (kStoreThrough); two pieces' are in flight together: 0.7 us a piece.
+template <int QB, bool IMM>
+__device__ __forceinline__ void merge_pieces(State<QB, IMM>& st, ParamsRef p, float c, int piece, int pieces, int wave, int lane) {
+  const float* ps = p.seg_stat + (size_t)piece * 2 * kTile + 32 * wave + (lane & 31);
+  auto stat = [&](int s, int which) {
+    return __hip_atomic_load(ps + (s * 2 + which) * kTile, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  float m[kMaxPieces], l[kMaxPieces], top = kNoMax, sum = 0.f;
+#pragma unroll
+  for (int s = 0; s < kMaxPieces; ++s) {
+    m[s] = stat(min(s, pieces - 1), 0);
+    l[s] = stat(min(s, pieces - 1), 1);
+    top = fmaxf(top, m[s]);
+  }
+#pragma unroll
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) st.oacc[0][db][r] = 0.f;
+#pragma unroll
+  for (int s0 = 0; s0 < kMaxPieces; s0 += 2) {
+    if (s0 >= pieces) break;
+    u32x4 x[2][16];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const auto po = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)(p.seg_o + ((size_t)(piece + min(s0 + u, pieces - 1)) * 4 + wave) * 4096), 0, 4 * 4096, 0x00020000);
+#pragma unroll
+      for (int g = 0; g < 16; ++g) x[u][g] = __builtin_amdgcn_raw_buffer_load_b128(po, 16 * lane, 1024 * g, kStoreThrough);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (s0 + u >= pieces) break;
+      const float f = __builtin_amdgcn_exp2f((m[s0 + u] - top) * c);
+      sum += f * l[s0 + u];
+#pragma unroll
+      for (int g = 0; g < 16; ++g) {
+        const f32x4 v = __builtin_bit_cast(f32x4, x[u][g]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) st.oacc[0][g >> 2][4 * (g & 3) + r] += f * v[r];
+      }
+    }
+  }
+  st.m_run[0] = top;
+  st.l_run[0] = 0.5f * sum;  // (each half of the wave: half of the row sum)
+}
+
+// The tiles of piece `s` of a row that fire, by one wave: lane l holds Q rows 2l and 2l+1 and walks the row maxima that the
+// pieces have left with the maximum carried over from the pieces before (see merge_segments_kernel).  Lane w returns word w.
+template <class Pinned>
+__device__ __forceinline__ uint64_t judge_piece(ParamsRef p, int row, int i, int piece, int pieces, int s, int lane,
+                                                Pinned pinned) {
+  uint64_t fired = 0;
+  if (s >= pieces) return fired;
+  LiveWalk walk;
+  int cnt, nruns;
+  walk.open(LiveWalk::load(p.bits + (size_t)row * p.W, false, p.W), p.Tk, p.W, p.diagonal_first ? i : 0);
+  walk.count(cnt, nruns);
+  const auto mloc = __builtin_amdgcn_make_buffer_rsrc((void*)(p.seg_mloc + (size_t)row * p.Tk * kTile), 0, p.Tk * kTile * 4, 0x00020000);
+  const auto stat = __builtin_amdgcn_make_buffer_rsrc((void*)(p.seg_stat + (size_t)piece * 2 * kTile), 0, pieces * 2 * kTile * 4, 0x00020000);
+  auto pair_of = [&](auto rsrc, int offset) {
+    return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, 8 * lane, offset, kStoreThrough));
+  };
+  const bool valid0 = i * kTile + 2 * lane < p.N, valid1 = i * kTile + 2 * lane + 1 < p.N;
+  f32x2 run = {-INFINITY, -INFINITY};
+#pragma unroll
+  for (int x = 0; x < kMaxPieces - 1; ++x) {
+    const f32x2 m = pair_of(stat, min(x, pieces - 1) * 2 * kTile * 4);
+    run[0] = x < s ? fmaxf(run[0], m[0]) : run[0];
+    run[1] = x < s ? fmaxf(run[1], m[1]) : run[1];
+  }
+  const int t0 = segment_start(cnt, s, pieces), t1 = segment_start(cnt, s + 1, pieces);
+  if (t0 == t1) return fired;
+  walk.rewind();
+  walk.skip(t0);
+  constexpr int kAhead = 8;  // tiles whose loads are in flight together
+  for (int t = t0; t < t1; t += kAhead) {
+    int j[kAhead];
+    f32x2 m[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      j[u] = u > 0 ? j[u - 1] : 0;
+      walk.next(j[u]);
+      m[u] = pair_of(mloc, j[u] * kTile * 4);
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      if (t + u >= t1) break;
+      run[0] = fmaxf(run[0], m[u][0]);
+      run[1] = fmaxf(run[1], m[u][1]);
+      const bool ok = (!valid0 || (m[u][0] - run[0]) * p.scale <= p.thr) && (!valid1 || (m[u][1] - run[1]) * p.scale <= p.thr);
+      if (__all(ok) && !pinned(j[u]) && lane == (j[u] >> 6)) fired |= 1ull << (j[u] & 63);
+    }
+  }
+  return fired;
+}
+
+// x plus that of all lower lanes; the largest x >= 0 of the wave.
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1, 2, 4, 8: within 16 lanes
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15, 31
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+  return x;
+}
+__device__ __forceinline__ int wave_max(int x) {
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
+  return __builtin_amdgcn_readlane(x, 63);
+}
+
+// Few rows that are whole at step 0, when a mask has made them unequal: every row is cut into ceil(live tiles / g) pieces, one
+// workgroup each, with the smallest g (found from below) for which the workgroups that run side by side do; the piece that
+// this workgroup computes.  Every workgroup counts the live tiles of all rows (1.2 us).  Literal PV skip: only rows of protected
+// tokens, whose tiles need no verdict, are cut.
+struct Piece {
+  int row, index, pieces, first;  // (row -1: no piece; first: number of the row's first piece)
+};
+template <bool IMM>
+__device__ __forceinline__ Piece pick_piece(const FwdParams& p, uint16_t* counts, int xcd, int slot, int tid, int threads) {
+  const int lane = tid & 63, rows = p.rows_total;
+  for (int r = tid; r < rows; r += threads) {
+    int n = 0;
+    for (int w = 0; w < p.W; ++w) {
+      uint64_t m = ~p.bits[(size_t)r * p.W + w];
+      if (w == p.W - 1 && (p.Tk & 63)) m &= (1ull << (p.Tk & 63)) - 1ull;
+      n += __popcll(m);
+    }
+    if constexpr (IMM) {
+      const int i = r % p.Tq;
+      if (!(i * kTile < p.protect_start + p.protect_len && p.protect_start < (i + 1) * kTile)) n = 1;
+    }
+    counts[r] = (uint16_t)max(n, 1);
+  }
+  __syncthreads();
+  constexpr int kPerLane = kFewRows / 64;
+  const int per_lane = (rows + 63) / 64;
+  int c[kPerLane], tiles = 0, longest = 0;
+#pragma unroll
+  for (int k = 0; k < kPerLane; ++k) {
+    const int r = lane * per_lane + k;
+    c[k] = k < per_lane && r < rows ? (int)counts[r] : -(1 << 20);  // (no row: no piece, whatever g)
+    tiles += max(c[k], 0);
+    longest = max(longest, c[k]);
+  }
+  tiles = __builtin_amdgcn_readlane(wave_scan(tiles), 63);
+  longest = wave_max(longest);
+  int g = max(quotient(tiles + p.piece_units - 1, p.piece_units), quotient(longest + kMaxPieces - 1, kMaxPieces));
+  int n[kPerLane], mine, upto, total;
+  for (;;) {
+    const float inv = __builtin_amdgcn_rcpf((float)g), add = ((float)g - 0.5f) * inv;
+    mine = 0;
+#pragma unroll
+    for (int k = 0; k < kPerLane; ++k) {  // ceil(c / g): (c + g - 1 + 1/2) / g is never near an integer
+      n[k] = 0;
+      if (k < per_lane) n[k] = max((int)__builtin_fmaf((float)c[k], inv, add), 0);
+      mine += n[k];
+    }
+    upto = wave_scan(mine);
+    total = __builtin_amdgcn_readlane(upto, 63);
+    if (total <= p.piece_units || g >= longest) break;  // (g = longest: a piece for every row; there are no more rows than units)
+    g = max(g + 1, quotient(g * total, p.piece_units));
+    if (4 * g > 3 * longest) g = longest;  // not worth the merging
+  }
+  Piece out = {-1, 0, 1, 0};
+  const int share = (total + 7) / 8, unit = xcd * share + slot;
+  if (slot >= share || unit >= total) return out;
+  const int owner = __popcll(__ballot(upto <= unit));  // lane that holds the row
+  int first = __builtin_amdgcn_readlane(upto - mine, owner);
+#pragma unroll
+  for (int k = 0; k < kPerLane; ++k) {
+    const int nk = __builtin_amdgcn_readlane(n[k], owner);
+    if (out.row < 0 && unit < first + nk) out = {owner * per_lane + k, unit - first, nk, first};
+    first += nk;
+  }
+  return out;
+}
+
 template <int QB, bool IMM, bool FEW, bool PAIR>
 __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void lite_attn_fwd_kernel(const FwdParams p) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -1177,7 +1363,18 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   // ways (chunks of 32 rows 19.7, of 128 19.6).
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   int row = -1, i, bh, seg = 0;
-  if (FEW && !p.tickets) {
+  int pieces = 1, piece = 0;  // a row cut into pieces (pick_piece): how many, and the first one's partial result
+  if (FEW && !p.tickets && p.piece_units) {
+    uint16_t* counts = reinterpret_cast<uint16_t*>(smem + (PAIR ? kPairXchOff : kFiredOff));
+    const Piece mine = pick_piece<IMM>(p, counts, xcd, slot, tid, kThreads);
+    if (mine.row < 0) return;
+    row = mine.row;
+    seg = mine.index;
+    pieces = mine.pieces;
+    piece = mine.first;
+    bh = quotient(row, p.Tq);
+    i = row - bh * p.Tq;
+  } else if (FEW && !p.tickets) {
     const int units = p.rows_total * p.nseg, share = (units + 7) / 8;
     const int unit = xcd * share + slot;
     if (slot >= share || unit >= units) return;
@@ -1203,7 +1400,8 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   const int64_t base = (int64_t)b * p.stride_b + (int64_t)(bh - b * p.H) * p.stride_h;
   uint16_t* ob = p.out + base;
   const int N = p.N;
-  const bool split = FEW && p.nseg > 1;
+  const bool split = FEW && (p.nseg > 1 || pieces > 1);
+  const int part = piece << 8 | pieces << 4 | seg;  // (one scalar register across the main loop)
   Lane<QB> ln;
   State<QB, IMM> st;
   ln.hi = lane >> 5;
@@ -1239,8 +1437,8 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
     load_q();
     walk.open(skipped, p.Tk, p.W, p.diagonal_first ? i : 0);
     walk.count(cnt, nruns);
-    t_lo = segment_start(cnt, seg, p.nseg);
-    t_hi = segment_start(cnt, seg + 1, p.nseg);
+    t_lo = segment_start(cnt, seg, p.nseg * pieces);
+    t_hi = segment_start(cnt, seg + 1, p.nseg * pieces);
     if (p.fresh && p.newly_rows && blockIdx.x == 0) clear_counters(p, tid, kThreads);
   } else {
     cnt = (int)p.live_cnt[row];
@@ -1257,7 +1455,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   uint64_t* fired_bits = reinterpret_cast<uint64_t*>(smem + kFiredOff);
   if (!FEW && p.build_next)
     for (int w = tid; w < p.W; w += kThreads) fired_bits[w] = 0;
-  if (tid == 0 && !split && p.stat_newly && !(FEW && p.fresh && p.newly_rows)) {  // statistics of the step: tiles skipped on entry, Skip-List entries
+  if (tid == 0 && !(FEW && p.nseg > 1) && seg == 0 && p.stat_newly && !(FEW && p.fresh && p.newly_rows)) {  // statistics of the step: tiles skipped on entry, Skip-List entries
     atomicAdd(p.stat_skipped_in, (unsigned long long)(p.Tk - cnt));
     atomicAdd(p.stat_runs, (unsigned long long)nruns);
   }
@@ -1450,7 +1648,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
         if (grp != 0) return;
         const float mloc = fmaxf(st.mloc_prev, other);
         st.m_all = fmaxf(st.m_all, mloc);
-        if (split) {
+        if (split && !IMM) {
           if (ln.hi == 0 && ln.thr > -INFINITY) store_through(mloc_out + j_prev * kTile, mloc);
         } else {
           const bool ok = __all(!ln.qvalid[0] || (mloc - st.m_all) * ln.scale <= ln.thr);
@@ -1626,14 +1824,12 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   const_params_ptr e = (const_params_ptr)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(e));
   if constexpr (FEW) {
-    if (split) {
-      // partial result of this segment, to be merged: O^T accumulators as the lanes hold them (1 KB per store), the
-      // row maxima (reference of the exponentials) and the row sums
-      const size_t s = (size_t)row * e->nseg + seg;
-      static_assert(QB == 1, "one Q block per wave");
+    static_assert(QB == 1, "one Q block per wave");
+    // partial result of a segment or piece: O^T accumulators as the lanes hold them (1 KB per store), the row maxima
+    // (reference of the exponentials) and the row sums
+    auto leave_partial = [&](size_t s, bool empty) {
       const auto po = __builtin_amdgcn_make_buffer_rsrc((void*)(e->seg_o + (s * 4 + wave) * 4096), 0, 4 * 4096, 0x00020000);
-      if (grp != 0) return;
-      if (t_hi > t_lo)
+      if (!empty)
 #pragma unroll
         for (int g = 0; g < 16; ++g) {
           const f32x16& a = st.oacc[0][g >> 2];
@@ -1647,7 +1843,29 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
         store_through(ps, st.m_run[0]);
         store_through(ps + kTile, l);
       }
+    };
+    if (e->nseg > 1) {  // merged by a pass of its own
+      if (grp == 0) leave_partial((size_t)row * e->nseg + (part & 15), t_hi == t_lo);
       return;
+    }
+    const int n_pieces = part >> 4 & 15, first_piece = part >> 8;
+    if (n_pieces > 1) {  // merged by the piece that arrives last
+      if (grp == 0) leave_partial((size_t)(first_piece + (part & 15)), false);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the partials are past the L2 before the arrival is)
+      __syncthreads();
+      if (tid == 0) *flags = (int)atomicInc(e->arrive + row, (unsigned)n_pieces - 1);
+      __syncthreads();
+      if (__builtin_amdgcn_readfirstlane(*flags) != n_pieces - 1) return;
+      uint64_t(*fired)[64] = reinterpret_cast<uint64_t(*)[64]>(smem);
+      if (grp == 0) merge_pieces<QB, IMM>(st, *e, ln.c, first_piece, n_pieces, wave, lane);
+      if constexpr (!IMM) {
+        if (ln.thr > -INFINITY) {
+          if (grp == (PAIR ? 1 : 0)) fired[wave][lane] = judge_piece(*e, row, i, first_piece, n_pieces, wave, lane, pinned);
+          __syncthreads();
+          if (tid < 64) fired_word = fired[0][lane] | fired[1][lane] | fired[2][lane] | fired[3][lane];
+          __syncthreads();  // (the results pass through the same memory)
+        }
+      }
     }
     if (tid < 64) {
       const uint64_t skipped = fired_word && !e->fresh ? e->bits[(size_t)row * e->W + lane] : 0ull;
@@ -1902,7 +2120,7 @@ hipError_t launch_fwd(const FwdParams& p, bool immediate, hipStream_t st) {
   // one workgroup per slot of the schedule table (FEW without a table: per segment or row); those past an XCD's last row
   // return at once
   const bool in_order = p.nseg > 0 && !p.scheduled && p.rows_total <= kSchedRows;
-  const int places = in_order ? (p.rows_total * p.nseg + 7) / 8 : p.per_xcd;
+  const int places = !in_order ? p.per_xcd : ((p.piece_units ? p.piece_units : p.rows_total * p.nseg) + 7) / 8;
   // with tickets an XCD may come to more rows than its list has
   const dim3 grid(8 * (p.tickets && !(p.nseg > 0 && p.scheduled) ? places + places / 8 + 8 : places)), block(Geo<kQB>::kThreads);
   if (p.nseg == 0) {

@@ -1,0 +1,107 @@
+"""Few rows under a mask: rows cut into pieces by their live tiles, merged and judged by the piece that arrives last.  Sizes at
+which that can go wrong: pairs and single groups; rows with no, one and all tiles; mask rows of one, exactly one and several
+words; a ragged last tile; protected rows; the most rows that are cut."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import parity
+from paper_2511_11062_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+class Path(ctypes.Structure):                              # la::Geometry, whole
+    _fields_ = [("Tq", ctypes.c_int), ("Tk", ctypes.c_int), ("W", ctypes.c_int), ("run_stride", ctypes.c_int),
+                ("BH", ctypes.c_int), ("pieces", ctypes.c_int), ("rows", ctypes.c_int64), ("chunks", ctypes.c_int),
+                ("pair", ctypes.c_int), ("nseg", ctypes.c_int), ("per_xcd", ctypes.c_int)]
+
+
+def path_of(heads, tokens, flags=0, protect=(0, 0)):
+    from paper_2511_11062_amd import lite_attn as la
+    f = la._lib._ZN2la8geometryERK16lite_attn_desc_t
+    old = f.restype, f.argtypes
+    f.restype, f.argtypes = Path, [ctypes.POINTER(la.Desc)]
+    p = f(ctypes.byref(la.make_desc(1, heads, tokens, flags=flags, protect=protect)))
+    f.restype, f.argtypes = old
+    return p
+
+
+def layer(heads, tokens, text):
+    return inputs.Workload("pieces", 1, heads, (1, 1, tokens - text), text_tokens=text, steps=3, seed=91)
+
+
+SHAPES = [(9, 128 * 15, 0, 256), (5, 128 * 31 - 55, 100, 256), (10, 128 * 29 + 1, 0, 512), (30, 128 * 10, 33, 512),
+          (4, 128 * 25, 0, 256), (2, 128 * 64, 0, 256), (2, 128 * 65 - 3, 200, 256), (1, 128 * 129 + 7, 0, 256),
+          (5, 128 * 60 + 9, 0, 512), (17, 128 * 21, 0, 512)]
+
+
+@pytest.mark.parametrize("diagonal_first", [False, True])
+@pytest.mark.parametrize("heads,tokens,text,pieces", SHAPES)
+def test_marking_across_pieces(heads, tokens, text, pieces, diagonal_first):
+    """Three steps with rising thresholds against the oracle: outputs, and the tiles of a later piece judged against the maximum
+    carried over from the earlier ones."""
+    wl = layer(heads, tokens, text)
+    assert path_of(heads, tokens, 2 * diagonal_first, wl.protect).pieces == pieces
+    reps = parity.run_sequence_check(wl, steps=3, thresholds=[-2.0, -1.2, -0.6], diagonal_first=diagonal_first, sample_rows=40)
+    assert reps[-1]["skipped_out"] > 0.02
+
+
+@pytest.mark.parametrize("heads,tokens,text", [(5, 128 * 31 - 55, 100), (8, 128 * 20, 300)])
+def test_protected_rows_of_the_literal_skip(heads, tokens, text):
+    wl = layer(heads, tokens, text)
+    assert path_of(heads, tokens, 3, wl.protect).pieces > 0 and path_of(heads, tokens, 1, wl.protect).pieces == 0
+    parity.run_sequence_check(wl, steps=3, thresholds=[-2.0, -1.2, -0.6], diagonal_first=True, immediate=True, sample_rows=30)
+
+
+@pytest.mark.parametrize("heads,tokens,pieces", [(9, 128 * 15 - 3, 256), (10, 128 * 29, 512), (2, 128 * 65 - 3, 256),
+                                                 (5, 128 * 60, 512), (1, 128 * 170 - 1, 256), (2, 128 * 179, 512)])
+def test_uneven_masks_handle_and_static(heads, tokens, pieces):
+    """Imported masks with rows of every length, one without a live tile, one with all: every row against block-masked softmax in
+    fp32; twice with the same result, bit for bit, whatever piece arrived last; then the allocation-free entry point's."""
+    from paper_2511_11062_amd import lite_attn as la
+    tiles, W = -(-tokens // 128), -(-tokens // 128 // 64)
+    assert path_of(heads, tokens).pieces == pieces
+    rng = np.random.default_rng(tokens)
+    skip = rng.random((heads, tiles, tiles)) >= rng.random((heads, tiles, 1)) ** 2
+    skip[0, 0] = True
+    skip[-1, -1] = False
+    skip[0, 1, 1:], skip[0, 1, 0] = True, False
+    g = torch.Generator(device="cuda").manual_seed(tokens)
+    q, k, v = (torch.randn(1, heads, tokens, 128, device="cuda", generator=g).to(torch.bfloat16) for _ in range(3))
+    stream = torch.cuda.current_stream().cuda_stream
+    packed = parity.pack_mask(skip.astype(np.uint8))
+    h = la.lite_attn_init_mask(1, heads, tokens, max_steps=2)
+    la.lite_attn_set_stream(h, stream)
+    outs = []
+    try:
+        for _ in range(2):
+            out = torch.full_like(q, float("nan"))
+            la.lite_attn_mask_import(h, packed, 1)
+            la.lite_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), h, -100.0, 1)   # (marks nothing)
+            st = la.lite_attn_skip_stats(h, 1)
+            assert np.array_equal(la.lite_attn_mask_export(h), packed.ravel())
+            outs.append(out)
+        # the counters of a step add up over its calls
+        assert st.tiles_skipped_in == 2 * int(skip.sum()) and st.tiles_newly_marked == 0
+    finally:
+        la.lite_attn_free_mask(h)
+    desc = la.make_desc(1, heads, tokens, max_steps=1)
+    mask = torch.from_numpy(packed.ravel().view(np.int64).copy()).cuda()
+    out = torch.full_like(q, float("nan"))
+    la.lite_attn_fwd_static(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), desc, mask.data_ptr(), -100.0, stream)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], out)
+    assert np.array_equal(mask.cpu().numpy().view(np.uint64), packed.ravel())
+    dead = torch.from_numpy(skip).cuda()
+    for x in range(heads):
+        kf, vf = k[0, x].float().t().contiguous(), v[0, x].float()
+        for i0 in range(0, tiles, 32):
+            r0, r1 = 128 * i0, min(tokens, 128 * (i0 + 32))
+            s = (q[0, x, r0:r1].float() @ kf) * 128 ** -0.5
+            cols = dead[x, i0:i0 + 32].repeat_interleave(128, 0)[:r1 - r0].repeat_interleave(128, 1)[:, :tokens]
+            ref = torch.nan_to_num(torch.softmax(s.masked_fill_(cols, -float("inf")), dim=1), nan=0.0) @ vf
+            # weights and result are rounded to bf16 (2^-9 each) of values up to max|O|
+            assert (out[0, x, r0:r1].float() - ref).abs().max().item() <= 1e-2 * ref.abs().max().clamp(min=1e-3).item()
