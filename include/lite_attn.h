@@ -71,8 +71,8 @@ typedef struct {
 
 /* Opaque handle: owns the device Skip-Mask ([B,H,Tq,ceil(Tk/64)] uint64, bit j%64 of word j/64 set = tile (i,j)
    skipped) and the statistics, the Skip-List buffers, and owns or borrows (lite_attn_init_mask_shared) the per-call
-   scratch: a copy of V^T (same size as V), or, for layers of at most 512 Q-tile rows, partial results (at most
-   104 MiB); other layers of at most 192 K/V tiles need none.
+   scratch: a copy of V^T (same size as V), or, for layers of at most 512 Q-tile rows or of at most 192 K/V tiles,
+   partial results of rows that several workgroups share (at most 104 MiB, none where no row is shared).
    Tq = ceil(N/tile_q), Tk = ceil(N/tile_k). */
 typedef struct lite_attn_mask lite_attn_mask_t;
 
@@ -98,10 +98,11 @@ int lite_attn_set_stream(lite_attn_mask_t* mask, void* hip_stream);
 
 /* Scratch shared by the layers of a model (this library's own arrangement, nothing of the paper's).
    A call needs device scratch that nothing reads after the call has finished: the Skip-List, the row schedule and
-   a transposed copy of V, together about the size of V (in place of that copy, layers of at most 512 Q-tile rows may
-   need partial results of rows cut into segments, at most 104 MiB; other layers of at most 192 K/V tiles need nothing).
-   A handle made by lite_attn_init_mask owns its own; a model with one handle per layer would hold that once per layer.  Handles made by lite_attn_init_mask_shared borrow the
-   scratch of a context instead: one buffer on the context's device, grown to the largest layer attached so far.
+   a transposed copy of V, together about the size of V (in place of that copy, layers of at most 512 Q-tile
+   rows or of at most 192 K/V tiles may need partial results of rows that several workgroups share, at most 104 MiB).
+   A handle made by lite_attn_init_mask owns its own; a model with one handle per layer would hold that once per
+   layer.  Handles made by lite_attn_init_mask_shared borrow the scratch of a context instead: one buffer on the
+   context's device, grown to the largest layer attached so far.
    Sharing is safe because all handles of a context run on the context's ONE stream, where calls are serial:
      lite_attn_ctx_create       context on the current HIP device, null stream, no scratch yet
      lite_attn_ctx_set_stream   waits for the work queued on the old stream, then every handle of the context

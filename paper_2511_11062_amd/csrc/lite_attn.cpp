@@ -32,8 +32,9 @@ struct lite_attn_mask {
   char* d_lists;      // Skip-Lists and row ranking (layout ll); kept between calls
   bool lists_valid;   // the lists describe the mask as it stands (left by the previous call's epilogue)
   unsigned long long* d_stats;  // [max_steps][3]: skipped on entry, newly marked, Skip-List runs
-  uint32_t* d_newly;            // few rows: [kFewRows] tiles that step 0 marked, per row (part of step 0's newly marked);
-                                // [kFewRows] arrivals of rows cut into pieces, zero between calls
+  uint32_t* d_newly;            // few rows: [kFewRows] tiles that step 0 marked, per row (part of step 0's newly marked)
+  uint32_t* d_arrive;           // behind it, [kFewRows] arrivals of rows cut into pieces, zero between calls
+  bool empty;                   // nothing can have marked a tile since step 0
   la_scratch own;               // used when ctx == nullptr
   lite_attn_ctx* ctx;           // shared scratch + stream, or nullptr
   hipStream_t stream;           // used when ctx == nullptr
@@ -66,7 +67,7 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
   const bool few = g.nseg > 0;
   hipError_t e = hipSuccess;
   // a table of rows comes with its ticket counters cleared; calls without one keep theirs where the table would be
-  const bool table = !few || (g.rows > kFewRows && g.rows <= kSchedRows && !a.fresh);
+  const bool table = !few || (g.rows > kFewRows && g.rows <= kSchedRows && !a.empty);
   const bool tickets = g.rows > kFewRows;
   if (!few && a.fresh) {
     e = launch_clear(a.bits, (size_t)g.rows * g.W, a.stats_all, a.stat_words, stream);
@@ -119,7 +120,7 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     p.fresh = a.fresh ? 1 : 0;
     p.v = static_cast<const uint16_t*>(a.v);
     // (a call that marks nothing is one of dense attention in all likelihood: its rows are alike)
-    if (g.pieces > 0 && !a.fresh && a.threshold > -INFINITY) {
+    if (g.pieces > 0 && g.rows <= kFewRows && !a.empty && a.threshold > -INFINITY) {
       p.nseg = 1;
       p.pair = g.pieces == kPairWorkgroups ? 1 : 0;
       p.piece_units = g.pieces;
@@ -130,8 +131,13 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
         if (e != hipSuccess) return e;
       }
     }
-    if (p.nseg > 1 || p.piece_units > 0) {
-      const ScratchLayout sl = scratch_layout(g, p.piece_units > 0);
+    if (g.rows > kFewRows && g.pieces > 0 && a.empty) {
+      p.cut_rows = cut_rows(g);
+      p.cut_pieces = cut_pieces(g);
+      p.arrive = a.arrive;
+    }
+    if (p.nseg > 1 || p.piece_units > 0 || p.cut_rows > 0) {
+      const ScratchLayout sl = scratch_layout(g, p.nseg <= 1);
       p.seg_o = reinterpret_cast<float*>(scratch + sl.seg_o);
       p.seg_stat = reinterpret_cast<float*>(scratch + sl.seg_stat);
       p.seg_mloc = reinterpret_cast<float*>(scratch + sl.seg_mloc);
@@ -199,6 +205,8 @@ int init_common(const lite_attn_desc_t* desc, lite_attn_ctx* ctx, lite_attn_mask
   m->d_bits = nullptr;
   m->d_stats = nullptr;
   m->d_newly = nullptr;
+  m->d_arrive = nullptr;
+  m->empty = false;
   const size_t words = (size_t)m->geo.rows * m->geo.W, nstats = 3 * (size_t)desc->max_steps;
   const size_t need = la::scratch_layout(m->geo).total;
   hipStream_t st = ctx ? ctx->stream : nullptr;
@@ -216,9 +224,12 @@ int init_common(const lite_attn_desc_t* desc, lite_attn_ctx* ctx, lite_attn_mask
     if (e == hipSuccess) e = hipMalloc(&m->d_lists, m->ll.total);
     if (e == hipSuccess) e = la::prepare_fwd();
     if (e == hipSuccess) e = la::launch_clear(m->d_bits, words, m->d_stats, nstats, st);
-    if (e == hipSuccess && m->geo.rows <= la::kFewRows) {
-      e = hipMalloc(&m->d_newly, sizeof(uint32_t) * 2 * la::kFewRows);
-      if (e == hipSuccess) e = la::launch_clear(reinterpret_cast<uint64_t*>(m->d_newly), la::kFewRows, m->d_stats, 0, st);
+    if (e == hipSuccess && (m->geo.rows <= la::kFewRows || m->geo.pieces > 0)) {
+      uint32_t* counters = nullptr;
+      e = hipMalloc(&counters, sizeof(uint32_t) * 2 * la::kFewRows);
+      m->d_newly = counters;
+      m->d_arrive = counters ? counters + la::kFewRows : nullptr;
+      if (e == hipSuccess) e = la::launch_clear(reinterpret_cast<uint64_t*>(counters), la::kFewRows, m->d_stats, 0, st);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) rc = hip_fail(e);
@@ -307,12 +318,14 @@ int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_a
   a.fresh = step == 0;
   a.stats_all = m->d_stats;
   a.stat_words = 3 * (size_t)d.max_steps;
-  a.newly_rows = m->d_newly;
-  a.arrive = m->d_newly ? m->d_newly + la::kFewRows : nullptr;
+  a.newly_rows = m->geo.rows <= la::kFewRows ? m->d_newly : nullptr;
+  a.arrive = m->d_arrive;
+  a.empty = step == 0 || m->empty;
   a.lists_ready = ready;
   a.build_next = true;
   LA_HIP(la::launch_call(d, m->geo, m->ll, m->d_lists, scratch_of(m), a, stream, ev ? ev[1] : nullptr));
   m->lists_valid = m->geo.nseg == 0;  // (calls with few or short rows keep no lists)
+  m->empty = a.empty && !(threshold > -INFINITY);
   if (ev) LA_HIP(hipEventRecord(ev[2], stream));
   m->next_step = step + 1;
   return LITE_ATTN_OK;
@@ -324,7 +337,7 @@ int lite_attn_skip_stats(lite_attn_mask_t* m, int step, lite_attn_stats_t* host_
   unsigned long long raw[3];
   LA_HIP(hipMemcpyAsync(raw, m->d_stats + 3 * (size_t)step, sizeof raw, hipMemcpyDeviceToHost, stream_of(m)));
   uint32_t newly[la::kFewRows] = {};
-  if (step == 0 && m->d_newly)
+  if (step == 0 && m->geo.rows <= la::kFewRows)
     LA_HIP(hipMemcpyAsync(newly, m->d_newly, sizeof newly, hipMemcpyDeviceToHost, stream_of(m)));
   LA_HIP(hipStreamSynchronize(stream_of(m)));
   for (const uint32_t n : newly) raw[1] += n;
@@ -388,6 +401,7 @@ int lite_attn_mask_import(lite_attn_mask_t* m, const uint64_t* host_bits, size_t
   LA_HIP(hipMemcpyAsync(m->d_bits, host_bits, words * sizeof(uint64_t), hipMemcpyHostToDevice, stream_of(m)));
   LA_HIP(hipStreamSynchronize(stream_of(m)));
   m->next_step = next_step;
+  m->empty = false;
   m->lists_valid = false;  // the next call rebuilds its Skip-Lists from the imported mask
   return LITE_ATTN_OK;
 }

@@ -80,8 +80,23 @@ void share_chip(Geometry& g, int flags) {
 }
 
 // Partial results and row maxima of rows cut into pieces.
+size_t piece_count(const Geometry& g) { return g.rows > kFewRows ? 8 * (size_t)cut_rows(g) * cut_pieces(g) : (size_t)g.pieces; }
 size_t piece_bytes(const Geometry& g) {
-  return g.pieces > 0 ? sizeof(float) * ((size_t)g.pieces * (128 * 128 + 2 * 128) + (size_t)g.rows * g.Tk * 128) : 0;
+  const size_t rows = g.rows > kFewRows ? 8 * (size_t)cut_rows(g) : (size_t)g.rows;  // that have row maxima to keep
+  return g.pieces > 0 ? sizeof(float) * (piece_count(g) * (128 * 128 + 2 * 128) + rows * g.Tk * 128) : 0;
+}
+
+// More rows than run side by side, all of the same length: the rows beyond whole rounds of workgroups would take a round of their
+// own with most of the chip idle, so they are cut, into the more pieces the fewer they are; not where they nearly fill it, and not
+// into pieces of fewer than six tiles (a piece costs about two tiles' time besides its own).  us, step 0, whole -> cut: 522 rows x
+// 58 tiles 311 -> 251 (4 pieces), 600 x 60 335 -> 287 (4), 800 x 40 277 -> 266 (3), 1100 x 55 500 -> 460 (4), 1308 x 110 1087 ->
+// 1034 (3), 1600 x 50 628 -> 600 (4), 896 x 128 893 -> 858 (2); no gain in two pieces at 2384 x 150 (2529 -> 2532).
+void cut_last_round(Geometry& g) {
+  const int rest = (int)(g.rows % kFewRows);
+  const int each = rest <= 128 ? 4 : rest <= 320 ? 3 : rest <= 400 && g.Tk >= 60 && g.rows < 3 * kFewRows ? 2 : 1;
+  if (rest == 0 || each == 1 || g.Tk < 6 * each) return;
+  g.pieces = (rest + 7) / 8 << 4 | each;
+  if (piece_bytes(g) > kMaxSegmentBytes) g.pieces = 0;
 }
 
 // Few rows: whether the steps after step 0, which know a mask, cut the rows by their live tiles (pick_piece() in
@@ -123,6 +138,8 @@ Geometry geometry(const lite_attn_desc_t& d) {
     if (g.rows <= kFewRows) {
       share_chip(g, d.flags);
       allow_pieces(g, d);
+    } else if (g.rows <= kSchedRows && !(d.flags & LITE_ATTN_PV_SKIP_IMMEDIATE)) {
+      cut_last_round(g);
     }
     g.per_xcd = (int)((g.rows * g.nseg + 7) / 8);
     if (g.rows > kSchedRows)
@@ -155,7 +172,7 @@ ListLayout list_layout(const Geometry& g) {
 }
 
 ScratchLayout scratch_layout(const Geometry& g, bool pieces) {
-  const size_t parts = pieces ? (size_t)g.pieces : (size_t)g.rows * g.nseg;
+  const size_t parts = pieces ? piece_count(g) : (size_t)g.rows * g.nseg;
   ScratchLayout l;
   l.seg_o = 0;
   l.seg_stat = sizeof(float) * parts * 128 * 128;

@@ -78,6 +78,7 @@ struct FwdParams {
   // > 0: the rows are cut into pieces by their live tiles, at most this many altogether (pick_piece).  Their partial results are
   // in seg_o and seg_stat, by piece, the row maxima in seg_mloc.
   int piece_units = 0;
+  int cut_rows = 0, cut_pieces = 1;      // more than kFewRows rows in order: of an XCD's rows the last cut_rows are cut alike
   uint32_t* arrive = nullptr;            // [rows] pieces that have arrived; zero between calls
   uint32_t* newly_rows = nullptr;        // few rows: [rows] tiles that step 0 marks, per row (the kernel clears the counters)
 };
@@ -89,7 +90,8 @@ struct Geometry {
                    // ceil(Tk/2); diagonal first can split one more run at the wrap-around)
   int BH;          // batch * heads
   int pieces;      // > 0: few rows, cut by their live tiles where there is a mask, into at most this many pieces (workgroups;
-                   // pairs, if it is kPairWorkgroups); nseg and pair are for step 0 then
+                   // pairs, if it is kPairWorkgroups); nseg and pair are for step 0 then.  Beyond kFewRows rows: how rows
+                   // of equal length are cut (cut_rows, cut_pieces)
   int64_t rows;    // BH * Tq
   int chunks;      // BH * ceil(Tq / kChunkRows): units of the row schedule
   int pair;        // workgroups of two groups of four waves (at most kPairWorkgroups of them)
@@ -98,6 +100,10 @@ struct Geometry {
   int per_xcd;     // entries per XCD in the schedule table: row slots, with lists (ceil(chunks / 8) + 1) chunks, short rows
                    // 1.5 shares, and the ticket counter; where there is no table, the workgroups of an XCD
 };
+
+// More than kFewRows rows in order, all of Tk tiles: rows of each XCD that are cut, and into how many pieces each.
+constexpr int cut_rows(const Geometry& g) { return g.rows > kFewRows ? g.pieces >> 4 : 0; }
+constexpr int cut_pieces(const Geometry& g) { return g.rows > kFewRows ? g.pieces & 15 : 0; }
 
 // Byte offsets of the Skip-List buffers inside one allocation (256-byte aligned pieces).  Handles keep them between
 // calls (a call's epilogue leaves the next call's lists there); the handle-free entry point rebuilds them per call.
@@ -136,6 +142,7 @@ struct CallArgs {
   float threshold;
   uint64_t* bits;              // the Skip-Mask
   unsigned long long* stats3;  // this step's counters, or null (nobody reads them)
+  bool empty;                  // the mask is empty (step 0, or nothing could have marked a tile since): rows are alike
   bool fresh;                  // step 0: the mask counts as empty, whatever it holds, and all counters start at zero
   unsigned long long* stats_all;
   size_t stat_words;

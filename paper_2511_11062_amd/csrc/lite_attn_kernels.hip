@@ -1078,14 +1078,17 @@ __device__ __forceinline__ int quotient(int a, int b) {
 // First visiting position of segment s of a row with cnt live tiles.
 __device__ __forceinline__ int segment_start(int cnt, int s, int nseg) { return nseg == 1 ? cnt * s : quotient(cnt * s, nseg); }
 
-// How many places XCD x's list of rows has, and the row at place t of it (-1: none).
+// How many places XCD x's list of rows has, and the row at place t of it (-1: none; FEW: the piece of it above kPieceShift).
 template <bool FEW>
 __device__ __forceinline__ int places_of(const FwdParams& p, int x) {
   if (!FEW || p.scheduled) return (int)p.xcd_rows[x];
   if (p.rows_total > kSchedRows) return p.per_xcd;
   const int share = (p.rows_total + 7) / 8;
+  if (p.cut_rows > 0) return share + p.cut_rows * (p.cut_pieces - 1);
   return max(0, min(share, p.rows_total - x * share));
 }
+constexpr int kPieceShift = 24;  // (there are at most 2^23 rows without lists)
+static_assert(kMaxListless <= 1 << (kPieceShift - 1), "row and piece in one word");
 template <bool FEW>
 __device__ __forceinline__ int row_at_place(const FwdParams& p, int x, int t) {
   if (t >= places_of<FEW>(p, x)) return -1;
@@ -1094,7 +1097,15 @@ __device__ __forceinline__ int row_at_place(const FwdParams& p, int x, int t) {
     const int row = dealt_chunk(t / kDealtRows, x) * kDealtRows + t % kDealtRows;
     return row < p.rows_total ? row : -1;
   }
-  return x * ((p.rows_total + 7) / 8) + t;
+  // in order, an eighth of the rows to every XCD; of those the last cut_rows in cut_pieces pieces each, row-fastest
+  const int share = (p.rows_total + 7) / 8;
+  int index = 0;
+  if (p.cut_rows > 0 && t >= share) {
+    index = 1 + quotient(t - share, p.cut_rows);
+    t -= index * p.cut_rows;
+  }
+  const int row = x * share + t;
+  return row < p.rows_total ? row | index << kPieceShift : -1;
 }
 
 // The next row for a workgroup that starts on XCD `home` after the first round, by one thread: the next place of its own
@@ -1205,15 +1216,15 @@ __device__ __forceinline__ void merge_pieces(State<QB, IMM>& st, ParamsRef p, fl
 // The tiles of piece `s` of a row that fire, by one wave: lane l holds Q rows 2l and 2l+1 and walks the row maxima that the
 // pieces have left with the maximum carried over from the pieces before (see merge_segments_kernel).  Lane w returns word w.
 template <class Pinned>
-__device__ __forceinline__ uint64_t judge_piece(ParamsRef p, int row, int i, int piece, int pieces, int s, int lane,
-                                                Pinned pinned) {
+__device__ __forceinline__ uint64_t judge_piece(ParamsRef p, int row, int cut_row, int i, int piece, int pieces, int s,
+                                                int lane, Pinned pinned) {
   uint64_t fired = 0;
   if (s >= pieces) return fired;
   LiveWalk walk;
   int cnt, nruns;
-  walk.open(LiveWalk::load(p.bits + (size_t)row * p.W, false, p.W), p.Tk, p.W, p.diagonal_first ? i : 0);
+  walk.open(LiveWalk::load(p.bits + (size_t)row * p.W, p.fresh, p.W), p.Tk, p.W, p.diagonal_first ? i : 0);
   walk.count(cnt, nruns);
-  const auto mloc = __builtin_amdgcn_make_buffer_rsrc((void*)(p.seg_mloc + (size_t)row * p.Tk * kTile), 0, p.Tk * kTile * 4, 0x00020000);
+  const auto mloc = __builtin_amdgcn_make_buffer_rsrc((void*)(p.seg_mloc + (size_t)cut_row * p.Tk * kTile), 0, p.Tk * kTile * 4, 0x00020000);
   const auto stat = __builtin_amdgcn_make_buffer_rsrc((void*)(p.seg_stat + (size_t)piece * 2 * kTile), 0, pieces * 2 * kTile * 4, 0x00020000);
   auto pair_of = [&](auto rsrc, int offset) {
     return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, 8 * lane, offset, kStoreThrough));
@@ -1392,6 +1403,17 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
       row = __builtin_amdgcn_readfirstlane(*told);
       if (row < 0) return;
       __syncthreads();  // (the flags are this word's next user)
+    }
+    if constexpr (FEW) {
+      seg = row >> kPieceShift;
+      row &= (1 << kPieceShift) - 1;
+      if (p.cut_rows > 0) {
+        const int share = (p.rows_total + 7) / 8, x = quotient(row, share), r = row - x * share - (share - p.cut_rows);
+        if (r >= 0) {
+          pieces = p.cut_pieces;
+          piece = (x * p.cut_rows + r) * pieces;
+        }
+      }
     }
     bh = FEW ? quotient(row, p.Tq) : row / p.Tq;
     i = row - bh * p.Tq;
@@ -1622,7 +1644,10 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
     };
     // split rows: whether a tile fires depends on the segments before this one; its row maxima go to the merge pass
     float* mloc_out = nullptr;
-    if constexpr (FEW) mloc_out = p.seg_mloc + (size_t)row * p.Tk * kTile + 32 * wave + lq;
+    if constexpr (FEW) {
+      const int at = p.tickets ? quotient(part >> 8, part >> 4 & 15) : row;  // (beyond kFewRows: by cut row)
+      mloc_out = p.seg_mloc + (size_t)at * p.Tk * kTile + 32 * wave + lq;
+    }
     auto verdict_load = [&]() {
       static_assert(IMM || kWaves == 4, "four per-wave flags per tile");
       if (split) {
@@ -1853,14 +1878,15 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
       if (grp == 0) leave_partial((size_t)(first_piece + (part & 15)), false);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the partials are past the L2 before the arrival is)
       __syncthreads();
-      if (tid == 0) *flags = (int)atomicInc(e->arrive + row, (unsigned)n_pieces - 1);
+      const int cut_row = e->tickets ? quotient(first_piece, n_pieces) : row;
+      if (tid == 0) *flags = (int)atomicInc(e->arrive + cut_row, (unsigned)n_pieces - 1);
       __syncthreads();
       if (__builtin_amdgcn_readfirstlane(*flags) != n_pieces - 1) return;
       uint64_t(*fired)[64] = reinterpret_cast<uint64_t(*)[64]>(smem);
       if (grp == 0) merge_pieces<QB, IMM>(st, *e, ln.c, first_piece, n_pieces, wave, lane);
       if constexpr (!IMM) {
         if (ln.thr > -INFINITY) {
-          if (grp == (PAIR ? 1 : 0)) fired[wave][lane] = judge_piece(*e, row, i, first_piece, n_pieces, wave, lane, pinned);
+          if (grp == (PAIR ? 1 : 0)) fired[wave][lane] = judge_piece(*e, row, cut_row, i, first_piece, n_pieces, wave, lane, pinned);
           __syncthreads();
           if (tid < 64) fired_word = fired[0][lane] | fired[1][lane] | fired[2][lane] | fired[3][lane];
           __syncthreads();  // (the results pass through the same memory)
@@ -2120,7 +2146,8 @@ hipError_t launch_fwd(const FwdParams& p, bool immediate, hipStream_t st) {
   // one workgroup per slot of the schedule table (FEW without a table: per segment or row); those past an XCD's last row
   // return at once
   const bool in_order = p.nseg > 0 && !p.scheduled && p.rows_total <= kSchedRows;
-  const int places = !in_order ? p.per_xcd : ((p.piece_units ? p.piece_units : p.rows_total * p.nseg) + 7) / 8;
+  const int places = !in_order ? p.per_xcd : ((p.piece_units ? p.piece_units : p.rows_total * p.nseg) + 7) / 8 +
+                                             p.cut_rows * (p.cut_pieces - 1);
   // with tickets an XCD may come to more rows than its list has
   const dim3 grid(8 * (p.tickets && !(p.nseg > 0 && p.scheduled) ? places + places / 8 + 8 : places)), block(Geo<kQB>::kThreads);
   if (p.nseg == 0) {

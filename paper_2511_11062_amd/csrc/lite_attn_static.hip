@@ -47,7 +47,8 @@ extern "C" int lite_attn_fwd_static(const void* q, const void* k, const void* v,
   rc = la::check_call(q, k, v, out, threshold);
   if (rc != LITE_ATTN_OK) return rc;
   if (!dev_skip_mask || ((uintptr_t)dev_skip_mask & 7)) return LITE_ATTN_EINVAL;
-  const la::Geometry geo = la::geometry(*desc);
+  la::Geometry geo = la::geometry(*desc);
+  if (geo.rows > la::kFewRows) geo.pieces = 0;  // (cut where the mask is known to be empty; here it is not)
   const la::ListLayout ll = la::list_layout(geo);  // the lists first, V^T behind them
   if (ll.total + la::scratch_layout(geo).total > (size_t)LITE_ATTN_STATIC_SCRATCH_BYTES) return LITE_ATTN_ESCRATCH;
   char* ptr = nullptr;
@@ -61,6 +62,7 @@ extern "C" int lite_attn_fwd_static(const void* q, const void* k, const void* v,
   a.threshold = threshold;
   a.bits = dev_skip_mask;
   a.stats3 = nullptr;
+  a.empty = false;
   a.fresh = false;
   a.stats_all = nullptr;
   a.stat_words = 0;

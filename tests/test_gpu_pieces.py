@@ -105,3 +105,41 @@ def test_uneven_masks_handle_and_static(heads, tokens, pieces):
             ref = torch.nan_to_num(torch.softmax(s.masked_fill_(cols, -float("inf")), dim=1), nan=0.0) @ vf
             # weights and result are rounded to bf16 (2^-9 each) of values up to max|O|
             assert (out[0, x, r0:r1].float() - ref).abs().max().item() <= 1e-2 * ref.abs().max().clamp(min=1e-3).item()
+
+
+# rows beyond whole rounds of workgroups, four, three and two pieces each; a head's last tile ragged; 1 row beyond a round
+@pytest.mark.parametrize("heads,tokens,each", [(9, 128 * 58 - 31, 4), (19, 128 * 27, 4), (12, 128 * 110 + 5, 3), (5, 128 * 161, 3),
+                                               (7, 128 * 128, 2)])
+@pytest.mark.parametrize("flags", [0, 2])
+def test_rows_beyond_whole_rounds(heads, tokens, each, flags):
+    """Step 0, whose last rows on every XCD are cut, and a step that skips, on sampled rows and on rows cut and not cut of every
+    XCD against the oracle; then the counters of both steps against the masks."""
+    from paper_2511_11062_amd import lite_attn as la
+    path = path_of(heads, tokens, flags)
+    cut, share = path.pieces >> 4, -(-path.rows // 8)
+    assert path.pieces & 15 == each and cut == -(-(path.rows % 512) // 8)
+    ends = sorted({min(path.rows - 1, r) for x in range(0, 8, 3)
+                   for r in (x * share + share - cut - 1, x * share + share - cut, x * share + share - 1)})
+    wl = layer(heads, tokens, 0)
+    reps = parity.run_sequence_check(wl, steps=2, thresholds=[-1.5, -0.8], diagonal_first=bool(flags), sample_rows=8, seed=flags,
+                                     extra_rows=ends)
+    assert reps[-1]["skipped_out"] > 0.02
+    seq = inputs.DriftSequence(wl, "cuda:0")
+    h = la.lite_attn_init_mask(1, heads, tokens, max_steps=2, flags=flags)
+    try:
+        la.lite_attn_set_stream(h, torch.cuda.current_stream().cuda_stream)
+        outs, skipped = [], 0
+        for t in range(2):
+            q, k, v = (x.contiguous() for x in next(seq))
+            for again in range(2 if t == 0 else 1):           # the same step 0 twice: the same bits, whatever piece came last
+                out = torch.full_like(q, float("nan"))
+                la.lite_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), h, -1.0, t)
+                outs.append(out)
+            st = la.lite_attn_skip_stats(h, t)
+            mask = parity.unpack_mask(la.lite_attn_mask_export(h).reshape(path.rows, path.W), path.Tk)
+            assert torch.isfinite(out).all()
+            assert st.tiles_skipped_in == skipped and st.tiles_newly_marked == int(mask.sum()) - skipped
+            skipped = int(mask.sum())
+        assert skipped > 0 and torch.equal(outs[0], outs[1])
+    finally:
+        la.lite_attn_free_mask(h)
