@@ -72,7 +72,8 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
   if (!few && a.fresh) {
     e = launch_clear(a.bits, (size_t)g.rows * g.W, a.stats_all, a.stat_words, stream);
   } else if (tickets && !table) {  // (the mask is overwritten; few rows: the fused kernel clears the counters)
-    e = launch_clear(reinterpret_cast<uint64_t*>(slots), 8 * kTicketWords / 2, a.stats_all, a.fresh ? a.stat_words : 0, stream);
+    e = launch_clear(reinterpret_cast<uint64_t*>(slots), 8 * (kTicketWords + kArrivals) / 2, a.stats_all,
+                     a.fresh ? a.stat_words : 0, stream);
   }
   if (e != hipSuccess) return e;
   if (!few) {
@@ -131,10 +132,11 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
         if (e != hipSuccess) return e;
       }
     }
-    if (g.rows > kFewRows && g.pieces > 0 && a.empty) {
+    if (cut_rows(g) > 0) {
       p.cut_rows = cut_rows(g);
       p.cut_pieces = cut_pieces(g);
-      p.arrive = a.arrive;
+      p.arrive = table ? slots + g.per_xcd - kTableTail + 1 : slots + 8 * kTicketWords;
+      p.arrive_stride = table ? g.per_xcd : kArrivals;
     }
     if (p.nseg > 1 || p.piece_units > 0 || p.cut_rows > 0) {
       const ScratchLayout sl = scratch_layout(g, p.nseg <= 1);
@@ -224,7 +226,7 @@ int init_common(const lite_attn_desc_t* desc, lite_attn_ctx* ctx, lite_attn_mask
     if (e == hipSuccess) e = hipMalloc(&m->d_lists, m->ll.total);
     if (e == hipSuccess) e = la::prepare_fwd();
     if (e == hipSuccess) e = la::launch_clear(m->d_bits, words, m->d_stats, nstats, st);
-    if (e == hipSuccess && (m->geo.rows <= la::kFewRows || m->geo.pieces > 0)) {
+    if (e == hipSuccess && m->geo.rows <= la::kFewRows) {
       uint32_t* counters = nullptr;
       e = hipMalloc(&counters, sizeof(uint32_t) * 2 * la::kFewRows);
       m->d_newly = counters;
@@ -318,7 +320,7 @@ int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_a
   a.fresh = step == 0;
   a.stats_all = m->d_stats;
   a.stat_words = 3 * (size_t)d.max_steps;
-  a.newly_rows = m->geo.rows <= la::kFewRows ? m->d_newly : nullptr;
+  a.newly_rows = m->d_newly;
   a.arrive = m->d_arrive;
   a.empty = step == 0 || m->empty;
   a.lists_ready = ready;
@@ -337,7 +339,7 @@ int lite_attn_skip_stats(lite_attn_mask_t* m, int step, lite_attn_stats_t* host_
   unsigned long long raw[3];
   LA_HIP(hipMemcpyAsync(raw, m->d_stats + 3 * (size_t)step, sizeof raw, hipMemcpyDeviceToHost, stream_of(m)));
   uint32_t newly[la::kFewRows] = {};
-  if (step == 0 && m->geo.rows <= la::kFewRows)
+  if (step == 0 && m->d_newly)
     LA_HIP(hipMemcpyAsync(newly, m->d_newly, sizeof newly, hipMemcpyDeviceToHost, stream_of(m)));
   LA_HIP(hipStreamSynchronize(stream_of(m)));
   for (const uint32_t n : newly) raw[1] += n;

@@ -86,11 +86,13 @@ size_t piece_bytes(const Geometry& g) {
   return g.pieces > 0 ? sizeof(float) * (piece_count(g) * (128 * 128 + 2 * 128) + rows * g.Tk * 128) : 0;
 }
 
-// More rows than run side by side, all of the same length: the rows beyond whole rounds of workgroups would take a round of their
-// own with most of the chip idle, so they are cut, into the more pieces the fewer they are; not where they nearly fill it, and not
+// More rows than run side by side: at an empty mask all are of one length, and the rows beyond whole rounds of workgroups would take
+// a round of their own with most of the chip idle, so they are cut, into the more pieces the fewer they are; not where they nearly fill it, and not
 // into pieces of fewer than six tiles (a piece costs about two tiles' time besides its own).  us, step 0, whole -> cut: 522 rows x
 // 58 tiles 311 -> 251 (4 pieces), 600 x 60 335 -> 287 (4), 800 x 40 277 -> 266 (3), 1100 x 55 500 -> 460 (4), 1308 x 110 1087 ->
-// 1034 (3), 1600 x 50 628 -> 600 (4), 896 x 128 893 -> 858 (2); no gain in two pieces at 2384 x 150 (2529 -> 2532).
+// 1034 (3), 1600 x 50 628 -> 600 (4), 896 x 128 893 -> 858 (2); no gain in two pieces at 2384 x 150 (2529 -> 2532).  Under a
+// mask rows stay whole (cut alike, 800 x 40 at 40 % skipped was 8 % slower).  Where the host does not know whether the mask is empty,
+// the row schedule tells, so that a call's result depends on its inputs and its mask, not on how the caller came by them.
 void cut_last_round(Geometry& g) {
   const int rest = (int)(g.rows % kFewRows);
   const int each = rest <= 128 ? 4 : rest <= 320 ? 3 : rest <= 400 && g.Tk >= 60 && g.rows < 3 * kFewRows ? 2 : 1;
@@ -98,6 +100,7 @@ void cut_last_round(Geometry& g) {
   g.pieces = (rest + 7) / 8 << 4 | each;
   if (piece_bytes(g) > kMaxSegmentBytes) g.pieces = 0;
 }
+static_assert(400 / 8 <= kArrivals, "a counter for every row that is cut");
 
 // Few rows: whether the steps after step 0, which know a mask, cut the rows by their live tiles (pick_piece() in
 // lite_attn_kernels.hip) instead of all alike: into at most as many pieces as the chip runs side by side, pairs or, with more
@@ -145,7 +148,7 @@ Geometry geometry(const lite_attn_desc_t& d) {
     if (g.rows > kSchedRows)
       g.per_xcd = (int)((g.rows + 8 * kDealtRows - 1) / (8 * kDealtRows)) * kDealtRows;
     else if (g.rows > kFewRows)
-      g.per_xcd += g.per_xcd / 2 + 1;  // room for an XCD whose rows are short
+      g.per_xcd += g.per_xcd / 2 + kTableTail;  // room for an XCD whose rows are short
   }
   return g;
 }

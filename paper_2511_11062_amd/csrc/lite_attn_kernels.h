@@ -25,6 +25,8 @@ constexpr int kDealtRows = kChunkRows;
 // workgroups draw theirs (FwdParams::tickets).
 constexpr int kResident = 64;
 constexpr int kTicketWords = 32;  // distance of the counters of an unscheduled call, a cache line
+constexpr int kArrivals = 64;     // arrival counters per XCD, of rows cut alike (cut_rows)
+constexpr int kTableTail = 2 + kArrivals;  // end of an XCD's share of a short rows' schedule table: a flag, those, the ticket
 constexpr int kPairWorkgroups = 256;
 constexpr int kMaxSegments = 16;
 constexpr int kMaxPieces = 4;
@@ -78,8 +80,10 @@ struct FwdParams {
   // > 0: the rows are cut into pieces by their live tiles, at most this many altogether (pick_piece).  Their partial results are
   // in seg_o and seg_stat, by piece, the row maxima in seg_mloc.
   int piece_units = 0;
-  int cut_rows = 0, cut_pieces = 1;      // more than kFewRows rows in order: of an XCD's rows the last cut_rows are cut alike
-  uint32_t* arrive = nullptr;            // [rows] pieces that have arrived; zero between calls
+  int cut_rows = 0, cut_pieces = 1;      // more than kFewRows rows: of each eighth, by number, the last cut_rows are cut alike if
+                                         //   the mask is empty (no schedule, or its flag says so)
+  uint32_t* arrive = nullptr;            // pieces that have arrived: [rows], zero between calls, or [8] at arrive_stride
+  int arrive_stride = 0;                 //   [cut_rows], cleared by the schedule or clearing kernel
   uint32_t* newly_rows = nullptr;        // few rows: [rows] tiles that step 0 marks, per row (the kernel clears the counters)
 };
 
@@ -90,18 +94,18 @@ struct Geometry {
                    // ceil(Tk/2); diagonal first can split one more run at the wrap-around)
   int BH;          // batch * heads
   int pieces;      // > 0: few rows, cut by their live tiles where there is a mask, into at most this many pieces (workgroups;
-                   // pairs, if it is kPairWorkgroups); nseg and pair are for step 0 then.  Beyond kFewRows rows: how rows
-                   // of equal length are cut (cut_rows, cut_pieces)
+                   // pairs, if it is kPairWorkgroups); nseg and pair are for step 0 then.  Beyond kFewRows rows: how some
+                   // of them are cut (cut_rows, cut_pieces)
   int64_t rows;    // BH * Tq
   int chunks;      // BH * ceil(Tq / kChunkRows): units of the row schedule
   int pair;        // workgroups of two groups of four waves (at most kPairWorkgroups of them)
   int nseg;        // > 0: few or short rows, each cut into this many segments (one workgroup each; 1 beyond kFewRows rows);
                    // 0: Skip-Lists, row ranking and V^T
   int per_xcd;     // entries per XCD in the schedule table: row slots, with lists (ceil(chunks / 8) + 1) chunks, short rows
-                   // 1.5 shares, and the ticket counter; where there is no table, the workgroups of an XCD
+                   // 1.5 shares and kArrivals counters, and the ticket counter; where there is no table, the workgroups of an XCD
 };
 
-// More than kFewRows rows in order, all of Tk tiles: rows of each XCD that are cut, and into how many pieces each.
+// More than kFewRows rows: rows of each eighth, by number, that are cut, and into how many pieces each.
 constexpr int cut_rows(const Geometry& g) { return g.rows > kFewRows ? g.pieces >> 4 : 0; }
 constexpr int cut_pieces(const Geometry& g) { return g.rows > kFewRows ? g.pieces & 15 : 0; }
 

@@ -371,6 +371,7 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
   uint32_t bar = 0;  // rows of more than bar / rows work count as long: all of them, those above the mean, none
   auto is_long = [&](uint32_t work) { return work * (uint32_t)rows > bar; };
   int l0, l1, o0, o1;  // this XCD's ranges: long rows of [l0, l1), others of [o0, o1)
+  const int room = per_xcd - kTableTail;  // for rows
   for (int attempt = 0;; ++attempt) {
     // this thread's contiguous piece, then a scan over the threads
     uint64_t sum = 0;
@@ -443,7 +444,7 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
     l0 = l1 = 0;
     for (int y = 1; y <= 8; ++y) {
       const int s = max(start, first_long[y]), c = max(count, longs_before[y]);
-      fits = fits && c - count + others_before[y] - others_before[y - 1] < per_xcd;
+      fits = fits && c - count + others_before[y] - others_before[y - 1] <= room;
       if (y == xcd + 1) {
         l0 = start;
         l1 = s;
@@ -453,7 +454,7 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
     }
     o0 = first_other[xcd];
     o1 = first_other[xcd + 1];
-    if (fits || attempt == 2) break;  // (an eighth of the rows, by number, always fits: 8 * (per_xcd - 1) >= rows)
+    if (fits || attempt == 2) break;  // (an eighth of the rows, by number, always fits: 8 * room >= rows)
     bar = attempt == 0 ? total : 0xffffffffu;
     __syncthreads();
   }
@@ -479,8 +480,11 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
       run += c;
     }
     xcd_rows[xcd] = run;
-    slots[(size_t)xcd * per_xcd + per_xcd - 1] = 0;  // this XCD's ticket
   }
+  // this XCD's ticket and arrival counters; before them, whether all rows are of full length, so that some are to be cut
+  if (tid < kTableTail)
+    slots[(size_t)xcd * per_xcd + per_xcd - 1 - tid] =
+        tid == kTableTail - 1 && total == (uint32_t)rows * (uint32_t)(Tk + kRowOverhead) ? 1u : 0u;
   __syncthreads();
   // positions inside the classes, in row order: kSchedThreads rows at a time
   for (int x0 = 0; x0 < n; x0 += kSchedThreads) {
@@ -1080,32 +1084,29 @@ __device__ __forceinline__ int segment_start(int cnt, int s, int nseg) { return 
 
 // How many places XCD x's list of rows has, and the row at place t of it (-1: none; FEW: the piece of it above kPieceShift).
 template <bool FEW>
-__device__ __forceinline__ int places_of(const FwdParams& p, int x) {
-  if (!FEW || p.scheduled) return (int)p.xcd_rows[x];
+__device__ __forceinline__ int places_of(const FwdParams& p, int x, int cut) {
+  if (!FEW) return (int)p.xcd_rows[x];
   if (p.rows_total > kSchedRows) return p.per_xcd;
-  const int share = (p.rows_total + 7) / 8;
-  if (p.cut_rows > 0) return share + p.cut_rows * (p.cut_pieces - 1);
-  return max(0, min(share, p.rows_total - x * share));
+  const int share = (p.rows_total + 7) / 8, extra = cut * (p.cut_pieces - 1);
+  return (p.scheduled ? (int)p.xcd_rows[x] : max(0, min(share, p.rows_total - x * share))) + extra;
 }
 constexpr int kPieceShift = 24;  // (there are at most 2^23 rows without lists)
 static_assert(kMaxListless <= 1 << (kPieceShift - 1), "row and piece in one word");
 template <bool FEW>
-__device__ __forceinline__ int row_at_place(const FwdParams& p, int x, int t) {
-  if (t >= places_of<FEW>(p, x)) return -1;
-  if (!FEW || p.scheduled) return (int)p.slots[(size_t)x * p.per_xcd + t];  // (-1 behind a chunk of fewer than kChunkRows)
+__device__ __forceinline__ int row_at_place(const FwdParams& p, int x, int t, int cut) {
+  const int places = places_of<FEW>(p, x, cut);
+  if (t >= places) return -1;
+  if (!FEW) return (int)p.slots[(size_t)x * p.per_xcd + t];  // (-1 behind a chunk of fewer than kChunkRows)
   if (p.rows_total > kSchedRows) {
     const int row = dealt_chunk(t / kDealtRows, x) * kDealtRows + t % kDealtRows;
     return row < p.rows_total ? row : -1;
   }
-  // in order, an eighth of the rows to every XCD; of those the last cut_rows in cut_pieces pieces each, row-fastest
-  const int share = (p.rows_total + 7) / 8;
-  int index = 0;
-  if (p.cut_rows > 0 && t >= share) {
-    index = 1 + quotient(t - share, p.cut_rows);
-    t -= index * p.cut_rows;
-  }
-  const int row = x * share + t;
-  return row < p.rows_total ? row | index << kPieceShift : -1;
+  // from the table, or in order, an eighth of the rows to every XCD; of each eighth by number the last `cut` rows in cut_pieces
+  // pieces each, of which all but the first end the list, row-fastest
+  const int share = (p.rows_total + 7) / 8, rows = places - cut * (p.cut_pieces - 1);
+  if (t < rows) return p.scheduled ? (int)p.slots[(size_t)x * p.per_xcd + t] : x * share + t;
+  const int index = quotient(t - rows, cut), row = x * share + share - cut + t - rows - index * cut;
+  return row < p.rows_total ? row | (index + 1) << kPieceShift : -1;
 }
 
 // The next row for a workgroup that starts on XCD `home` after the first round, by one thread: the next place of its own
@@ -1118,18 +1119,18 @@ __device__ __forceinline__ int row_at_place(const FwdParams& p, int x, int t) {
 // 2331 us; 12 x 110, diagonal first, four steps 2128 -> 2102; no gain where few rounds of equally long rows leave nothing to
 // draw (12 x 256 dense, six rounds).
 template <bool FEW>
-__device__ __forceinline__ int draw_row(const FwdParams& p, int home) {
+__device__ __forceinline__ int draw_row(const FwdParams& p, int home, int cut) {
   for (int from = home;;) {
     const int t = kResident + (int)atomicAdd(p.tickets + (size_t)from * p.ticket_stride, 1u);
-    if (t < places_of<FEW>(p, from)) {
-      const int row = row_at_place<FEW>(p, from, t);
+    if (t < places_of<FEW>(p, from, cut)) {
+      const int row = row_at_place<FEW>(p, from, t, cut);
       if (row >= 0) return row;
       continue;
     }
     int most = 0;
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
-      const int left = places_of<FEW>(p, x) - kResident -
+      const int left = places_of<FEW>(p, x, cut) - kResident -
                        (int)__hip_atomic_load(p.tickets + (size_t)x * p.ticket_stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (left > most) {
         most = left;
@@ -1395,10 +1396,13 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
     i = unit - u * p.Tq;
     row = bh * p.Tq + i;
   } else {
-    if (slot < kResident) row = row_at_place<FEW>(p, xcd, slot);
+    int cut = 0;  // rows of each eighth that are cut
+    if (FEW && p.cut_rows > 0)
+      cut = !p.scheduled || p.slots[(size_t)(xcd + 1) * p.per_xcd - kTableTail] ? p.cut_rows : 0;
+    if (slot < kResident) row = row_at_place<FEW>(p, xcd, slot, cut);
     if (row < 0) {
       int* told = reinterpret_cast<int*>(smem + (PAIR ? kPairFlagsOff : kFlagsOff));
-      if (tid == 0) *told = draw_row<FEW>(p, xcd);
+      if (tid == 0) *told = draw_row<FEW>(p, xcd, cut);
       __syncthreads();
       row = __builtin_amdgcn_readfirstlane(*told);
       if (row < 0) return;
@@ -1407,11 +1411,11 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
     if constexpr (FEW) {
       seg = row >> kPieceShift;
       row &= (1 << kPieceShift) - 1;
-      if (p.cut_rows > 0) {
-        const int share = (p.rows_total + 7) / 8, x = quotient(row, share), r = row - x * share - (share - p.cut_rows);
+      if (cut > 0) {
+        const int share = (p.rows_total + 7) / 8, x = quotient(row, share), r = row - x * share - (share - cut);
         if (r >= 0) {
           pieces = p.cut_pieces;
-          piece = (x * p.cut_rows + r) * pieces;
+          piece = (x * cut + r) * pieces;
         }
       }
     }
@@ -1878,8 +1882,13 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
       if (grp == 0) leave_partial((size_t)(first_piece + (part & 15)), false);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the partials are past the L2 before the arrival is)
       __syncthreads();
-      const int cut_row = e->tickets ? quotient(first_piece, n_pieces) : row;
-      if (tid == 0) *flags = (int)atomicInc(e->arrive + cut_row, (unsigned)n_pieces - 1);
+      int cut_row = row, counter = row;
+      if (e->tickets) {
+        cut_row = quotient(first_piece, n_pieces);
+        const int x = quotient(cut_row, e->cut_rows);
+        counter = x * e->arrive_stride + cut_row - x * e->cut_rows;
+      }
+      if (tid == 0) *flags = (int)atomicInc(e->arrive + counter, (unsigned)n_pieces - 1);
       __syncthreads();
       if (__builtin_amdgcn_readfirstlane(*flags) != n_pieces - 1) return;
       uint64_t(*fired)[64] = reinterpret_cast<uint64_t(*)[64]>(smem);
@@ -2146,8 +2155,8 @@ hipError_t launch_fwd(const FwdParams& p, bool immediate, hipStream_t st) {
   // one workgroup per slot of the schedule table (FEW without a table: per segment or row); those past an XCD's last row
   // return at once
   const bool in_order = p.nseg > 0 && !p.scheduled && p.rows_total <= kSchedRows;
-  const int places = !in_order ? p.per_xcd : ((p.piece_units ? p.piece_units : p.rows_total * p.nseg) + 7) / 8 +
-                                             p.cut_rows * (p.cut_pieces - 1);
+  const int places = (!in_order ? p.per_xcd : ((p.piece_units ? p.piece_units : p.rows_total * p.nseg) + 7) / 8) +
+                     p.cut_rows * (p.cut_pieces - 1);
   // with tickets an XCD may come to more rows than its list has
   const dim3 grid(8 * (p.tickets && !(p.nseg > 0 && p.scheduled) ? places + places / 8 + 8 : places)), block(Geo<kQB>::kThreads);
   if (p.nseg == 0) {

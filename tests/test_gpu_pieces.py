@@ -143,3 +143,14 @@ def test_rows_beyond_whole_rounds(heads, tokens, each, flags):
         assert skipped > 0 and torch.equal(outs[0], outs[1])
     finally:
         la.lite_attn_free_mask(h)
+    # the allocation-free entry point learns from the mask itself that it is empty, and cuts the same rows
+    desc = la.make_desc(1, heads, tokens, max_steps=1, flags=flags)
+    mask = torch.zeros(la.static_mask_words(desc), dtype=torch.int64, device="cuda")
+    seq = inputs.DriftSequence(wl, "cuda:0")
+    for t in range(2):
+        q, k, v = (x.contiguous() for x in next(seq))
+        out = torch.full_like(q, float("nan"))
+        la.lite_attn_fwd_static(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), desc, mask.data_ptr(), -1.0,
+                                torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert torch.equal(out, outs[2 * t])
