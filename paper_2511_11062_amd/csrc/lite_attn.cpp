@@ -33,7 +33,8 @@ struct lite_attn_mask {
   bool lists_valid;   // the lists describe the mask as it stands (left by the previous call's epilogue)
   unsigned long long* d_stats;  // [max_steps][3]: skipped on entry, newly marked, Skip-List runs
   uint32_t* d_newly;            // few rows: [kFewRows] tiles that step 0 marked, per row (part of step 0's newly marked)
-  uint32_t* d_arrive;           // behind it, [kFewRows] arrivals of rows cut into pieces, zero between calls
+  uint32_t* d_arrive;           // behind it, [kFewRows] arrivals of rows cut into pieces, zero between calls; behind them
+                                //   [2][kFewRows] live tiles of the rows (live_rows())
   bool empty;                   // nothing can have marked a tile since step 0
   la_scratch own;               // used when ctx == nullptr
   lite_attn_ctx* ctx;           // shared scratch + stream, or nullptr
@@ -126,9 +127,12 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
       p.pair = g.pieces == kPairWorkgroups ? 1 : 0;
       p.piece_units = g.pieces;
       p.arrive = a.arrive;
-      if (!p.arrive) {  // (where the table would be)
+      p.live_rows = a.live_rows;
+      if (!p.arrive) {  // (where the table and the lists would be)
+        uint32_t* live = reinterpret_cast<uint32_t*>(lists + ll.live_cnt);
         p.arrive = slots;
-        e = launch_clear(reinterpret_cast<uint64_t*>(slots), (size_t)(g.rows + 1) / 2, nullptr, 0, stream);
+        p.live_rows = live;
+        e = launch_count_rows(a.bits, (int)g.rows, g.Tk, g.W, live, slots, stream);
         if (e != hipSuccess) return e;
       }
     }
@@ -146,6 +150,7 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     }
     p.stats_all = a.stats_all;
     p.newly_rows = a.newly_rows;
+    p.live_next = a.live_next;
     p.stat_words = (int)a.stat_words;
     // nothing to schedule where all workgroups start together or all rows are equally long; beyond kSchedRows rows the kernel
     // deals chunks of them in turn
@@ -176,6 +181,12 @@ using la::hip_fail;
 
 hipStream_t stream_of(const lite_attn_mask* m) { return m->ctx ? m->ctx->stream : m->stream; }
 char* scratch_of(const lite_attn_mask* m) { return static_cast<char*>(m->ctx ? m->ctx->scratch.base : m->own.base); }
+// Layers of few rows that may be cut into pieces: the rows' live tiles at the start of `step`, left by the call before or by an
+// import (two sets in turn, as a call reads one while it leaves the other).
+uint32_t* live_rows(const lite_attn_mask* m, int step) {
+  if (m->geo.pieces == 0 || m->geo.rows > la::kFewRows) return nullptr;
+  return m->d_arrive + (1 + (step & 1)) * la::kFewRows;
+}
 
 int grow(la_scratch* s, size_t bytes) {
   if (bytes <= s->bytes) return LITE_ATTN_OK;
@@ -228,10 +239,10 @@ int init_common(const lite_attn_desc_t* desc, lite_attn_ctx* ctx, lite_attn_mask
     if (e == hipSuccess) e = la::launch_clear(m->d_bits, words, m->d_stats, nstats, st);
     if (e == hipSuccess && m->geo.rows <= la::kFewRows) {
       uint32_t* counters = nullptr;
-      e = hipMalloc(&counters, sizeof(uint32_t) * 2 * la::kFewRows);
+      e = hipMalloc(&counters, sizeof(uint32_t) * 4 * la::kFewRows);
       m->d_newly = counters;
       m->d_arrive = counters ? counters + la::kFewRows : nullptr;
-      if (e == hipSuccess) e = la::launch_clear(reinterpret_cast<uint64_t*>(counters), la::kFewRows, m->d_stats, 0, st);
+      if (e == hipSuccess) e = la::launch_clear(reinterpret_cast<uint64_t*>(counters), 2 * la::kFewRows, m->d_stats, 0, st);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) rc = hip_fail(e);
@@ -322,6 +333,8 @@ int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_a
   a.stat_words = 3 * (size_t)d.max_steps;
   a.newly_rows = m->d_newly;
   a.arrive = m->d_arrive;
+  a.live_rows = live_rows(m, step);
+  a.live_next = live_rows(m, step + 1);
   a.empty = step == 0 || m->empty;
   a.lists_ready = ready;
   a.build_next = true;
@@ -401,6 +414,8 @@ int lite_attn_mask_import(lite_attn_mask_t* m, const uint64_t* host_bits, size_t
   if (!m || !host_bits || words != lite_attn_mask_words(m)) return LITE_ATTN_EINVAL;
   if (next_step < 0 || next_step >= m->desc.max_steps) return LITE_ATTN_ESTEP;
   LA_HIP(hipMemcpyAsync(m->d_bits, host_bits, words * sizeof(uint64_t), hipMemcpyHostToDevice, stream_of(m)));
+  if (uint32_t* live = live_rows(m, next_step))
+    LA_HIP(la::launch_count_rows(m->d_bits, (int)m->geo.rows, m->geo.Tk, m->geo.W, live, nullptr, stream_of(m)));
   LA_HIP(hipStreamSynchronize(stream_of(m)));
   m->next_step = next_step;
   m->empty = false;

@@ -84,6 +84,8 @@ struct FwdParams {
                                          //   the mask is empty (no schedule, or its flag says so)
   uint32_t* arrive = nullptr;            // pieces that have arrived: [rows], zero between calls, or [8] at arrive_stride
   int arrive_stride = 0;                 //   [cut_rows], cleared by the schedule or clearing kernel
+  const uint32_t* live_rows = nullptr;   // piece_units > 0: [rows] live tiles, counted before the launch
+  uint32_t* live_next = nullptr;         // [rows] live tiles that this call leaves, for the next one; may be null
   uint32_t* newly_rows = nullptr;        // few rows: [rows] tiles that step 0 marks, per row (the kernel clears the counters)
 };
 
@@ -152,6 +154,8 @@ struct CallArgs {
   size_t stat_words;
   uint32_t* newly_rows;        // few rows: marks of step 0, per row; null elsewhere
   uint32_t* arrive;            // few rows: kFewRows counters that are zero between calls; null: to be cleared by the call
+  const uint32_t* live_rows;   // few rows that may be cut into pieces: live tiles, left by the previous call; null: to be counted
+  uint32_t* live_next;         //   the same for the next call, or null
   bool lists_ready, build_next;
 };
 hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListLayout& ll, char* lists, char* scratch,
@@ -160,6 +164,8 @@ int hip_fail(hipError_t e);  // remembers e for lite_attn_last_hip_error() and m
 
 hipError_t prepare_fwd();
 hipError_t launch_clear(uint64_t* bits, size_t words, unsigned long long* stats, size_t nstats, hipStream_t st);
+hipError_t launch_count_rows(const uint64_t* bits, int rows, int Tk, int W, uint32_t* live, uint32_t* arrive,
+                             hipStream_t st);
 hipError_t launch_compact(const uint64_t* bits, int rows, int Tq, int Tk, int W, int diagonal_first, int run_stride,
                           uint32_t* runs, uint32_t* nruns, uint32_t* live_cnt, hipStream_t st);
 hipError_t launch_transpose_v(const uint16_t* v, uint16_t* vt, int64_t stride_b, int64_t stride_h, int64_t stride_n,

@@ -1153,17 +1153,31 @@ __device__ __forceinline__ void clear_counters(const FwdParams& p, int tid, int 
     p.stats_all[x] = x == 2 ? (unsigned long long)(p.rows_total + (p.diagonal_first ? p.rows_total - p.rows_total / p.Tq : 0)) : 0ull;
 }
 
+// Live tiles of mask word w as it stands.
+__device__ __forceinline__ int live_in_word(uint64_t skipped, int w, int Tk) {
+  const uint64_t tiles = Tk - 64 * w >= 64 ? ~0ull : (1ull << (Tk - 64 * w)) - 1ull;
+  return __popcll(~skipped & tiles);
+}
+// Lane 0: the sum of what lanes 0 .. W-1 hold (the others hold 0).
+__device__ __forceinline__ int sum_words(int n, int W) {
+  for (int d = 1; d < W; d <<= 1) n += __shfl_xor(n, d, 64);
+  return n;
+}
+
 // The end of a row without lists, by one wave: the tiles that fired (lane w: word w) join the Skip-Mask row as it was on entry
-// (`skipped`; only of interest where something fired), the step's counter moves.
+// (`skipped`; only of interest where something fired or live_next is set), the step's counter moves.
 __device__ __forceinline__ void finish_mask_row(ParamsRef p, int row, int lane, uint64_t skipped, uint64_t fired) {
   if (lane < p.W && (p.fresh || fired)) p.bits[(size_t)row * p.W + lane] = skipped | fired;
+  if (p.live_next) {
+    const int n = sum_words(lane < p.W ? live_in_word(skipped | fired, lane, p.Tk) : 0, p.W);
+    if (lane == 0) p.live_next[row] = (uint32_t)n;
+  }
   if (!p.stat_newly) return;
   if (!p.fresh || !p.newly_rows) {
     if (fired) atomicAdd(p.stat_newly, (unsigned long long)__popcll(fired));
     return;
   }
-  int n = __popcll(fired);
-  for (int d = 1; d < p.W; d <<= 1) n += __shfl_xor(n, d, 64);
+  const int n = sum_words(__popcll(fired), p.W);
   if (lane == 0) p.newly_rows[row] = (uint32_t)n;
 }
 
@@ -1286,8 +1300,10 @@ __device__ __forceinline__ int wave_max(int x) {
 
 // Few rows that are whole at step 0, when a mask has made them unequal: every row is cut into ceil(live tiles / g) pieces, one
 // workgroup each, with the smallest g (found from below) for which the workgroups that run side by side do; the piece that
-// this workgroup computes.  Every workgroup counts the live tiles of all rows (1.2 us).  Literal PV skip: only rows of protected
-// tokens, whose tiles need no verdict, are cut.
+// this workgroup computes.  All workgroups have to find the same cut, so the rows' live tiles come from counts made before this
+// launch and not from the mask, which rows that end early change while workgroups of a busy chip may still have to start.  (Each
+// row's own tiles do come from the mask, and nobody changes them before all of its pieces have arrived: any counts give right
+// results.)  Literal PV skip: only rows of protected tokens, whose tiles need no verdict, are cut.
 struct Piece {
   int row, index, pieces, first;  // (row -1: no piece; first: number of the row's first piece)
 };
@@ -1295,12 +1311,7 @@ template <bool IMM>
 __device__ __forceinline__ Piece pick_piece(const FwdParams& p, uint16_t* counts, int xcd, int slot, int tid, int threads) {
   const int lane = tid & 63, rows = p.rows_total;
   for (int r = tid; r < rows; r += threads) {
-    int n = 0;
-    for (int w = 0; w < p.W; ++w) {
-      uint64_t m = ~p.bits[(size_t)r * p.W + w];
-      if (w == p.W - 1 && (p.Tk & 63)) m &= (1ull << (p.Tk & 63)) - 1ull;
-      n += __popcll(m);
-    }
+    int n = (int)p.live_rows[r];
     if constexpr (IMM) {
       const int i = r % p.Tq;
       if (!(i * kTile < p.protect_start + p.protect_len && p.protect_start < (i + 1) * kTile)) n = 1;
@@ -1903,7 +1914,8 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
       }
     }
     if (tid < 64) {
-      const uint64_t skipped = fired_word && !e->fresh ? e->bits[(size_t)row * e->W + lane] : 0ull;
+      const bool wanted = lane < e->W && !e->fresh && (fired_word || e->live_next);
+      const uint64_t skipped = wanted ? e->bits[(size_t)row * e->W + lane] : 0ull;
       finish_mask_row(*e, row, lane, skipped, fired_word);
     }
   } else {
@@ -2080,6 +2092,23 @@ __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const Fwd
     atomicAdd(p.stat_skipped_in, (unsigned long long)(p.Tk - cnt));
     atomicAdd(p.stat_runs, (unsigned long long)nruns);
   }
+}
+
+// Few rows: the live tiles of every row of a mask that no call of a handle has left (pick_piece() reads them), one thread per
+// row; `arrive`, if not null, is cleared.
+__global__ void count_rows_kernel(const uint64_t* bits, int rows, int Tk, int W, uint32_t* live, uint32_t* arrive) {
+  const int row = blockIdx.x * blockDim.x + threadIdx.x;
+  if (row >= rows) return;
+  int n = 0;
+  for (int w = 0; w < W; ++w) n += live_in_word(bits[(size_t)row * W + w], w, Tk);
+  live[row] = (uint32_t)n;
+  if (arrive) arrive[row] = 0;
+}
+
+hipError_t launch_count_rows(const uint64_t* bits, int rows, int Tk, int W, uint32_t* live, uint32_t* arrive,
+                             hipStream_t st) {
+  hipLaunchKernelGGL(count_rows_kernel, dim3((rows + 63) / 64), dim3(64), 0, st, bits, rows, Tk, W, live, arrive);
+  return hipGetLastError();
 }
 
 hipError_t launch_clear(uint64_t* bits, size_t words, unsigned long long* stats, size_t nstats, hipStream_t st) {

@@ -68,6 +68,8 @@ extern "C" int lite_attn_fwd_static(const void* q, const void* k, const void* v,
   a.stats_all = nullptr;
   a.stat_words = 0;
   a.newly_rows = nullptr;
+  a.live_rows = nullptr;
+  a.live_next = nullptr;
   a.arrive = nullptr;  // (nothing that outlives a call could be vouched for: calls that overlap are the caller's mistake, once)
   a.lists_ready = false;  // lists rebuilt from the caller's mask on every call, none left behind for a next one
   a.build_next = false;

@@ -22,6 +22,14 @@ hipError_t launch_clear(uint64_t* bits, size_t words, unsigned long long* stats,
   return hipSuccess;
 }
 
+hipError_t launch_count_rows(const uint64_t* bits, int rows, int, int W, uint32_t* live, uint32_t* arrive, hipStream_t) {
+  uint64_t any = 0;
+  for (size_t x = 0; x < (size_t)rows * W; ++x) any |= bits[x];
+  for (int r = 0; r < rows; ++r) live[r] = any ? 1 : 2;
+  if (arrive) memset(arrive, 0, sizeof(uint32_t) * rows);
+  return hipSuccess;
+}
+
 hipError_t launch_compact(const uint64_t* bits, int rows, int, int Tk, int W, int, int run_stride, uint32_t* runs,
                           uint32_t* nruns, uint32_t* live_cnt, hipStream_t) {
   uint64_t any = 0;

@@ -154,3 +154,67 @@ def test_rows_beyond_whole_rounds(heads, tokens, each, flags):
                                 torch.cuda.current_stream().cuda_stream)
         torch.cuda.synchronize()
         assert torch.equal(out, outs[2 * t])
+
+
+@pytest.mark.parametrize("heads,tokens,pieces", [(9, 128 * 15, 256), (10, 128 * 29 + 1, 512), (1, 128 * 129 + 7, 256)])
+def test_pieces_on_a_busy_chip(heads, tokens, pieces):
+    """Two handles on two streams, each with workgroups enough for the whole chip: many start when others of their call have ended
+    and marked their rows.  Same outputs, masks and counters, bit for bit, as with the chip to itself."""
+    from paper_2511_11062_amd import lite_attn as la
+    path = path_of(heads, tokens)
+    assert path.pieces == pieces
+    wl = layer(heads, tokens, 0)
+    seq = inputs.DriftSequence(wl, "cuda:0")
+    data = [tuple(x.contiguous() for x in next(seq)) for _ in range(3)]
+    thresholds = [-2.0, -1.2, -0.6]
+
+    def trajectories(streams, rounds):
+        handles = [la.lite_attn_init_mask(1, heads, tokens, max_steps=3) for _ in streams]
+        outs = [[torch.full_like(data[0][0], float("nan")) for _ in data] for _ in streams]
+        torch.cuda.synchronize()
+        try:
+            for h, s in zip(handles, streams):
+                la.lite_attn_set_stream(h, s.cuda_stream)
+            for _ in range(rounds):
+                for t, (q, k, v) in enumerate(data):
+                    for h, o in zip(handles, outs):
+                        la.lite_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o[t].data_ptr(), h, thresholds[t], t)
+            torch.cuda.synchronize()
+            return [(o, la.lite_attn_mask_export(h), [la.lite_attn_skip_stats(h, t).tiles_newly_marked for t in range(3)])
+                    for h, o in zip(handles, outs)]
+        finally:
+            for h in handles:
+                la.lite_attn_free_mask(h)
+
+    alone = trajectories([torch.cuda.Stream()], 1)[0]
+    assert min(alone[2]) > 0
+    for out, mask, newly in trajectories([torch.cuda.Stream(), torch.cuda.Stream()], 6):
+        assert all(torch.equal(a, b) for a, b in zip(out, alone[0]))
+        assert np.array_equal(mask, alone[1]) and newly == alone[2]
+
+
+def test_import_goes_on_as_the_trajectory_would():
+    """A step after an import of the mask gives what it gives in the trajectory that left the mask."""
+    from paper_2511_11062_amd import lite_attn as la
+    heads, tokens = 9, 128 * 15
+    seq = inputs.DriftSequence(layer(heads, tokens, 0), "cuda:0")
+    data = [tuple(x.contiguous() for x in next(seq)) for _ in range(3)]
+    h, g = (la.lite_attn_init_mask(1, heads, tokens, max_steps=3) for _ in range(2))
+    try:
+        for x in (h, g):
+            la.lite_attn_set_stream(x, torch.cuda.current_stream().cuda_stream)
+        outs = [torch.full_like(data[0][0], float("nan")) for _ in data]
+        for t, (q, k, v) in enumerate(data):
+            mask = la.lite_attn_mask_export(h)
+            la.lite_attn_skipruns_export(h, heads * 15)        # (leaves what the next call needs alone)
+            la.lite_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), outs[t].data_ptr(), h, [-2.0, -1.2, -0.6][t], t)
+            if t == 0:
+                continue
+            out = torch.full_like(q, float("nan"))
+            la.lite_attn_mask_import(g, mask, t)
+            la.lite_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), g, [-2.0, -1.2, -0.6][t], t)
+            assert torch.equal(out, outs[t])
+            assert np.array_equal(la.lite_attn_mask_export(g), la.lite_attn_mask_export(h))
+    finally:
+        for x in (h, g):
+            la.lite_attn_free_mask(x)
