@@ -122,18 +122,22 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     p.fresh = a.fresh ? 1 : 0;
     p.v = static_cast<const uint16_t*>(a.v);
     // (a call that marks nothing is one of dense attention in all likelihood: its rows are alike)
-    if (g.pieces > 0 && g.rows <= kFewRows && !a.empty && a.threshold > -INFINITY) {
-      p.nseg = 1;
+    if (g.pieces > 0 && g.rows <= kFewRows && a.threshold > -INFINITY) {
       p.pair = g.pieces == kPairWorkgroups ? 1 : 0;
-      p.piece_units = g.pieces;
-      p.arrive = a.arrive;
-      p.live_rows = a.live_rows;
-      if (!p.arrive) {  // (where the table and the lists would be)
-        uint32_t* live = reinterpret_cast<uint32_t*>(lists + ll.live_cnt);
-        p.arrive = slots;
-        p.live_rows = live;
-        e = launch_count_rows(a.bits, (int)g.rows, g.Tk, g.W, live, slots, stream);
-        if (e != hipSuccess) return e;
+      p.nseg = equal_pieces(g);
+      if (!a.empty) {  // pieces by the rows' live tiles, or, where these turn out to be all, the same number of each
+        p.equal_pieces = p.nseg;
+        p.nseg = 1;
+        p.piece_units = g.pieces;
+        p.arrive = a.arrive;
+        p.live_rows = a.live_rows;
+        if (!p.arrive) {  // (where the table and the lists would be)
+          uint32_t* live = reinterpret_cast<uint32_t*>(lists + ll.live_cnt);
+          p.arrive = slots;
+          p.live_rows = live;
+          e = launch_count_rows(a.bits, (int)g.rows, g.Tk, g.W, live, slots, stream);
+          if (e != hipSuccess) return e;
+        }
       }
     }
     if (cut_rows(g) > 0) {
@@ -143,7 +147,7 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
       p.arrive_stride = table ? g.per_xcd : kArrivals;
     }
     if (p.nseg > 1 || p.piece_units > 0 || p.cut_rows > 0) {
-      const ScratchLayout sl = scratch_layout(g, p.nseg <= 1);
+      const ScratchLayout sl = scratch_layout(g, p.nseg);
       p.seg_o = reinterpret_cast<float*>(scratch + sl.seg_o);
       p.seg_stat = reinterpret_cast<float*>(scratch + sl.seg_stat);
       p.seg_mloc = reinterpret_cast<float*>(scratch + sl.seg_mloc);

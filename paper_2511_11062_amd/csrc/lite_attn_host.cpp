@@ -80,7 +80,9 @@ void share_chip(Geometry& g, int flags) {
 }
 
 // Partial results and row maxima of rows cut into pieces.
-size_t piece_count(const Geometry& g) { return g.rows > kFewRows ? 8 * (size_t)cut_rows(g) * cut_pieces(g) : (size_t)g.pieces; }
+size_t piece_count(const Geometry& g) {
+  return g.rows > kFewRows ? 8 * (size_t)cut_rows(g) * cut_pieces(g) : std::max<size_t>(g.pieces, g.rows * equal_pieces(g));
+}
 size_t piece_bytes(const Geometry& g) {
   const size_t rows = g.rows > kFewRows ? 8 * (size_t)cut_rows(g) : (size_t)g.rows;  // that have row maxima to keep
   return g.pieces > 0 ? sizeof(float) * (piece_count(g) * (128 * 128 + 2 * 128) + rows * g.Tk * 128) : 0;
@@ -102,9 +104,8 @@ void cut_last_round(Geometry& g) {
 }
 static_assert(400 / 8 <= kArrivals, "a counter for every row that is cut");
 
-// Few rows: whether the steps after step 0, which know a mask, cut the rows by their live tiles (pick_piece() in
-// lite_attn_kernels.hip) instead of all alike: into at most as many pieces as the chip runs side by side, pairs or, with more
-// rows, single groups.  us per call of a sequence of 3-4 steps (the first is dense), alike -> by live tiles: whole rows, 135 x
+// Few rows: whether calls that mark cut the rows by their live tiles (pick_piece() in lite_attn_kernels.hip) instead of all
+// alike: into at most as many pieces as the chip runs side by side, pairs or, with more rows, single groups.  us per call of a sequence of 3-4 steps (the first is dense), alike -> by live tiles: whole rows, 135 x
 // 15 tiles 31.8 -> 28.7, 155 x 31 56 -> 46.6, 290 x 29 90.9 -> 71.5, 300 x 10 38.3 -> 36.3; segments and merge pass, 100 x 25
 // 34.0 -> 30.8, 128 x 64 66.4 -> 62.2, 99 x 99 80.6 -> 73.7, 300 x 60 137.5 -> 124.1.  Not where the room is taken by the rows
 // themselves (184 of 256 -3 %, 250 -2 %), nor where a row has so few tiles that finding the pieces (1-2 us) costs what it saves
@@ -122,6 +123,20 @@ void allow_pieces(Geometry& g, const lite_attn_desc_t& d) {
   if (piece_bytes(g) > kMaxSegmentBytes) g.pieces = 0;
 }
 }  // namespace
+
+// Few rows that may be cut into pieces: how many of each a call that marks makes where the mask is empty, whether the caller
+// knows it (segments and merge pass) or the counts say so (pieces; the same sums in the same order).  As many as share_chip()
+// finds, if that is for the same kind of workgroups; else as many as fill one round of pairs, or, with more than half as many
+// rows as that, three in two rounds.  us, step 0, share_chip()'s single groups -> pairs: 80 x 20 31.9 -> 30.1, 100 x 25 41.7 ->
+// 38.3, 105 x 35 47.1 -> 48.6, 128 x 64 80.3 -> 82.0, 99 x 99 95.7 -> 102.2, 130 x 65 90.1 -> 101.7, 150 x 150 197.3 -> 208.8:
+// what it costs that a mask's pieces are pairs, and that a call's result depends on its inputs and its mask, not on how the
+// caller came by them.
+int equal_pieces(const Geometry& g) {
+  if (g.rows > kFewRows) return 1;
+  if (g.nseg == 1 || (g.pieces == kPairWorkgroups) == (g.pair != 0)) return g.nseg;
+  const int rows = (int)g.rows;
+  return 2 * rows <= kPairWorkgroups ? kPairWorkgroups / rows : 3 * rows <= 2 * kPairWorkgroups ? 3 : 1;
+}
 
 Geometry geometry(const lite_attn_desc_t& d) {
   Geometry g;
@@ -174,8 +189,8 @@ ListLayout list_layout(const Geometry& g) {
   return l;
 }
 
-ScratchLayout scratch_layout(const Geometry& g, bool pieces) {
-  const size_t parts = pieces ? piece_count(g) : (size_t)g.rows * g.nseg;
+ScratchLayout scratch_layout(const Geometry& g, int nseg) {
+  const size_t parts = nseg > 1 ? (size_t)g.rows * nseg : piece_count(g);
   ScratchLayout l;
   l.seg_o = 0;
   l.seg_stat = sizeof(float) * parts * 128 * 128;

@@ -80,6 +80,7 @@ struct FwdParams {
   // > 0: the rows are cut into pieces by their live tiles, at most this many altogether (pick_piece).  Their partial results are
   // in seg_o and seg_stat, by piece, the row maxima in seg_mloc.
   int piece_units = 0;
+  int equal_pieces = 1;                  //   where their lengths do not ask for another cut: into this many each
   int cut_rows = 0, cut_pieces = 1;      // more than kFewRows rows: of each eighth, by number, the last cut_rows are cut alike if
                                          //   the mask is empty (no schedule, or its flag says so)
   uint32_t* arrive = nullptr;            // pieces that have arrived: [rows], zero between calls, or [8] at arrive_stride
@@ -95,9 +96,9 @@ struct Geometry {
   int run_stride;  // capacity of one row's run-length Skip-List: floor(Tk/2) + 1 runs (ascending order needs at most
                    // ceil(Tk/2); diagonal first can split one more run at the wrap-around)
   int BH;          // batch * heads
-  int pieces;      // > 0: few rows, cut by their live tiles where there is a mask, into at most this many pieces (workgroups;
-                   // pairs, if it is kPairWorkgroups); nseg and pair are for step 0 then.  Beyond kFewRows rows: how some
-                   // of them are cut (cut_rows, cut_pieces)
+  int pieces;      // > 0: few rows, cut by their live tiles into at most this many pieces (workgroups; pairs, if it is
+                   // kPairWorkgroups), or, at an empty mask, into equal_pieces() each; nseg and pair are then for calls that
+                   // mark nothing.  Beyond kFewRows rows: how some of them are cut (cut_rows, cut_pieces)
   int64_t rows;    // BH * Tq
   int chunks;      // BH * ceil(Tq / kChunkRows): units of the row schedule
   int pair;        // workgroups of two groups of four waves (at most kPairWorkgroups of them)
@@ -129,12 +130,13 @@ int check_desc(const lite_attn_desc_t* d);  // LITE_ATTN_OK or the error the hea
 int check_call(const void* q, const void* k, const void* v, const void* out, float threshold);
 Geometry geometry(const lite_attn_desc_t& d);
 ListLayout list_layout(const Geometry& g);
-// Scratch of one call: V^T ([BH][128][128*Tk] bf16), or the partial results of rows cut into segments or pieces; rows that
-// stay whole and take no lists need neither (total 0).
+int equal_pieces(const Geometry& g);
+// Scratch of a layer's calls: V^T ([BH][128][128*Tk] bf16), or the partial results of rows cut into nseg segments or, at 1, into
+// pieces; rows that stay whole and take no lists need neither (total 0, the most that any of the layer's calls needs).
 struct ScratchLayout {
   size_t seg_o, seg_stat, seg_mloc, total;
 };
-ScratchLayout scratch_layout(const Geometry& g, bool pieces = false);
+ScratchLayout scratch_layout(const Geometry& g, int nseg = 1);
 
 // lite_attn.cpp: the launches of one attention call on `stream`.  lists_ready: the Skip-Lists in `lists` already
 // describe the mask (left by the previous call's epilogue); otherwise the compaction kernel builds them first.  Then

@@ -49,8 +49,8 @@
 //     lite_attn_host.cpp); merge_segments_kernel adds up the partial results.  The predicate stays exact: the
 //     segments record every tile's row maxima, and the merge pass judges them against the running maximum carried
 //     over the segments, the value a single pass would have had;
-//   * where rows stay whole at step 0, a sparse step cuts the long ones into pieces of about equal length (pick_piece), merged by
-//     the workgroup that finishes last.
+//   * under a mask rows may be cut by their live tiles, into pieces of about equal length (pick_piece), merged by the workgroup
+//     that finishes last.
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <stdint.h>
@@ -1196,13 +1196,12 @@ __device__ __forceinline__ void merge_pieces(State<QB, IMM>& st, ParamsRef p, fl
     l[s] = stat(min(s, pieces - 1), 1);
     top = fmaxf(top, m[s]);
   }
+  for (int s = kMaxPieces; s < pieces; ++s) top = fmaxf(top, stat(s, 0));  // (rows cut alike)
 #pragma unroll
   for (int db = 0; db < 4; ++db)
 #pragma unroll
     for (int r = 0; r < 16; ++r) st.oacc[0][db][r] = 0.f;
-#pragma unroll
-  for (int s0 = 0; s0 < kMaxPieces; s0 += 2) {
-    if (s0 >= pieces) break;
+  auto add_two = [&](int s0, const float (&m)[2], const float (&l)[2]) __attribute__((always_inline)) {
     u32x4 x[2][16];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -1214,8 +1213,8 @@ __device__ __forceinline__ void merge_pieces(State<QB, IMM>& st, ParamsRef p, fl
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       if (s0 + u >= pieces) break;
-      const float f = __builtin_amdgcn_exp2f((m[s0 + u] - top) * c);
-      sum += f * l[s0 + u];
+      const float f = __builtin_amdgcn_exp2f((m[u] - top) * c);
+      sum += f * l[u];
 #pragma unroll
       for (int g = 0; g < 16; ++g) {
         const f32x4 v = __builtin_bit_cast(f32x4, x[u][g]);
@@ -1223,6 +1222,15 @@ __device__ __forceinline__ void merge_pieces(State<QB, IMM>& st, ParamsRef p, fl
         for (int r = 0; r < 4; ++r) st.oacc[0][g >> 2][4 * (g & 3) + r] += f * v[r];
       }
     }
+  };
+#pragma unroll
+  for (int s0 = 0; s0 < kMaxPieces; s0 += 2) {
+    if (s0 >= pieces) break;
+    add_two(s0, {m[s0], m[s0 + 1]}, {l[s0], l[s0 + 1]});
+  }
+  for (int s0 = kMaxPieces; s0 < pieces; s0 += 2) {
+    const int s1 = min(s0 + 1, pieces - 1);
+    add_two(s0, {stat(s0, 0), stat(s1, 0)}, {stat(s0, 1), stat(s1, 1)});
   }
   st.m_run[0] = top;
   st.l_run[0] = 0.5f * sum;  // (each half of the wave: half of the row sum)
@@ -1234,7 +1242,6 @@ template <class Pinned>
 __device__ __forceinline__ uint64_t judge_piece(ParamsRef p, int row, int cut_row, int i, int piece, int pieces, int s,
                                                 int lane, Pinned pinned) {
   uint64_t fired = 0;
-  if (s >= pieces) return fired;
   LiveWalk walk;
   int cnt, nruns;
   walk.open(LiveWalk::load(p.bits + (size_t)row * p.W, p.fresh, p.W), p.Tk, p.W, p.diagonal_first ? i : 0);
@@ -1251,6 +1258,11 @@ __device__ __forceinline__ uint64_t judge_piece(ParamsRef p, int row, int cut_ro
     const f32x2 m = pair_of(stat, min(x, pieces - 1) * 2 * kTile * 4);
     run[0] = x < s ? fmaxf(run[0], m[0]) : run[0];
     run[1] = x < s ? fmaxf(run[1], m[1]) : run[1];
+  }
+  for (int x = kMaxPieces - 1; x < s; ++x) {  // (rows cut alike)
+    const f32x2 m = pair_of(stat, x * 2 * kTile * 4);
+    run[0] = fmaxf(run[0], m[0]);
+    run[1] = fmaxf(run[1], m[1]);
   }
   const int t0 = segment_start(cnt, s, pieces), t1 = segment_start(cnt, s + 1, pieces);
   if (t0 == t1) return fired;
@@ -1298,37 +1310,50 @@ __device__ __forceinline__ int wave_max(int x) {
   return __builtin_amdgcn_readlane(x, 63);
 }
 
-// Few rows that are whole at step 0, when a mask has made them unequal: every row is cut into ceil(live tiles / g) pieces, one
-// workgroup each, with the smallest g (found from below) for which the workgroups that run side by side do; the piece that
-// this workgroup computes.  All workgroups have to find the same cut, so the rows' live tiles come from counts made before this
-// launch and not from the mask, which rows that end early change while workgroups of a busy chip may still have to start.  (Each
-// row's own tiles do come from the mask, and nobody changes them before all of its pieces have arrived: any counts give right
-// results.)  Literal PV skip: only rows of protected tokens, whose tiles need no verdict, are cut.
+// Few rows that a mask has made unequal: every row is cut into ceil(live tiles / g) pieces, one workgroup each, with the
+// smallest g (found from below) for which the workgroups that run side by side do; the piece that this workgroup computes.  All
+// workgroups have to find the same cut, so the rows' live tiles come from counts made before this launch and not from the mask,
+// which rows that end early change while workgroups of a busy chip may still have to start.  (Each row's own tiles do come from
+// the mask, and nobody changes them before all of its pieces have arrived: any counts give right results.)  Literal PV skip:
+// only rows of protected tokens, whose tiles need no verdict, are cut.  Where the counts say that the mask is empty, the rows
+// are cut alike, as where the caller knows that it is: what a call gives depends on the mask, not on how it came about.  They
+// are also cut alike, in as many rounds of workgroups as it takes, where one round would leave most rows nearly whole: us, 40 %
+// of the tiles of each row skipped, 15 % in brackets, one round -> alike: 348 x 87 205 -> 192, 300 x 60 (175 -> 153), 304 x 304
+// 597 -> 493, 150 x 150 165 -> 147, 129 x 129 (191 -> 171).
 struct Piece {
-  int row, index, pieces, first;  // (row -1: no piece; first: number of the row's first piece)
+  int row, index, pieces, first;  // (row -1: no piece, kAlike: cut alike; first: number of the row's first piece)
 };
+constexpr int kAlike = -2, kFullRow = 1 << 15;
 template <bool IMM>
 __device__ __forceinline__ Piece pick_piece(const FwdParams& p, uint16_t* counts, int xcd, int slot, int tid, int threads) {
   const int lane = tid & 63, rows = p.rows_total;
   for (int r = tid; r < rows; r += threads) {
     int n = (int)p.live_rows[r];
+    const int full = n == p.Tk ? kFullRow : 0;
     if constexpr (IMM) {
       const int i = r % p.Tq;
       if (!(i * kTile < p.protect_start + p.protect_len && p.protect_start < (i + 1) * kTile)) n = 1;
     }
-    counts[r] = (uint16_t)max(n, 1);
+    counts[r] = (uint16_t)(max(n, 1) | full);
   }
   __syncthreads();
   constexpr int kPerLane = kFewRows / 64;
   const int per_lane = (rows + 63) / 64;
   int c[kPerLane], tiles = 0, longest = 0;
+  bool alike = true;
 #pragma unroll
   for (int k = 0; k < kPerLane; ++k) {
     const int r = lane * per_lane + k;
-    c[k] = k < per_lane && r < rows ? (int)counts[r] : -(1 << 20);  // (no row: no piece, whatever g)
+    c[k] = -(1 << 20);  // (no row: no piece, whatever g)
+    if (k < per_lane && r < rows) {
+      c[k] = counts[r];
+      alike = alike && c[k] >= kFullRow;
+      c[k] &= kFullRow - 1;
+    }
     tiles += max(c[k], 0);
     longest = max(longest, c[k]);
   }
+  if (__all(alike)) return {kAlike, 0, 1, 0};
   tiles = __builtin_amdgcn_readlane(wave_scan(tiles), 63);
   longest = wave_max(longest);
   int g = max(quotient(tiles + p.piece_units - 1, p.piece_units), quotient(longest + kMaxPieces - 1, kMaxPieces));
@@ -1348,6 +1373,9 @@ __device__ __forceinline__ Piece pick_piece(const FwdParams& p, uint16_t* counts
     g = max(g + 1, quotient(g * total, p.piece_units));
     if (4 * g > 3 * longest) g = longest;  // not worth the merging
   }
+  // (a piece costs about two tiles' time besides its own)
+  const int rounds = quotient(rows * p.equal_pieces + p.piece_units - 1, p.piece_units);
+  if (p.equal_pieces > 1 && g > rounds * (quotient(longest + p.equal_pieces - 1, p.equal_pieces) + 2)) return {kAlike, 0, 1, 0};
   Piece out = {-1, 0, 1, 0};
   const int share = (total + 7) / 8, unit = xcd * share + slot;
   if (slot >= share || unit >= total) return out;
@@ -1387,25 +1415,32 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   int row = -1, i, bh, seg = 0;
   int pieces = 1, piece = 0;  // a row cut into pieces (pick_piece): how many, and the first one's partial result
-  if (FEW && !p.tickets && p.piece_units) {
-    uint16_t* counts = reinterpret_cast<uint16_t*>(smem + (PAIR ? kPairXchOff : kFiredOff));
-    const Piece mine = pick_piece<IMM>(p, counts, xcd, slot, tid, kThreads);
-    if (mine.row < 0) return;
-    row = mine.row;
-    seg = mine.index;
-    pieces = mine.pieces;
-    piece = mine.first;
-    bh = quotient(row, p.Tq);
-    i = row - bh * p.Tq;
-  } else if (FEW && !p.tickets) {
-    const int units = p.rows_total * p.nseg, share = (units + 7) / 8;
-    const int unit = xcd * share + slot;
-    if (slot >= share || unit >= units) return;
-    const int u = quotient(unit, p.Tq);
-    bh = quotient(u, p.nseg);
-    seg = u - bh * p.nseg;
-    i = unit - u * p.Tq;
-    row = bh * p.Tq + i;
+  if (FEW && !p.tickets) {
+    Piece mine = {kAlike, 0, 1, 0};
+    if (p.piece_units) {
+      uint16_t* counts = reinterpret_cast<uint16_t*>(smem + (PAIR ? kPairXchOff : kFiredOff));
+      mine = pick_piece<IMM>(p, counts, xcd, slot, tid, kThreads);
+      if (mine.row == -1) return;
+    }
+    if (mine.row >= 0) {
+      row = mine.row;
+      seg = mine.index;
+      pieces = mine.pieces;
+      piece = mine.first;
+      bh = quotient(row, p.Tq);
+      i = row - bh * p.Tq;
+    } else {  // all rows alike: segments, or as many pieces
+      const int n = p.nseg * p.equal_pieces, units = p.rows_total * n, share = (units + 7) / 8;
+      const int unit = xcd * share + slot;
+      if (slot >= share || unit >= units) return;
+      const int u = quotient(unit, p.Tq);
+      bh = quotient(u, n);
+      seg = u - bh * n;
+      i = unit - u * p.Tq;
+      row = bh * p.Tq + i;
+      pieces = p.equal_pieces;
+      piece = row * pieces;
+    }
   } else {
     int cut = 0;  // rows of each eighth that are cut
     if (FEW && p.cut_rows > 0)
@@ -1906,7 +1941,11 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
       if (grp == 0) merge_pieces<QB, IMM>(st, *e, ln.c, first_piece, n_pieces, wave, lane);
       if constexpr (!IMM) {
         if (ln.thr > -INFINITY) {
-          if (grp == (PAIR ? 1 : 0)) fired[wave][lane] = judge_piece(*e, row, cut_row, i, first_piece, n_pieces, wave, lane, pinned);
+          if (grp == (PAIR ? 1 : 0)) {
+            uint64_t f = 0;
+            for (int s = wave; s < n_pieces; s += 4) f |= judge_piece(*e, row, cut_row, i, first_piece, n_pieces, s, lane, pinned);
+            fired[wave][lane] = f;
+          }
           __syncthreads();
           if (tid < 64) fired_word = fired[0][lane] | fired[1][lane] | fired[2][lane] | fired[3][lane];
           __syncthreads();  // (the results pass through the same memory)
@@ -2184,7 +2223,8 @@ hipError_t launch_fwd(const FwdParams& p, bool immediate, hipStream_t st) {
   // one workgroup per slot of the schedule table (FEW without a table: per segment or row); those past an XCD's last row
   // return at once
   const bool in_order = p.nseg > 0 && !p.scheduled && p.rows_total <= kSchedRows;
-  const int places = (!in_order ? p.per_xcd : ((p.piece_units ? p.piece_units : p.rows_total * p.nseg) + 7) / 8) +
+  const int alike = p.rows_total * p.nseg * p.equal_pieces;
+  const int places = (!in_order ? p.per_xcd : (std::max(alike, p.piece_units) + 7) / 8) +
                      p.cut_rows * (p.cut_pieces - 1);
   // with tickets an XCD may come to more rows than its list has
   const dim3 grid(8 * (p.tickets && !(p.nseg > 0 && p.scheduled) ? places + places / 8 + 8 : places)), block(Geo<kQB>::kThreads);

@@ -218,3 +218,55 @@ def test_import_goes_on_as_the_trajectory_would():
     finally:
         for x in (h, g):
             la.lite_attn_free_mask(x)
+
+
+# whole rows and two to seven equal segments, in pairs and in single groups; more segments than run side by side (4 x 87: 1392);
+# protected rows of the literal skip
+@pytest.mark.parametrize("heads,tokens,flags,text,nseg", [
+    (9, 128 * 15 - 3, 0, 0, 1), (10, 128 * 29, 2, 0, 1), (6, 128 * 20, 2, 0, 2), (4, 128 * 86, 0, 0, 2), (5, 128 * 16 - 9, 0, 0, 3),
+    (3, 128 * 27, 0, 0, 3), (3, 128 * 35, 2, 50, 4), (2, 128 * 64 - 1, 0, 0, 4), (4, 128 * 87, 0, 0, 4), (4, 128 * 25 - 70, 0, 0, 5),
+    (4, 128 * 70, 0, 0, 5), (1, 128 * 129 + 7, 0, 0, 7), (1, 128 * 180, 2, 0, 7), (5, 128 * 31 - 55, 3, 100, 1)])
+def test_empty_mask_however_the_caller_came_by_it(heads, tokens, flags, text, nseg):
+    """The first call of a handle, later calls on a mask that is still empty (known to be, or not), a call on an imported empty
+    mask and the allocation-free call: the same bits out of all of them, and the same mask behind."""
+    from paper_2511_11062_amd import lite_attn as la
+    wl = layer(heads, tokens, text)
+    path = path_of(heads, tokens, flags, wl.protect)
+    assert path.pieces > 0 and path.nseg == nseg
+    q, k, v = (x.contiguous() for x in next(inputs.DriftSequence(wl, "cuda:0")))
+    stream = torch.cuda.current_stream().cuda_stream
+    fields = {"max_steps": 2, "flags": flags, "protect": wl.protect}
+    results = {}
+
+    def call(h, threshold, step):
+        out = torch.full_like(q, float("nan"))
+        la.lite_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), h, threshold, step)
+        return out
+
+    for way, before in (("first", None), ("known empty", -float("inf")), ("nothing marked", -1e30), ("import", 0)):
+        h = la.lite_attn_init_mask(1, heads, tokens, **fields)
+        try:
+            la.lite_attn_set_stream(h, stream)
+            if way == "import":
+                la.lite_attn_mask_import(h, np.zeros(la.lite_attn_mask_words(h), np.uint64), 1)
+            elif before is not None:
+                call(h, before, 0)
+            step = 0 if before is None else 1
+            out = call(h, -1.0, step)
+            st = la.lite_attn_skip_stats(h, step)
+            results[way] = out, la.lite_attn_mask_export(h)
+            marked = int(parity.unpack_mask(results[way][1].reshape(path.rows, path.W), path.Tk).sum())
+            assert st.tiles_skipped_in == 0 and st.tiles_newly_marked == marked > 0, way
+        finally:
+            la.lite_attn_free_mask(h)
+    desc = la.make_desc(1, heads, tokens, **fields)
+    mask = torch.zeros(la.static_mask_words(desc), dtype=torch.int64, device="cuda")
+    out = torch.full_like(q, float("nan"))
+    la.lite_attn_fwd_static(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), desc, mask.data_ptr(), -1.0, stream)
+    torch.cuda.synchronize()
+    results["static"] = out, mask.cpu().numpy().view(np.uint64)
+    first = results.pop("first")
+    assert torch.isfinite(first[0]).all()
+    for way, (o, m) in results.items():
+        assert np.array_equal(m, first[1]), way
+        assert torch.equal(o, first[0]), (way, int((o != first[0]).sum()))
