@@ -270,3 +270,45 @@ def test_empty_mask_however_the_caller_came_by_it(heads, tokens, flags, text, ns
     for way, (o, m) in results.items():
         assert np.array_equal(m, first[1]), way
         assert torch.equal(o, first[0]), (way, int((o != first[0]).sum()))
+
+
+@pytest.mark.parametrize("heads,tokens,flags", [(9, 128 * 58 - 31, 0), (12, 128 * 110 + 5, 2), (7, 128 * 128, 0)])
+def test_later_steps_on_a_mask_known_to_be_empty(heads, tokens, flags):
+    """More rows than run side by side, two dense steps, then steps that mark: the third finds an empty mask without a schedule,
+    cuts the last rows and judges them.  Its bits are those of a new handle's first call; the fourth's those of a call on the
+    imported mask; masks and counters of every step."""
+    from paper_2511_11062_amd import lite_attn as la
+    path = path_of(heads, tokens, flags)
+    assert path.rows > 512 and path.pieces & 15 > 1
+    seq = inputs.DriftSequence(layer(heads, tokens, 0), "cuda:0")
+    data = [tuple(x.contiguous() for x in next(seq)) for _ in range(2)]
+    data = [data[0], data[1], data[0], data[1]]
+    thresholds = [-float("inf"), -float("inf"), -1.0, -0.8]
+    handles = [la.lite_attn_init_mask(1, heads, tokens, max_steps=4, flags=flags) for _ in range(3)]
+    outs, masks = [], []
+
+    def call(h, t, step):
+        out = torch.full_like(data[t][0], float("nan"))
+        la.lite_attn_fwd(*(x.data_ptr() for x in data[t]), out.data_ptr(), h, thresholds[t], step)
+        return out
+
+    try:
+        for h in handles:
+            la.lite_attn_set_stream(h, torch.cuda.current_stream().cuda_stream)
+        for t in range(4):
+            outs.append(call(handles[0], t, t))
+            st = la.lite_attn_skip_stats(handles[0], t)
+            masks.append(la.lite_attn_mask_export(handles[0]))
+            marked = [int(parity.unpack_mask(m.reshape(path.rows, path.W), path.Tk).sum()) for m in masks]
+            before = marked[-2] if t else 0
+            assert st.tiles_skipped_in == before and st.tiles_newly_marked == marked[-1] - before
+            assert torch.isfinite(outs[-1]).all()
+        assert marked[1] == 0 < marked[2] < marked[3]
+        assert torch.equal(call(handles[1], 2, 0), outs[2])
+        assert np.array_equal(la.lite_attn_mask_export(handles[1]), masks[2])
+        la.lite_attn_mask_import(handles[2], masks[2], 3)
+        assert torch.equal(call(handles[2], 3, 3), outs[3])
+        assert np.array_equal(la.lite_attn_mask_export(handles[2]), masks[3])
+    finally:
+        for h in handles:
+            la.lite_attn_free_mask(h)
