@@ -1088,7 +1088,7 @@ __device__ __forceinline__ int places_of(const FwdParams& p, int x, int cut) {
   if (!FEW) return (int)p.xcd_rows[x];
   if (p.rows_total > kSchedRows) return p.per_xcd;
   const int share = (p.rows_total + 7) / 8, extra = cut * (p.cut_pieces - 1);
-  return (p.scheduled ? (int)p.xcd_rows[x] : max(0, min(share, p.rows_total - x * share))) + extra;
+  return (p.scheduled && cut == 0 ? (int)p.xcd_rows[x] : max(0, min(share, p.rows_total - x * share))) + extra;
 }
 constexpr int kPieceShift = 24;  // (there are at most 2^23 rows without lists)
 static_assert(kMaxListless <= 1 << (kPieceShift - 1), "row and piece in one word");
@@ -1104,7 +1104,7 @@ __device__ __forceinline__ int row_at_place(const FwdParams& p, int x, int t, in
   // from the table, or in order, an eighth of the rows to every XCD; of each eighth by number the last `cut` rows in cut_pieces
   // pieces each, of which all but the first end the list, row-fastest
   const int share = (p.rows_total + 7) / 8, rows = places - cut * (p.cut_pieces - 1);
-  if (t < rows) return p.scheduled ? (int)p.slots[(size_t)x * p.per_xcd + t] : x * share + t;
+  if (t < rows) return p.scheduled && cut == 0 ? (int)p.slots[(size_t)x * p.per_xcd + t] : x * share + t;
   const int index = quotient(t - rows, cut), row = x * share + share - cut + t - rows - index * cut;
   return row < p.rows_total ? row | (index + 1) << kPieceShift : -1;
 }
