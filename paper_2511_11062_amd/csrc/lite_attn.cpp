@@ -69,11 +69,11 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
   hipError_t e = hipSuccess;
   // a table of rows comes with its ticket counters cleared; calls without one keep theirs where the table would be
   const bool table = !few || (g.rows > kFewRows && g.rows <= kSchedRows && !a.empty);
-  const bool tickets = g.rows > kFewRows;
+  const bool tickets = g.rows > kFewRows, draws = tickets && (!few || g.Tk >= kDrawTiles);
   if (!few && a.fresh) {
     e = launch_clear(a.bits, (size_t)g.rows * g.W, a.stats_all, a.stat_words, stream);
-  } else if (tickets && !table) {  // (the mask is overwritten; few rows: the fused kernel clears the counters)
-    e = launch_clear(reinterpret_cast<uint64_t*>(slots), 8 * (kTicketWords + kArrivals) / 2, a.stats_all,
+  } else if (tickets && !table && (draws || a.fresh)) {  // (the mask is overwritten; few rows: the kernel clears the counters)
+    e = launch_clear(reinterpret_cast<uint64_t*>(slots), draws ? 8 * (kTicketWords + kArrivals) / 2 : 0, a.stats_all,
                      a.fresh ? a.stat_words : 0, stream);
   }
   if (e != hipSuccess) return e;
@@ -114,6 +114,7 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
   p.slots = slots; p.per_xcd = g.per_xcd; p.xcd_rows = xcd_rows;
   p.tickets = !tickets ? nullptr : table ? slots + g.per_xcd - 1 : slots;
   p.ticket_stride = table ? g.per_xcd : kTicketWords;
+  p.resident = draws ? kResident : kNoDraws;
   p.build_next = a.build_next ? 1 : 0;
   p.diagonal_first = diagonal_first;
   if (few) {

@@ -103,6 +103,7 @@ void cut_last_round(Geometry& g) {
   if (piece_bytes(g) > kMaxSegmentBytes) g.pieces = 0;
 }
 static_assert(400 / 8 <= kArrivals, "a counter for every row that is cut");
+static_assert(6 * 3 >= kDrawTiles, "calls that cut rows clear their counters");
 
 // Few rows: whether calls that mark cut the rows by their live tiles (pick_piece() in lite_attn_kernels.hip) instead of all
 // alike: into at most as many pieces as the chip runs side by side, pairs or, with more rows, single groups.  us per call of a sequence of 3-4 steps (the first is dense), alike -> by live tiles: whole rows, 135 x

@@ -24,6 +24,12 @@ constexpr int kDealtRows = kChunkRows;
 // Workgroups that an XCD holds at once (two per CU): the first round takes the rows that its place in the grid names, later
 // workgroups draw theirs (FwdParams::tickets).
 constexpr int kResident = 64;
+constexpr int kNoDraws = 1 << 30;
+// Rows of fewer tiles than this go by place alone.  us, drawn (and a workgroup for every entry of the table's tail) -> by place: a
+// later step of 1000 rows of 1 tile 38.4 -> 28.3, 4000 x 1 123 -> 96, 2000 x 2 71 -> 55, 4900 x 7 278 -> 258, 33001 x 1 714 ->
+// 629, 80000 x 4 2834 -> 2688; 36000 x 12 2527 -> 2505; drawn / by place, without the tail's workgroups: 1200 x 12 90.2 / 89.8,
+// 12000 x 12 1001 / 988, 8000 x 16 822 / 835, 33600 x 16 2926 / 2946, 7200 x 24 1039 / 1059, 33600 x 24 4105 / 4167.
+constexpr int kDrawTiles = 16;
 constexpr int kTicketWords = 32;  // distance of the counters of an unscheduled call, a cache line
 constexpr int kArrivals = 64;     // arrival counters per XCD, of rows cut alike (cut_rows)
 constexpr int kTableTail = 2 + kArrivals;  // end of an XCD's share of a short rows' schedule table: a flag, those, the ticket
@@ -60,7 +66,9 @@ struct FwdParams {
   int per_xcd;                           //   XCD computes, written by launch_deal_rows; entries >= xcd_rows[xcd] unused
   const uint32_t* xcd_rows;              // [8] rows dealt to each XCD
   uint32_t* tickets;                     // [8] at ticket_stride: rows drawn so far from each XCD's list beyond the first
-  int ticket_stride;                     //   kResident; null: one round of workgroups, each has its place
+  int ticket_stride;                     //   `resident`; null: few rows, each workgroup has its place
+  int resident;                          // places per XCD that go by the grid: kResident, or, where rows are too short to be
+                                         //   drawn, kNoDraws
   // build_next != 0: the epilogue rewrites runs / nruns / live_cnt for the NEXT call from the mask this call leaves;
   // diagonal_first: visiting order of the lists
   int build_next, diagonal_first;

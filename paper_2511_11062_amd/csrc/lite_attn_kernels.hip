@@ -1114,7 +1114,7 @@ __device__ __forceinline__ int row_at_place(const FwdParams& p, int x, int t, in
 // belong to the first round's workgroups, which need no counter.  Ends: a draw that fails has found its list used up, which
 // it then stays.  Why: workgroups go to XCDs by id, but equal lists do not end together, because the XCDs' clocks differ (a
 // tile took 3.2 us on the fastest, 3.6 on the slowest, the same ones in every kernel of a session; lists of the 12-head
-// dense step ended between 5.14 and 5.68 ms).  A row drawn costs a counter's round trip (0.35 us).  Lists by place -> drawn:
+// dense step ended between 5.14 and 5.68 ms).  A row drawn costs a counter's round trip (0.35 us; kDrawTiles).  Lists by place -> drawn:
 // 40 heads x 591 tiles, dense + sparse step, 170.7 -> 164.8 ms; 24 x 931 253.8 -> 245.4; a sparse step of 12 x 256 2379 ->
 // 2331 us; 12 x 110, diagonal first, four steps 2128 -> 2102; no gain where few rounds of equally long rows leave nothing to
 // draw (12 x 256 dense, six rounds).
@@ -1445,8 +1445,9 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
     int cut = 0;  // rows of each eighth that are cut
     if (FEW && p.cut_rows > 0)
       cut = !p.scheduled || p.slots[(size_t)(xcd + 1) * p.per_xcd - kTableTail] ? p.cut_rows : 0;
-    if (slot < kResident) row = row_at_place<FEW>(p, xcd, slot, cut);
+    if (slot < p.resident) row = row_at_place<FEW>(p, xcd, slot, cut);
     if (row < 0) {
+      if (p.resident == kNoDraws) return;
       int* told = reinterpret_cast<int*>(smem + (PAIR ? kPairFlagsOff : kFlagsOff));
       if (tid == 0) *told = draw_row<FEW>(p, xcd, cut);
       __syncthreads();
@@ -2220,14 +2221,18 @@ hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int Tk, int W, i
 }
 
 hipError_t launch_fwd(const FwdParams& p, bool immediate, hipStream_t st) {
-  // one workgroup per slot of the schedule table (FEW without a table: per segment or row); those past an XCD's last row
-  // return at once
-  const bool in_order = p.nseg > 0 && !p.scheduled && p.rows_total <= kSchedRows;
-  const int alike = p.rows_total * p.nseg * p.equal_pieces;
-  const int places = (!in_order ? p.per_xcd : (std::max(alike, p.piece_units) + 7) / 8) +
-                     p.cut_rows * (p.cut_pieces - 1);
-  // with tickets an XCD may come to more rows than its list has
-  const dim3 grid(8 * (p.tickets && !(p.nseg > 0 && p.scheduled) ? places + places / 8 + 8 : places)), block(Geo<kQB>::kThreads);
+  // Workgroups per XCD: one for every segment, piece or row of its share, in order; one for every entry of its list, where these
+  // go by place (those past the last row return at once); where rows are drawn, of its share and an eighth more, as an XCD may
+  // come to more rows than its list has: not for every entry of a table that has room for unequal lists, since a workgroup that
+  // draws in vain costs a counter's round trip too (a later step of 1200 rows x 12 tiles 96 -> 90 us, 8000 x 16 839 -> 822).
+  const bool draws = p.tickets && p.resident == kResident, table = p.nseg > 0 && p.scheduled;
+  const int rows = (p.rows_total + 7) / 8;
+  int places = p.per_xcd;
+  if (p.nseg > 0 && !p.tickets)
+    places = (std::max(p.rows_total * p.nseg * p.equal_pieces, p.piece_units) + 7) / 8;
+  else if (p.nseg > 0 && p.rows_total <= kSchedRows)
+    places = !table || draws ? rows + p.cut_rows * (p.cut_pieces - 1) : p.per_xcd - kTableTail;
+  const dim3 grid(8 * (draws ? places + places / 8 + 8 : places)), block(Geo<kQB>::kThreads);
   if (p.nseg == 0) {
     if (immediate)
       hipLaunchKernelGGL((lite_attn_fwd_kernel<1, true, false, false>), grid, block, kLdsBytes, st, p);

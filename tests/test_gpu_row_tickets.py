@@ -10,9 +10,10 @@ pytestmark = pytest.mark.gpu
 
 
 # one row beyond the few; lists a row longer than the first round, and of unequal lengths; an XCD (or four) without any chunk of
-# rows, with one that is not full; more rows than are scheduled (their last chunks have places without rows)
+# rows, with one that is not full; more rows than are scheduled (their last chunks have places without rows); rows too short to
+# be drawn, which go by place (up to 15 tiles)
 @pytest.mark.parametrize("heads,tiles", [(513, 1), (521, 1), (27, 19), (40, 64), (3, 193), (1, 600), (9, 200), (33001, 1),
-                                         (4681, 7)])
+                                         (4681, 7), (2053, 16)])
 def test_every_row_once_call_after_call(heads, tiles):
     """Scores of zero: a row's output is the mean of the values of its live tiles, each of them one number.  The counters of a
     call add up over its rows, so a row computed twice, or not at all, shows there too."""
