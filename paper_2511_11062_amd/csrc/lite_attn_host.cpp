@@ -79,7 +79,8 @@ void share_chip(Geometry& g, int flags) {
   }
 }
 
-// Partial results and row maxima of rows cut into pieces.
+// Partial results and row maxima of rows cut into pieces.  (For no layer more than kMaxSegmentBytes, nor with the lists more than
+// LITE_ATTN_STATIC_SCRATCH_BYTES: few rows have few tiles each, and of more rows only those beyond whole rounds are cut.)
 size_t piece_count(const Geometry& g) {
   return g.rows > kFewRows ? 8 * (size_t)cut_rows(g) * cut_pieces(g) : std::max<size_t>(g.pieces, g.rows * equal_pieces(g));
 }
@@ -100,7 +101,6 @@ void cut_last_round(Geometry& g) {
   const int each = rest <= 128 ? 4 : rest <= 320 ? 3 : rest <= 400 && g.Tk >= 60 && g.rows < 3 * kFewRows ? 2 : 1;
   if (rest == 0 || each == 1 || g.Tk < 6 * each) return;
   g.pieces = (rest + 7) / 8 << 4 | each;
-  if (piece_bytes(g) > kMaxSegmentBytes) g.pieces = 0;
 }
 static_assert(400 / 8 <= kArrivals, "a counter for every row that is cut");
 static_assert(6 * 3 >= kDrawTiles, "calls that cut rows clear their counters");
@@ -121,7 +121,6 @@ void allow_pieces(Geometry& g, const lite_attn_desc_t& d) {
   const int room = pairs ? kPairWorkgroups : kFewRows;
   if (10 * g.rows > 7 * room) return;
   g.pieces = room;
-  if (piece_bytes(g) > kMaxSegmentBytes) g.pieces = 0;
 }
 }  // namespace
 

@@ -47,10 +47,8 @@ extern "C" int lite_attn_fwd_static(const void* q, const void* k, const void* v,
   rc = la::check_call(q, k, v, out, threshold);
   if (rc != LITE_ATTN_OK) return rc;
   if (!dev_skip_mask || ((uintptr_t)dev_skip_mask & 7)) return LITE_ATTN_EINVAL;
-  la::Geometry geo = la::geometry(*desc);
+  const la::Geometry geo = la::geometry(*desc);
   const la::ListLayout ll = la::list_layout(geo);  // the lists first, V^T behind them
-  if (geo.rows > la::kFewRows && ll.total + la::scratch_layout(geo).total > (size_t)LITE_ATTN_STATIC_SCRATCH_BYTES)
-    geo.pieces = 0;  // rows stay whole where their pieces would not fit
   if (ll.total + la::scratch_layout(geo).total > (size_t)LITE_ATTN_STATIC_SCRATCH_BYTES) return LITE_ATTN_ESCRATCH;
   char* ptr = nullptr;
   rc = scratch_of_current_device(&ptr);
