@@ -3,6 +3,8 @@
 // whether the host code handed it buffers of the right size (scratch layout, mask and statistics allocations).
 #include <string.h>
 
+#include <algorithm>
+
 #include "lite_attn_kernels.h"
 
 namespace {
@@ -25,7 +27,7 @@ hipError_t launch_clear(uint64_t* bits, size_t words, unsigned long long* stats,
 hipError_t launch_count_rows(const uint64_t* bits, int rows, int, int W, uint32_t* live, uint32_t* arrive, hipStream_t) {
   uint64_t any = 0;
   for (size_t x = 0; x < (size_t)rows * W; ++x) any |= bits[x];
-  for (int r = 0; r < rows; ++r) live[r] = any ? 1 : 2;
+  for (int r = 0; r < rows; ++r) live[r] = any ? 1 : 0;
   if (arrive) memset(arrive, 0, sizeof(uint32_t) * rows);
   return hipSuccess;
 }
@@ -79,21 +81,49 @@ hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int, int W, int 
 
 namespace {
 
-// Few or short rows: no lists and no V^T.  Rows cut into segments leave partial results in the scratch, for the merge pass
-// behind the fused kernel; at step 0 the mask is overwritten and, with segments, all counters are cleared.
+// Partial results of `parts` segments or pieces and the row maxima of `rows` rows, each before the next.
+bool partials(const FwdParams& p, size_t parts, size_t rows) {
+  if (!before(p.seg_o + parts * 128 * 128, p.seg_stat) || !before(p.seg_stat + parts * 2 * 128, p.seg_mloc)) return false;
+  memset(p.seg_o, 0, sizeof(float) * parts * 128 * 128);
+  memset(p.seg_stat, 0, sizeof(float) * parts * 2 * 128);
+  memset(p.seg_mloc, 0, sizeof(float) * rows * p.Tk * 128);
+  return true;
+}
+
+// Few or short rows: no lists and no V^T.  Rows that several workgroups share leave partial results in the scratch; rows beyond
+// the first round are drawn; at step 0 the mask is overwritten and, with few rows, all counters are cleared.
 hipError_t fwd_without_lists(const FwdParams& p) {
   const size_t rows = (size_t)p.rows_total;
   volatile uint32_t sink = 0;
   if (p.scheduled) sink = p.slots[8 * (size_t)p.per_xcd - 1] + p.xcd_rows[7];
   (void)sink;
-  if (p.nseg > 1) {
-    if (!before(p.seg_o + rows * p.nseg * 128 * 128, p.seg_stat) ||
-        !before(p.seg_stat + rows * p.nseg * 2 * 128, p.seg_mloc))
-      return hipErrorInvalidValue;
-    memset(p.seg_o, 0, sizeof(float) * rows * p.nseg * 128 * 128);
-    memset(p.seg_stat, 0, sizeof(float) * rows * p.nseg * 2 * 128);
-    memset(p.seg_mloc, 0, sizeof(float) * rows * p.Tk * 128);
-    if (p.fresh) memset(p.stats_all, 0, sizeof(unsigned long long) * (size_t)p.stat_words);
+  if (p.tickets && p.resident == kResident)  // counters start at zero
+    for (int x = 0; x < 8; ++x)
+      if (!before(p.tickets + x * p.ticket_stride + 1, p.xcd_rows) || p.tickets[x * p.ticket_stride]++ != 0)
+        return hipErrorInvalidValue;
+  if (p.nseg > 1 && !partials(p, rows * p.nseg, rows)) return hipErrorInvalidValue;
+  if (p.piece_units > 0) {
+    if (!partials(p, std::max<size_t>(p.piece_units, rows * p.equal_pieces), rows)) return hipErrorInvalidValue;
+    for (size_t r = 0; r < rows; ++r)  // arrivals start at zero and are zero again behind the call
+      if (p.arrive[r] != 0 || (int)p.live_rows[r] > p.Tk) return hipErrorInvalidValue;
+  }
+  if (p.cut_rows > 0) {
+    const size_t cut = 8 * (size_t)p.cut_rows;
+    if (!partials(p, cut * p.cut_pieces, cut)) return hipErrorInvalidValue;
+    for (int x = 0; x < 8; ++x)
+      for (int r = 0; r < p.cut_rows; ++r) {
+        uint32_t* at = p.arrive + x * p.arrive_stride + r;
+        // (not the ticket, which the loop above has moved)
+        if (!before(at + 1, p.xcd_rows) || *at != 0) return hipErrorInvalidValue;
+      }
+  }
+  if (p.fresh && p.newly_rows) {
+    memset(p.stats_all, 0, sizeof(unsigned long long) * (size_t)p.stat_words);
+    memset(p.newly_rows, 0, sizeof(uint32_t) * rows);
+  }
+  if (p.live_next) {
+    if (p.piece_units > 0 && p.live_next == p.live_rows) return hipErrorInvalidValue;  // (read while it is written)
+    for (size_t r = 0; r < rows; ++r) p.live_next[r] = (uint32_t)p.Tk;
   }
   for (size_t x = 0; x < rows * p.W; ++x) p.bits[x] = p.fresh ? 0 : p.bits[x];
   return hipSuccess;

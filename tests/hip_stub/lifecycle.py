@@ -94,6 +94,9 @@ def exercise(h, heads, n, steps):
     assert lib.lite_attn_mask_import(h, bits.ctypes.data, words, steps) == -2
     back = np.zeros(words, dtype=np.uint64)
     assert lib.lite_attn_mask_export(h, back.ctypes.data, words) == 0 and (back == 5).all()
+    assert lib.lite_attn_fwd(p, p, p, p, h, ctypes.c_float(-1.0), 1) == 0                # on the imported mask
+    assert lib.lite_attn_fwd(p, p, p, p, h, ctypes.c_float(-float("inf")), 0) == 0      # dense, then on a mask known to be empty
+    assert lib.lite_attn_fwd(p, p, p, p, h, ctypes.c_float(-1.0), 1) == 0
     stride = lib.lite_attn_skipruns_stride(h)
     assert stride == tk // 2 + 1
     runs = np.zeros((rows, stride), dtype=np.uint32)
@@ -106,6 +109,8 @@ def exercise(h, heads, n, steps):
 
 
 for heads, n, way in ((1, 1, "in order"), (2, 300, None), (3, 128 * 65 + 7, "in order"), (2, 2048, "segments"),
+                      (9, 128 * 15, "in order"), (10, 128 * 29 + 1, "in order"), (4, 128 * 25, "segments"), (1, 128 * 129, "segments"),
+                      (4, 128 * 87, "segments"), (9, 128 * 58 - 31, "schedule"), (600, 300, "schedule"), (7, 128 * 128, "schedule"),
                       (16, 128 * 40 - 9, "schedule"), (3, 128 * 193, "lists"), (33000, 3, "dealt")):
     for flags in (0, 1, 2, 3):
         assert way is None or flags & 1 or path(heads, n, flags) == way, (heads, n, path(heads, n, flags))
