@@ -32,7 +32,8 @@ struct lite_attn_mask {
   char* d_lists;      // Skip-Lists and row ranking (layout ll); kept between calls
   bool lists_valid;   // the lists describe the mask as it stands (left by the previous call's epilogue)
   unsigned long long* d_stats;  // [max_steps][3]: skipped on entry, newly marked, Skip-List runs
-  uint32_t* d_newly;            // few rows: [kFewRows] tiles that step 0 marked, per row (part of step 0's newly marked)
+  uint32_t* d_newly;            // few rows, behind them: [kFewRows] tiles that step 0 marked, per row (part of step 0's newly
+                                //   marked)
   uint32_t* d_arrive;           // behind it, [kFewRows] arrivals of rows cut into pieces, zero between calls; behind them
                                 //   [2][kFewRows] live tiles of the rows (live_rows())
   bool empty;                   // nothing can have marked a tile since step 0
@@ -226,6 +227,7 @@ int init_common(const lite_attn_desc_t* desc, lite_attn_ctx* ctx, lite_attn_mask
   m->d_arrive = nullptr;
   m->empty = false;
   const size_t words = (size_t)m->geo.rows * m->geo.W, nstats = 3 * (size_t)desc->max_steps;
+  const size_t counters = m->geo.rows <= la::kFewRows ? 4 * la::kFewRows * sizeof(uint32_t) / sizeof(unsigned long long) : 0;
   const size_t need = la::scratch_layout(m->geo).total;
   hipStream_t st = ctx ? ctx->stream : nullptr;
   rc = LITE_ATTN_OK;
@@ -238,16 +240,13 @@ int init_common(const lite_attn_desc_t* desc, lite_attn_ctx* ctx, lite_attn_mask
   }
   if (rc == LITE_ATTN_OK) {
     hipError_t e = hipMalloc(&m->d_bits, sizeof(uint64_t) * words);
-    if (e == hipSuccess) e = hipMalloc(&m->d_stats, sizeof(unsigned long long) * nstats);
+    if (e == hipSuccess) e = hipMalloc(&m->d_stats, sizeof(unsigned long long) * (nstats + counters));
     if (e == hipSuccess) e = hipMalloc(&m->d_lists, m->ll.total);
     if (e == hipSuccess) e = la::prepare_fwd();
-    if (e == hipSuccess) e = la::launch_clear(m->d_bits, words, m->d_stats, nstats, st);
-    if (e == hipSuccess && m->geo.rows <= la::kFewRows) {
-      uint32_t* counters = nullptr;
-      e = hipMalloc(&counters, sizeof(uint32_t) * 4 * la::kFewRows);
-      m->d_newly = counters;
-      m->d_arrive = counters ? counters + la::kFewRows : nullptr;
-      if (e == hipSuccess) e = la::launch_clear(reinterpret_cast<uint64_t*>(counters), 2 * la::kFewRows, m->d_stats, 0, st);
+    if (e == hipSuccess) e = la::launch_clear(m->d_bits, words, m->d_stats, nstats + counters, st);
+    if (e == hipSuccess && counters) {
+      m->d_newly = reinterpret_cast<uint32_t*>(m->d_stats + nstats);
+      m->d_arrive = m->d_newly + la::kFewRows;
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) rc = hip_fail(e);
@@ -477,7 +476,6 @@ void lite_attn_free_mask(lite_attn_mask_t* m) {
   }
   if (m->d_bits) (void)hipFree(m->d_bits);
   if (m->d_stats) (void)hipFree(m->d_stats);
-  if (m->d_newly) (void)hipFree(m->d_newly);
   if (m->d_lists) (void)hipFree(m->d_lists);
   if (m->own.base) (void)hipFree(m->own.base);
   if (m->events) {
