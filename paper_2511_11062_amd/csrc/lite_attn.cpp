@@ -157,7 +157,12 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     p.stats_all = a.stats_all;
     p.newly_rows = a.newly_rows;
     p.live_next = a.live_next;
-    p.stat_words = (int)a.stat_words;
+    p.stat_words = (int64_t)a.stat_words;
+    if (a.fresh && a.newly_rows && p.stat_words > (int64_t)kClearWords * 256 * p.rows_total * p.nseg) {
+      e = launch_clear(a.bits, 0, a.stats_all, a.stat_words, stream);
+      if (e != hipSuccess) return e;
+      p.stat_words = 3;  // (step 0's, which do not start at zero)
+    }
     // nothing to schedule where all workgroups start together or all rows are equally long; beyond kSchedRows rows the kernel
     // deals chunks of them in turn
     if (table) {

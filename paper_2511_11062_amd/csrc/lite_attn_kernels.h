@@ -34,6 +34,7 @@ constexpr int kTicketWords = 32;  // distance of the counters of an unscheduled 
 constexpr int kArrivals = 64;     // arrival counters per XCD, of rows cut alike (cut_rows)
 constexpr int kTableTail = 2 + kArrivals;  // end of an XCD's share of a short rows' schedule table: a flag, those, the ticket
 constexpr int kPairWorkgroups = 256;
+constexpr int kClearWords = 64;   // us, 3 rows x 1 tile, 64 for each thread 9.6 (a launch: 8.9), 4096 for each 174 (12.1)
 constexpr int kMaxSegments = 16;
 constexpr int kMaxPieces = 4;
 constexpr size_t kMaxSegmentBytes = (size_t)104 << 20;
@@ -84,7 +85,7 @@ struct FwdParams {
   float* seg_stat = nullptr;             // [rows][nseg][2][128]: row maximum (the exponents' reference), row sum
   float* seg_mloc = nullptr;             // [rows][Tk][128]: row maxima of the visited tiles
   unsigned long long* stats_all = nullptr;  // all counters of the handle (stat_words of them)
-  int stat_words = 0;
+  int64_t stat_words = 0;
   // > 0: the rows are cut into pieces by their live tiles, at most this many altogether (pick_piece).  Their partial results are
   // in seg_o and seg_stat, by piece, the row maxima in seg_mloc.
   int piece_units = 0;

@@ -1144,12 +1144,13 @@ __device__ __forceinline__ int draw_row(const FwdParams& p, int home, int cut) {
 typedef const __attribute__((address_space(4))) FwdParams* const_params_ptr;
 typedef const __attribute__((address_space(4))) FwdParams& ParamsRef;
 
-// Step 0 of a call with few rows, by one workgroup: nothing was skipped on entry, a row is one run (two, if its visit starts at
-// a diagonal tile that is not the first), what the rows mark goes to newly_rows; the later steps' counters start at zero.  The
-// launch that cleared them before the kernel cost 1.5-3.4 us (one call of 2 rows x 1 tile 8.1 -> 6.7 us, 32 x 4 14.7 -> 12.5,
-// 120 x 2 12.8 -> 9.4).
-__device__ __forceinline__ void clear_counters(const FwdParams& p, int tid, int threads) {
-  for (int x = tid; x < p.stat_words; x += threads)
+// Step 0 of a call with few rows: nothing was skipped on entry, a row is one run (two, if its visit starts at a diagonal tile
+// that is not the first), what the rows mark goes to newly_rows; the later steps' counters start at zero.  The launch that
+// cleared them before the kernel cost 1.5-3.4 us (one call of 2 rows x 1 tile 8.1 -> 6.7 us, 32 x 4 14.7 -> 12.5, 120 x 2 12.8 ->
+// 9.4).  All the call's threads share it (by one workgroup's, counters of 16384 steps held up a call of 135 x 15 from 31.3 to
+// 35.5 us); more than kClearWords for each of them are cleared by a launch beforehand all the same.
+__device__ __forceinline__ void clear_counters(const FwdParams& p, int thread, int threads) {
+  for (int64_t x = thread; x < p.stat_words; x += threads)
     p.stats_all[x] = x == 2 ? (unsigned long long)(p.rows_total + (p.diagonal_first ? p.rows_total - p.rows_total / p.Tq : 0)) : 0ull;
 }
 
@@ -1512,7 +1513,8 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
     walk.count(cnt, nruns);
     t_lo = segment_start(cnt, seg, p.nseg * pieces);
     t_hi = segment_start(cnt, seg + 1, p.nseg * pieces);
-    if (p.fresh && p.newly_rows && blockIdx.x == 0) clear_counters(p, tid, kThreads);
+    if (p.fresh && p.newly_rows)
+      clear_counters(p, ((bh * p.nseg + seg) * p.Tq + i) * kThreads + tid, p.rows_total * p.nseg * kThreads);
   } else {
     cnt = (int)p.live_cnt[row];
     nruns = (int)p.nruns[row];

@@ -42,3 +42,26 @@ def test_second_trajectory_counts_like_the_first(heads, tokens, flags):
             assert skipped > 0
     finally:
         la.lite_attn_free_mask(h)
+
+
+@pytest.mark.parametrize("heads,tokens,max_steps", [(2, 300, 700), (1, 128 * 16, 700), (1, 200, 1 << 20)])
+def test_counters_of_many_steps(heads, tokens, max_steps):
+    """More counters than a workgroup has threads: every step of a second trajectory counts as in the first."""
+    from paper_2511_11062_amd import lite_attn as la
+    steps = 700                                                # (2^20: cleared by a launch)
+    path = parity.path_of(1, heads, tokens)
+    wl = inputs.Workload("counters", 1, heads, (1, 1, tokens), steps=1, seed=12)
+    q, k, v = (x.to("cuda:0").contiguous() for x in next(inputs.DriftSequence(wl, "cuda:0")))
+    out = torch.empty_like(q)
+    h = la.lite_attn_init_mask(1, heads, tokens, max_steps=max_steps)
+    la.lite_attn_set_stream(h, torch.cuda.current_stream().cuda_stream)
+    try:
+        for trajectory in range(2):
+            for t in range(steps):
+                la.lite_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), h, -0.5, t)
+            stats = [la.lite_attn_skip_stats(h, t) for t in range(steps)]
+            marked = stats[0].tiles_newly_marked
+            assert all(st.tiles_skipped_in == marked and st.tiles_newly_marked == 0 for st in stats[1:])
+            assert len({st.live_list_bytes for st in stats[1:]}) == 1 and stats[0].live_list_bytes == 4 * path.rows
+    finally:
+        la.lite_attn_free_mask(h)
