@@ -127,7 +127,12 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     if (g.pieces > 0 && g.rows <= kFewRows && a.threshold > -INFINITY) {
       p.pair = g.pieces == kPairWorkgroups ? 1 : 0;
       p.nseg = equal_pieces(g);
-      if (!a.empty) {  // pieces by the rows' live tiles, or, where these turn out to be all, the same number of each
+      // Pieces by the rows' live tiles, or, where these turn out to be all, the same number of each.  Where they are known to be
+      // all, segments and merge pass unless the pieces run in one round and have few row maxima to walk: us, step 0, merge pass
+      // -> last piece, 80 x 16 27.4 -> 25.1, 120 x 20 36.4 -> 33.5, 105 x 35 46.8 -> 46.1; 128 x 64 80.8 -> 81.0, 99 x 99 102.1 ->
+      // 103.0; in two rounds 344 x 86 258 -> 295, as the second's workgroups then meet in pairs on the CUs that end first.
+      if (!a.empty || (p.nseg > 1 && g.rows * p.nseg <= g.pieces && g.Tk < 64)) {
+        p.alike = a.empty ? 1 : 0;
         p.equal_pieces = p.nseg;
         p.nseg = 1;
         p.piece_units = g.pieces;
@@ -158,7 +163,7 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     p.newly_rows = a.newly_rows;
     p.live_next = a.live_next;
     p.stat_words = (int64_t)a.stat_words;
-    if (a.fresh && a.newly_rows && p.stat_words > (int64_t)kClearWords * 256 * p.rows_total * p.nseg) {
+    if (a.fresh && a.newly_rows && p.stat_words > (int64_t)kClearWords * 256 * p.rows_total * p.nseg * p.equal_pieces) {
       e = launch_clear(a.bits, 0, a.stats_all, a.stat_words, stream);
       if (e != hipSuccess) return e;
       p.stat_words = 3;  // (step 0's, which do not start at zero)

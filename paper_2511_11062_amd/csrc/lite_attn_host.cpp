@@ -127,8 +127,8 @@ void allow_pieces(Geometry& g, const lite_attn_desc_t& d) {
 // Few rows that may be cut into pieces: how many of each a call that marks makes where the mask is empty, whether the caller
 // knows it (segments and merge pass) or the counts say so (pieces; the same sums in the same order).  As many as share_chip()
 // finds, if that is for the same kind of workgroups; else as many as fill one round of pairs, or, with more than half as many
-// rows as that, three in two rounds.  us, step 0, share_chip()'s single groups -> pairs: 80 x 20 31.9 -> 30.1, 100 x 25 41.7 ->
-// 38.3, 105 x 35 47.1 -> 48.6, 128 x 64 80.3 -> 82.0, 99 x 99 95.7 -> 102.2, 130 x 65 90.1 -> 101.7, 150 x 150 197.3 -> 208.8:
+// rows as that, three in two rounds.  us, step 0, share_chip()'s single groups -> pairs: 80 x 20 27.9 -> 27.3, 100 x 25 39.4 ->
+// 36.3, 105 x 35 46.4 -> 46.1, 128 x 64 80.4 -> 80.8, 99 x 99 96.3 -> 102.1, 130 x 65 90.4 -> 101.8, 150 x 150 199.8 -> 211.3:
 // what it costs that a mask's pieces are pairs, and that a call's result depends on its inputs and its mask, not on how the
 // caller came by them.
 int equal_pieces(const Geometry& g) {

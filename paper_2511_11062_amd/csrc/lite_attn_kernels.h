@@ -90,6 +90,7 @@ struct FwdParams {
   // in seg_o and seg_stat, by piece, the row maxima in seg_mloc.
   int piece_units = 0;
   int equal_pieces = 1;                  //   where their lengths do not ask for another cut: into this many each
+  int alike = 0;                         //   (which the caller knows: alike != 0)
   int cut_rows = 0, cut_pieces = 1;      // more than kFewRows rows: of each eighth, by number, the last cut_rows are cut alike if
                                          //   the mask is empty (no schedule, or its flag says so)
   uint32_t* arrive = nullptr;            // pieces that have arrived: [rows], zero between calls, or [8] at arrive_stride

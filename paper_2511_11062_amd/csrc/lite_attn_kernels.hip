@@ -1418,7 +1418,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   int pieces = 1, piece = 0;  // a row cut into pieces (pick_piece): how many, and the first one's partial result
   if (FEW && !p.tickets) {
     Piece mine = {kAlike, 0, 1, 0};
-    if (p.piece_units) {
+    if (p.piece_units && !p.alike) {
       uint16_t* counts = reinterpret_cast<uint16_t*>(smem + (PAIR ? kPairXchOff : kFiredOff));
       mine = pick_piece<IMM>(p, counts, xcd, slot, tid, kThreads);
       if (mine.row == -1) return;
@@ -1513,8 +1513,10 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
     walk.count(cnt, nruns);
     t_lo = segment_start(cnt, seg, p.nseg * pieces);
     t_hi = segment_start(cnt, seg + 1, p.nseg * pieces);
-    if (p.fresh && p.newly_rows)
-      clear_counters(p, ((bh * p.nseg + seg) * p.Tq + i) * kThreads + tid, p.rows_total * p.nseg * kThreads);
+    if (p.fresh && p.newly_rows) {
+      const int n = p.nseg * p.equal_pieces;
+      clear_counters(p, ((bh * n + seg) * p.Tq + i) * kThreads + tid, p.rows_total * n * kThreads);
+    }
   } else {
     cnt = (int)p.live_cnt[row];
     nruns = (int)p.nruns[row];
