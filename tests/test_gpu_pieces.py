@@ -312,3 +312,56 @@ def test_later_steps_on_a_mask_known_to_be_empty(heads, tokens, flags):
     finally:
         for h in handles:
             la.lite_attn_free_mask(h)
+
+
+# more equal pieces than four, and more of them than run side by side: pairs (three of each row), single groups (three, four, five)
+@pytest.mark.parametrize("heads,tokens,equal", [(1, 128 * 129 + 7, 3), (5, 128 * 60 - 1, 3), (4, 128 * 87, 4), (1, 128 * 202 - 64, 5)])
+def test_rows_cut_alike_under_a_mask(heads, tokens, equal):
+    """15 % of every row's tiles skipped, which leaves no room for pieces of the rows' own: outputs against block-masked softmax
+    in fp32, marks against the predicate, whose running maximum goes through all pieces; twice with the same bits."""
+    from paper_2511_11062_amd import lite_attn as la
+    path = path_of(heads, tokens)
+    tiles, thr = path.Tk, -1.0
+    assert path.pieces > 0 and heads * tiles * equal > path.pieces
+    rng = np.random.default_rng(tokens)
+    skip = rng.random((heads, tiles, tiles)) < 0.15
+    g = torch.Generator(device="cuda").manual_seed(tokens)
+    q, k, v = (torch.randn(1, heads, tokens, 128, device="cuda", generator=g) for _ in range(3))
+    # tiles of keys that lie far off for all queries, so that some fire
+    far = torch.from_numpy(rng.random(tiles) < 0.3).cuda().repeat_interleave(128)[:tokens]
+    q[..., 0], k[..., 0] = 4.0, torch.where(far, -12.0, 2.0)
+    q, k, v = (x.to(torch.bfloat16).contiguous() for x in (q, k, v))
+    packed = parity.pack_mask(skip.astype(np.uint8))
+    h = la.lite_attn_init_mask(1, heads, tokens, max_steps=2)
+    la.lite_attn_set_stream(h, torch.cuda.current_stream().cuda_stream)
+    outs, masks = [], []
+    try:
+        for _ in range(2):
+            out = torch.full_like(q, float("nan"))
+            la.lite_attn_mask_import(h, packed, 1)
+            la.lite_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), h, thr, 1)
+            masks.append(la.lite_attn_mask_export(h))
+            outs.append(out)
+    finally:
+        la.lite_attn_free_mask(h)
+    assert torch.equal(outs[0], outs[1]) and np.array_equal(masks[0], masks[1])
+    marked = torch.from_numpy(parity.unpack_mask(masks[0].reshape(heads, tiles, path.W), tiles)).cuda().bool()
+    dead = torch.from_numpy(skip).cuda()
+    assert bool((marked | ~dead).all()) and int((marked & ~dead).sum()) > 50 * heads
+    for x in range(heads):
+        kf, vf = k[0, x].float().t().contiguous(), v[0, x].float()
+        for i0 in range(0, tiles, 32):
+            n, r0, r1 = min(32, tiles - i0), 128 * i0, min(tokens, 128 * (i0 + 32))
+            s = torch.full((128 * n, 128 * tiles), -float("inf"), device="cuda")
+            s[:r1 - r0, :tokens] = (q[0, x, r0:r1].float() @ kf) * 128 ** -0.5
+            s4 = s.view(n, 128, tiles, 128).masked_fill_(dead[x, i0:i0 + n][:, None, :, None], -float("inf"))
+            mloc = s4.amax(dim=3)
+            gap = mloc - mloc.cummax(dim=2).values                               # NaN where nothing has been visited yet
+            gap[(torch.arange(128 * n, device="cuda") + r0 >= tokens).view(n, 128)] = -float("inf")
+            worst = gap.amax(dim=1)
+            here, gone = marked[x, i0:i0 + n], dead[x, i0:i0 + n]
+            clear = ~gone & ((worst - thr).abs() > parity.G_BAND)
+            assert torch.equal(here[clear], worst[clear] <= thr)
+            ref = torch.softmax(s[:r1 - r0], dim=1)[:, :tokens] @ vf
+            # weights and result are rounded to bf16 (2^-9 each) of values up to max|O|
+            assert (outs[0][0, x, r0:r1].float() - ref).abs().max().item() <= 1e-2 * ref.abs().max().item()
