@@ -1197,7 +1197,7 @@ __device__ __forceinline__ void merge_pieces(State<QB, IMM>& st, ParamsRef p, fl
     l[s] = stat(min(s, pieces - 1), 1);
     top = fmaxf(top, m[s]);
   }
-  for (int s = kMaxPieces; s < pieces; ++s) top = fmaxf(top, stat(s, 0));  // (rows cut alike)
+  for (int s = kMaxPieces; !IMM && s < pieces; ++s) top = fmaxf(top, stat(s, 0));  // (rows cut alike)
 #pragma unroll
   for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -1229,7 +1229,7 @@ __device__ __forceinline__ void merge_pieces(State<QB, IMM>& st, ParamsRef p, fl
     if (s0 >= pieces) break;
     add_two(s0, {m[s0], m[s0 + 1]}, {l[s0], l[s0 + 1]});
   }
-  for (int s0 = kMaxPieces; s0 < pieces; s0 += 2) {
+  for (int s0 = kMaxPieces; !IMM && s0 < pieces; s0 += 2) {
     const int s1 = min(s0 + 1, pieces - 1);
     add_two(s0, {stat(s0, 0), stat(s1, 0)}, {stat(s0, 1), stat(s1, 1)});
   }
@@ -1374,9 +1374,10 @@ __device__ __forceinline__ Piece pick_piece(const FwdParams& p, uint16_t* counts
     g = max(g + 1, quotient(g * total, p.piece_units));
     if (4 * g > 3 * longest) g = longest;  // not worth the merging
   }
-  // (a piece costs about two tiles' time besides its own)
-  const int rounds = quotient(rows * p.equal_pieces + p.piece_units - 1, p.piece_units);
-  if (p.equal_pieces > 1 && g > rounds * (quotient(longest + p.equal_pieces - 1, p.equal_pieces) + 2)) return {kAlike, 0, 1, 0};
+  if constexpr (!IMM) {  // (a piece costs about two tiles' time besides its own)
+    const int rounds = quotient(rows * p.equal_pieces + p.piece_units - 1, p.piece_units);
+    if (p.equal_pieces > 1 && g > rounds * (quotient(longest + p.equal_pieces - 1, p.equal_pieces) + 2)) return {kAlike, 0, 1, 0};
+  }
   Piece out = {-1, 0, 1, 0};
   const int share = (total + 7) / 8, unit = xcd * share + slot;
   if (slot >= share || unit >= total) return out;
@@ -1416,22 +1417,18 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   int row = -1, i, bh, seg = 0;
   int pieces = 1, piece = 0;  // a row cut into pieces (pick_piece): how many, and the first one's partial result
+  if (FEW && !p.tickets && p.piece_units && !p.alike) {
+    uint16_t* counts = reinterpret_cast<uint16_t*>(smem + (PAIR ? kPairXchOff : kFiredOff));
+    const Piece mine = pick_piece<IMM>(p, counts, xcd, slot, tid, kThreads);
+    if (mine.row == -1) return;
+    row = mine.row;
+    seg = mine.index;
+    pieces = mine.pieces;
+    piece = mine.first;
+  }
   if (FEW && !p.tickets) {
-    Piece mine = {kAlike, 0, 1, 0};
-    if (p.piece_units && !p.alike) {
-      uint16_t* counts = reinterpret_cast<uint16_t*>(smem + (PAIR ? kPairXchOff : kFiredOff));
-      mine = pick_piece<IMM>(p, counts, xcd, slot, tid, kThreads);
-      if (mine.row == -1) return;
-    }
-    if (mine.row >= 0) {
-      row = mine.row;
-      seg = mine.index;
-      pieces = mine.pieces;
-      piece = mine.first;
-      bh = quotient(row, p.Tq);
-      i = row - bh * p.Tq;
-    } else {  // all rows alike: segments, or as many pieces
-      const int n = p.nseg * p.equal_pieces, units = p.rows_total * n, share = (units + 7) / 8;
+    if (row < 0) {  // all rows alike: segments, or as many pieces
+      const int n = IMM ? 1 : p.nseg * p.equal_pieces, units = p.rows_total * n, share = (units + 7) / 8;
       const int unit = xcd * share + slot;
       if (slot >= share || unit >= units) return;
       const int u = quotient(unit, p.Tq);
@@ -1439,8 +1436,13 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
       seg = u - bh * n;
       i = unit - u * p.Tq;
       row = bh * p.Tq + i;
-      pieces = p.equal_pieces;
-      piece = row * pieces;
+      if constexpr (!IMM) {
+        pieces = p.equal_pieces;
+        piece = row * pieces;
+      }
+    } else {
+      bh = quotient(row, p.Tq);
+      i = row - bh * p.Tq;
     }
   } else {
     int cut = 0;  // rows of each eighth that are cut
@@ -1514,7 +1516,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
     t_lo = segment_start(cnt, seg, p.nseg * pieces);
     t_hi = segment_start(cnt, seg + 1, p.nseg * pieces);
     if (p.fresh && p.newly_rows) {
-      const int n = p.nseg * p.equal_pieces;
+      const int n = IMM ? 1 : p.nseg * p.equal_pieces;
       clear_counters(p, ((bh * n + seg) * p.Tq + i) * kThreads + tid, p.rows_total * n * kThreads);
     }
   } else {
