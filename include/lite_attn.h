@@ -168,8 +168,8 @@ int lite_attn_skip_stats(lite_attn_mask_t* mask, int step, lite_attn_stats_t* ho
    stream around its two phases (events are created on the first enabled call; a few microseconds per call).
    lite_attn_kernel_times returns the durations of a completed step in milliseconds -- host_prep_ms: what runs
    before the attention kernel (clearing, Skip-List compaction, row schedule, V transposition, as far as the call has
-   them); host_fwd_ms: the fused attention kernel and, for rows cut into segments, the pass that merges them -- it synchronises the
-   stream and fails with LITE_ATTN_ESTEP if that step was not run with profiling enabled. */
+   them); host_fwd_ms: the fused attention kernel and, for rows cut into segments, the pass that merges them -- it
+   synchronises the stream and fails with LITE_ATTN_ESTEP if that step was not run with profiling enabled. */
 int lite_attn_profile(lite_attn_mask_t* mask, int enable);
 int lite_attn_kernel_times(lite_attn_mask_t* mask, int step, float* host_prep_ms, float* host_fwd_ms);
 

@@ -32,8 +32,8 @@ struct lite_attn_mask {
   char* d_lists;      // Skip-Lists and row ranking (layout ll); kept between calls
   bool lists_valid;   // the lists describe the mask as it stands (left by the previous call's epilogue)
   unsigned long long* d_stats;  // [max_steps][3]: skipped on entry, newly marked, Skip-List runs
-  uint32_t* d_newly;            // few rows, behind them: [kFewRows] tiles that step 0 marked, per row (part of step 0's newly
-                                //   marked)
+  uint32_t* d_newly;            // few rows, behind them: [kFewRows] tiles that step 0 marked, per row (part of step
+                                //   0's newly marked)
   uint32_t* d_arrive;           // behind it, [kFewRows] arrivals of rows cut into pieces, zero between calls; behind them
                                 //   [2][kFewRows] live tiles of the rows (live_rows())
   bool empty;                   // nothing can have marked a tile since step 0
@@ -73,7 +73,7 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
   const bool tickets = g.rows > kFewRows, draws = tickets && (!few || g.Tk >= kDrawTiles);
   if (!few && a.fresh) {
     e = launch_clear(a.bits, (size_t)g.rows * g.W, a.stats_all, a.stat_words, stream);
-  } else if (tickets && !table && (draws || a.fresh)) {  // (the mask is overwritten; few rows: the kernel clears the counters)
+  } else if (tickets && !table && (draws || a.fresh)) {  // (the mask is overwritten; few rows: the kernel clears)
     e = launch_clear(reinterpret_cast<uint64_t*>(slots), draws ? 8 * (kTicketWords + kArrivals) / 2 : 0, a.stats_all,
                      a.fresh ? a.stat_words : 0, stream);
   }
@@ -127,10 +127,11 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     if (g.pieces > 0 && g.rows <= kFewRows && a.threshold > -INFINITY) {
       p.pair = g.pieces == kPairWorkgroups ? 1 : 0;
       p.nseg = equal_pieces(g);
-      // Pieces by the rows' live tiles, or, where these turn out to be all, the same number of each.  Where they are known to be
-      // all, segments and merge pass unless the pieces run in one round and have few row maxima to walk: us, step 0, merge pass
-      // -> last piece, 80 x 16 27.4 -> 25.1, 120 x 20 36.4 -> 33.5, 105 x 35 46.8 -> 46.1; 128 x 64 80.8 -> 81.0, 99 x 99 102.1 ->
-      // 103.0; in two rounds 344 x 86 258 -> 295, as the second's workgroups then meet in pairs on the CUs that end first.
+      // Pieces by the rows' live tiles, or, where these turn out to be all, the same number of each.  Where they are
+      // known to be all, segments and merge pass unless the pieces run in one round and have few row maxima to walk:
+      // us, step 0, merge pass -> last piece, 80 x 16 27.4 -> 25.1, 120 x 20 36.4 -> 33.5, 105 x 35 46.8 -> 46.1; 128 x
+      // 64 80.8 -> 81.0, 99 x 99 102.1 -> 103.0; in two rounds 344 x 86 258 -> 295, as the second's workgroups then
+      // meet in pairs on the CUs that end first.
       if (!a.empty || (p.nseg > 1 && g.rows * p.nseg <= g.pieces && g.Tk < 64)) {
         p.alike = a.empty ? 1 : 0;
         p.equal_pieces = p.nseg;
@@ -168,8 +169,8 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
       if (e != hipSuccess) return e;
       p.stat_words = 3;  // (step 0's, which do not start at zero)
     }
-    // nothing to schedule where all workgroups start together or all rows are equally long; beyond kSchedRows rows the kernel
-    // deals chunks of them in turn
+    // nothing to schedule where all workgroups start together or all rows are equally long; beyond kSchedRows rows the
+    // kernel deals chunks of them in turn
     if (table) {
       p.scheduled = 1;
       e = launch_schedule_rows(a.bits, (int)g.rows, g.Tk, g.W, g.per_xcd, slots, xcd_rows, stream);
@@ -197,8 +198,8 @@ using la::hip_fail;
 
 hipStream_t stream_of(const lite_attn_mask* m) { return m->ctx ? m->ctx->stream : m->stream; }
 char* scratch_of(const lite_attn_mask* m) { return static_cast<char*>(m->ctx ? m->ctx->scratch.base : m->own.base); }
-// Layers of few rows that may be cut into pieces: the rows' live tiles at the start of `step`, left by the call before or by an
-// import (two sets in turn, as a call reads one while it leaves the other).
+// Layers of few rows that may be cut into pieces: the rows' live tiles at the start of `step`, left by the call before
+// or by an import (two sets in turn, as a call reads one while it leaves the other).
 uint32_t* live_rows(const lite_attn_mask* m, int step) {
   if (m->geo.pieces == 0 || m->geo.rows > la::kFewRows) return nullptr;
   return m->d_arrive + (1 + (step & 1)) * la::kFewRows;

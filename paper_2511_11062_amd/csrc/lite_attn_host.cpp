@@ -79,8 +79,9 @@ void share_chip(Geometry& g, int flags) {
   }
 }
 
-// Partial results and row maxima of rows cut into pieces.  (For no layer more than kMaxSegmentBytes, nor with the lists more than
-// LITE_ATTN_STATIC_SCRATCH_BYTES: few rows have few tiles each, and of more rows only those beyond whole rounds are cut.)
+// Partial results and row maxima of rows cut into pieces.  (For no layer more than kMaxSegmentBytes, nor with the lists
+// more than LITE_ATTN_STATIC_SCRATCH_BYTES: few rows have few tiles each, and of more rows only those beyond whole
+// rounds are cut.)
 size_t piece_count(const Geometry& g) {
   return g.rows > kFewRows ? 8 * (size_t)cut_rows(g) * cut_pieces(g) : std::max<size_t>(g.pieces, g.rows * equal_pieces(g));
 }
@@ -89,13 +90,15 @@ size_t piece_bytes(const Geometry& g) {
   return g.pieces > 0 ? sizeof(float) * (piece_count(g) * (128 * 128 + 2 * 128) + rows * g.Tk * 128) : 0;
 }
 
-// More rows than run side by side: at an empty mask all are of one length, and the rows beyond whole rounds of workgroups would take
-// a round of their own with most of the chip idle, so they are cut, into the more pieces the fewer they are; not where they nearly fill it, and not
-// into pieces of fewer than six tiles (a piece costs about two tiles' time besides its own).  us, step 0, whole -> cut: 522 rows x
-// 58 tiles 311 -> 251 (4 pieces), 600 x 60 335 -> 287 (4), 800 x 40 277 -> 266 (3), 1100 x 55 500 -> 460 (4), 1308 x 110 1087 ->
-// 1034 (3), 1600 x 50 628 -> 600 (4), 896 x 128 893 -> 858 (2); no gain in two pieces at 2384 x 150 (2529 -> 2532).  Under a
-// mask rows stay whole (cut alike, 800 x 40 at 40 % skipped was 8 % slower).  Where the host does not know whether the mask is empty,
-// the row schedule tells, so that a call's result depends on its inputs and its mask, not on how the caller came by them.
+// More rows than run side by side: at an empty mask all are of one length, and the rows beyond whole rounds of
+// workgroups would take a round of their own with most of the chip idle, so they are cut, into the more pieces the
+// fewer they are; not where they nearly fill it, and not into pieces of fewer than six tiles (a piece costs about two
+// tiles' time besides its own).  us, step 0, whole -> cut: 522 rows x 58 tiles 311 -> 251 (4 pieces), 600 x 60 335 ->
+// 287 (4), 800 x 40 277 -> 266 (3), 1100 x 55 500 -> 460 (4), 1308 x 110 1087 -> 1034 (3), 1600 x 50 628 -> 600 (4),
+// 896 x 128 893 -> 858 (2), 868 x 62 455 -> 442 (2), 870 x 145 1023 -> 983 (2), 1386 x 66 742 -> 717 (2), 1350 x 150
+// 1618 -> 1542 (2); no gain in two pieces at 2384 x 150 (2529 -> 2532).  Under a mask rows stay whole (cut
+// alike, 800 x 40 at 40 % skipped was 8 % slower).  Where the host does not know whether the mask is empty, the row
+// schedule tells, so that a call's result depends on its inputs and its mask, not on how the caller came by them.
 void cut_last_round(Geometry& g) {
   const int rest = (int)(g.rows % kFewRows);
   const int each = rest <= 128 ? 4 : rest <= 320 ? 3 : rest <= 400 && g.Tk >= 60 && g.rows < 3 * kFewRows ? 2 : 1;
@@ -105,14 +108,19 @@ void cut_last_round(Geometry& g) {
 static_assert(400 / 8 <= kArrivals, "a counter for every row that is cut");
 static_assert(6 * 3 >= kDrawTiles, "calls that cut rows clear their counters");
 
-// Few rows: whether calls that mark cut the rows by their live tiles (pick_piece() in lite_attn_kernels.hip) instead of all
-// alike: into at most as many pieces as the chip runs side by side, pairs or, with more rows, single groups.  us per call of a sequence of 3-4 steps (the first is dense), alike -> by live tiles: whole rows, 135 x
-// 15 tiles 31.8 -> 28.7, 155 x 31 56 -> 46.6, 290 x 29 90.9 -> 71.5, 300 x 10 38.3 -> 36.3; segments and merge pass, 100 x 25
-// 34.0 -> 30.8, 128 x 64 66.4 -> 62.2, 99 x 99 80.6 -> 73.7, 300 x 60 137.5 -> 124.1.  Not where the room is taken by the rows
-// themselves (184 of 256 -3 %, 250 -2 %), nor where a row has so few tiles that finding the pieces (1-2 us) costs what it saves
-// (128 x 8 -11 %, 72 x 12 in segments -10 %) or so many segments that more than kMaxPieces would be needed (64 x 32 -1 %).  The
-// literal PV skip can only cut rows of protected tokens, whose tiles need no verdict; diagonal first they are the only long ones
-// (155 x 31, 10 of them protected, four steps 247 -> 155 us; in ascending order -2 %).
+// Few rows: whether calls that mark cut the rows by their live tiles (pick_piece() in lite_attn_kernels.hip) instead of
+// all alike: into at most as many pieces as the chip runs side by side, pairs or, with more rows, single groups.  us
+// per call of a sequence of 3-4 steps (the first is dense), alike -> by live tiles: whole rows, 135 x 15 tiles 31.8 ->
+// 28.7, 155 x 31 56 -> 46.6, 290 x 29 90.9 -> 71.5, 300 x 10 38.3 -> 36.3; segments and merge pass, 100 x 25 34.0 ->
+// 30.8, 128 x 64 66.4 -> 62.2, 99 x 99 80.6 -> 73.7, 300 x 60 137.5 -> 124.1.  Not where the room is taken by the rows
+// themselves (184 of 256 -3 %, 250 -2 %), nor where a row has so few tiles that finding the pieces (1-2 us) costs what
+// it saves (128 x 8 -11 %, 72 x 12 in segments -10 %) or so many segments that more than kMaxPieces would be needed (64
+// x 32 -1 %).  The literal PV skip can only cut rows of protected tokens, whose tiles need no verdict; diagonal first
+// they are the only long ones (155 x 31, 10 of them protected, four steps 247 -> 155 us; in ascending order -2 %).
+// Rows that a mask has left alike gain nothing and pay 1-2 us.  The allocation-free call, which has nobody to count for
+// it, pays a launch more, 2.5 us, even at an empty mask: us, before there were pieces -> now, empty / 40 % of each row's
+// tiles skipped / rows of 0 to 100 %, 155 x 31 56.2 -> 58.1 / 45.1 -> 40.4 / 54.1 -> 40.0, 135 x 15 31.1 -> 33.4 / 26.9 ->
+// 26.5 / 30.3 -> 24.6, 300 x 10 38.8 -> 40.5 / 31.2 -> 32.5 / 33.9 -> 31.7.
 void allow_pieces(Geometry& g, const lite_attn_desc_t& d) {
   const bool immediate = (d.flags & LITE_ATTN_PV_SKIP_IMMEDIATE) != 0;
   if (immediate && (d.protect_len == 0 || !(d.flags & LITE_ATTN_ORDER_DIAGONAL_FIRST))) return;
@@ -124,13 +132,13 @@ void allow_pieces(Geometry& g, const lite_attn_desc_t& d) {
 }
 }  // namespace
 
-// Few rows that may be cut into pieces: how many of each a call that marks makes where the mask is empty, whether the caller
-// knows it (segments and merge pass) or the counts say so (pieces; the same sums in the same order).  As many as share_chip()
-// finds, if that is for the same kind of workgroups; else as many as fill one round of pairs, or, with more than half as many
-// rows as that, three in two rounds.  us, step 0, share_chip()'s single groups -> pairs: 80 x 20 27.9 -> 27.3, 100 x 25 39.4 ->
-// 36.3, 105 x 35 46.4 -> 46.1, 128 x 64 80.4 -> 80.8, 99 x 99 96.3 -> 102.1, 130 x 65 90.4 -> 101.8, 150 x 150 199.8 -> 211.3:
-// what it costs that a mask's pieces are pairs, and that a call's result depends on its inputs and its mask, not on how the
-// caller came by them.
+// Few rows that may be cut into pieces: how many of each a call that marks makes where the mask is empty, whether the
+// caller knows it (segments and merge pass) or the counts say so (pieces; the same sums in the same order).  As many as
+// share_chip() finds, if that is for the same kind of workgroups; else as many as fill one round of pairs, or, with
+// more than half as many rows as that, three in two rounds.  us, step 0, share_chip()'s single groups -> pairs: 80 x 20
+// 27.9 -> 27.3, 100 x 25 39.4 -> 36.3, 105 x 35 46.4 -> 46.1, 128 x 64 80.4 -> 80.8, 99 x 99 96.3 -> 102.1, 130 x 65
+// 90.4 -> 101.8, 150 x 150 199.8 -> 211.3: what it costs that a mask's pieces are pairs, and that a call's result
+// depends on its inputs and its mask, not on how the caller came by them.
 int equal_pieces(const Geometry& g) {
   if (g.rows > kFewRows) return 1;
   if (g.nseg == 1 || (g.pieces == kPairWorkgroups) == (g.pair != 0)) return g.nseg;

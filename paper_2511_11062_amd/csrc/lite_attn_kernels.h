@@ -25,17 +25,21 @@ constexpr int kDealtRows = kChunkRows;
 // workgroups draw theirs (FwdParams::tickets).
 constexpr int kResident = 64;
 constexpr int kNoDraws = 1 << 30;
-// Rows of fewer tiles than this go by place alone.  us, drawn (and a workgroup for every entry of the table's tail) -> by place: a
-// later step of 1000 rows of 1 tile 38.4 -> 28.3, 4000 x 1 123 -> 96, 2000 x 2 71 -> 55, 4900 x 7 278 -> 258, 33001 x 1 714 ->
-// 629, 80000 x 4 2834 -> 2688; 36000 x 12 2527 -> 2505; drawn / by place, without the tail's workgroups: 1200 x 12 90.2 / 89.8,
-// 12000 x 12 1001 / 988, 8000 x 16 822 / 835, 33600 x 16 2926 / 2946, 7200 x 24 1039 / 1059, 33600 x 24 4105 / 4167.
+// Rows of fewer tiles than this go by place alone.  us, drawn (and a workgroup for every entry of the table's tail) ->
+// by place: a later step of 1000 rows of 1 tile 38.4 -> 28.3, 4000 x 1 123 -> 96, 2000 x 2 71 -> 55, 4900 x 7 278 ->
+// 258, 33001 x 1 714 -> 629, 80000 x 4 2834 -> 2688; 36000 x 12 2527 -> 2505; drawn / by place, without the tail's
+// workgroups: 1200 x 12 90.2 / 89.8, 12000 x 12 1001 / 988, 8000 x 16 822 / 835, 33600 x 16 2926 / 2946, 7200 x 24 1039
+// / 1059, 33600 x 24 4105 / 4167.
 constexpr int kDrawTiles = 16;
 constexpr int kTicketWords = 32;  // distance of the counters of an unscheduled call, a cache line
 constexpr int kArrivals = 64;     // arrival counters per XCD, of rows cut alike (cut_rows)
-constexpr int kTableTail = 2 + kArrivals;  // end of an XCD's share of a short rows' schedule table: a flag, those, the ticket
+constexpr int kTableTail = 2 + kArrivals;  // end of an XCD's share of a short rows' table: a flag, those, the ticket
 constexpr int kPairWorkgroups = 256;
 constexpr int kClearWords = 64;   // us, 3 rows x 1 tile, 64 for each thread 9.6 (a launch: 8.9), 4096 for each 174 (12.1)
 constexpr int kMaxSegments = 16;
+// Pieces of a row that a mask asks for.  us, four steps, at most 2 / 3 / 4 / 8: 100 x 25 140 / 125 / 123 / 123, 105 x 35
+// 173 / 149 / 146 / 146, 99 x 99 364 / 307 / 285 / 286, 300 x 60 495 / 481 / 480 / 480; literal skip, whose protected
+// rows alone are long, 155 x 31 192 / 169 / 157 / 152, 126 x 63 329 / 275 / 251 / 242.
 constexpr int kMaxPieces = 4;
 constexpr size_t kMaxSegmentBytes = (size_t)104 << 20;
 
@@ -86,18 +90,18 @@ struct FwdParams {
   float* seg_mloc = nullptr;             // [rows][Tk][128]: row maxima of the visited tiles
   unsigned long long* stats_all = nullptr;  // all counters of the handle (stat_words of them)
   int64_t stat_words = 0;
-  // > 0: the rows are cut into pieces by their live tiles, at most this many altogether (pick_piece).  Their partial results are
-  // in seg_o and seg_stat, by piece, the row maxima in seg_mloc.
+  // > 0: the rows are cut into pieces by their live tiles, at most this many altogether (pick_piece).  Their partial
+  // results are in seg_o and seg_stat, by piece, the row maxima in seg_mloc.
   int piece_units = 0;
   int equal_pieces = 1;                  //   where their lengths do not ask for another cut: into this many each
   int alike = 0;                         //   (which the caller knows: alike != 0)
-  int cut_rows = 0, cut_pieces = 1;      // more than kFewRows rows: of each eighth, by number, the last cut_rows are cut alike if
-                                         //   the mask is empty (no schedule, or its flag says so)
+  int cut_rows = 0, cut_pieces = 1;      // more than kFewRows rows: of each eighth, by number, the last cut_rows are
+                                         //   cut alike if the mask is empty (no schedule, or its flag says so)
   uint32_t* arrive = nullptr;            // pieces that have arrived: [rows], zero between calls, or [8] at arrive_stride
   int arrive_stride = 0;                 //   [cut_rows], cleared by the schedule or clearing kernel
   const uint32_t* live_rows = nullptr;   // piece_units > 0: [rows] live tiles, counted before the launch
   uint32_t* live_next = nullptr;         // [rows] live tiles that this call leaves, for the next one; may be null
-  uint32_t* newly_rows = nullptr;        // few rows: [rows] tiles that step 0 marks, per row (the kernel clears the counters)
+  uint32_t* newly_rows = nullptr;        // few rows: [rows] tiles that step 0 marks (the kernel clears the counters)
 };
 
 // Tile geometry of a layer, derived from its descriptor.
@@ -115,7 +119,8 @@ struct Geometry {
   int nseg;        // > 0: few or short rows, each cut into this many segments (one workgroup each; 1 beyond kFewRows rows);
                    // 0: Skip-Lists, row ranking and V^T
   int per_xcd;     // entries per XCD in the schedule table: row slots, with lists (ceil(chunks / 8) + 1) chunks, short rows
-                   // 1.5 shares and kArrivals counters, and the ticket counter; where there is no table, the workgroups of an XCD
+                   // 1.5 shares and kArrivals counters, and the ticket counter; where there is no table, the workgroups
+                   // of an XCD
 };
 
 // More than kFewRows rows: rows of each eighth, by number, that are cut, and into how many pieces each.
@@ -141,8 +146,9 @@ int check_call(const void* q, const void* k, const void* v, const void* out, flo
 Geometry geometry(const lite_attn_desc_t& d);
 ListLayout list_layout(const Geometry& g);
 int equal_pieces(const Geometry& g);
-// Scratch of a layer's calls: V^T ([BH][128][128*Tk] bf16), or the partial results of rows cut into nseg segments or, at 1, into
-// pieces; rows that stay whole and take no lists need neither (total 0, the most that any of the layer's calls needs).
+// Scratch of a layer's calls: V^T ([BH][128][128*Tk] bf16), or the partial results of rows cut into nseg segments or,
+// at 1, into pieces; rows that stay whole and take no lists need neither (total 0, the most that any of the layer's
+// calls needs).
 struct ScratchLayout {
   size_t seg_o, seg_stat, seg_mloc, total;
 };
@@ -166,8 +172,8 @@ struct CallArgs {
   size_t stat_words;
   uint32_t* newly_rows;        // few rows: marks of step 0, per row; null elsewhere
   uint32_t* arrive;            // few rows: kFewRows counters that are zero between calls; null: to be cleared by the call
-  const uint32_t* live_rows;   // few rows that may be cut into pieces: live tiles, left by the previous call; null: to be counted
-  uint32_t* live_next;         //   the same for the next call, or null
+  const uint32_t* live_rows;   // few rows that may be cut into pieces: live tiles, left by the previous call; null: to
+  uint32_t* live_next;         //   be counted.  The same for the next call, or null
   bool lists_ready, build_next;
 };
 hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListLayout& ll, char* lists, char* scratch,

@@ -33,24 +33,24 @@
 //     first of its two PV products is issued; a fired tile's PV MFMAs and row sums are then dropped.
 //
 // Calls with few rows (at most kFewRows = 512, which all fit the chip at once) or short rows (at most kShortTiles = 192
-// tiles, any number of them up to kMaxListless) take the template argument FEW of the fused kernel.  The former are bound by
-// launches and by latency, not by the matrix cores: the tiny layer's step was 36 us of attention on 32 of 256 CUs behind four
-// to six launches of 4 us each; for the latter the passes before the kernel cost more than they save.  They run in one or two
-// launches:
+// tiles, any number of them up to kMaxListless) take the template argument FEW of the fused kernel.  The former are
+// bound by launches and by latency, not by the matrix cores: the tiny layer's step was 36 us of attention on 32 of 256
+// CUs behind four to six launches of 4 us each; for the latter the passes before the kernel cost more than they save.
+// They run in one or two launches:
 //   * no lists and no ranking: a workgroup finds its live tiles from the mask row itself (LiveWalk); more than kFewRows rows
 //     are scheduled from the mask in one launch (schedule_rows_kernel; not at step 0 and not beyond kSchedRows rows);
 //   * no V^T: the V fragments come from V as it lies in memory through transposing LDS reads (ds_read_b64_tr_b16), 16 LDS
 //     instructions more per stage, the same LDS cycles (no bank conflicts): 1.8 % of the kernel's time on the 12-head
 //     N = 32760 dense step, against a launch and a pass over V;
-//   * with few rows a workgroup may be a PAIR of groups of four waves, each with its own stage buffers and one 64-column half
-//     of every tile (a CU with one wave per SIMD issues too slowly to keep the matrix cores busy); the groups' results meet
-//     in LDS at the end, their row maxima once per tile, for the predicate;
+//   * with few rows a workgroup may be a PAIR of groups of four waves, each with its own stage buffers and one
+//     64-column half of every tile (a CU with one wave per SIMD issues too slowly to keep the matrix cores busy); the
+//     groups' results meet in LDS at the end, their row maxima once per tile, for the predicate;
 //   * with few rows a row may be cut into segments, one workgroup each (the rule and its measurements: share_chip() in
 //     lite_attn_host.cpp); merge_segments_kernel adds up the partial results.  The predicate stays exact: the
 //     segments record every tile's row maxima, and the merge pass judges them against the running maximum carried
 //     over the segments, the value a single pass would have had;
-//   * under a mask rows may be cut by their live tiles, into pieces of about equal length (pick_piece), merged by the workgroup
-//     that finishes last.
+//   * under a mask rows may be cut by their live tiles, into pieces of about equal length (pick_piece), merged by the
+//     workgroup that finishes last.
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <stdint.h>
@@ -79,9 +79,9 @@ __device__ __forceinline__ void static_for(std::integer_sequence<int, Ks...>, F&
   (f(std::integral_constant<int, Ks>{}), ...);
 }
 
-// Stores past the XCD's L2 (scope bit sc1, the agent scope), for what the next launch reads: a line left in the L2 is written
-// back at the end of the kernel, and that launch waits for it (5 us behind a call that leaves 16 MB of partial results, 2 us
-// behind one without).
+// Stores past the XCD's L2 (scope bit sc1, the agent scope), for what the next launch reads: a line left in the L2 is
+// written back at the end of the kernel, and that launch waits for it (5 us behind a call that leaves 16 MB of partial
+// results, 2 us behind one without).
 constexpr int kStoreThrough = 16;  // cache policy of a buffer store
 __device__ __forceinline__ void store_through(float* at, float x) {
   __hip_atomic_store(at, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -568,8 +568,8 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(const uint16_t* __rest
 }
 
 // The live K/V tiles of one Skip-Mask row in visiting order, walked from the mask words themselves (calls with few or
-// short rows, where a list built by an earlier kernel would cost more than it saves): lane w of the wave holds word w of the row's
-// live set, the position is scalar.  Rows of at most 64 words (4096 tiles).  Used by whole waves only.
+// short rows, where a list built by an earlier kernel would cost more than it saves): lane w of the wave holds word w
+// of the row's live set, the position is scalar.  Rows of at most 64 words (4096 tiles).  Used by whole waves only.
 struct LiveWalk {
   uint32_t lo, hi;   // this lane's word of the live set
   int W, start;      // words of a row; tile the visit starts with (diagonal first: the diagonal tile)
@@ -1080,7 +1080,9 @@ __device__ __forceinline__ int quotient(int a, int b) {
 }
 
 // First visiting position of segment s of a row with cnt live tiles.
-__device__ __forceinline__ int segment_start(int cnt, int s, int nseg) { return nseg == 1 ? cnt * s : quotient(cnt * s, nseg); }
+__device__ __forceinline__ int segment_start(int cnt, int s, int nseg) {
+  return nseg == 1 ? cnt * s : quotient(cnt * s, nseg);
+}
 
 // How many places XCD x's list of rows has, and the row at place t of it (-1: none; FEW: the piece of it above kPieceShift).
 template <bool FEW>
@@ -1101,23 +1103,23 @@ __device__ __forceinline__ int row_at_place(const FwdParams& p, int x, int t, in
     const int row = dealt_chunk(t / kDealtRows, x) * kDealtRows + t % kDealtRows;
     return row < p.rows_total ? row : -1;
   }
-  // from the table, or in order, an eighth of the rows to every XCD; of each eighth by number the last `cut` rows in cut_pieces
-  // pieces each, of which all but the first end the list, row-fastest
+  // from the table, or in order, an eighth of the rows to every XCD; of each eighth by number the last `cut` rows in
+  // cut_pieces pieces each, of which all but the first end the list, row-fastest
   const int share = (p.rows_total + 7) / 8, rows = places - cut * (p.cut_pieces - 1);
   if (t < rows) return p.scheduled && cut == 0 ? (int)p.slots[(size_t)x * p.per_xcd + t] : x * share + t;
   const int index = quotient(t - rows, cut), row = x * share + share - cut + t - rows - index * cut;
   return row < p.rows_total ? row | (index + 1) << kPieceShift : -1;
 }
 
-// The next row for a workgroup that starts on XCD `home` after the first round, by one thread: the next place of its own
-// XCD's list; if that list is used up, of the one with most places left; -1 if there are none.  Places below kResident
-// belong to the first round's workgroups, which need no counter.  Ends: a draw that fails has found its list used up, which
-// it then stays.  Why: workgroups go to XCDs by id, but equal lists do not end together, because the XCDs' clocks differ (a
-// tile took 3.2 us on the fastest, 3.6 on the slowest, the same ones in every kernel of a session; lists of the 12-head
-// dense step ended between 5.14 and 5.68 ms).  A row drawn costs a counter's round trip (0.35 us; kDrawTiles).  Lists by place -> drawn:
-// 40 heads x 591 tiles, dense + sparse step, 170.7 -> 164.8 ms; 24 x 931 253.8 -> 245.4; a sparse step of 12 x 256 2379 ->
-// 2331 us; 12 x 110, diagonal first, four steps 2128 -> 2102; no gain where few rounds of equally long rows leave nothing to
-// draw (12 x 256 dense, six rounds).
+// The next row for a workgroup that starts on XCD `home` after the first round, by one thread: the next place of its
+// own XCD's list; if that list is used up, of the one with most places left; -1 if there are none.  Places below
+// kResident belong to the first round's workgroups, which need no counter.  Ends: a draw that fails has found its list
+// used up, which it then stays.  Why: workgroups go to XCDs by id, but equal lists do not end together, because the
+// XCDs' clocks differ (a tile took 3.2 us on the fastest, 3.6 on the slowest, the same ones in every kernel of a
+// session; lists of the 12-head dense step ended between 5.14 and 5.68 ms).  A row drawn costs a counter's round trip
+// (0.35 us; kDrawTiles).  Lists by place -> drawn: 40 heads x 591 tiles, dense + sparse step, 170.7 -> 164.8 ms; 24 x
+// 931 253.8 -> 245.4; a sparse step of 12 x 256 2379 -> 2331 us; 12 x 110, diagonal first, four steps 2128 -> 2102; no
+// gain where few rounds of equally long rows leave nothing to draw (12 x 256 dense, six rounds).
 template <bool FEW>
 __device__ __forceinline__ int draw_row(const FwdParams& p, int home, int cut) {
   for (int from = home;;) {
@@ -1130,8 +1132,9 @@ __device__ __forceinline__ int draw_row(const FwdParams& p, int home, int cut) {
     int most = 0;
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
-      const int left = places_of<FEW>(p, x, cut) - kResident -
-                       (int)__hip_atomic_load(p.tickets + (size_t)x * p.ticket_stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint32_t drawn =
+          __hip_atomic_load(p.tickets + (size_t)x * p.ticket_stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int left = places_of<FEW>(p, x, cut) - kResident - (int)drawn;
       if (left > most) {
         most = left;
         from = x;
@@ -1144,14 +1147,17 @@ __device__ __forceinline__ int draw_row(const FwdParams& p, int home, int cut) {
 typedef const __attribute__((address_space(4))) FwdParams* const_params_ptr;
 typedef const __attribute__((address_space(4))) FwdParams& ParamsRef;
 
-// Step 0 of a call with few rows: nothing was skipped on entry, a row is one run (two, if its visit starts at a diagonal tile
-// that is not the first), what the rows mark goes to newly_rows; the later steps' counters start at zero.  The launch that
-// cleared them before the kernel cost 1.5-3.4 us (one call of 2 rows x 1 tile 8.1 -> 6.7 us, 32 x 4 14.7 -> 12.5, 120 x 2 12.8 ->
-// 9.4).  All the call's threads share it (by one workgroup's, counters of 16384 steps held up a call of 135 x 15 from 31.3 to
-// 35.5 us); more than kClearWords for each of them are cleared by a launch beforehand all the same.
+// Step 0 of a call with few rows: nothing was skipped on entry, a row is one run (two, if its visit starts at a
+// diagonal tile that is not the first), what the rows mark goes to newly_rows; the later steps' counters start at zero.
+// The launch that cleared them before the kernel cost 1.5-3.4 us (one call of 2 rows x 1 tile 8.1 -> 6.7 us, 32 x 4
+// 14.7 -> 12.5, 120 x 2 12.8 -> 9.4).  All the call's threads share it (by one workgroup's, counters of 16384 steps
+// held up a call of 135 x 15 from 31.3 to 35.5 us); more than kClearWords for each of them are cleared by a launch
+// beforehand all the same.
 __device__ __forceinline__ void clear_counters(const FwdParams& p, int thread, int threads) {
-  for (int64_t x = thread; x < p.stat_words; x += threads)
-    p.stats_all[x] = x == 2 ? (unsigned long long)(p.rows_total + (p.diagonal_first ? p.rows_total - p.rows_total / p.Tq : 0)) : 0ull;
+  for (int64_t x = thread; x < p.stat_words; x += threads) {
+    const int runs = p.rows_total + (p.diagonal_first ? p.rows_total - p.rows_total / p.Tq : 0);
+    p.stats_all[x] = x == 2 ? (unsigned long long)runs : 0ull;
+  }
 }
 
 // Live tiles of mask word w as it stands.
@@ -1165,8 +1171,8 @@ __device__ __forceinline__ int sum_words(int n, int W) {
   return n;
 }
 
-// The end of a row without lists, by one wave: the tiles that fired (lane w: word w) join the Skip-Mask row as it was on entry
-// (`skipped`; only of interest where something fired or live_next is set), the step's counter moves.
+// The end of a row without lists, by one wave: the tiles that fired (lane w: word w) join the Skip-Mask row as it was
+// on entry (`skipped`; only of interest where something fired or live_next is set), the step's counter moves.
 __device__ __forceinline__ void finish_mask_row(ParamsRef p, int row, int lane, uint64_t skipped, uint64_t fired) {
   if (lane < p.W && (p.fresh || fired)) p.bits[(size_t)row * p.W + lane] = skipped | fired;
   if (p.live_next) {
@@ -1182,10 +1188,12 @@ __device__ __forceinline__ void finish_mask_row(ParamsRef p, int row, int lane, 
   if (lane == 0) p.newly_rows[row] = (uint32_t)n;
 }
 
-// Adds up the partial results of a row's pieces, in their order whichever arrived last, into what the end of the kernel expects
-// of a whole row.  Loads have agent scope, like the stores (kStoreThrough); two pieces' are in flight together: 0.7 us a piece.
+// Adds up the partial results of a row's pieces, in their order whichever arrived last, into what the end of the kernel
+// expects of a whole row.  Loads have agent scope, like the stores (kStoreThrough); two pieces' are in flight together:
+// 0.7 us a piece.
 template <int QB, bool IMM>
-__device__ __forceinline__ void merge_pieces(State<QB, IMM>& st, ParamsRef p, float c, int piece, int pieces, int wave, int lane) {
+__device__ __forceinline__ void merge_pieces(State<QB, IMM>& st, ParamsRef p, float c, int piece, int pieces, int wave,
+                                             int lane) {
   const float* ps = p.seg_stat + (size_t)piece * 2 * kTile + 32 * wave + (lane & 31);
   auto stat = [&](int s, int which) {
     return __hip_atomic_load(ps + (s * 2 + which) * kTile, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1247,8 +1255,10 @@ __device__ __forceinline__ uint64_t judge_piece(ParamsRef p, int row, int cut_ro
   int cnt, nruns;
   walk.open(LiveWalk::load(p.bits + (size_t)row * p.W, p.fresh, p.W), p.Tk, p.W, p.diagonal_first ? i : 0);
   walk.count(cnt, nruns);
-  const auto mloc = __builtin_amdgcn_make_buffer_rsrc((void*)(p.seg_mloc + (size_t)cut_row * p.Tk * kTile), 0, p.Tk * kTile * 4, 0x00020000);
-  const auto stat = __builtin_amdgcn_make_buffer_rsrc((void*)(p.seg_stat + (size_t)piece * 2 * kTile), 0, pieces * 2 * kTile * 4, 0x00020000);
+  const auto mloc = __builtin_amdgcn_make_buffer_rsrc((void*)(p.seg_mloc + (size_t)cut_row * p.Tk * kTile), 0,
+                                                      p.Tk * kTile * 4, 0x00020000);
+  const auto stat = __builtin_amdgcn_make_buffer_rsrc((void*)(p.seg_stat + (size_t)piece * 2 * kTile), 0,
+                                                      pieces * 2 * kTile * 4, 0x00020000);
   auto pair_of = [&](auto rsrc, int offset) {
     return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, 8 * lane, offset, kStoreThrough));
   };
@@ -1284,7 +1294,8 @@ __device__ __forceinline__ uint64_t judge_piece(ParamsRef p, int row, int cut_ro
       if (t + u >= t1) break;
       run[0] = fmaxf(run[0], m[u][0]);
       run[1] = fmaxf(run[1], m[u][1]);
-      const bool ok = (!valid0 || (m[u][0] - run[0]) * p.scale <= p.thr) && (!valid1 || (m[u][1] - run[1]) * p.scale <= p.thr);
+      const bool ok = (!valid0 || (m[u][0] - run[0]) * p.scale <= p.thr) &&
+                      (!valid1 || (m[u][1] - run[1]) * p.scale <= p.thr);
       if (__all(ok) && !pinned(j[u]) && lane == (j[u] >> 6)) fired |= 1ull << (j[u] & 63);
     }
   }
@@ -1311,16 +1322,17 @@ __device__ __forceinline__ int wave_max(int x) {
   return __builtin_amdgcn_readlane(x, 63);
 }
 
-// Few rows that a mask has made unequal: every row is cut into ceil(live tiles / g) pieces, one workgroup each, with the
-// smallest g (found from below) for which the workgroups that run side by side do; the piece that this workgroup computes.  All
-// workgroups have to find the same cut, so the rows' live tiles come from counts made before this launch and not from the mask,
-// which rows that end early change while workgroups of a busy chip may still have to start.  (Each row's own tiles do come from
-// the mask, and nobody changes them before all of its pieces have arrived: any counts give right results.)  Literal PV skip:
-// only rows of protected tokens, whose tiles need no verdict, are cut.  Where the counts say that the mask is empty, the rows
-// are cut alike, as where the caller knows that it is: what a call gives depends on the mask, not on how it came about.  They
-// are also cut alike, in as many rounds of workgroups as it takes, where one round would leave most rows nearly whole: us, 40 %
-// of the tiles of each row skipped, 15 % in brackets, one round -> alike: 348 x 87 205 -> 192, 300 x 60 (175 -> 153), 304 x 304
-// 597 -> 493, 150 x 150 165 -> 147, 129 x 129 (191 -> 171).
+// Few rows that a mask has made unequal: every row is cut into ceil(live tiles / g) pieces, one workgroup each, with
+// the smallest g (found from below) for which the workgroups that run side by side do; the piece that this workgroup
+// computes.  All workgroups have to find the same cut, so the rows' live tiles come from counts made before this launch
+// and not from the mask, which rows that end early change while workgroups of a busy chip may still have to start.
+// (Each row's own tiles do come from the mask, and nobody changes them before all of its pieces have arrived: any
+// counts give right results.)  Literal PV skip: only rows of protected tokens, whose tiles need no verdict, are cut.
+// Where the counts say that the mask is empty, the rows are cut alike, as where the caller knows that it is: what a
+// call gives depends on the mask, not on how it came about.  They are also cut alike, in as many rounds of workgroups
+// as it takes, where one round would leave most rows nearly whole: us, 40 % of the tiles of each row skipped, 15 % in
+// brackets, one round -> alike: 348 x 87 205 -> 192, 300 x 60 (175 -> 153), 304 x 304 597 -> 493, 150 x 150 165 -> 147,
+// 129 x 129 (191 -> 171).
 struct Piece {
   int row, index, pieces, first;  // (row -1: no piece, kAlike: cut alike; first: number of the row's first piece)
 };
@@ -1370,13 +1382,14 @@ __device__ __forceinline__ Piece pick_piece(const FwdParams& p, uint16_t* counts
     }
     upto = wave_scan(mine);
     total = __builtin_amdgcn_readlane(upto, 63);
-    if (total <= p.piece_units || g >= longest) break;  // (g = longest: a piece for every row; there are no more rows than units)
+    if (total <= p.piece_units || g >= longest) break;  // (g = longest: a piece for every row, and rows <= units)
     g = max(g + 1, quotient(g * total, p.piece_units));
     if (4 * g > 3 * longest) g = longest;  // not worth the merging
   }
   if constexpr (!IMM) {  // (a piece costs about two tiles' time besides its own)
     const int rounds = quotient(rows * p.equal_pieces + p.piece_units - 1, p.piece_units);
-    if (p.equal_pieces > 1 && g > rounds * (quotient(longest + p.equal_pieces - 1, p.equal_pieces) + 2)) return {kAlike, 0, 1, 0};
+    const int each = quotient(longest + p.equal_pieces - 1, p.equal_pieces);
+    if (p.equal_pieces > 1 && g > rounds * (each + 2)) return {kAlike, 0, 1, 0};
   }
   Piece out = {-1, 0, 1, 0};
   const int share = (total + 7) / 8, unit = xcd * share + slot;
@@ -1403,17 +1416,16 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   const int grp = PAIR ? __builtin_amdgcn_readfirstlane(tid >> 8) : 0;  // PAIR: which half of every tile's columns
   const int lq = lane & 31;
 
-  // Consecutive workgroup ids land on different XCDs (id % 8): workgroup `slot` of an XCD computes the row at that place of
-  // the XCD's list in the schedule table (deal_rows_kernel: chunks of kChunkRows rows of one head side by side, so that the
-  // workgroups sharing one L2 stream the same K/V; equal work per XCD; long rows first) or, after the first round, the one
-  // that it draws (draw_row).
-  // FEW: the table of schedule_rows_kernel if the call has one; else the (head, segment, row) triples, numbered
-  // row-fastest, an eighth to every XCD, so that the rows walking the same K/V tiles of a head share an L2; beyond kSchedRows
-  // rows, where the XCDs' shares would be whole heads, chunks of rows dealt to the XCDs in turn.  Over 200 seeded sets of
-  // head densities (260-1000 heads, alike to 0.05 against 0.95, with and without a period) the busiest XCD has 1.035 times
-  // the mean work, at worst 1.18; eighths give 4.4 where an eighth of the heads is dense and the others 10 % live.  320
-  // heads x 128 tiles, ms: that mask 30.6 -> 9.3, half the heads 90 % and half 15 % live 34.8 -> 21.7, all 45 % 19.6 both
-  // ways (chunks of 32 rows 19.7, of 128 19.6).
+  // Consecutive workgroup ids land on different XCDs (id % 8): workgroup `slot` of an XCD computes the row at that
+  // place of the XCD's list in the schedule table (deal_rows_kernel: chunks of kChunkRows rows of one head side by
+  // side, so that the workgroups sharing one L2 stream the same K/V; equal work per XCD; long rows first) or, after the
+  // first round, the one that it draws (draw_row). FEW: the table of schedule_rows_kernel if the call has one; else the
+  // (head, segment, row) triples, numbered row-fastest, an eighth to every XCD, so that the rows walking the same K/V
+  // tiles of a head share an L2; beyond kSchedRows rows, where the XCDs' shares would be whole heads, chunks of rows
+  // dealt to the XCDs in turn.  Over 200 seeded sets of head densities (260-1000 heads, alike to 0.05 against 0.95,
+  // with and without a period) the busiest XCD has 1.035 times the mean work, at worst 1.18; eighths give 4.4 where an
+  // eighth of the heads is dense and the others 10 % live.  320 heads x 128 tiles, ms: that mask 30.6 -> 9.3, half the
+  // heads 90 % and half 15 % live 34.8 -> 21.7, all 45 % 19.6 both ways (chunks of 32 rows 19.7, of 128 19.6).
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   int row = -1, i, bh, seg = 0;
   int pieces = 1, piece = 0;  // a row cut into pieces (pick_piece): how many, and the first one's partial result
@@ -1534,7 +1546,8 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   uint64_t* fired_bits = reinterpret_cast<uint64_t*>(smem + kFiredOff);
   if (!FEW && p.build_next)
     for (int w = tid; w < p.W; w += kThreads) fired_bits[w] = 0;
-  if (tid == 0 && !(FEW && p.nseg > 1) && seg == 0 && p.stat_newly && !(FEW && p.fresh && p.newly_rows)) {  // statistics of the step: tiles skipped on entry, Skip-List entries
+  // statistics of the step: tiles skipped on entry, Skip-List entries
+  if (tid == 0 && !(FEW && p.nseg > 1) && seg == 0 && p.stat_newly && !(FEW && p.fresh && p.newly_rows)) {
     atomicAdd(p.stat_skipped_in, (unsigned long long)(p.Tk - cnt));
     atomicAdd(p.stat_runs, (unsigned long long)nruns);
   }
@@ -1880,7 +1893,8 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
     } else if constexpr (IMM) {
       // drain: the second V^T stage of the last tile is still to be loaded; then both of its PV products, the
       // rescale factor of its second stage in between
-      dma_stage<QB, kVOff + kStageBytes>(ln.vrsrc, ln.vdma, (uint32_t)(j_prev * kTile + kSub) * (FEW ? ln.stride2 : 2u), ln.lds_wave);
+      dma_stage<QB, kVOff + kStageBytes>(ln.vrsrc, ln.vdma,
+                                         (uint32_t)(j_prev * kTile + kSub) * (FEW ? ln.stride2 : 2u), ln.lds_wave);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
       if (pv_on) mma_pv<QB, FEW>(st.oacc, st.pw0, kVOff, ln.vread);
@@ -1950,7 +1964,8 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
         if (ln.thr > -INFINITY) {
           if (grp == (PAIR ? 1 : 0)) {
             uint64_t f = 0;
-            for (int s = wave; s < n_pieces; s += 4) f |= judge_piece(*e, row, cut_row, i, first_piece, n_pieces, s, lane, pinned);
+            for (int s = wave; s < n_pieces; s += 4)
+              f |= judge_piece(*e, row, cut_row, i, first_piece, n_pieces, s, lane, pinned);
             fired[wave][lane] = f;
           }
           __syncthreads();
@@ -2015,15 +2030,15 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
 }
 
 // Bound by latency and by the partials' way through memory (64 KB per segment; 16 MB for 256 segments): loads of four
-// segments, or of eight tiles' maxima, in flight together (call of 32 rows x 4 segments of 4 tiles 22.0 -> 20.7
-// us, of 128 rows x 2 segments of 64 tiles 163 -> 147 us, against one load at a time); written past the L2 and read without
-// leaving a trace there (a step of 32 rows x 16 tiles 18.8 -> 16.5 us, of 72 x 12 24.1 -> 19.5, of 100 x 25 36.1 -> 34.6; the
-// stores alone give a third of it, nt in place of sc1 half).  All segments' loads at once: no faster with 8, slower with 2-4.
-// Rows that were cut into segments (FEW, nseg > 1): merges the segments' partial results and judges the tiles.
-// Workgroups 0 .. 4*rows-1: 32 Q rows each, one thread per (row, 8 features): O = sum_s 2^(c (m_s - M)) O_s / sum_s ... .
-// Workgroups 4*rows .. 5*rows-1: one Skip-Mask row each; two waves per segment walk its tiles with the running maximum
-// carried over from the segments before it (exactly the maximum a single pass would have), set the row's mask bits and
-// add the step's counters.
+// segments, or of eight tiles' maxima, in flight together (call of 32 rows x 4 segments of 4 tiles 22.0 -> 20.7 us, of
+// 128 rows x 2 segments of 64 tiles 163 -> 147 us, against one load at a time); written past the L2 and read without
+// leaving a trace there (a step of 32 rows x 16 tiles 18.8 -> 16.5 us, of 72 x 12 24.1 -> 19.5, of 100 x 25 36.1 ->
+// 34.6; the stores alone give a third of it, nt in place of sc1 half).  All segments' loads at once: no faster with 8,
+// slower with 2-4. Rows that were cut into segments (FEW, nseg > 1): merges the segments' partial results and judges
+// the tiles. Workgroups 0 .. 4*rows-1: 32 Q rows each, one thread per (row, 8 features): O = sum_s 2^(c (m_s - M)) O_s
+// / sum_s ... . Workgroups 4*rows .. 5*rows-1: one Skip-Mask row each; two waves per segment walk its tiles with the
+// running maximum carried over from the segments before it (exactly the maximum a single pass would have), set the
+// row's mask bits and add the step's counters.
 constexpr int kMergeThreads = 512;
 __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const FwdParams p) {
   touch_arguments(sizeof(FwdParams));
@@ -2140,8 +2155,8 @@ __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const Fwd
   }
 }
 
-// Few rows: the live tiles of every row of a mask that no call of a handle has left (pick_piece() reads them), one thread per
-// row; `arrive`, if not null, is cleared.
+// Few rows: the live tiles of every row of a mask that no call of a handle has left (pick_piece() reads them), one
+// thread per row; `arrive`, if not null, is cleared.
 __global__ void count_rows_kernel(const uint64_t* bits, int rows, int Tk, int W, uint32_t* live, uint32_t* arrive) {
   const int row = blockIdx.x * blockDim.x + threadIdx.x;
   if (row >= rows) return;
@@ -2227,10 +2242,11 @@ hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int Tk, int W, i
 }
 
 hipError_t launch_fwd(const FwdParams& p, bool immediate, hipStream_t st) {
-  // Workgroups per XCD: one for every segment, piece or row of its share, in order; one for every entry of its list, where these
-  // go by place (those past the last row return at once); where rows are drawn, of its share and an eighth more, as an XCD may
-  // come to more rows than its list has: not for every entry of a table that has room for unequal lists, since a workgroup that
-  // draws in vain costs a counter's round trip too (a later step of 1200 rows x 12 tiles 96 -> 90 us, 8000 x 16 839 -> 822).
+  // Workgroups per XCD: one for every segment, piece or row of its share, in order; one for every entry of its list,
+  // where these go by place (those past the last row return at once); where rows are drawn, of its share and an eighth
+  // more, as an XCD may come to more rows than its list has: not for every entry of a table that has room for unequal
+  // lists, since a workgroup that draws in vain costs a counter's round trip too (a later step of 1200 rows x 12 tiles
+  // 96 -> 90 us, 8000 x 16 839 -> 822).
   const bool draws = p.tickets && p.resident == kResident, table = p.nseg > 0 && p.scheduled;
   const int rows = (p.rows_total + 7) / 8;
   int places = p.per_xcd;

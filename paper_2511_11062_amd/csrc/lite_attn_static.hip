@@ -68,7 +68,7 @@ extern "C" int lite_attn_fwd_static(const void* q, const void* k, const void* v,
   a.newly_rows = nullptr;
   a.live_rows = nullptr;
   a.live_next = nullptr;
-  a.arrive = nullptr;  // (nothing that outlives a call could be vouched for: calls that overlap are the caller's mistake, once)
+  a.arrive = nullptr;  // (nothing that outlives a call could be vouched for: overlapping calls are a mistake, once)
   a.lists_ready = false;  // lists rebuilt from the caller's mask on every call, none left behind for a next one
   a.build_next = false;
   const hipError_t e = la::launch_call(*desc, geo, ll, ptr, ptr + ll.total, a, stream, nullptr);
