@@ -177,6 +177,10 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
       if (e != hipSuccess) return e;
     }
   }
+  p.parts = few ? p.nseg * p.equal_pieces : 1;
+  p.per_Tq = reciprocal(g.Tq);
+  p.per_H = reciprocal(d.heads);
+  p.per_parts = reciprocal(p.parts);
   if (mid) {
     e = hipEventRecord(mid, stream);
     if (e != hipSuccess) return e;

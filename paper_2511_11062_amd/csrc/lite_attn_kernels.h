@@ -102,7 +102,17 @@ struct FwdParams {
   const uint32_t* live_rows = nullptr;   // piece_units > 0: [rows] live tiles, counted before the launch
   uint32_t* live_next = nullptr;         // [rows] live tiles that this call leaves, for the next one; may be null
   uint32_t* newly_rows = nullptr;        // few rows: [rows] tiles that step 0 marks (the kernel clears the counters)
+  int parts = 1;                         // nseg * equal_pieces
+  uint32_t per_Tq, per_H, per_parts = 0;  // reciprocals for the kernel's short division
 };
+
+// a / b (a >= 0, b >= 1, a + b < 2^31) with the host's per_b = reciprocal(b): a * per_b / 2^32 is short of a / b by less than
+// one.  On the GPU a few scalar instructions; a workgroup with few tiles waits for its indexes before its first load.
+constexpr uint32_t reciprocal(int b) { return b == 1 ? 0xffffffffu : (uint32_t)(((uint64_t)1 << 32) / (uint32_t)b); }
+constexpr int quotient(int a, int b, uint32_t per_b) {
+  const int q = (int)((uint64_t)(uint32_t)a * per_b >> 32);
+  return (q + 1) * b <= a ? q + 1 : q;
+}
 
 // Tile geometry of a layer, derived from its descriptor.
 struct Geometry {

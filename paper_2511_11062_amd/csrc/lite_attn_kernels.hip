@@ -577,9 +577,11 @@ struct LiveWalk {
                      // from `start` on first, those before it last)
   uint64_t cur;      // tiles of the current word still to come
 
+  // Lanes past the row, and all of them for an empty mask, lie past the end of the buffer and read zeros: with a branch around
+  // it the load was waited for before the Q loads behind it were issued (options clip, four steps, 198 -> 195 us).
   static __device__ __forceinline__ uint64_t load(const uint64_t* mrow, bool empty_mask, int words) {
-    const int lane = threadIdx.x & 63;
-    return !empty_mask && lane < words ? mrow[lane] : 0ull;
+    const auto at = __builtin_amdgcn_make_buffer_rsrc((void*)mrow, 0, empty_mask ? 0 : 8 * words, 0x00020000);
+    return __builtin_bit_cast(uint64_t, __builtin_amdgcn_raw_buffer_load_b64(at, 8 * (int)(threadIdx.x & 63), 0, 0));
   }
   __device__ __forceinline__ void open(uint64_t skipped, int Tk, int W_, int start_) {
     const int lane = threadIdx.x & 63;
@@ -1155,7 +1157,7 @@ typedef const __attribute__((address_space(4))) FwdParams& ParamsRef;
 // beforehand all the same.
 __device__ __forceinline__ void clear_counters(const FwdParams& p, int thread, int threads) {
   for (int64_t x = thread; x < p.stat_words; x += threads) {
-    const int runs = p.rows_total + (p.diagonal_first ? p.rows_total - p.rows_total / p.Tq : 0);
+    const int runs = p.rows_total + (p.diagonal_first ? p.rows_total - quotient(p.rows_total, p.Tq, p.per_Tq) : 0);
     p.stats_all[x] = x == 2 ? (unsigned long long)runs : 0ull;
   }
 }
@@ -1336,33 +1338,29 @@ __device__ __forceinline__ int wave_max(int x) {
 struct Piece {
   int row, index, pieces, first;  // (row -1: no piece, kAlike: cut alike; first: number of the row's first piece)
 };
-constexpr int kAlike = -2, kFullRow = 1 << 15;
+constexpr int kAlike = -2;
 template <bool IMM>
-__device__ __forceinline__ Piece pick_piece(const FwdParams& p, uint16_t* counts, int xcd, int slot, int tid, int threads) {
-  const int lane = tid & 63, rows = p.rows_total;
-  for (int r = tid; r < rows; r += threads) {
-    int n = (int)p.live_rows[r];
-    const int full = n == p.Tk ? kFullRow : 0;
-    if constexpr (IMM) {
-      const int i = r % p.Tq;
-      if (!(i * kTile < p.protect_start + p.protect_len && p.protect_start < (i + 1) * kTile)) n = 1;
-    }
-    counts[r] = (uint16_t)(max(n, 1) | full);
-  }
-  __syncthreads();
+__device__ __forceinline__ Piece pick_piece(const FwdParams& p, int xcd, int slot, int lane) {
+  const int rows = p.rows_total;
   constexpr int kPerLane = kFewRows / 64;
   const int per_lane = (rows + 63) / 64;
+  // every wave for itself, all loads in flight together (through LDS, one wave for all, the pieces were found 0.6 us later)
+  const auto live = __builtin_amdgcn_make_buffer_rsrc((void*)p.live_rows, 0, rows * 4, 0x00020000);
   int c[kPerLane], tiles = 0, longest = 0;
+#pragma unroll
+  for (int k = 0; k < kPerLane; ++k)
+    c[k] = k < per_lane ? (int)__builtin_amdgcn_raw_buffer_load_b32(live, 4 * (lane * per_lane + k), 0, 0) : 0;
   bool alike = true;
 #pragma unroll
   for (int k = 0; k < kPerLane; ++k) {
     const int r = lane * per_lane + k;
-    c[k] = -(1 << 20);  // (no row: no piece, whatever g)
-    if (k < per_lane && r < rows) {
-      c[k] = counts[r];
-      alike = alike && c[k] >= kFullRow;
-      c[k] &= kFullRow - 1;
+    const bool is_row = k < per_lane && r < rows;
+    alike = alike && (!is_row || c[k] == p.Tk);
+    if constexpr (IMM) {
+      const int i = r - (int)__umulhi((uint32_t)r, p.per_Tq) * p.Tq, at = i < p.Tq ? i : i - p.Tq;
+      if (!(at * kTile < p.protect_start + p.protect_len && p.protect_start < (at + 1) * kTile)) c[k] = 1;
     }
+    c[k] = is_row ? max(c[k], 1) : -(1 << 20);  // (no row: no piece, whatever g)
     tiles += max(c[k], 0);
     longest = max(longest, c[k]);
   }
@@ -1430,8 +1428,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   int row = -1, i, bh, seg = 0;
   int pieces = 1, piece = 0;  // a row cut into pieces (pick_piece): how many, and the first one's partial result
   if (FEW && !p.tickets && p.piece_units && !p.alike) {
-    uint16_t* counts = reinterpret_cast<uint16_t*>(smem + (PAIR ? kPairXchOff : kFiredOff));
-    const Piece mine = pick_piece<IMM>(p, counts, xcd, slot, tid, kThreads);
+    const Piece mine = pick_piece<IMM>(p, xcd, slot, lane);
     if (mine.row == -1) return;
     row = mine.row;
     seg = mine.index;
@@ -1440,11 +1437,11 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   }
   if (FEW && !p.tickets) {
     if (row < 0) {  // all rows alike: segments, or as many pieces
-      const int n = IMM ? 1 : p.nseg * p.equal_pieces, units = p.rows_total * n, share = (units + 7) / 8;
+      const int n = IMM ? 1 : p.parts, units = p.rows_total * n, share = (units + 7) / 8;
       const int unit = xcd * share + slot;
       if (slot >= share || unit >= units) return;
-      const int u = quotient(unit, p.Tq);
-      bh = quotient(u, n);
+      const int u = quotient(unit, p.Tq, p.per_Tq);
+      bh = n == 1 ? u : quotient(u, n, p.per_parts);
       seg = u - bh * n;
       i = unit - u * p.Tq;
       row = bh * p.Tq + i;
@@ -1453,7 +1450,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
         piece = row * pieces;
       }
     } else {
-      bh = quotient(row, p.Tq);
+      bh = quotient(row, p.Tq, p.per_Tq);
       i = row - bh * p.Tq;
     }
   } else {
@@ -1481,10 +1478,10 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
         }
       }
     }
-    bh = FEW ? quotient(row, p.Tq) : row / p.Tq;
+    bh = quotient(row, p.Tq, p.per_Tq);
     i = row - bh * p.Tq;
   }
-  const int b = FEW ? quotient(bh, p.H) : bh / p.H;
+  const int b = quotient(bh, p.H, p.per_H);
   const int64_t base = (int64_t)b * p.stride_b + (int64_t)(bh - b * p.H) * p.stride_h;
   uint16_t* ob = p.out + base;
   const int N = p.N;
@@ -1515,6 +1512,50 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
       }
     }
   };
+  char* const stages = smem + (PAIR ? grp * 4 * kStageBytes : 0);  // this group's stage buffers
+  auto lane_constants = [&]() {
+    ln.N = N;
+    ln.scale = p.scale;
+    ln.thr = p.thr;
+    ln.c = p.scale * 1.4426950408889634f;
+    ln.stride2 = (uint32_t)(p.stride_n * 2);
+    ln.krsrc = make_rsrc(p.k + base, head_bytes);
+    const uint32_t vt_row_bytes = (uint32_t)p.Tk * kTile * 2;  // one feature row of V^T: n_pad bf16
+    ln.vrsrc = FEW ? make_rsrc(p.v + base, head_bytes)
+                   : make_rsrc(p.vt + (size_t)bh * 128 * ((size_t)p.Tk * kTile), 128u * vt_row_bytes);
+    ln.lds_wave = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(LA_LDS char*)stages + 1024 * kChunks * wave);
+    ln.col = grp * kSub;
+#pragma unroll
+    for (int x = 0; x < kChunks; ++x) {
+      const int r = 4 * (kChunks * wave + x) + (lane >> 4);  // row inside the stage that this lane's piece belongs to
+      const int pc = lane & 15;                              // physical 16-byte chunk inside the 256-byte LDS row
+      ln.kdma[x] = (uint32_t)r * ln.stride2 + 16 * (pc ^ (r & 15));
+      if constexpr (FEW) {  // V stage: 64 token rows x 256 bytes; four rows' 64-byte pieces of a d-block meet all banks
+        ln.vdma[x] = (uint32_t)r * ln.stride2 + 16 * (pc ^ (4 * (r & 3)));
+        continue;
+      }
+      // V^T stage: 128 feature rows x 128 bytes; this lane's piece is row rv, physical 16-byte slot pv
+      const int rv = 8 * (kChunks * wave + x) + (lane >> 3), pv = lane & 7;
+      ln.vdma[x] = (uint32_t)rv * vt_row_bytes + 16 * (pv ^ ((rv >> 1) & 7));
+    }
+    const uint32_t lds0 = (uint32_t)(size_t)(LA_LDS char*)stages;
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) ln.kread[kk] = lds0 + lq * 256 + ((32 * kk) ^ (16 * (ln.hi ^ (lq & 15))));
+#pragma unroll
+    for (int cc = 0; cc < 4; ++cc) {
+      if constexpr (FEW) {  // d-block cc: row 4*hi + (lane>>2 & 3) of a chunk, 8-byte piece lane & 3 of its 16 features
+        const int r = 4 * ln.hi + ((lane >> 2) & 3), c = 4 * cc + 2 * ((lane >> 4) & 1) + ((lane >> 1) & 1);
+        ln.vread[cc] = lds0 + r * 256 + 16 * (c ^ (4 * (r & 3))) + 8 * (lane & 1);
+      } else {
+        ln.vread[cc] = lds0 + lq * 128 + ((32 * cc + 16 * ln.hi) ^ (16 * ((lq >> 1) & 7)));
+      }
+    }
+  };
+  auto clear_odd_v = [&]() {  // the odd V^T buffer is read (times P~ = 0) before it is first filled: make it finite
+#pragma unroll
+    for (int x = tid & (64 * kWaves - 1); x < kStageBytes / 16; x += 64 * kWaves)
+      *reinterpret_cast<uint4*>(stages + kVOff + kStageBytes + 16 * x) = uint4{0u, 0u, 0u, 0u};
+  };
   LiveWalk walk;
   int cnt, nruns, t_lo = 0, t_hi;
   if constexpr (FEW) {
@@ -1523,13 +1564,27 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
     // too, to have their pages mapped early, was slower: 20.3)
     const uint64_t skipped = LiveWalk::load(p.bits + (size_t)row * p.W, p.fresh, p.W);
     load_q();
-    walk.open(skipped, p.Tk, p.W, p.diagonal_first ? i : 0);
+    // what the main loop needs besides, while the mask row is on its way, and held here (the compiler would move it behind
+    // the wait): 32 rows x 16 tiles, four steps, 66 -> 63 us, 72 x 12, three, 58.9 -> 56.7
+    lane_constants();
+    if (!IMM) clear_odd_v();
+#pragma unroll
+    for (int x = 0; x < kChunks; ++x) asm volatile("" : "+v"(ln.kdma[x]), "+v"(ln.vdma[x]));
+#pragma unroll
+    for (int x = 0; x < 4; ++x) asm volatile("" : "+v"(ln.kread[2 * x]), "+v"(ln.kread[2 * x + 1]), "+v"(ln.vread[x]));
+    __builtin_amdgcn_sched_barrier(0);
+    if (p.fresh) {  // no wait for the mask row
+      walk.open(0, p.Tk, p.W, p.diagonal_first ? i : 0);
+      asm volatile("" : "+v"(walk.lo), "+v"(walk.hi));
+    } else {
+      walk.open(skipped, p.Tk, p.W, p.diagonal_first ? i : 0);
+    }
     walk.count(cnt, nruns);
     t_lo = segment_start(cnt, seg, p.nseg * pieces);
     t_hi = segment_start(cnt, seg + 1, p.nseg * pieces);
     if (p.fresh && p.newly_rows) {
-      const int n = IMM ? 1 : p.nseg * p.equal_pieces;
-      clear_counters(p, ((bh * n + seg) * p.Tq + i) * kThreads + tid, p.rows_total * n * kThreads);
+      const int n = IMM ? 1 : p.parts;
+      clear_counters(p, (row * n + seg) * kThreads + tid, p.rows_total * n * kThreads);
     }
   } else {
     cnt = (int)p.live_cnt[row];
@@ -1541,7 +1596,6 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   const_u32_ptr runs = (const_u32_ptr)(p.runs + (size_t)row * p.run_stride);
   int* flags = reinterpret_cast<int*>(smem + (PAIR ? kPairFlagsOff : kFlagsOff));
   float* xch = reinterpret_cast<float*>(smem + kPairXchOff);  // PAIR: group 1's row maxima, by parity of the tile
-  char* const stages = smem + (PAIR ? grp * 4 * kStageBytes : 0);  // this group's stage buffers
   // mask bits set by this workgroup during the call (thread 0 writes them, wave 0 reads them in the epilogue)
   uint64_t* fired_bits = reinterpret_cast<uint64_t*>(smem + kFiredOff);
   if (!FEW && p.build_next)
@@ -1552,42 +1606,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
     atomicAdd(p.stat_runs, (unsigned long long)nruns);
   }
 
-  ln.N = N;
-  ln.scale = p.scale;
-  ln.thr = p.thr;
-  ln.c = p.scale * 1.4426950408889634f;
-  ln.stride2 = (uint32_t)(p.stride_n * 2);
-  ln.krsrc = make_rsrc(p.k + base, head_bytes);
-  const uint32_t vt_row_bytes = (uint32_t)p.Tk * kTile * 2;  // one feature row of V^T: n_pad bf16
-  ln.vrsrc = FEW ? make_rsrc(p.v + base, head_bytes)
-                 : make_rsrc(p.vt + (size_t)bh * 128 * ((size_t)p.Tk * kTile), 128u * vt_row_bytes);
-  ln.lds_wave = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(LA_LDS char*)stages + 1024 * kChunks * wave);
-  ln.col = grp * kSub;
-#pragma unroll
-  for (int x = 0; x < kChunks; ++x) {
-    const int r = 4 * (kChunks * wave + x) + (lane >> 4);  // row inside the stage that this lane's piece belongs to
-    const int pc = lane & 15;                              // physical 16-byte chunk inside the 256-byte LDS row
-    ln.kdma[x] = (uint32_t)r * ln.stride2 + 16 * (pc ^ (r & 15));
-    if constexpr (FEW) {  // V stage: 64 token rows x 256 bytes; four rows' 64-byte pieces of a d-block meet all banks
-      ln.vdma[x] = (uint32_t)r * ln.stride2 + 16 * (pc ^ (4 * (r & 3)));
-      continue;
-    }
-    // V^T stage: 128 feature rows x 128 bytes; this lane's piece is row rv, physical 16-byte slot pv
-    const int rv = 8 * (kChunks * wave + x) + (lane >> 3), pv = lane & 7;
-    ln.vdma[x] = (uint32_t)rv * vt_row_bytes + 16 * (pv ^ ((rv >> 1) & 7));
-  }
-  const uint32_t lds0 = (uint32_t)(size_t)(LA_LDS char*)stages;
-#pragma unroll
-  for (int kk = 0; kk < 8; ++kk) ln.kread[kk] = lds0 + lq * 256 + ((32 * kk) ^ (16 * (ln.hi ^ (lq & 15))));
-#pragma unroll
-  for (int cc = 0; cc < 4; ++cc) {
-    if constexpr (FEW) {  // d-block cc: row 4*hi + (lane>>2 & 3) of a chunk, 8-byte piece lane & 3 of its 16 features
-      const int r = 4 * ln.hi + ((lane >> 2) & 3), c = 4 * cc + 2 * ((lane >> 4) & 1) + ((lane >> 1) & 1);
-      ln.vread[cc] = lds0 + r * 256 + 16 * (c ^ (4 * (r & 3))) + 8 * (lane & 1);
-    } else {
-      ln.vread[cc] = lds0 + lq * 128 + ((32 * cc + 16 * ln.hi) ^ (16 * ((lq >> 1) & 7)));
-    }
-  }
+  if constexpr (!FEW) lane_constants();
   const bool q_pinned = p.protect_len > 0 && i * kTile < p.protect_start + p.protect_len &&
                         p.protect_start < min(N, (i + 1) * kTile);
 
@@ -1639,7 +1658,9 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
     }
     auto advance = [&]() {
       if constexpr (FEW) {
-        walk.next(c_j);
+        // behind the last tile, one before the sequence: past the end of the buffer, so that no K is fetched that nobody
+        // needs (0.3-0.9 % of calls with few tiles a workgroup)
+        if (!walk.next(c_j)) c_j = -1;
       } else if (c_j + 1 < c_end) {
         ++c_j;
       } else if (c_run + 1 < nruns) {
@@ -1656,11 +1677,8 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
     // with this one on the scalar unit (a bool would travel between their blocks as a lane mask)
     const int j_tail = (N & (kTile - 1)) != 0 ? p.Tk - 1 : -1;
 
-    // prologue: the odd V^T buffer is read (times P~ = 0) before it is first filled: make it finite; K of
-    // stages 0 and 1; then S^T(0)
-    if (!IMM)
-      for (int x = tid & (64 * kWaves - 1); x < kStageBytes / 16; x += 64 * kWaves)
-        *reinterpret_cast<uint4*>(stages + kVOff + kStageBytes + 16 * x) = uint4{0u, 0u, 0u, 0u};
+    // prologue: K of stages 0 and 1; then S^T(0)
+    if (!FEW && !IMM) clear_odd_v();
     dma_stage<QB, kKOff>(ln.krsrc, ln.kdma, (uint32_t)(j_cur * kTile + ln.col) * ln.stride2, ln.lds_wave);
     dma_stage<QB, kKOff + kStageBytes>(
         ln.krsrc, ln.kdma, (uint32_t)(PAIR ? j_nxt * kTile + ln.col : j_cur * kTile + kSub) * ln.stride2, ln.lds_wave);
@@ -1919,6 +1937,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   // registers across the main loop)
   const_params_ptr e = (const_params_ptr)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(e));
+  uint64_t skipped_on_entry = 0;
   if constexpr (FEW) {
     static_assert(QB == 1, "one Q block per wave");
     // partial result of a segment or piece: O^T accumulators as the lanes hold them (1 KB per store), the row maxima
@@ -1974,11 +1993,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
         }
       }
     }
-    if (tid < 64) {
-      const bool wanted = lane < e->W && !e->fresh && (fired_word || e->live_next);
-      const uint64_t skipped = wanted ? e->bits[(size_t)row * e->W + lane] : 0ull;
-      finish_mask_row(*e, row, lane, skipped, fired_word);
-    }
+    skipped_on_entry = LiveWalk::load(e->bits + (size_t)row * e->W, e->fresh, e->W);
   } else {
     if (tid == 0 && newly && e->stat_newly) atomicAdd(e->stat_newly, (unsigned long long)newly);
   }
@@ -2013,7 +2028,10 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
       *reinterpret_cast<u32x4*>(ob + (int64_t)grow * p.stride_n + 8 * (tid & 15)) = o;
   }
 
-  if constexpr (FEW) return;
+  if constexpr (FEW) {  // behind the results, while these are on their way
+    if (tid < 64) finish_mask_row(*e, row, lane, skipped_on_entry, fired_word);
+    return;
+  }
   // ---- second epilogue: the Skip-List this row will walk in the NEXT call, compacted from the mask row as this call
   // leaves it: the row as it was on entry (nobody else writes it) OR the bits this workgroup set, which it kept in
   // LDS, so that nothing depends on when its own atomics become visible to its loads.  The row's list is private to
@@ -2033,45 +2051,60 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
 // segments, or of eight tiles' maxima, in flight together (call of 32 rows x 4 segments of 4 tiles 22.0 -> 20.7 us, of
 // 128 rows x 2 segments of 64 tiles 163 -> 147 us, against one load at a time); written past the L2 and read without
 // leaving a trace there (a step of 32 rows x 16 tiles 18.8 -> 16.5 us, of 72 x 12 24.1 -> 19.5, of 100 x 25 36.1 ->
-// 34.6; the stores alone give a third of it, nt in place of sc1 half).  All segments' loads at once: no faster with 8,
-// slower with 2-4. Rows that were cut into segments (FEW, nseg > 1): merges the segments' partial results and judges
-// the tiles. Workgroups 0 .. 4*rows-1: 32 Q rows each, one thread per (row, 8 features): O = sum_s 2^(c (m_s - M)) O_s
-// / sum_s ... . Workgroups 4*rows .. 5*rows-1: one Skip-Mask row each; two waves per segment walk its tiles with the
-// running maximum carried over from the segments before it (exactly the maximum a single pass would have), set the
-// row's mask bits and add the step's counters.
+// 34.6; the stores alone give a third of it, nt in place of sc1 half).  What a workgroup asks for goes out together, not the
+// partial O behind the row maxima or the tiles' maxima behind the mask row, and the workgroups with the longer chain, which
+// judge, come first: with that, 32 x 16, four steps, 68.9 -> 63.3 us, 72 x 12, three, 58.5 -> 56.6; judging last, the latter
+// 59.5, as its loads then wait behind all partial results.  All segments' O at once: slower (32 x 16 65.1).
+// Rows that were cut into segments (FEW, nseg > 1): merges the segments' partial results and judges the tiles.
+// Workgroups 0 .. rows-1: one Skip-Mask row each: the tiles' maxima are walked with the running maximum carried over
+// (exactly the maximum a single pass would have), the row's mask bits are set and the step's counters added.  Workgroups
+// rows .. 5*rows-1: 32 Q rows each, one thread per (row, 8 features): O = sum_s 2^(c (m_s - M)) O_s / sum_s ... .
 constexpr int kMergeThreads = 512;
+constexpr int kJudged = 64;  // tiles of a row that are judged in one trip to memory; longer rows go by segments, two waves each
 __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const FwdParams p) {
   touch_arguments(sizeof(FwdParams));
   const int tid = threadIdx.x, lane = tid & 63;
   const int nseg = p.nseg;
-  if ((int)blockIdx.x < 4 * p.rows_total) {
-    const int row = blockIdx.x >> 2, wave = blockIdx.x & 3;
-    const int i = row % p.Tq, bh = row / p.Tq;
+  if ((int)blockIdx.x >= p.rows_total) {
+    const int row = (blockIdx.x - p.rows_total) >> 2, wave = (blockIdx.x - p.rows_total) & 3;
+    const int bh = quotient(row, p.Tq, p.per_Tq), i = row - bh * p.Tq;
     const int lq = tid & 31, e = tid >> 5;  // e = 4 * d-block + group of four accumulator registers
     const int qrow = i * kTile + 32 * wave + lq;
     const float* ps = p.seg_stat + (size_t)row * nseg * 2 * kTile + 32 * wave + lq;
     const float* po = p.seg_o + ((size_t)row * nseg * 4 + wave) * 4096 + 256 * e + 4 * lq;
     const float c = p.scale * 1.4426950408889634f;
-    float top = kNoMax, l = 0.f;
-    for (int s = 0; s < nseg; ++s) top = fmaxf(top, ps[s * 2 * kTile]);
-    float4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
-    constexpr int kAhead = 4;  // segments whose loads are in flight together
-    for (int s0 = 0; s0 < nseg; s0 += kAhead) {
-      float m[kAhead], ls[kAhead];
-      f32x4 x[kAhead], y[kAhead];
+    constexpr int kAhead = 4;  // segments whose O is in flight together
+    float m[kMaxSegments], ls[kMaxSegments], top = kNoMax, l = 0.f;
+    f32x4 x[kAhead], y[kAhead];
+    auto load_o = [&](int s0) __attribute__((always_inline)) {
 #pragma unroll
       for (int u = 0; u < kAhead; ++u) {
-        const int s = min(s0 + u, nseg - 1);
-        m[u] = ps[s * 2 * kTile];
-        ls[u] = ps[s * 2 * kTile + kTile];
-        x[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(po + (size_t)s * 4 * 4096));
-        y[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(po + (size_t)s * 4 * 4096 + 128));
+        const float* at = po + (size_t)min(s0 + u, nseg - 1) * 4 * 4096;
+        x[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(at));
+        y[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(at + 128));
       }
+    };
+    // all segments' row maxima and sums and the first segments' O in flight together
+#pragma unroll
+    for (int s = 0; s < kMaxSegments; ++s) {
+      m[s] = kNoMax;
+      if (s / kAhead * kAhead >= nseg) continue;
+      m[s] = ps[min(s, nseg - 1) * 2 * kTile];
+      ls[s] = ps[min(s, nseg - 1) * 2 * kTile + kTile];
+    }
+    load_o(0);
+#pragma unroll
+    for (int s = 0; s < kMaxSegments; ++s) top = fmaxf(top, m[s]);
+    float4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s0 = 0; s0 < kMaxSegments; s0 += kAhead) {
+      if (s0 >= nseg) break;
+      if (s0 > 0) load_o(s0);
 #pragma unroll
       for (int u = 0; u < kAhead; ++u) {
-        if (s0 + u >= nseg || m[u] == kNoMax) continue;  // a segment without tiles has written no O
-        const float f = __builtin_amdgcn_exp2f((m[u] - top) * c);
-        l += f * ls[u];
+        if (s0 + u >= nseg || m[s0 + u] == kNoMax) continue;  // a segment without tiles has written no O
+        const float f = __builtin_amdgcn_exp2f((m[s0 + u] - top) * c);
+        l += f * ls[s0 + u];
         a.x += f * x[u].x; a.y += f * x[u].y; a.z += f * x[u].z; a.w += f * x[u].w;
         b.x += f * y[u].x; b.y += f * y[u].y; b.z += f * y[u].z; b.w += f * y[u].w;
       }
@@ -2083,14 +2116,15 @@ __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const Fwd
     o.y = pack_bf16x2(a.z * inv, a.w * inv);
     o.z = pack_bf16x2(b.x * inv, b.y * inv);
     o.w = pack_bf16x2(b.z * inv, b.w * inv);
-    uint16_t* out = p.out + (int64_t)(bh / p.H) * p.stride_b + (int64_t)(bh % p.H) * p.stride_h;
+    const int batch = quotient(bh, p.H, p.per_H);
+    uint16_t* out = p.out + (int64_t)batch * p.stride_b + (int64_t)(bh - batch * p.H) * p.stride_h;
     *reinterpret_cast<uint4*>(out + (int64_t)qrow * p.stride_n + 8 * e) = o;
     return;
   }
   constexpr int kPairs = kMergeThreads / 128;
   __shared__ uint64_t fired[2 * kPairs][64];  // per wave (half of a segment's Q rows): tiles that fire for its rows
-  const int row = blockIdx.x - 4 * p.rows_total;
-  const int i = row % p.Tq;
+  const int row = blockIdx.x;
+  const int i = row - quotient(row, p.Tq, p.per_Tq) * p.Tq;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = tid & 127, pair = wave >> 1;
   LiveWalk walk;
@@ -2100,16 +2134,48 @@ __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const Fwd
   float seg_max[kMaxSegments];
 #pragma unroll
   for (int x = 0; x < kMaxSegments; ++x)
-    if (x < 4 || nseg > 4)
+    if (p.Tk > kJudged && (x < 4 || nseg > 4))
       seg_max[x] = p.seg_stat[((size_t)row * nseg + min(x, nseg - 1)) * 2 * kTile + r];
-  walk.open(skipped, p.Tk, p.W, p.diagonal_first ? i : 0);
-  walk.count(cnt, nruns);
   const bool q_pinned = p.protect_len > 0 && i * kTile < p.protect_start + p.protect_len &&
                         p.protect_start < min(p.N, (i + 1) * kTile);
   uint64_t mine = 0;  // lane w: bits of mask word w
-  if (p.thr > -INFINITY && !q_pinned) {
-    const bool qvalid = i * kTile + r < p.N;
-    const float* mloc = p.seg_mloc + (size_t)row * p.Tk * kTile + r;
+  const bool qvalid = i * kTile + r < p.N;
+  const float* mloc = p.seg_mloc + (size_t)row * p.Tk * kTile + r;
+  const int start = p.diagonal_first ? i : 0;
+  if (p.thr > -INFINITY && !q_pinned && p.Tk <= kJudged) {
+    // Short rows: each pair of waves takes a quarter of the row's places in visiting order, whatever the segments were, and
+    // asks for the maxima of all of them, skipped or not, before the mask row is here: one trip to memory.  The quarters'
+    // maxima meet in LDS.
+    constexpr int kEach = kJudged / kPairs;
+    __shared__ float quarter[kPairs][kTile];
+    const int each = (p.Tk + kPairs - 1) / kPairs, v0 = pair * each, count = min(each, p.Tk - v0);
+    const uint64_t dead = (uint32_t)__builtin_amdgcn_readfirstlane((int)skipped) |
+                          (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(skipped >> 32)) << 32;
+    auto tile = [&](int u) { return start + v0 + u >= p.Tk ? start + v0 + u - p.Tk : start + v0 + u; };
+    float m[kEach], top = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < kEach; ++u)
+      if (u < count) m[u] = mloc[tile(u) * kTile];
+#pragma unroll
+    for (int u = 0; u < kEach; ++u)
+      if (u < count && !(dead >> tile(u) & 1)) top = fmaxf(top, m[u]);
+    quarter[pair][r] = top;
+    __syncthreads();
+    float run = -INFINITY;
+    for (int x = 0; x < pair; ++x) run = fmaxf(run, quarter[x][r]);
+#pragma unroll
+    for (int u = 0; u < kEach; ++u) {
+      if (u >= count || (dead >> tile(u) & 1)) continue;
+      run = fmaxf(run, m[u]);
+      if (__all(!qvalid || (m[u] - run) * p.scale <= p.thr) && lane == 0) {
+        const bool k_pinned = p.protect_len > 0 && tile(u) * kTile < p.protect_start + p.protect_len &&
+                              p.protect_start < min(p.N, (tile(u) + 1) * kTile);
+        if (!k_pinned) mine |= 1ull << tile(u);
+      }
+    }
+  } else if (p.thr > -INFINITY && !q_pinned) {
+    walk.open(skipped, p.Tk, p.W, start);
+    walk.count(cnt, nruns);
     for (int s = pair; s < nseg; s += kPairs) {
       const int t0 = segment_start(cnt, s, nseg), t1 = segment_start(cnt, s + 1, nseg);
       if (t0 == t1) continue;
@@ -2149,7 +2215,10 @@ __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const Fwd
     for (int x = 0; x < kPairs; ++x) f |= fired[2 * x][lane] & fired[2 * x + 1][lane];
     finish_mask_row(*(const_params_ptr)__builtin_amdgcn_kernarg_segment_ptr(), row, lane, skipped, f);
   }
-  if (tid == 0 && p.stat_newly && !p.fresh) {
+  if (wave == 1 && p.stat_newly && !p.fresh) {
+    walk.open(skipped, p.Tk, p.W, start);
+    walk.count(cnt, nruns);
+    if (lane != 0) return;
     atomicAdd(p.stat_skipped_in, (unsigned long long)(p.Tk - cnt));
     atomicAdd(p.stat_runs, (unsigned long long)nruns);
   }

@@ -111,3 +111,14 @@ def test_every_row_under_sparse_masks(heads, tiles, live):
             assert torch.isfinite(out[0, x, r0:r1]).all()
             # weights and result are rounded to bf16 (2^-9 each) of values up to max|O|
             assert d.max().item() <= 1e-2 * ref.abs().max().clamp(min=1e-3).item(), (x, i0)
+
+
+@pytest.mark.parametrize("diagonal_first", [False, True])
+@pytest.mark.parametrize("batch,heads,tokens,text", [(1, 1, 128 * 5 - 60, 0), (2, 1, 128 * 6, 0), (1, 1, 128 * 7, 0),
+                                                     (1, 1, 128 * 33 + 1, 0), (1, 1, 128 * 49, 200), (3, 1, 128 * 17, 0)])
+def test_marking_in_quarters(batch, heads, tokens, text, diagonal_first):
+    """The merge pass judges a short row's tiles in quarters of its places, whatever the segments were: quarters
+    with a remainder or empty, batch entries; masks and outputs of three steps against the oracle."""
+    assert parity.path_of(batch, heads, tokens).nseg > 1
+    parity.run_sequence_check(layer(heads, tokens, text, batch), steps=3, thresholds=[-2.0, -1.0, -0.4],
+                              diagonal_first=diagonal_first)
