@@ -30,6 +30,9 @@ struct lite_attn_mask {
   la::ListLayout ll;
   uint64_t* d_bits;
   char* d_lists;      // Skip-Lists and row ranking (layout ll); kept between calls
+  int table_calls;    // calls that the row schedule has served; 0: there is none that can serve another
+  float loosest;        // largest threshold of the trajectory's calls so far (-inf: none has marked)
+  float table_loosest;  // what it was when the row schedule was made
   bool lists_valid;   // the lists describe the mask as it stands (left by the previous call's epilogue)
   unsigned long long* d_stats;  // [max_steps][3]: skipped on entry, newly marked, Skip-List runs
   uint32_t* d_newly;            // few rows, behind them: [kFewRows] tiles that step 0 marked, per row (part of step
@@ -88,12 +91,14 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     }
     // ranking a head's rows needs the counts of all of them, dealing the ranked chunks to the XCDs those of all heads:
     // two small kernels of their own
-    e = launch_order_rows(live_cnt, g.BH, g.Tq, g.Tk, order, chunk_work, stream);
-    if (e != hipSuccess) return e;
-    e = launch_deal_rows(chunk_work, order, g.BH, g.Tq, g.chunks, g.per_xcd, slots, xcd_rows, stream);
-    if (e != hipSuccess) return e;
+    if (a.table_calls == 0) {
+      e = launch_order_rows(live_cnt, g.BH, g.Tq, g.Tk, order, chunk_work, stream);
+      if (e != hipSuccess) return e;
+      e = launch_deal_rows(chunk_work, order, g.BH, g.Tq, g.chunks, g.per_xcd, slots, xcd_rows, stream);
+      if (e != hipSuccess) return e;
+    }
     e = launch_transpose_v(static_cast<const uint16_t*>(a.v), vt, d.stride_b, d.stride_h, d.stride_n, g.BH, d.heads,
-                           d.seqlen, g.Tk, stream);
+                           d.seqlen, g.Tk, a.table_calls > 0 ? slots + g.per_xcd - 1 : nullptr, g.per_xcd, stream);
     if (e != hipSuccess) return e;
   }
   FwdParams p;
@@ -116,6 +121,7 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
   p.tickets = !tickets ? nullptr : table ? slots + g.per_xcd - 1 : slots;
   p.ticket_stride = table ? g.per_xcd : kTicketWords;
   p.resident = draws ? kResident : kNoDraws;
+  p.table_calls = a.table_calls;
   p.build_next = a.build_next ? 1 : 0;
   p.diagonal_first = diagonal_first;
   if (few) {
@@ -173,7 +179,10 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     // kernel deals chunks of them in turn
     if (table) {
       p.scheduled = 1;
-      e = launch_schedule_rows(a.bits, (int)g.rows, g.Tk, g.W, g.per_xcd, slots, xcd_rows, stream);
+      if (a.table_calls == 0)
+        e = launch_schedule_rows(a.bits, (int)g.rows, g.Tk, g.W, g.per_xcd, slots, xcd_rows, stream);
+      else if (draws)
+        e = launch_clear_tickets(p.tickets, p.ticket_stride, stream);
       if (e != hipSuccess) return e;
     }
   }
@@ -230,6 +239,8 @@ int init_common(const lite_attn_desc_t* desc, lite_attn_ctx* ctx, lite_attn_mask
   m->ll = la::list_layout(m->geo);
   m->d_lists = nullptr;
   m->lists_valid = false;
+  m->table_calls = 0;
+  m->loosest = m->table_loosest = -INFINITY;
   m->ctx = nullptr;
   m->stream = nullptr;
   m->next_step = 0;
@@ -357,8 +368,19 @@ int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_a
   a.empty = step == 0 || m->empty;
   a.lists_ready = ready;
   a.build_next = true;
+  // The row schedule serves up to kTableCalls calls of a trajectory, as long as no call has marked with a looser threshold
+  // than the mask that it was made for has seen: what a threshold marks, it marks nearly all at once.
+  if (step == 0) m->loosest = -INFINITY;
+  const bool keeps = la::keeps_table(m->geo) && (m->geo.nseg == 0 || !a.empty);
+  const bool ready_table = keeps && step != 0 && m->table_calls < la::kTableCalls && m->table_loosest == m->loosest;
+  a.table_calls = ready_table ? m->table_calls : 0;
+  const int served = keeps ? a.table_calls + 1 : 0;
+  m->table_calls = 0;
   LA_HIP(la::launch_call(d, m->geo, m->ll, m->d_lists, scratch_of(m), a, stream, ev ? ev[1] : nullptr));
   m->lists_valid = m->geo.nseg == 0;  // (calls with few or short rows keep no lists)
+  m->table_calls = served;
+  m->table_loosest = m->loosest;
+  m->loosest = std::fmax(m->loosest, threshold);
   m->empty = a.empty && !(threshold > -INFINITY);
   if (ev) LA_HIP(hipEventRecord(ev[2], stream));
   m->next_step = step + 1;
@@ -438,6 +460,7 @@ int lite_attn_mask_import(lite_attn_mask_t* m, const uint64_t* host_bits, size_t
   LA_HIP(hipStreamSynchronize(stream_of(m)));
   m->next_step = next_step;
   m->empty = false;
+  m->table_calls = 0;
   m->lists_valid = false;  // the next call rebuilds its Skip-Lists from the imported mask
   return LITE_ATTN_OK;
 }

@@ -176,6 +176,10 @@ Geometry geometry(const lite_attn_desc_t& d) {
   return g;
 }
 
+// A row schedule is an order of the rows, good for any mask; when later calls have marked some more tiles, the lengths it was
+// made for are a little off, and rows are drawn.
+bool keeps_table(const Geometry& g) { return g.nseg == 0 || (g.rows > kFewRows && g.rows <= kSchedRows); }
+
 ListLayout list_layout(const Geometry& g) {
   ListLayout l;
   size_t at = 0;

@@ -72,6 +72,7 @@ struct FwdParams {
   const uint32_t* xcd_rows;              // [8] rows dealt to each XCD
   uint32_t* tickets;                     // [8] at ticket_stride: rows drawn so far from each XCD's list beyond the first
   int ticket_stride;                     //   `resident`; null: few rows, each workgroup has its place
+  int table_calls = 0;                   // calls that the table has served before this one
   int resident;                          // places per XCD that go by the grid: kResident, or, where rows are too short to be
                                          //   drawn, kNoDraws
   // build_next != 0: the epilogue rewrites runs / nruns / live_cnt for the NEXT call from the mask this call leaves;
@@ -185,7 +186,15 @@ struct CallArgs {
   const uint32_t* live_rows;   // few rows that may be cut into pieces: live tiles, left by the previous call; null: to
   uint32_t* live_next;         //   be counted.  The same for the next call, or null
   bool lists_ready, build_next;
+  int table_calls;             // calls of the trajectory that the row schedule in place has served; 0: to be made
 };
+// A row schedule made once and used by several calls: an order of the rows is good for any mask.  us, made for every call ->
+// for up to eight (a launch of 10 us, or two of 17, less; where rows are drawn, one of 3 more): six steps of 640 rows of
+// 8 tiles 340 -> 308, three of 888 x 37 666 -> 660, four of 1200 x 40 979 -> 966, six of 600 x 200 3682 -> 3645, ten of
+// 3072 x 256 27523 -> 27342.
+bool keeps_table(const Geometry& g);  // layers that make one
+constexpr int kTableCalls = 8;
+
 hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListLayout& ll, char* lists, char* scratch,
                        const CallArgs& a, hipStream_t stream, hipEvent_t mid);
 int hip_fail(hipError_t e);  // remembers e for lite_attn_last_hip_error() and maps it to a lite_attn_error
@@ -197,7 +206,8 @@ hipError_t launch_count_rows(const uint64_t* bits, int rows, int Tk, int W, uint
 hipError_t launch_compact(const uint64_t* bits, int rows, int Tq, int Tk, int W, int diagonal_first, int run_stride,
                           uint32_t* runs, uint32_t* nruns, uint32_t* live_cnt, hipStream_t st);
 hipError_t launch_transpose_v(const uint16_t* v, uint16_t* vt, int64_t stride_b, int64_t stride_h, int64_t stride_n,
-                              int BH, int H, int N, int Tk, hipStream_t st);
+                              int BH, int H, int N, int Tk, uint32_t* tickets, int ticket_stride, hipStream_t st);
+hipError_t launch_clear_tickets(uint32_t* tickets, int stride, hipStream_t st);
 hipError_t launch_order_rows(const uint32_t* live_cnt, int BH, int Tq, int Tk, uint32_t* order, uint32_t* chunk_work,
                              hipStream_t st);
 hipError_t launch_deal_rows(const uint32_t* chunk_work, const uint32_t* order, int BH, int Tq, int chunks, int per_xcd,

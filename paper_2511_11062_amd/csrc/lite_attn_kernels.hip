@@ -115,6 +115,11 @@ __device__ __forceinline__ void touch_arguments(size_t bytes) {
   asm volatile("" ::"s"(x0), "s"(x1), "s"(x2), "s"(x3), "s"(x4), "s"(x5));
 }
 
+// Tickets of a table that serves another call (a launch of 3 us; the table 10).
+__global__ void clear_tickets_kernel(uint32_t* tickets, int stride) {
+  if (threadIdx.x < 8) tickets[(size_t)threadIdx.x * stride] = 0;
+}
+
 __global__ void clear_state_kernel(uint64_t* bits, size_t words, unsigned long long* stats, size_t nstats) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -522,10 +527,12 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
 // kernel holds its P~ values.  One workgroup transposes one 128 x 128 tile through LDS, twice: once with
 // transposing reads, once to regroup, because a wave that stores the transposed pieces as it reads them writes 64
 // separate 16-byte pieces.  Bound by memory: 55 -> 39 us for 12 heads x 32760 tokens (3.7 -> 5.1 TB/s; a large copy
-// reaches 4.9).
+// reaches 4.9).  `tickets`, if not null, are cleared on the way: those of a table that serves another call.
 __global__ __launch_bounds__(256) void transpose_v_kernel(const uint16_t* __restrict__ v, uint16_t* __restrict__ vt,
                                                            int64_t stride_b, int64_t stride_h, int64_t stride_n,
-                                                           int H, int N, int Tk) {
+                                                           int H, int N, int Tk, uint32_t* __restrict__ tickets,
+                                                           int ticket_stride) {
+  if (tickets && blockIdx.x == 0 && threadIdx.x < 8) tickets[(size_t)threadIdx.x * ticket_stride] = 0;
   constexpr int kRow = 256 + 16;  // padded LDS row (bytes)
   __shared__ __attribute__((aligned(16))) char tile[128 * kRow];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1455,8 +1462,12 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
     }
   } else {
     int cut = 0;  // rows of each eighth that are cut
-    if (FEW && p.cut_rows > 0)
+    if (FEW && p.cut_rows > 0) {
       cut = !p.scheduled || p.slots[(size_t)(xcd + 1) * p.per_xcd - kTableTail] ? p.cut_rows : 0;
+      // (a table made by an earlier call, for an empty mask: whether any call since has marked a tile)
+      for (int x = 1; cut > 0 && x <= p.table_calls; ++x)
+        if (p.stat_newly[-3 * x]) cut = 0;
+    }
     if (slot < p.resident) row = row_at_place<FEW>(p, xcd, slot, cut);
     if (row < 0) {
       if (p.resident == kNoDraws) return;
@@ -2250,6 +2261,11 @@ hipError_t launch_clear(uint64_t* bits, size_t words, unsigned long long* stats,
   return hipGetLastError();
 }
 
+hipError_t launch_clear_tickets(uint32_t* tickets, int stride, hipStream_t st) {
+  hipLaunchKernelGGL(clear_tickets_kernel, dim3(1), dim3(64), 0, st, tickets, stride);
+  return hipGetLastError();
+}
+
 hipError_t launch_compact(const uint64_t* bits, int rows, int Tq, int Tk, int W, int diagonal_first, int run_stride,
                           uint32_t* runs, uint32_t* nruns, uint32_t* live_cnt, hipStream_t st) {
   hipLaunchKernelGGL(compact_skiplist, dim3((rows + 4 * kRowsPerWave - 1) / (4 * kRowsPerWave)), dim3(256), 0, st, bits,
@@ -2258,9 +2274,9 @@ hipError_t launch_compact(const uint64_t* bits, int rows, int Tq, int Tk, int W,
 }
 
 hipError_t launch_transpose_v(const uint16_t* v, uint16_t* vt, int64_t stride_b, int64_t stride_h, int64_t stride_n,
-                              int BH, int H, int N, int Tk, hipStream_t st) {
+                              int BH, int H, int N, int Tk, uint32_t* tickets, int ticket_stride, hipStream_t st) {
   hipLaunchKernelGGL(transpose_v_kernel, dim3((unsigned)(BH * Tk)), dim3(256), 0, st, v, vt, stride_b, stride_h,
-                     stride_n, H, N, Tk);
+                     stride_n, H, N, Tk, tickets, ticket_stride);
   return hipGetLastError();
 }
 

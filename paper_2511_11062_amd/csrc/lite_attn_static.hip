@@ -71,6 +71,7 @@ extern "C" int lite_attn_fwd_static(const void* q, const void* k, const void* v,
   a.arrive = nullptr;  // (nothing that outlives a call could be vouched for: overlapping calls are a mistake, once)
   a.lists_ready = false;  // lists rebuilt from the caller's mask on every call, none left behind for a next one
   a.build_next = false;
+  a.table_calls = 0;
   const hipError_t e = la::launch_call(*desc, geo, ll, ptr, ptr + ll.total, a, stream, nullptr);
   return e == hipSuccess ? LITE_ATTN_OK : la::hip_fail(e);
 }

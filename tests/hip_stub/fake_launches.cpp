@@ -64,8 +64,13 @@ hipError_t launch_deal_rows(const uint32_t* chunk_work, const uint32_t* order, i
 }
 
 hipError_t launch_transpose_v(const uint16_t*, uint16_t* vt, int64_t, int64_t, int64_t, int BH, int, int, int Tk,
-                              hipStream_t) {
+                              uint32_t* tickets, int ticket_stride, hipStream_t st) {
   memset(vt, 0, sizeof(uint16_t) * (size_t)BH * 128 * ((size_t)Tk * 128));
+  return tickets ? launch_clear_tickets(tickets, ticket_stride, st) : hipSuccess;
+}
+
+hipError_t launch_clear_tickets(uint32_t* tickets, int stride, hipStream_t) {
+  for (int x = 0; x < 8; ++x) tickets[(size_t)x * stride] = 0;
   return hipSuccess;
 }
 
