@@ -2058,14 +2058,16 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   }
 }
 
-// Bound by latency and by the partials' way through memory (64 KB per segment; 16 MB for 256 segments): loads of four
+// Bound by latency and by the partials' way through memory (64 KB per segment; 16 MB for 256 segments): loads of several
 // segments, or of eight tiles' maxima, in flight together (call of 32 rows x 4 segments of 4 tiles 22.0 -> 20.7 us, of
 // 128 rows x 2 segments of 64 tiles 163 -> 147 us, against one load at a time); written past the L2 and read without
 // leaving a trace there (a step of 32 rows x 16 tiles 18.8 -> 16.5 us, of 72 x 12 24.1 -> 19.5, of 100 x 25 36.1 ->
 // 34.6; the stores alone give a third of it, nt in place of sc1 half).  What a workgroup asks for goes out together, not the
 // partial O behind the row maxima or the tiles' maxima behind the mask row, and the workgroups with the longer chain, which
 // judge, come first: with that, 32 x 16, four steps, 68.9 -> 63.3 us, 72 x 12, three, 58.5 -> 56.6; judging last, the latter
-// 59.5, as its loads then wait behind all partial results.  All segments' O at once: slower (32 x 16 65.1).
+// 59.5, as its loads then wait behind all partial results.  O of two segments at a time in flight: 32 x 16
+// 63.5 -> 61.8 us against four (eight 63.7, one 69.8), 72 x 12 56.3 -> 55.6 (60.5, 55.1), 100 x 25 dense, three steps,
+// 106.1 -> 101.4, 64 x 64 131.4 -> 130.5: all workgroups ask at the same moment.
 // Rows that were cut into segments (FEW, nseg > 1): merges the segments' partial results and judges the tiles.
 // Workgroups 0 .. rows-1: one Skip-Mask row each: the tiles' maxima are walked with the running maximum carried over
 // (exactly the maximum a single pass would have), the row's mask bits are set and the step's counters added.  Workgroups
@@ -2084,7 +2086,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const Fwd
     const float* ps = p.seg_stat + (size_t)row * nseg * 2 * kTile + 32 * wave + lq;
     const float* po = p.seg_o + ((size_t)row * nseg * 4 + wave) * 4096 + 256 * e + 4 * lq;
     const float c = p.scale * 1.4426950408889634f;
-    constexpr int kAhead = 4;  // segments whose O is in flight together
+    constexpr int kAhead = 2;  // segments whose O is in flight together
     float m[kMaxSegments], ls[kMaxSegments], top = kNoMax, l = 0.f;
     f32x4 x[kAhead], y[kAhead];
     auto load_o = [&](int s0) __attribute__((always_inline)) {
