@@ -86,19 +86,13 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     uint32_t* chunk_work = reinterpret_cast<uint32_t*>(lists + ll.chunk_work);
     if (!a.lists_ready) {
       e = launch_compact(a.bits, (int)g.rows, g.Tq, g.Tk, g.W, diagonal_first, g.run_stride, runs, nruns, live_cnt,
-                         stream);
+                         xcd_rows + 8, stream);
       if (e != hipSuccess) return e;
     }
-    // ranking a head's rows needs the counts of all of them, dealing the ranked chunks to the XCDs those of all heads:
-    // two small kernels of their own
-    if (a.table_calls == 0) {
-      e = launch_order_rows(live_cnt, g.BH, g.Tq, g.Tk, order, chunk_work, stream);
-      if (e != hipSuccess) return e;
-      e = launch_deal_rows(chunk_work, order, g.BH, g.Tq, g.chunks, g.per_xcd, slots, xcd_rows, stream);
-      if (e != hipSuccess) return e;
-    }
-    e = launch_transpose_v(static_cast<const uint16_t*>(a.v), vt, d.stride_b, d.stride_h, d.stride_n, g.BH, d.heads,
-                           d.seqlen, g.Tk, a.table_calls > 0 ? slots + g.per_xcd - 1 : nullptr, g.per_xcd, stream);
+    const RowSchedule sched = {live_cnt, order, chunk_work, slots, xcd_rows, xcd_rows + 8, g.Tq, g.Tk,
+                               a.table_calls == 0 ? g.BH : 0, g.chunks, g.per_xcd};
+    e = launch_prepare_rows(sched, static_cast<const uint16_t*>(a.v), vt, d.stride_b, d.stride_h, d.stride_n, g.BH, d.heads,
+                            d.seqlen, g.Tq, g.Tk, a.table_calls > 0 ? slots + g.per_xcd - 1 : nullptr, g.per_xcd, stream);
     if (e != hipSuccess) return e;
   }
   FwdParams p;
@@ -474,7 +468,7 @@ int lite_attn_skipruns_export(lite_attn_mask_t* m, uint32_t* host_runs, uint32_t
   // (if the lists were already in place -- left by the last call's epilogue -- this writes the same values again)
   LA_HIP(la::launch_compact(m->d_bits, (int)g.rows, g.Tq, g.Tk, g.W, m->desc.flags & LITE_ATTN_ORDER_DIAGONAL_FIRST,
                             g.run_stride, runs, nruns, reinterpret_cast<uint32_t*>(m->d_lists + m->ll.live_cnt),
-                            stream));
+                            reinterpret_cast<uint32_t*>(m->d_lists + m->ll.xcd_rows) + 8, stream));
   LA_HIP(hipMemcpyAsync(host_runs, runs, sizeof(uint32_t) * (size_t)g.rows * g.run_stride, hipMemcpyDeviceToHost,
                         stream));
   LA_HIP(hipMemcpyAsync(host_nruns, nruns, sizeof(uint32_t) * (size_t)g.rows, hipMemcpyDeviceToHost, stream));

@@ -176,8 +176,8 @@ Geometry geometry(const lite_attn_desc_t& d) {
   return g;
 }
 
-// A row schedule is an order of the rows, good for any mask; when later calls have marked some more tiles, the lengths it was
-// made for are a little off, and rows are drawn.
+// A row schedule is an order of the rows, good for any mask; when later calls have marked some more tiles, the lengths it
+// was made for are a little off, and rows are drawn.
 bool keeps_table(const Geometry& g) { return g.nseg == 0 || (g.rows > kFewRows && g.rows <= kSchedRows); }
 
 ListLayout list_layout(const Geometry& g) {
@@ -194,7 +194,7 @@ ListLayout list_layout(const Geometry& g) {
   l.slots = at;
   at += up256(sizeof(uint32_t) * 8 * (size_t)g.per_xcd);
   l.xcd_rows = at;
-  at += up256(sizeof(uint32_t) * 8);
+  at += up256(sizeof(uint32_t) * 9);
   l.runs = at;
   at += up256(sizeof(uint32_t) * (size_t)g.rows * g.run_stride);
   l.total = at;

@@ -51,7 +51,7 @@ constexpr int dealt_chunk(int group, int xcd) { return 8 * group + ((xcd - group
 struct FwdParams {
   const uint16_t* q;
   const uint16_t* k;
-  const uint16_t* vt;                    // V^T scratch: [B*H][128][128*Tk], written by launch_transpose_v
+  const uint16_t* vt;                    // V^T scratch: [B*H][128][128*Tk], written by launch_prepare_rows
   uint16_t* out;
   int64_t stride_b, stride_h, stride_n;  // elements
   int H, N, Tq, Tk, W;                   // W = uint64 words per mask row
@@ -68,7 +68,7 @@ struct FwdParams {
   int protect_start, protect_len;
   int rows_total;                        // B*H*Tq
   const uint32_t* slots;                 // [8][per_xcd]: the row (index into [B*H][Tq]) that workgroup `slot` of an
-  int per_xcd;                           //   XCD computes, written by launch_deal_rows; entries >= xcd_rows[xcd] unused
+  int per_xcd;                           //   XCD computes, written by launch_prepare_rows; entries >= xcd_rows[xcd] unused
   const uint32_t* xcd_rows;              // [8] rows dealt to each XCD
   uint32_t* tickets;                     // [8] at ticket_stride: rows drawn so far from each XCD's list beyond the first
   int ticket_stride;                     //   `resident`; null: few rows, each workgroup has its place
@@ -107,8 +107,8 @@ struct FwdParams {
   uint32_t per_Tq, per_H, per_parts = 0;  // reciprocals for the kernel's short division
 };
 
-// a / b (a >= 0, b >= 1, a + b < 2^31) with the host's per_b = reciprocal(b): a * per_b / 2^32 is short of a / b by less than
-// one.  On the GPU a few scalar instructions; a workgroup with few tiles waits for its indexes before its first load.
+// a / b (a >= 0, b >= 1, a + b < 2^31) with the host's per_b = reciprocal(b): a * per_b / 2^32 is short of a / b by less
+// than one.  On the GPU a few scalar instructions; a workgroup with few tiles waits for its indexes before its first load.
 constexpr uint32_t reciprocal(int b) { return b == 1 ? 0xffffffffu : (uint32_t)(((uint64_t)1 << 32) / (uint32_t)b); }
 constexpr int quotient(int a, int b, uint32_t per_b) {
   const int q = (int)((uint64_t)(uint32_t)a * per_b >> 32);
@@ -146,7 +146,7 @@ struct ListLayout {
   size_t order;     // [BH][Tq] uint32 row ranking (none with few or short rows)
   size_t chunk_work;  // [chunks] uint32 work of each chunk (live tiles + a per-row constant)
   size_t slots;     // [8][per_xcd] uint32 schedule table
-  size_t xcd_rows;  // [8] uint32
+  size_t xcd_rows;  // [8] uint32, and a counter of prepare_rows_kernel, zero between launches
   size_t runs;      // [rows][run_stride] uint32 Skip-List
   size_t total;
 };
@@ -164,6 +164,13 @@ struct ScratchLayout {
   size_t seg_o, seg_stat, seg_mloc, total;
 };
 ScratchLayout scratch_layout(const Geometry& g, int nseg = 1);
+
+// The row schedule of rows with Skip-Lists, made beside V^T; BH 0: an earlier call's serves.
+struct RowSchedule {
+  const uint32_t* live_cnt;
+  uint32_t *order, *chunk_work, *slots, *xcd_rows, *heads_ranked;
+  int Tq, Tk, BH, chunks, per_xcd;
+};
 
 // lite_attn.cpp: the launches of one attention call on `stream`.  lists_ready: the Skip-Lists in `lists` already
 // describe the mask (left by the previous call's epilogue); otherwise the compaction kernel builds them first.  Then
@@ -204,14 +211,11 @@ hipError_t launch_clear(uint64_t* bits, size_t words, unsigned long long* stats,
 hipError_t launch_count_rows(const uint64_t* bits, int rows, int Tk, int W, uint32_t* live, uint32_t* arrive,
                              hipStream_t st);
 hipError_t launch_compact(const uint64_t* bits, int rows, int Tq, int Tk, int W, int diagonal_first, int run_stride,
-                          uint32_t* runs, uint32_t* nruns, uint32_t* live_cnt, hipStream_t st);
-hipError_t launch_transpose_v(const uint16_t* v, uint16_t* vt, int64_t stride_b, int64_t stride_h, int64_t stride_n,
-                              int BH, int H, int N, int Tk, uint32_t* tickets, int ticket_stride, hipStream_t st);
+                          uint32_t* runs, uint32_t* nruns, uint32_t* live_cnt, uint32_t* heads_ranked, hipStream_t st);
+hipError_t launch_prepare_rows(const RowSchedule& sched, const uint16_t* v, uint16_t* vt, int64_t stride_b, int64_t stride_h,
+                               int64_t stride_n, int BH, int H, int N, int Tq, int Tk, uint32_t* tickets, int ticket_stride,
+                               hipStream_t st);
 hipError_t launch_clear_tickets(uint32_t* tickets, int stride, hipStream_t st);
-hipError_t launch_order_rows(const uint32_t* live_cnt, int BH, int Tq, int Tk, uint32_t* order, uint32_t* chunk_work,
-                             hipStream_t st);
-hipError_t launch_deal_rows(const uint32_t* chunk_work, const uint32_t* order, int BH, int Tq, int chunks, int per_xcd,
-                            uint32_t* slots, uint32_t* xcd_rows, hipStream_t st);
 hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int Tk, int W, int per_xcd, uint32_t* slots,
                                 uint32_t* xcd_rows, hipStream_t st);
 hipError_t launch_fwd(const FwdParams& p, bool immediate, hipStream_t st);

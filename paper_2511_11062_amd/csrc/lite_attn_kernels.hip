@@ -4,11 +4,11 @@
 //   compact_skiplist     : Skip-Mask row -> run-length list of its live K/V tiles, (start,end) per run
 //                          (Implementation, "Producer and Skip-List Optimization"); only at the start of a trajectory
 //                          or after a mask import: the fused kernel's epilogue builds the next call's Skip-Lists
-//   order_rows_kernel    : per head, Q-tile rows ranked by Skip-List length (the launch order of the fused kernel)
-//   deal_rows_kernel     : the ranked rows dealt to the XCDs
+//   prepare_rows_kernel  : per head, Q-tile rows ranked by Skip-List length and the ranked rows dealt to the XCDs (the
+//                          launch order of the fused kernel), beside V -> V^T scratch, so that the PV operand is read from
+//                          LDS like the QK operand
 //   schedule_rows_kernel : the row schedule of layers with short rows, from the mask itself
 //   merge_segments_kernel: partial results of rows that were cut into segments -> O, mask bits, statistics
-//   transpose_v_kernel   : V -> V^T scratch, so that the PV operand is read from LDS like the QK operand
 //   lite_attn_fwd_kernel : fused tiled forward over the live tiles with the skip predicate
 //                          (Algorithm 2; eq. sparge_cond; tile recurrences of the Preliminaries)
 //
@@ -21,7 +21,7 @@
 //   * a 128-column mask tile is streamed as two 64-column stages.  K and V stages go global -> LDS with
 //     buffer_load ... lds (no registers, rows past the end of the sequence arrive as zeros through the buffer
 //     descriptor's range check); both are stored unpadded with an XOR swizzle applied on the global-address
-//     side.  V is transposed once per call into a scratch (transpose_v_kernel), so that K and V^T fragments are
+//     side.  V is transposed once per call into a scratch (prepare_rows_kernel), so that K and V^T fragments are
 //     both plain 16-byte LDS reads.
 //   * software pipeline: in stage s the matrix cores run S(s+1) = K(s+1) Q^T and O += V(s-1) P(s-1) while the
 //     vector ALU runs the online softmax of stage s; LDS holds two K and two V stages (64 KB), one barrier per
@@ -83,7 +83,8 @@ __device__ __forceinline__ void static_for(std::integer_sequence<int, Ks...>, F&
 // written back at the end of the kernel, and that launch waits for it (5 us behind a call that leaves 16 MB of partial
 // results, 2 us behind one without).
 constexpr int kStoreThrough = 16;  // cache policy of a buffer store
-__device__ __forceinline__ void store_through(float* at, float x) {
+template <class T>
+__device__ __forceinline__ void store_through(T* at, T x) {
   __hip_atomic_store(at, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -186,8 +187,9 @@ __device__ __forceinline__ void compact_row(const uint64_t* __restrict__ mrow, E
 __global__ __launch_bounds__(256) void compact_skiplist(const uint64_t* __restrict__ bits, int rows, int Tq, int Tk,
                                                          int W, int diagonal_first, int run_stride,
                                                          uint32_t* __restrict__ runs, uint32_t* __restrict__ nruns,
-                                                         uint32_t* __restrict__ live_cnt) {
+                                                         uint32_t* __restrict__ live_cnt, uint32_t* heads_ranked) {
   const int lane = threadIdx.x & 63;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *heads_ranked = 0;
   const int wave = blockIdx.x * 4 + (threadIdx.x >> 6);
   for (int row = wave * kRowsPerWave; row < min(rows, (wave + 1) * kRowsPerWave); ++row) {
     uint32_t ns, n;
@@ -219,20 +221,18 @@ __device__ __forceinline__ float other_half_sum(float x) {
   return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
 }
 
-// Row schedule, first half.  For every head, ranks its Q-tile rows by the length of their Skip-List, longest first
-// (counting sort: one workgroup per head, histogram in LDS), and cuts the ranking into chunks of kChunkRows rows
+// The row schedule of rows with Skip-Lists.  First half, a workgroup per head: ranks its Q-tile rows by the length of
+// their Skip-List, longest first (counting sort, histogram in LDS), and cuts the ranking into chunks of kChunkRows rows
 // ("rank c" = rows ranked [c*kChunkRows, (c+1)*kChunkRows)).  The chunks of all heads are numbered rank-major,
 // u = c * BH + (h + c) % BH; chunk_work[u] = the chunk's live tiles plus kRowOverhead per row (what a row costs
-// besides its tiles, in tile times).
+// besides its tiles, in tile times).  The results go past the L2: a workgroup of another XCD may read them in this launch.
 constexpr int kRowOverhead = 2;
-__global__ __launch_bounds__(256) void order_rows_kernel(const uint32_t* __restrict__ live_cnt, int Tq, int Tk, int BH,
-                                                          uint32_t* __restrict__ order,
-                                                          uint32_t* __restrict__ chunk_work) {
-  extern __shared__ uint32_t hist[];  // Tk + 1 bins; bin b counts rows with Tk - b live tiles; then one sum per chunk
+__device__ __forceinline__ void rank_head(const RowSchedule& p, int bh, uint32_t* hist) {
+  // hist: Tk + 1 bins; bin b counts rows with Tk - b live tiles; then one sum per chunk
+  const int Tq = p.Tq, Tk = p.Tk, BH = p.BH, tid = threadIdx.x;
   uint32_t* csum = hist + (Tk + 1);
   const int ranks = (Tq + kChunkRows - 1) / kChunkRows;
-  const int bh = blockIdx.x, tid = threadIdx.x;
-  const uint32_t* cnt = live_cnt + (size_t)bh * Tq;
+  const uint32_t* cnt = p.live_cnt + (size_t)bh * Tq;
   for (int b = tid; b <= Tk + ranks; b += 256) hist[b] = 0;
   __syncthreads();
   for (int i = tid; i < Tq; i += 256) atomicAdd(&hist[Tk - min((int)cnt[i], Tk)], 1u);
@@ -249,26 +249,24 @@ __global__ __launch_bounds__(256) void order_rows_kernel(const uint32_t* __restr
   for (int i = tid; i < Tq; i += 256) {
     const uint32_t live = (uint32_t)min((int)cnt[i], Tk);
     const uint32_t pos = atomicAdd(&hist[Tk - live], 1u);
-    order[(size_t)bh * Tq + pos] = (uint32_t)i;
+    store_through(p.order + (size_t)bh * Tq + pos, (uint32_t)i);
     atomicAdd(&csum[pos / kChunkRows], live + kRowOverhead);
   }
   __syncthreads();
-  for (int c = tid; c < ranks; c += 256) chunk_work[(size_t)c * BH + (bh + c) % BH] = csum[c];
+  for (int c = tid; c < ranks; c += 256) store_through(p.chunk_work + (size_t)c * BH + (bh + c) % BH, csum[c]);
 }
 
-// Row schedule, second half: deals the chunks to the eight XCDs (workgroup id % 8) and writes the table the fused
-// kernel reads its row from: slots[x * per_xcd + s] = row of the s-th workgroup of XCD x (0xffffffff: none; a chunk
-// always occupies kChunkRows slots, so the chunks of a head's last rank leave some empty); xcd_rows[x] = slots in use.
-// Chunks are taken in the order of u (longest ranks first; consecutive u of a rank belong to different heads), each
-// going to the XCD with the least work so far among those holding fewer than per_xcd / kChunkRows chunks (the
-// lowest-numbered one on a tie): every XCD ends up with the same work to within about one chunk, whatever the
-// number of heads and however the sparsity differs between heads and ranks, and an XCD walks its chunks from long rows
-// to short ones.  The workgroups sharing one L2 stream the K/V of the same head (a chunk stays together).
+// Second half, by the workgroup that has ranked the last head: deals the chunks to the eight XCDs (workgroup id % 8) and
+// writes the table the fused kernel reads its row from: slots[x * per_xcd + s] = row of the s-th workgroup of XCD x
+// (0xffffffff: none; a chunk always occupies kChunkRows slots, so the chunks of a head's last rank leave some empty);
+// xcd_rows[x] = slots in use.  Chunks are taken in the order of u (longest ranks first; consecutive u of a rank belong to
+// different heads), each going to the XCD with the least work so far among those holding fewer than per_xcd /
+// kChunkRows chunks (the lowest-numbered one on a tie): every XCD ends up with the same work to within about one chunk,
+// whatever the number of heads and however the sparsity differs between heads and ranks, and an XCD walks its chunks from
+// long rows to short ones.  The workgroups sharing one L2 stream the K/V of the same head (a chunk stays together).
 // The greedy pass is serial in the chunks (about 0.1 us each): wave 0 runs it with the state of XCD y in lane y --
 // key = work << 3 | y, minimum over the eight lanes by three DPP steps -- for up to kDealMax chunks; with more chunks
 // than that (64 per XCD) dealing them round-robin is balanced to within a percent or two and needs no pass at all.
-// Every workgroup of this kernel repeats the pass (same inputs, same integers) and then fills its own share of the
-// table.
 constexpr int kDealMax = 512;
 __device__ __forceinline__ uint32_t min_over_8_lanes(uint32_t key) {
   // lanes 8k..8k+7 all end up with the minimum of their eight keys
@@ -278,19 +276,17 @@ __device__ __forceinline__ uint32_t min_over_8_lanes(uint32_t key) {
   return key;
 }
 
-__global__ __launch_bounds__(256) void deal_rows_kernel(const uint32_t* __restrict__ chunk_work,
-                                                         const uint32_t* __restrict__ order, int BH, int Tq,
-                                                         int chunks, int per_xcd, uint32_t* __restrict__ slots,
-                                                         uint32_t* __restrict__ xcd_rows) {
-  __shared__ uint32_t work[kDealMax];  // work of chunk u
-  __shared__ uint32_t dest[kDealMax];  // xcd << 29 | first slot of chunk u
+__device__ __forceinline__ void deal_rows(const RowSchedule& p, uint32_t* work) {
+  uint32_t* dest = work + kDealMax;  // work of chunk u; xcd << 29 | first slot of chunk u
+  const int BH = p.BH, Tq = p.Tq, chunks = p.chunks, per_xcd = p.per_xcd;
   const int tid = threadIdx.x, lane = tid & 63;
   const int ranks = (Tq + kChunkRows - 1) / kChunkRows;
   const uint32_t cap = (uint32_t)(per_xcd / kChunkRows);  // (the last entry of an XCD's share of the table is its ticket)
-  if (blockIdx.x == 0 && tid < 8) slots[(size_t)tid * per_xcd + per_xcd - 1] = 0;
+  auto through = [](const uint32_t* at) { return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  if (tid < 8) p.slots[(size_t)tid * per_xcd + per_xcd - 1] = 0;
   const bool greedy = chunks <= kDealMax;
   if (greedy) {
-    for (int u = tid; u < chunks; u += 256) work[u] = chunk_work[u];
+    for (int u = tid; u < chunks; u += 256) work[u] = through(p.chunk_work + u);
     __syncthreads();
     if (tid < 64) {
       // a chunk's work is below 2^21 (64 rows of at most 16383 + kRowOverhead tiles), an XCD's below 2^27
@@ -306,24 +302,33 @@ __global__ __launch_bounds__(256) void deal_rows_kernel(const uint32_t* __restri
         }
         w = w_next;
       }
-      if (blockIdx.x == 0 && lane < 8) xcd_rows[lane] = nch * kChunkRows;
+      if (lane < 8) p.xcd_rows[lane] = nch * kChunkRows;
     }
     __syncthreads();
-  } else if (blockIdx.x == 0 && tid < 8) {  // round-robin: XCD x holds chunks x, x + 8, ...
-    xcd_rows[tid] = (uint32_t)((chunks - tid + 7) / 8) * kChunkRows;
+  } else if (tid < 8) {  // round-robin: XCD x holds chunks x, x + 8, ...
+    p.xcd_rows[tid] = (uint32_t)((chunks - tid + 7) / 8) * kChunkRows;
   }
-  // the table: one entry per (head, position in its ranking padded to whole chunks)
+  // the table: one entry per (head, position in its ranking padded to whole chunks), eight rankings in flight together
   const long long padded = (long long)ranks * kChunkRows, total = (long long)BH * padded;
-  const long long per_wg = (total + gridDim.x - 1) / gridDim.x;
-  const long long lo = min(total, (long long)blockIdx.x * per_wg), hi = min(total, lo + per_wg);
-  for (long long idx = lo + tid; idx < hi; idx += 256) {
-    const int bh = (int)(idx / padded), pos = (int)(idx % padded);
-    const int c = pos / kChunkRows, r = pos % kChunkRows;
-    const int u = c * BH + (bh + c) % BH;
-    const uint32_t d = greedy ? dest[u] : (((uint32_t)(u & 7) << 29) | (uint32_t)((u >> 3) * kChunkRows));
-    const uint32_t s = (d & 0x1fffffffu) + (uint32_t)r;
-    if (s < (uint32_t)per_xcd)
-      slots[(size_t)(d >> 29) * per_xcd + s] = pos < Tq ? (uint32_t)bh * Tq + order[(size_t)bh * Tq + pos] : 0xffffffffu;
+  constexpr int kAhead = 8;
+  for (long long idx0 = tid; idx0 < total; idx0 += 256 * kAhead) {
+    uint32_t at[kAhead], row[kAhead];
+#pragma unroll
+    for (int x = 0; x < kAhead; ++x) {
+      const long long idx = idx0 + 256 * x;
+      at[x] = 0xffffffffu;
+      row[x] = 0xffffffffu;
+      if (idx >= total) continue;
+      const int bh = (int)(idx / padded), pos = (int)(idx % padded);
+      const int c = pos / kChunkRows, u = c * BH + (bh + c) % BH;
+      const uint32_t d = greedy ? dest[u] : (((uint32_t)(u & 7) << 29) | (uint32_t)((u >> 3) * kChunkRows));
+      const uint32_t s = (d & 0x1fffffffu) + (uint32_t)(pos % kChunkRows);
+      if (s < (uint32_t)per_xcd) at[x] = (d >> 29) * (uint32_t)per_xcd + s;
+      if (pos < Tq) row[x] = (uint32_t)bh * Tq + through(p.order + (size_t)bh * Tq + pos);
+    }
+#pragma unroll
+    for (int x = 0; x < kAhead; ++x)
+      if (at[x] != 0xffffffffu) p.slots[at[x]] = row[x];
   }
 }
 
@@ -527,16 +532,34 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
 // kernel holds its P~ values.  One workgroup transposes one 128 x 128 tile through LDS, twice: once with
 // transposing reads, once to regroup, because a wave that stores the transposed pieces as it reads them writes 64
 // separate 16-byte pieces.  Bound by memory: 55 -> 39 us for 12 heads x 32760 tokens (3.7 -> 5.1 TB/s; a large copy
-// reaches 4.9).  `tickets`, if not null, are cleared on the way: those of a table that serves another call.
-__global__ __launch_bounds__(256) void transpose_v_kernel(const uint16_t* __restrict__ v, uint16_t* __restrict__ vt,
-                                                           int64_t stride_b, int64_t stride_h, int64_t stride_n,
-                                                           int H, int N, int Tk, uint32_t* __restrict__ tickets,
-                                                           int ticket_stride) {
-  if (tickets && blockIdx.x == 0 && threadIdx.x < 8) tickets[(size_t)threadIdx.x * ticket_stride] = 0;
-  constexpr int kRow = 256 + 16;  // padded LDS row (bytes)
-  __shared__ __attribute__((aligned(16))) char tile[128 * kRow];
+// reaches 4.9).
+// The first workgroups, one per head, make the row schedule (none where an earlier call's serves): a chain of latencies on a
+// few CUs, hidden behind the transposing ones.  As launches of their own its halves took 17 us and two gaps: a late step of
+// 12 heads x 256 tiles 2250 -> 2236 us, a dense one 5553 -> 5536.  `tickets`, if not null, are cleared on the way: those of
+// a table that serves another call.
+constexpr int kVtRow = 256 + 16;  // padded LDS row (bytes)
+__global__ __launch_bounds__(256) void prepare_rows_kernel(const RowSchedule sched, const uint16_t* __restrict__ v,
+                                                            uint16_t* __restrict__ vt, int64_t stride_b, int64_t stride_h,
+                                                            int64_t stride_n, int H, int N, int Tk,
+                                                            uint32_t* __restrict__ tickets, int ticket_stride) {
+  extern __shared__ __attribute__((aligned(16))) char tile[];
+  constexpr int kRow = kVtRow;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int j = blockIdx.x % Tk, bh = blockIdx.x / Tk;
+  if ((int)blockIdx.x < sched.BH) {
+    uint32_t* lds = reinterpret_cast<uint32_t*>(tile);
+    rank_head(sched, blockIdx.x, lds);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the ranking is past the L2 before it is counted)
+    __syncthreads();
+    if (tid == 0) lds[0] = atomicInc(sched.heads_ranked, (unsigned)sched.BH - 1);
+    __syncthreads();
+    const bool last = lds[0] == (uint32_t)sched.BH - 1;
+    __syncthreads();
+    if (last) deal_rows(sched, lds);
+    return;
+  }
+  const int block = blockIdx.x - sched.BH;
+  if (tickets && block == 0 && tid < 8) tickets[(size_t)tid * ticket_stride] = 0;
+  const int j = block % Tk, bh = block / Tk;
   const uint16_t* vb = v + (int64_t)(bh / H) * stride_b + (int64_t)(bh % H) * stride_h;
 #pragma unroll
   for (int t = 0; t < 8; ++t) {
@@ -584,8 +607,8 @@ struct LiveWalk {
                      // from `start` on first, those before it last)
   uint64_t cur;      // tiles of the current word still to come
 
-  // Lanes past the row, and all of them for an empty mask, lie past the end of the buffer and read zeros: with a branch around
-  // it the load was waited for before the Q loads behind it were issued (options clip, four steps, 198 -> 195 us).
+  // Lanes past the row, and all of them for an empty mask, lie past the end of the buffer and read zeros: with a branch
+  // around it the load was waited for before the Q loads behind it were issued (options clip, four steps, 198 -> 195 us).
   static __device__ __forceinline__ uint64_t load(const uint64_t* mrow, bool empty_mask, int words) {
     const auto at = __builtin_amdgcn_make_buffer_rsrc((void*)mrow, 0, empty_mask ? 0 : 8 * words, 0x00020000);
     return __builtin_bit_cast(uint64_t, __builtin_amdgcn_raw_buffer_load_b64(at, 8 * (int)(threadIdx.x & 63), 0, 0));
@@ -1422,7 +1445,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
   const int lq = lane & 31;
 
   // Consecutive workgroup ids land on different XCDs (id % 8): workgroup `slot` of an XCD computes the row at that
-  // place of the XCD's list in the schedule table (deal_rows_kernel: chunks of kChunkRows rows of one head side by
+  // place of the XCD's list in the schedule table (deal_rows(): chunks of kChunkRows rows of one head side by
   // side, so that the workgroups sharing one L2 stream the same K/V; equal work per XCD; long rows first) or, after the
   // first round, the one that it draws (draw_row). FEW: the table of schedule_rows_kernel if the call has one; else the
   // (head, segment, row) triples, numbered row-fastest, an eighth to every XCD, so that the rows walking the same K/V
@@ -2073,7 +2096,7 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
 // (exactly the maximum a single pass would have), the row's mask bits are set and the step's counters added.  Workgroups
 // rows .. 5*rows-1: 32 Q rows each, one thread per (row, 8 features): O = sum_s 2^(c (m_s - M)) O_s / sum_s ... .
 constexpr int kMergeThreads = 512;
-constexpr int kJudged = 64;  // tiles of a row that are judged in one trip to memory; longer rows go by segments, two waves each
+constexpr int kJudged = 64;  // tiles of a row that are judged in one trip to memory; longer rows: two waves per segment
 __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const FwdParams p) {
   touch_arguments(sizeof(FwdParams));
   const int tid = threadIdx.x, lane = tid & 63;
@@ -2269,25 +2292,30 @@ hipError_t launch_clear_tickets(uint32_t* tickets, int stride, hipStream_t st) {
 }
 
 hipError_t launch_compact(const uint64_t* bits, int rows, int Tq, int Tk, int W, int diagonal_first, int run_stride,
-                          uint32_t* runs, uint32_t* nruns, uint32_t* live_cnt, hipStream_t st) {
+                          uint32_t* runs, uint32_t* nruns, uint32_t* live_cnt, uint32_t* heads_ranked, hipStream_t st) {
   hipLaunchKernelGGL(compact_skiplist, dim3((rows + 4 * kRowsPerWave - 1) / (4 * kRowsPerWave)), dim3(256), 0, st, bits,
-                     rows, Tq, Tk, W, diagonal_first, run_stride, runs, nruns, live_cnt);
+                     rows, Tq, Tk, W, diagonal_first, run_stride, runs, nruns, live_cnt, heads_ranked);
   return hipGetLastError();
 }
 
-hipError_t launch_transpose_v(const uint16_t* v, uint16_t* vt, int64_t stride_b, int64_t stride_h, int64_t stride_n,
-                              int BH, int H, int N, int Tk, uint32_t* tickets, int ticket_stride, hipStream_t st) {
-  hipLaunchKernelGGL(transpose_v_kernel, dim3((unsigned)(BH * Tk)), dim3(256), 0, st, v, vt, stride_b, stride_h,
-                     stride_n, H, N, Tk, tickets, ticket_stride);
+// LDS of prepare_rows_kernel: a 128 x 128 tile, or Tk + 1 bins and one sum per chunk of a head (more than 64 KB for the
+// longest sequences), or the dealing's two words per chunk
+static size_t prepare_lds_bytes(int Tq, int Tk) {
+  const size_t rank = sizeof(uint32_t) * ((size_t)(Tk + 1) + (size_t)((Tq + kChunkRows - 1) / kChunkRows));
+  static_assert(128 * kVtRow >= 2 * sizeof(uint32_t) * kDealMax, "dealing");
+  return std::max<size_t>(128 * kVtRow, rank);
+}
+
+hipError_t launch_prepare_rows(const RowSchedule& sched, const uint16_t* v, uint16_t* vt, int64_t stride_b, int64_t stride_h,
+                               int64_t stride_n, int BH, int H, int N, int Tq, int Tk, uint32_t* tickets, int ticket_stride,
+                               hipStream_t st) {
+  hipLaunchKernelGGL(prepare_rows_kernel, dim3((unsigned)(sched.BH + BH * Tk)), dim3(256),
+                     sched.BH > 0 ? prepare_lds_bytes(Tq, Tk) : 128 * kVtRow, st, sched, v, vt, stride_b, stride_h, stride_n,
+                     H, N, Tk, tickets, ticket_stride);
   return hipGetLastError();
 }
 
 constexpr int kQB = 1;  // 32 Q rows per wave, 4 waves per workgroup, 2 workgroups per CU
-
-// LDS of order_rows_kernel: Tk + 1 bins and one sum per chunk of a head (more than 64 KB for the longest sequences)
-static size_t order_lds_bytes(int Tq, int Tk) {
-  return sizeof(uint32_t) * ((size_t)(Tk + 1) + (size_t)((Tq + kChunkRows - 1) / kChunkRows));
-}
 
 hipError_t prepare_fwd() {
   const void* fused[] = {reinterpret_cast<const void*>(lite_attn_fwd_kernel<kQB, false, false, false>),
@@ -2301,25 +2329,8 @@ hipError_t prepare_fwd() {
                                        std::max(kLdsBytes, kPairLdsBytes));
     if (e != hipSuccess) return e;
   }
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(order_rows_kernel),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)order_lds_bytes(16383, 16383));
-}
-
-hipError_t launch_order_rows(const uint32_t* live_cnt, int BH, int Tq, int Tk, uint32_t* order, uint32_t* chunk_work,
-                             hipStream_t st) {
-  hipLaunchKernelGGL(order_rows_kernel, dim3(BH), dim3(256), order_lds_bytes(Tq, Tk), st, live_cnt, Tq, Tk, BH, order,
-                     chunk_work);
-  return hipGetLastError();
-}
-
-hipError_t launch_deal_rows(const uint32_t* chunk_work, const uint32_t* order, int BH, int Tq, int chunks, int per_xcd,
-                            uint32_t* slots, uint32_t* xcd_rows, hipStream_t st) {
-  // every workgroup repeats the dealing and fills its share of the table: enough of them to keep the filling short
-  const long long rows = (long long)BH * Tq;
-  const int grid = (int)std::min<long long>(32, std::max<long long>(1, rows / 1024));
-  hipLaunchKernelGGL(deal_rows_kernel, dim3(grid), dim3(256), 0, st, chunk_work, order, BH, Tq, chunks, per_xcd, slots,
-                     xcd_rows);
-  return hipGetLastError();
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(prepare_rows_kernel),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)prepare_lds_bytes(16383, 16383));
 }
 
 hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int Tk, int W, int per_xcd, uint32_t* slots,

@@ -33,7 +33,8 @@ hipError_t launch_count_rows(const uint64_t* bits, int rows, int, int W, uint32_
 }
 
 hipError_t launch_compact(const uint64_t* bits, int rows, int, int Tk, int W, int, int run_stride, uint32_t* runs,
-                          uint32_t* nruns, uint32_t* live_cnt, hipStream_t) {
+                          uint32_t* nruns, uint32_t* live_cnt, uint32_t* heads_ranked, hipStream_t) {
+  *heads_ranked = 0;
   uint64_t any = 0;
   for (size_t x = 0; x < (size_t)rows * W; ++x) any |= bits[x];  // reads the whole mask
   for (int r = 0; r < rows; ++r) {                               // one run covering the row: [0, Tk)
@@ -45,33 +46,23 @@ hipError_t launch_compact(const uint64_t* bits, int rows, int, int Tk, int W, in
   return hipSuccess;
 }
 
-hipError_t launch_order_rows(const uint32_t* live_cnt, int BH, int Tq, int, uint32_t* order, uint32_t* chunk_work,
-                             hipStream_t) {
-  for (int x = 0; x < BH * Tq; ++x) order[x] = live_cnt[x] ? (uint32_t)(x % Tq) : 0u;
-  const int chunks = BH * ((Tq + kChunkRows - 1) / kChunkRows);
-  for (int u = 0; u < chunks; ++u) chunk_work[u] = 1;
-  return hipSuccess;
-}
-
-hipError_t launch_deal_rows(const uint32_t* chunk_work, const uint32_t* order, int BH, int Tq, int chunks, int per_xcd,
-                            uint32_t* slots, uint32_t* xcd_rows, hipStream_t) {
-  volatile uint32_t sink = chunk_work[chunks - 1] + order[(size_t)BH * Tq - 1];
-  (void)sink;
-  if (!before(slots + 8 * (size_t)per_xcd, xcd_rows)) return hipErrorInvalidValue;
-  memset(slots, 0, sizeof(uint32_t) * 8 * (size_t)per_xcd);   // the whole table may be written
-  for (int x = 0; x < 8; ++x) xcd_rows[x] = 0;
-  return hipSuccess;
-}
-
-hipError_t launch_transpose_v(const uint16_t*, uint16_t* vt, int64_t, int64_t, int64_t, int BH, int, int, int Tk,
-                              uint32_t* tickets, int ticket_stride, hipStream_t st) {
-  memset(vt, 0, sizeof(uint16_t) * (size_t)BH * 128 * ((size_t)Tk * 128));
-  return tickets ? launch_clear_tickets(tickets, ticket_stride, st) : hipSuccess;
-}
-
 hipError_t launch_clear_tickets(uint32_t* tickets, int stride, hipStream_t) {
   for (int x = 0; x < 8; ++x) tickets[(size_t)x * stride] = 0;
   return hipSuccess;
+}
+
+hipError_t launch_prepare_rows(const RowSchedule& p, const uint16_t*, uint16_t* vt, int64_t, int64_t, int64_t, int BH, int,
+                               int, int, int Tk, uint32_t* tickets, int ticket_stride, hipStream_t st) {
+  if (p.BH > 0) {
+    if (*p.heads_ranked != 0) return hipErrorInvalidValue;  // zero between launches
+    for (int x = 0; x < p.BH * p.Tq; ++x) p.order[x] = p.live_cnt[x] ? (uint32_t)(x % p.Tq) : 0u;
+    for (int u = 0; u < p.chunks; ++u) p.chunk_work[u] = 1;
+    if (!before(p.slots + 8 * (size_t)p.per_xcd, p.xcd_rows)) return hipErrorInvalidValue;
+    memset(p.slots, 0, sizeof(uint32_t) * 8 * (size_t)p.per_xcd);  // the whole table may be written
+    for (int x = 0; x < 8; ++x) p.xcd_rows[x] = 0;
+  }
+  memset(vt, 0, sizeof(uint16_t) * (size_t)BH * 128 * ((size_t)Tk * 128));
+  return tickets ? launch_clear_tickets(tickets, ticket_stride, st) : hipSuccess;
 }
 
 hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int, int W, int per_xcd, uint32_t* slots,
