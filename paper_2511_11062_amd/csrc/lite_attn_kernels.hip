@@ -906,7 +906,7 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
   for (int k = 0; k < kPrefetch; ++k)
     if (!IMM || pv_on) frag[k] = load_frag<VROWS, kKSrc, kVSrc>(k, ln.kread, ln.vread);
 
-  float pm[QB][4], mx[QB], m_new[QB], mc[QB], alpha[QB], lsum[QB], ta0[QB], ta1[QB], tb0[QB], tb1[QB];
+  float pm[QB], mx[QB], m_new[QB], mc[QB], alpha[QB], lsum[QB], ta0[QB], ta1[QB], tb0[QB], tb1[QB];
   uint32_t wb[QB];  // (kPackLate) packed pair whose sum is still to be taken
   bool ok = true, grew = false;
   // The ragged last tile of the sequence: its columns past the end leave the row maxima and sums (one scalar compare
@@ -974,14 +974,18 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
     constexpr int pend = PAIR ? H : 0;
     // ---- vector ALU: slice k of the online softmax of stage s (raw dot products; 1/sqrt(d) folded into c) ----
     {
-      if (k < 4) {  // m_local: partial row maxima over 8 of this lane's 32 scores
-        const int blk = k >> 1, r0 = 8 * (k & 1);
-        float v = cur[qb][blk][r0];
+      if (k < 4) {
+        // m_local: this lane's 32 scores in one chain, two more per instruction.  With four chains of eight, which take two
+        // more to join, and the predicate below in lane masks: 12 heads x 256 tiles 5639 -> 5573 us, 40 x 591, two steps,
+        // 162.0 -> 161.0 ms, 24 x 931 239.7 -> 238.9 (three rounds of both sides: 0.1-1.2 %, 0.4-0.6, 0.3-0.4)
+        const int e0 = k == 0 ? 1 : 8 * k + 1, e1 = k == 3 ? 32 : 8 * k + 9;
+        float v = k == 0 ? cur[qb][0][0] : pm[qb];
 #pragma unroll
-        for (int r = r0 + 1; r < r0 + 8; ++r) v = fmaxf(v, cur[qb][blk][r]);
-        pm[qb][k] = v;
+        for (int e = e0; e < e1; ++e) v = fmaxf(v, cur[qb][e >> 4][e & 15]);
+        asm volatile("" : "+v"(v));
+        pm[qb] = v;
       } else if (k == 4) {
-        mx[qb] = other_half_max(fmaxf(fmaxf(pm[qb][0], pm[qb][1]), fmaxf(pm[qb][2], pm[qb][3])));
+        mx[qb] = other_half_max(pm[qb]);
       } else if (k == 5) {  // m_ij = max(m_{i,j-1}, m_local) and the rescale factor of the earlier stages
         if (!PAIR) st.mloc_tile[qb] = H ? fmaxf(st.mloc_tile[qb], mx[qb]) : mx[qb];
         // the reference of the exponentials is the running maximum itself, at every stage: a row's largest weight is then
@@ -1061,7 +1065,7 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
         }
         if (!PAIR && H) {  // skip predicate of the whole 128-column tile, once its second half is in (eq. sparge_cond)
           const float g = (st.mloc_tile[qb] - m_new[qb]) * ln.scale;  // this row; max over rows = ballot below
-          ok = ok && (!ln.qvalid[qb] || (g <= ln.thr));
+          ok = ok && g <= (ln.qvalid[qb] ? ln.thr : INFINITY);
         }
       }
     }
