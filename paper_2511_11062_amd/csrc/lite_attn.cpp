@@ -33,6 +33,8 @@ struct lite_attn_mask {
   int table_calls;    // calls that the row schedule has served; 0: there is none that can serve another
   float loosest;        // largest threshold of the trajectory's calls so far (-inf: none has marked)
   float table_loosest;  // what it was when the row schedule was made
+  unsigned long long capture;  // the capture that the last call was recorded in; 0: it ran
+  bool recorded;               // a call has been recorded: it may run again whenever its graph is replayed
   bool lists_valid;   // the lists describe the mask as it stands (left by the previous call's epilogue)
   unsigned long long* d_stats;  // [max_steps][3]: skipped on entry, newly marked, Skip-List runs
   uint32_t* d_newly;            // few rows, behind them: [kFewRows] tiles that step 0 marked, per row (part of step
@@ -67,17 +69,19 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
   uint32_t* live_cnt = reinterpret_cast<uint32_t*>(lists + ll.live_cnt);
   uint32_t* slots = reinterpret_cast<uint32_t*>(lists + ll.slots);
   uint32_t* xcd_rows = reinterpret_cast<uint32_t*>(lists + ll.xcd_rows);
+  uint32_t* own_tickets = reinterpret_cast<uint32_t*>(lists + ll.tickets);
   uint16_t* vt = reinterpret_cast<uint16_t*>(scratch);
   const int diagonal_first = (d.flags & LITE_ATTN_ORDER_DIAGONAL_FIRST) ? 1 : 0;
   const bool few = g.nseg > 0;
   hipError_t e = hipSuccess;
-  // a table of rows comes with its ticket counters cleared; calls without one keep theirs where the table would be
+  // a table of rows comes with its ticket counters cleared; calls without one have theirs apart, as later calls, recorded
+  // ones above all, may go by a table that is in place
   const bool table = !few || (g.rows > kFewRows && g.rows <= kSchedRows && !a.empty);
   const bool tickets = g.rows > kFewRows, draws = tickets && (!few || g.Tk >= kDrawTiles);
   if (!few && a.fresh) {
     e = launch_clear(a.bits, (size_t)g.rows * g.W, a.stats_all, a.stat_words, stream);
   } else if (tickets && !table && (draws || a.fresh)) {  // (the mask is overwritten; few rows: the kernel clears)
-    e = launch_clear(reinterpret_cast<uint64_t*>(slots), draws ? 8 * (kTicketWords + kArrivals) / 2 : 0, a.stats_all,
+    e = launch_clear(reinterpret_cast<uint64_t*>(own_tickets), draws ? 8 * (kTicketWords + kArrivals) / 2 : 0, a.stats_all,
                      a.fresh ? a.stat_words : 0, stream);
   }
   if (e != hipSuccess) return e;
@@ -112,7 +116,7 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
   p.protect_start = d.protect_start; p.protect_len = d.protect_len;
   p.rows_total = (int)g.rows;
   p.slots = slots; p.per_xcd = g.per_xcd; p.xcd_rows = xcd_rows;
-  p.tickets = !tickets ? nullptr : table ? slots + g.per_xcd - 1 : slots;
+  p.tickets = !tickets ? nullptr : table ? slots + g.per_xcd - 1 : own_tickets;
   p.ticket_stride = table ? g.per_xcd : kTicketWords;
   p.resident = draws ? kResident : kNoDraws;
   p.table_calls = a.table_calls;
@@ -151,7 +155,7 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     if (cut_rows(g) > 0) {
       p.cut_rows = cut_rows(g);
       p.cut_pieces = cut_pieces(g);
-      p.arrive = table ? slots + g.per_xcd - kTableTail + 1 : slots + 8 * kTicketWords;
+      p.arrive = table ? slots + g.per_xcd - kTableTail + 1 : own_tickets + 8 * kTicketWords;
       p.arrive_stride = table ? g.per_xcd : kArrivals;
     }
     if (p.nseg > 1 || p.piece_units > 0 || p.cut_rows > 0) {
@@ -212,6 +216,17 @@ uint32_t* live_rows(const lite_attn_mask* m, int step) {
   return m->d_arrive + (1 + (step & 1)) * la::kFewRows;
 }
 
+// The capture under way on a stream, 0 if there is none (the null stream cannot be captured).
+hipError_t capture_on(hipStream_t stream, unsigned long long* capture) {
+  *capture = 0;
+  if (!stream) return hipSuccess;
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  unsigned long long id = 0;
+  const hipError_t e = hipStreamGetCaptureInfo(stream, &status, &id);
+  if (e == hipSuccess && status != hipStreamCaptureStatusNone) *capture = id + 1;
+  return e;
+}
+
 int grow(la_scratch* s, size_t bytes) {
   if (bytes <= s->bytes) return LITE_ATTN_OK;
   if (s->base) LA_HIP(hipFree(s->base));
@@ -235,6 +250,8 @@ int init_common(const lite_attn_desc_t* desc, lite_attn_ctx* ctx, lite_attn_mask
   m->lists_valid = false;
   m->table_calls = 0;
   m->loosest = m->table_loosest = -INFINITY;
+  m->capture = 0;
+  m->recorded = false;
   m->ctx = nullptr;
   m->stream = nullptr;
   m->next_step = 0;
@@ -347,6 +364,14 @@ int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_a
   // was just cleared) and not after an import.  This call's epilogue then leaves the lists of the next call.
   const bool ready = m->lists_valid && step != 0;
   m->lists_valid = false;
+  // A recorded call runs when its graph is replayed, of which the host hears nothing: what it knows of the device's state (an
+  // empty mask, a row schedule that fits) holds among the calls of one capture, and among eager ones while no call has been
+  // recorded.  Elsewhere a call finds out for itself, with the same bits.
+  unsigned long long capture;
+  LA_HIP(capture_on(stream, &capture));
+  const bool known = capture == m->capture && (capture != 0 || !m->recorded);
+  m->capture = capture;
+  m->recorded = m->recorded || capture != 0;
   la::CallArgs a;
   a.q = q; a.k = k; a.v = v; a.out = out;
   a.threshold = threshold;
@@ -359,14 +384,14 @@ int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_a
   a.arrive = m->d_arrive;
   a.live_rows = live_rows(m, step);
   a.live_next = live_rows(m, step + 1);
-  a.empty = step == 0 || m->empty;
+  a.empty = step == 0 || (known && m->empty);
   a.lists_ready = ready;
   a.build_next = true;
   // The row schedule serves up to kTableCalls calls of a trajectory, as long as no call has marked with a looser threshold
   // than the mask that it was made for has seen: what a threshold marks, it marks nearly all at once.
   if (step == 0) m->loosest = -INFINITY;
   const bool keeps = la::keeps_table(m->geo) && (m->geo.nseg == 0 || !a.empty);
-  const bool ready_table = keeps && step != 0 && m->table_calls < la::kTableCalls && m->table_loosest == m->loosest;
+  const bool ready_table = keeps && known && step != 0 && m->table_calls < la::kTableCalls && m->table_loosest == m->loosest;
   a.table_calls = ready_table ? m->table_calls : 0;
   const int served = keeps ? a.table_calls + 1 : 0;
   m->table_calls = 0;

@@ -195,6 +195,11 @@ ListLayout list_layout(const Geometry& g) {
   at += up256(sizeof(uint32_t) * 8 * (size_t)g.per_xcd);
   l.xcd_rows = at;
   at += up256(sizeof(uint32_t) * 9);
+  l.tickets = l.slots;
+  if (g.nseg > 0 && keeps_table(g)) {
+    l.tickets = at;
+    at += up256(sizeof(uint32_t) * 8 * (kTicketWords + kArrivals));
+  }
   l.runs = at;
   at += up256(sizeof(uint32_t) * (size_t)g.rows * g.run_stride);
   l.total = at;

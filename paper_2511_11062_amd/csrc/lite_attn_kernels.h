@@ -147,6 +147,8 @@ struct ListLayout {
   size_t chunk_work;  // [chunks] uint32 work of each chunk (live tiles + a per-row constant)
   size_t slots;     // [8][per_xcd] uint32 schedule table
   size_t xcd_rows;  // [8] uint32, and a counter of prepare_rows_kernel, zero between launches
+  size_t tickets;   // [8] tickets at kTicketWords, [8][kArrivals] arrival counters, of calls that make no table: behind the
+                    //   table of layers that also make one, else where it would be
   size_t runs;      // [rows][run_stride] uint32 Skip-List
   size_t total;
 };

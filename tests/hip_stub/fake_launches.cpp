@@ -1,78 +1,153 @@
 // TEST INFRASTRUCTURE (see hip/hip_runtime.h next to this file): host stand-ins for the kernel launchers.  They compute
 // nothing of the method; each one writes every byte its kernel is entitled to write, so that AddressSanitizer sees
-// whether the host code handed it buffers of the right size (scratch layout, mask and statistics allocations).
+// whether the host code handed it buffers of the right size (scratch layout, mask and statistics allocations).  Schedules
+// hold a real permutation of the rows, and an attention launch checks that the one it is given does; calls that can mark set
+// a bit of every row.
+#include <math.h>
 #include <string.h>
 
 #include <algorithm>
+#include <functional>
+#include <vector>
 
 #include "lite_attn_kernels.h"
 
+unsigned long long fake_capture = 0;
+
 namespace {
+
+std::vector<std::vector<std::function<hipError_t()>>> graphs;  // graph x: the launches of capture x + 1
+
+// A launch: made at once, or kept for the replays of the capture under way on its stream.
+template <class F>
+hipError_t launch(hipStream_t st, F f) {
+  if (!st || !fake_capture) return f();
+  graphs.back().push_back(f);
+  return hipSuccess;
+}
 
 // Pieces of one allocation that must not run into the piece behind them (AddressSanitizer sees only the allocation's end).
 bool before(const void* end, const void* next) { return (uintptr_t)end <= (uintptr_t)next; }
 
+// All rows, dealt to the XCDs in turn; no entry of the table but these is a row.
+void deal(uint32_t* slots, int per_xcd, uint32_t* xcd_rows, int rows) {
+  memset(slots, 0xff, sizeof(uint32_t) * 8 * (size_t)per_xcd);  // the whole table may be written
+  for (int x = 0; x < 8; ++x) {
+    xcd_rows[x] = 0;
+    for (int r = x; r < rows; r += 8) slots[(size_t)x * per_xcd + xcd_rows[x]++] = (uint32_t)r;
+  }
+}
+
+bool every_row_once(const uint32_t* slots, int per_xcd, const uint32_t* xcd_rows, int rows) {
+  std::vector<char> seen(rows);
+  for (int x = 0; x < 8; ++x)
+    for (uint32_t t = 0; t < xcd_rows[x]; ++t) {
+      if (t >= (uint32_t)per_xcd) return false;
+      const uint32_t r = slots[(size_t)x * per_xcd + t];
+      if (r == 0xffffffffu) continue;
+      if (r >= (uint32_t)rows || seen[r]++) return false;
+    }
+  return std::count(seen.begin(), seen.end(), 1) == rows;
+}
+
+bool all_zero(const uint64_t* bits, size_t words) { return std::count(bits, bits + words, 0) == (long)words; }
+
 }  // namespace
+
+extern "C" {
+void fake_begin_capture() {
+  graphs.emplace_back();
+  fake_capture = graphs.size();
+}
+int fake_end_capture() {
+  fake_capture = 0;
+  return (int)graphs.size();
+}
+int fake_replay(int graph) {
+  for (auto& f : graphs[graph - 1])
+    if (const hipError_t e = f()) return e;
+  return 0;
+}
+}
 
 namespace la {
 
 hipError_t prepare_fwd() { return hipSuccess; }
 
-hipError_t launch_clear(uint64_t* bits, size_t words, unsigned long long* stats, size_t nstats, hipStream_t) {
+static hipError_t clear(uint64_t* bits, size_t words, unsigned long long* stats, size_t nstats) {
   if (words) memset(bits, 0, words * sizeof(uint64_t));
   if (nstats) memset(stats, 0, nstats * sizeof(unsigned long long));
   return hipSuccess;
 }
+hipError_t launch_clear(uint64_t* bits, size_t words, unsigned long long* stats, size_t nstats, hipStream_t st) {
+  return launch(st, [=] { return clear(bits, words, stats, nstats); });
+}
 
-hipError_t launch_count_rows(const uint64_t* bits, int rows, int, int W, uint32_t* live, uint32_t* arrive, hipStream_t) {
-  uint64_t any = 0;
-  for (size_t x = 0; x < (size_t)rows * W; ++x) any |= bits[x];
-  for (int r = 0; r < rows; ++r) live[r] = any ? 1 : 0;
+static hipError_t count_rows(const uint64_t* bits, int rows, int W, uint32_t* live, uint32_t* arrive) {
+  const bool empty = all_zero(bits, (size_t)rows * W);
+  for (int r = 0; r < rows; ++r) live[r] = empty ? 0 : 1;
   if (arrive) memset(arrive, 0, sizeof(uint32_t) * rows);
   return hipSuccess;
 }
+hipError_t launch_count_rows(const uint64_t* bits, int rows, int, int W, uint32_t* live, uint32_t* arrive, hipStream_t st) {
+  return launch(st, [=] { return count_rows(bits, rows, W, live, arrive); });
+}
 
-hipError_t launch_compact(const uint64_t* bits, int rows, int, int Tk, int W, int, int run_stride, uint32_t* runs,
-                          uint32_t* nruns, uint32_t* live_cnt, uint32_t* heads_ranked, hipStream_t) {
+static hipError_t compact(const uint64_t* bits, int rows, int Tk, int W, int run_stride, uint32_t* runs, uint32_t* nruns,
+                          uint32_t* live_cnt, uint32_t* heads_ranked) {
   *heads_ranked = 0;
-  uint64_t any = 0;
-  for (size_t x = 0; x < (size_t)rows * W; ++x) any |= bits[x];  // reads the whole mask
-  for (int r = 0; r < rows; ++r) {                               // one run covering the row: [0, Tk)
+  volatile bool sink = all_zero(bits, (size_t)rows * W);  // reads the whole mask
+  (void)sink;
+  for (int r = 0; r < rows; ++r) {  // one run covering the row: [0, Tk)
     memset(runs + (size_t)r * run_stride, 0, sizeof(uint32_t) * run_stride);
     runs[(size_t)r * run_stride] = (uint32_t)Tk << 16;
     nruns[r] = 1;
-    live_cnt[r] = (uint32_t)Tk + (any ? 0u : 0u);
+    live_cnt[r] = (uint32_t)Tk;
   }
   return hipSuccess;
 }
+hipError_t launch_compact(const uint64_t* bits, int rows, int, int Tk, int W, int, int run_stride, uint32_t* runs,
+                          uint32_t* nruns, uint32_t* live_cnt, uint32_t* heads_ranked, hipStream_t st) {
+  return launch(st, [=] { return compact(bits, rows, Tk, W, run_stride, runs, nruns, live_cnt, heads_ranked); });
+}
 
-hipError_t launch_clear_tickets(uint32_t* tickets, int stride, hipStream_t) {
+static hipError_t clear_tickets(uint32_t* tickets, int stride) {
   for (int x = 0; x < 8; ++x) tickets[(size_t)x * stride] = 0;
   return hipSuccess;
 }
+hipError_t launch_clear_tickets(uint32_t* tickets, int stride, hipStream_t st) {
+  return launch(st, [=] { return clear_tickets(tickets, stride); });
+}
 
-hipError_t launch_prepare_rows(const RowSchedule& p, const uint16_t*, uint16_t* vt, int64_t, int64_t, int64_t, int BH, int,
-                               int, int, int Tk, uint32_t* tickets, int ticket_stride, hipStream_t st) {
+static hipError_t prepare_rows(const RowSchedule& p, uint16_t* vt, int BH, int Tk, uint32_t* tickets, int ticket_stride) {
   if (p.BH > 0) {
     if (*p.heads_ranked != 0) return hipErrorInvalidValue;  // zero between launches
     for (int x = 0; x < p.BH * p.Tq; ++x) p.order[x] = p.live_cnt[x] ? (uint32_t)(x % p.Tq) : 0u;
     for (int u = 0; u < p.chunks; ++u) p.chunk_work[u] = 1;
     if (!before(p.slots + 8 * (size_t)p.per_xcd, p.xcd_rows)) return hipErrorInvalidValue;
-    memset(p.slots, 0, sizeof(uint32_t) * 8 * (size_t)p.per_xcd);  // the whole table may be written
-    for (int x = 0; x < 8; ++x) p.xcd_rows[x] = 0;
+    deal(p.slots, p.per_xcd, p.xcd_rows, p.BH * p.Tq);
+    clear_tickets(p.slots + p.per_xcd - 1, p.per_xcd);
   }
   memset(vt, 0, sizeof(uint16_t) * (size_t)BH * 128 * ((size_t)Tk * 128));
-  return tickets ? launch_clear_tickets(tickets, ticket_stride, st) : hipSuccess;
+  return tickets ? clear_tickets(tickets, ticket_stride) : hipSuccess;
+}
+hipError_t launch_prepare_rows(const RowSchedule& p, const uint16_t*, uint16_t* vt, int64_t, int64_t, int64_t, int BH, int,
+                               int, int, int Tk, uint32_t* tickets, int ticket_stride, hipStream_t st) {
+  return launch(st, [=] { return prepare_rows(p, vt, BH, Tk, tickets, ticket_stride); });
 }
 
-hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int, int W, int per_xcd, uint32_t* slots,
-                                uint32_t* xcd_rows, hipStream_t) {
-  volatile uint64_t sink = bits[0] + bits[(size_t)rows * W - 1];
-  (void)sink;
+static hipError_t schedule_rows(const uint64_t* bits, int rows, int W, int per_xcd, uint32_t* slots, uint32_t* xcd_rows) {
   if (!before(slots + 8 * (size_t)per_xcd, xcd_rows)) return hipErrorInvalidValue;
-  memset(slots, 0, sizeof(uint32_t) * 8 * (size_t)per_xcd);
-  for (int x = 0; x < 8; ++x) xcd_rows[x] = 0;
+  deal(slots, per_xcd, xcd_rows, rows);
+  for (int x = 1; x <= 8; ++x) {  // flag, arrivals, ticket
+    memset(slots + (size_t)x * per_xcd - kTableTail, 0, sizeof(uint32_t) * kTableTail);
+    slots[(size_t)x * per_xcd - kTableTail] = all_zero(bits, (size_t)rows * W);
+  }
   return hipSuccess;
+}
+hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int, int W, int per_xcd, uint32_t* slots,
+                                uint32_t* xcd_rows, hipStream_t st) {
+  return launch(st, [=] { return schedule_rows(bits, rows, W, per_xcd, slots, xcd_rows); });
 }
 
 namespace {
@@ -90,12 +165,12 @@ bool partials(const FwdParams& p, size_t parts, size_t rows) {
 // the first round are drawn; at step 0 the mask is overwritten and, with few rows, all counters are cleared.
 hipError_t fwd_without_lists(const FwdParams& p) {
   const size_t rows = (size_t)p.rows_total;
-  volatile uint32_t sink = 0;
-  if (p.scheduled) sink = p.slots[8 * (size_t)p.per_xcd - 1] + p.xcd_rows[7];
-  (void)sink;
+  if (p.scheduled && !every_row_once(p.slots, p.per_xcd, p.xcd_rows, p.rows_total)) return hipErrorInvalidValue;
+  // what lies behind the tickets and the arrival counters of a call: the end of its table, or of those that have no table
+  const uint32_t* behind = p.tickets > p.xcd_rows ? p.runs : p.xcd_rows;
   if (p.tickets && p.resident == kResident)  // counters start at zero
     for (int x = 0; x < 8; ++x)
-      if (!before(p.tickets + x * p.ticket_stride + 1, p.xcd_rows) || p.tickets[x * p.ticket_stride]++ != 0)
+      if (!before(p.tickets + x * p.ticket_stride + 1, behind) || p.tickets[x * p.ticket_stride]++ != 0)
         return hipErrorInvalidValue;
   if (p.nseg > 1 && !partials(p, rows * p.nseg, rows)) return hipErrorInvalidValue;
   if (p.piece_units > 0) {
@@ -110,7 +185,7 @@ hipError_t fwd_without_lists(const FwdParams& p) {
       for (int r = 0; r < p.cut_rows; ++r) {
         uint32_t* at = p.arrive + x * p.arrive_stride + r;
         // (not the ticket, which the loop above has moved)
-        if (!before(at + 1, p.xcd_rows) || *at != 0) return hipErrorInvalidValue;
+        if (!before(at + 1, behind) || *at != 0) return hipErrorInvalidValue;
       }
   }
   if (p.fresh && p.newly_rows) {
@@ -121,13 +196,13 @@ hipError_t fwd_without_lists(const FwdParams& p) {
     if (p.piece_units > 0 && p.live_next == p.live_rows) return hipErrorInvalidValue;  // (read while it is written)
     for (size_t r = 0; r < rows; ++r) p.live_next[r] = (uint32_t)p.Tk;
   }
-  for (size_t x = 0; x < rows * p.W; ++x) p.bits[x] = p.fresh ? 0 : p.bits[x];
+  if (p.fresh) memset(p.bits, 0, sizeof(uint64_t) * rows * p.W);
   return hipSuccess;
 }
 
 }  // namespace
 
-hipError_t launch_fwd(const FwdParams& p, bool, hipStream_t) {
+static hipError_t fwd(const FwdParams& p) {
   const size_t rows = (size_t)p.rows_total;
   if (p.nseg > 0) {
     const hipError_t e = fwd_without_lists(p);
@@ -135,11 +210,11 @@ hipError_t launch_fwd(const FwdParams& p, bool, hipStream_t) {
   } else {
     // the first and last element of everything the kernel reads or writes besides q, k, v, out
     volatile uint32_t sink = p.runs[0] + p.runs[rows * p.run_stride - 1] + p.nruns[rows - 1] + p.live_cnt[rows - 1] +
-                             p.slots[8 * (size_t)p.per_xcd - 1] + p.xcd_rows[7] +
                              p.vt[(size_t)(rows / p.Tq) * 128 * ((size_t)p.Tk * 128) - 1];
     (void)sink;
-    p.bits[0] |= 0;
-    p.bits[rows * p.W - 1] |= 0;
+    if (!every_row_once(p.slots, p.per_xcd, p.xcd_rows, p.rows_total)) return hipErrorInvalidValue;
+    for (int x = 0; x < 8; ++x)
+      if (p.tickets && p.tickets[x * p.ticket_stride]++ != 0) return hipErrorInvalidValue;
     if (p.build_next) {  // the epilogue rewrites the lists in full
       memset(p.runs, 0, sizeof(uint32_t) * rows * p.run_stride);
       for (size_t r = 0; r < rows; ++r) {
@@ -149,10 +224,16 @@ hipError_t launch_fwd(const FwdParams& p, bool, hipStream_t) {
       }
     }
   }
+  for (size_t r = 0; p.thr > -INFINITY && r < rows; ++r) {
+    *p.stat_newly += !(p.bits[r * p.W] & 1);
+    p.bits[r * p.W] |= 1;
+  }
   *p.stat_skipped_in += 0;
-  *p.stat_newly += 0;
   *p.stat_runs += (unsigned long long)rows;
   return hipSuccess;
+}
+hipError_t launch_fwd(const FwdParams& p, bool, hipStream_t st) {
+  return launch(st, [=] { return fwd(p); });
 }
 
 }  // namespace la

@@ -28,6 +28,16 @@ inline hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpy
   return hipSuccess;
 }
 inline hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+// Capture (fake_launches.cpp): launches made while one is under way are kept and run by fake_replay().  The null stream cannot
+// be captured.
+enum hipStreamCaptureStatus { hipStreamCaptureStatusNone, hipStreamCaptureStatusActive };
+extern unsigned long long fake_capture;  // its number, 0 if none is under way
+inline hipError_t hipStreamGetCaptureInfo(hipStream_t st, hipStreamCaptureStatus* status, unsigned long long* id) {
+  *status = st && fake_capture ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  *id = fake_capture;
+  return hipSuccess;
+}
+inline hipError_t hipGetLastError() { return hipSuccess; }
 inline hipError_t hipGetDevice(int* d) {
   *d = 0;
   return hipSuccess;

@@ -108,6 +108,56 @@ def exercise(h, heads, n, steps):
     assert (cnt == tk).all() and (idx == np.arange(tk, dtype=np.uint16)).all()
 
 
+def replays(heads, n, flags):
+    """Recorded calls run later, between calls that the host knows nothing of when it records them: each has to find what it
+    reads in place, a schedule that names every row above all (the attention launch checks it)."""
+    h, d, none, mark = H(), desc(heads, n, steps=4, flags=flags), ctypes.c_float(-float("inf")), ctypes.c_float(-1.5)
+    assert lib.lite_attn_init_mask(ctypes.byref(d), ctypes.byref(h)) == 0
+    assert lib.lite_attn_set_stream(h, ctypes.c_void_p(64)) == 0
+    words = lib.lite_attn_mask_words(h)
+    buf = (ctypes.c_uint8 * (heads * n * 128 * 2 + 16))()
+    p = (ctypes.addressof(buf) + 15) & ~15
+
+    def call(thr, *steps):
+        for t in steps:
+            assert lib.lite_attn_fwd(p, p, p, p, h, thr, t) == 0, (heads, n, flags, t)
+
+    def record(thr, *steps):
+        lib.fake_begin_capture()
+        call(thr, *steps)
+        return lib.fake_end_capture()
+
+    def replay(g):
+        assert lib.fake_replay(g) == 0, (heads, n, flags)
+
+    # recorded on a handle on which nothing has run: each graph by itself, in order, and out of order
+    first, second, both = record(mark, 0), record(mark, 1), record(mark, 2, 3)
+    for g in (second, both, first, both, second, first, second, both):
+        replay(g)
+    call(mark, 0, 1)
+    later = record(mark, 2)
+    call(none, 0, 1)                         # the next trajectory starts with dense calls
+    replay(later)
+    call(mark, 2, 3)
+    call(none, 0)
+    replay(later)                            # straight behind step 0
+    bits = np.zeros(words, dtype=np.uint64)
+    for word in (0, 1):
+        bits[:] = word
+        assert lib.lite_attn_mask_import(h, bits.ctypes.data, words, 2) == 0
+        replay(later)
+        call(mark, 2)
+        replay(later)
+        call(mark, 3)
+    whole = record(mark, 0, 1, 2)
+    call(none, 0)
+    replay(whole)
+    call(none, 1)
+    replay(later)
+    call(mark, 2, 3)
+    lib.lite_attn_free_mask(h)
+
+
 for heads, n, way in ((1, 1, "in order"), (2, 300, None), (3, 128 * 65 + 7, "in order"), (2, 2048, "segments"),
                       (9, 128 * 15, "in order"), (10, 128 * 29 + 1, "in order"), (4, 128 * 25, "segments"), (1, 128 * 129, "segments"),
                       (4, 128 * 87, "segments"), (9, 128 * 58 - 31, "schedule"), (600, 300, "schedule"), (7, 128 * 128, "schedule"),
@@ -120,6 +170,7 @@ for heads, n, way in ((1, 1, "in order"), (2, 300, None), (3, 128 * 65 + 7, "in 
         assert lib.lite_attn_set_stream(h, None) == 0
         exercise(h, heads, n, 3)
         lib.lite_attn_free_mask(h)
+        replays(heads, n, flags)
 
 ctx = H()
 assert lib.lite_attn_ctx_create(ctypes.byref(ctx)) == 0

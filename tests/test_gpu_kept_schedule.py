@@ -102,3 +102,65 @@ def test_kept_schedule_in_a_graph(heads, tokens, flags):
         assert torch.equal(out[0].view(torch.int16).cpu(), ref[0])
     finally:
         la.lite_attn_free_mask(h)
+
+
+# (short rows of every kind, few rows in pieces and in segments)
+@pytest.mark.parametrize("heads,tokens,flags", SHAPES[:4] + [(18, 128 * 29, 3), (5, 128 * 31, 0), (2, 128 * 16, 2)])
+def test_later_call_recorded_alone(heads, tokens, flags):
+    """Step 2 by itself in a graph, replayed between calls of which the host knew nothing when it was recorded: output and
+    mask, bit for bit, are those of an eager call on a handle that has imported the mask."""
+    from paper_2511_11062_amd import lite_attn as la
+    q, k, v = layer(heads, tokens)
+    path = parity.path_of(1, heads, tokens, flags)
+    dense, marking = -float("inf"), -1.5
+    h = la.lite_attn_init_mask(1, heads, tokens, max_steps=4, flags=flags)
+    eager = la.lite_attn_init_mask(1, heads, tokens, max_steps=4, flags=flags)
+    out, ref = torch.empty_like(q), torch.empty_like(q)
+    side = torch.cuda.Stream()
+
+    def call(handle, o, threshold, step, s):
+        la.lite_attn_fwd(q[s:s + 1].data_ptr(), k[s:s + 1].data_ptr(), v[s:s + 1].data_ptr(), o[:1].data_ptr(), handle, threshold,
+                         step)
+
+    def check(what, run, step, s):
+        mask = la.lite_attn_mask_export(h)
+        la.lite_attn_mask_import(eager, mask, step)
+        ref.fill_(float("nan"))
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        call(eager, ref, marking, step, s)
+        run()
+        torch.cuda.synchronize()
+        assert torch.equal(out[0].view(torch.int16), ref[0].view(torch.int16)), what
+        assert np.array_equal(la.lite_attn_mask_export(h), la.lite_attn_mask_export(eager)), what
+
+    try:
+        la.lite_attn_set_stream(h, side.cuda_stream)
+        la.lite_attn_set_stream(eager, side.cuda_stream)
+        torch.cuda.synchronize()
+        for t in (0, 1):
+            call(h, out, marking, t, 0)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            call(h, out, marking, 2, 1)
+        check("as it was recorded", graph.replay, 2, 1)
+        for t in (0, 1):
+            call(h, out, dense, t, 0)
+        check("behind dense calls", graph.replay, 2, 1)
+        if path.rows > 512:  # (few rows are cut by the live tiles that step 1 has counted)
+            call(h, out, dense, 0, 0)
+            check("behind step 0", graph.replay, 2, 1)
+            check("again", graph.replay, 2, 1)
+        rng = np.random.default_rng(3)
+        for share in (0.0, 0.5):
+            tiles = rng.random((path.rows, path.Tk)) < share
+            la.lite_attn_mask_import(h, parity.pack_mask(tiles.astype(np.uint8)).ravel(), 2)
+            check("imported, %g" % share, graph.replay, 2, 1)
+        call(h, out, dense, 0, 0)
+        graph.replay()
+        torch.cuda.synchronize()
+        check("eager behind a replay", lambda: call(h, out, marking, 1, 0), 1, 0)
+    finally:
+        la.lite_attn_free_mask(h)
+        la.lite_attn_free_mask(eager)
