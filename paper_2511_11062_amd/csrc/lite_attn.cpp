@@ -69,6 +69,8 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
   uint32_t* live_cnt = reinterpret_cast<uint32_t*>(lists + ll.live_cnt);
   uint32_t* slots = reinterpret_cast<uint32_t*>(lists + ll.slots);
   uint32_t* xcd_rows = reinterpret_cast<uint32_t*>(lists + ll.xcd_rows);
+  uint32_t* heads_ranked = reinterpret_cast<uint32_t*>(lists + ll.heads_ranked);
+  uint32_t* marked = reinterpret_cast<uint32_t*>(lists + ll.marked);
   uint32_t* own_tickets = reinterpret_cast<uint32_t*>(lists + ll.tickets);
   uint16_t* vt = reinterpret_cast<uint16_t*>(scratch);
   const int diagonal_first = (d.flags & LITE_ATTN_ORDER_DIAGONAL_FIRST) ? 1 : 0;
@@ -90,10 +92,10 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     uint32_t* chunk_work = reinterpret_cast<uint32_t*>(lists + ll.chunk_work);
     if (!a.lists_ready) {
       e = launch_compact(a.bits, (int)g.rows, g.Tq, g.Tk, g.W, diagonal_first, g.run_stride, runs, nruns, live_cnt,
-                         xcd_rows + 8, stream);
+                         heads_ranked, stream);
       if (e != hipSuccess) return e;
     }
-    const RowSchedule sched = {live_cnt, order, chunk_work, slots, xcd_rows, xcd_rows + 8, g.Tq, g.Tk,
+    const RowSchedule sched = {live_cnt, order, chunk_work, slots, xcd_rows, heads_ranked, g.Tq, g.Tk,
                                a.table_calls == 0 ? g.BH : 0, g.chunks, g.per_xcd};
     e = launch_prepare_rows(sched, static_cast<const uint16_t*>(a.v), vt, d.stride_b, d.stride_h, d.stride_n, g.BH, d.heads,
                             d.seqlen, g.Tq, g.Tk, a.table_calls > 0 ? slots + g.per_xcd - 1 : nullptr, g.per_xcd, stream);
@@ -157,6 +159,7 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
       p.cut_pieces = cut_pieces(g);
       p.arrive = table ? slots + g.per_xcd - kTableTail + 1 : own_tickets + 8 * kTicketWords;
       p.arrive_stride = table ? g.per_xcd : kArrivals;
+      p.marked = table ? marked : nullptr;
     }
     if (p.nseg > 1 || p.piece_units > 0 || p.cut_rows > 0) {
       const ScratchLayout sl = scratch_layout(g, p.nseg);
@@ -178,7 +181,7 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     if (table) {
       p.scheduled = 1;
       if (a.table_calls == 0)
-        e = launch_schedule_rows(a.bits, (int)g.rows, g.Tk, g.W, g.per_xcd, slots, xcd_rows, stream);
+        e = launch_schedule_rows(a.bits, (int)g.rows, g.Tk, g.W, g.per_xcd, slots, xcd_rows, marked, stream);
       else if (draws)
         e = launch_clear_tickets(p.tickets, p.ticket_stride, stream);
       if (e != hipSuccess) return e;
@@ -493,7 +496,7 @@ int lite_attn_skipruns_export(lite_attn_mask_t* m, uint32_t* host_runs, uint32_t
   // (if the lists were already in place -- left by the last call's epilogue -- this writes the same values again)
   LA_HIP(la::launch_compact(m->d_bits, (int)g.rows, g.Tq, g.Tk, g.W, m->desc.flags & LITE_ATTN_ORDER_DIAGONAL_FIRST,
                             g.run_stride, runs, nruns, reinterpret_cast<uint32_t*>(m->d_lists + m->ll.live_cnt),
-                            reinterpret_cast<uint32_t*>(m->d_lists + m->ll.xcd_rows) + 8, stream));
+                            reinterpret_cast<uint32_t*>(m->d_lists + m->ll.heads_ranked), stream));
   LA_HIP(hipMemcpyAsync(host_runs, runs, sizeof(uint32_t) * (size_t)g.rows * g.run_stride, hipMemcpyDeviceToHost,
                         stream));
   LA_HIP(hipMemcpyAsync(host_nruns, nruns, sizeof(uint32_t) * (size_t)g.rows, hipMemcpyDeviceToHost, stream));

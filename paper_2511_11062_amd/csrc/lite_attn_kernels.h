@@ -42,6 +42,7 @@ constexpr int kMaxSegments = 16;
 // rows alone are long, 155 x 31 192 / 169 / 157 / 152, 126 x 63 329 / 275 / 251 / 242.
 constexpr int kMaxPieces = 4;
 constexpr size_t kMaxSegmentBytes = (size_t)104 << 20;
+constexpr int kTableCalls = 8;  // calls that a row schedule serves (keeps_table)
 
 // The chunk of rows that XCD `xcd` takes of the `group`-th eight chunks.  The assignment turns from group to group, in
 // three periods, so that heads that differ with a period of their own (the heads of a layer, batch entry after batch entry)
@@ -73,6 +74,8 @@ struct FwdParams {
   uint32_t* tickets;                     // [8] at ticket_stride: rows drawn so far from each XCD's list beyond the first
   int ticket_stride;                     //   `resident`; null: few rows, each workgroup has its place
   int table_calls = 0;                   // calls that the table has served before this one
+  uint32_t* marked = nullptr;            // cut_rows > 0, scheduled: [kTableCalls] whether the table's calls have marked a tile,
+                                         //   by call; a call looks at those before it
   int resident;                          // places per XCD that go by the grid: kResident, or, where rows are too short to be
                                          //   drawn, kNoDraws
   // build_next != 0: the epilogue rewrites runs / nruns / live_cnt for the NEXT call from the mask this call leaves;
@@ -146,7 +149,9 @@ struct ListLayout {
   size_t order;     // [BH][Tq] uint32 row ranking (none with few or short rows)
   size_t chunk_work;  // [chunks] uint32 work of each chunk (live tiles + a per-row constant)
   size_t slots;     // [8][per_xcd] uint32 schedule table
-  size_t xcd_rows;  // [8] uint32, and a counter of prepare_rows_kernel, zero between launches
+  size_t xcd_rows;  // [8] uint32
+  size_t heads_ranked;  // uint32, a counter of prepare_rows_kernel, zero between launches
+  size_t marked;    // [kTableCalls] uint32 (FwdParams::marked)
   size_t tickets;   // [8] tickets at kTicketWords, [8][kArrivals] arrival counters, of calls that make no table: behind the
                     //   table of layers that also make one, else where it would be
   size_t runs;      // [rows][run_stride] uint32 Skip-List
@@ -202,7 +207,6 @@ struct CallArgs {
 // 8 tiles 340 -> 308, three of 888 x 37 666 -> 660, four of 1200 x 40 979 -> 966, six of 600 x 200 3682 -> 3645, ten of
 // 3072 x 256 27523 -> 27342.
 bool keeps_table(const Geometry& g);  // layers that make one
-constexpr int kTableCalls = 8;
 
 hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListLayout& ll, char* lists, char* scratch,
                        const CallArgs& a, hipStream_t stream, hipEvent_t mid);
@@ -219,7 +223,7 @@ hipError_t launch_prepare_rows(const RowSchedule& sched, const uint16_t* v, uint
                                hipStream_t st);
 hipError_t launch_clear_tickets(uint32_t* tickets, int stride, hipStream_t st);
 hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int Tk, int W, int per_xcd, uint32_t* slots,
-                                uint32_t* xcd_rows, hipStream_t st);
+                                uint32_t* xcd_rows, uint32_t* marked, hipStream_t st);
 hipError_t launch_fwd(const FwdParams& p, bool immediate, hipStream_t st);
 
 }  // namespace la

@@ -355,7 +355,8 @@ constexpr int kSchedThreads = 1024;
 __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint64_t* __restrict__ bits, int rows,
                                                                        int Tk, int W, int per_xcd,
                                                                        uint32_t* __restrict__ slots,
-                                                                       uint32_t* __restrict__ xcd_rows) {
+                                                                       uint32_t* __restrict__ xcd_rows,
+                                                                       uint32_t* __restrict__ marked) {
   constexpr int kWaves = kSchedThreads / 64;
   // before each thread's piece of the rows: work of the long rows | work of the others << 24 | number of the others << 48
   __shared__ uint64_t part[kSchedThreads];
@@ -495,6 +496,7 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
   if (tid < kTableTail)
     slots[(size_t)xcd * per_xcd + per_xcd - 1 - tid] =
         tid == kTableTail - 1 && total == (uint32_t)rows * (uint32_t)(Tk + kRowOverhead) ? 1u : 0u;
+  if (xcd == 0 && tid < kTableCalls) marked[tid] = 0;
   __syncthreads();
   // positions inside the classes, in row order: kSchedThreads rows at a time
   for (int x0 = 0; x0 < n; x0 += kSchedThreads) {
@@ -1211,6 +1213,7 @@ __device__ __forceinline__ int sum_words(int n, int W) {
 // on entry (`skipped`; only of interest where something fired or live_next is set), the step's counter moves.
 __device__ __forceinline__ void finish_mask_row(ParamsRef p, int row, int lane, uint64_t skipped, uint64_t fired) {
   if (lane < p.W && (p.fresh || fired)) p.bits[(size_t)row * p.W + lane] = skipped | fired;
+  if (p.marked && fired) store_through(p.marked + p.table_calls, 1u);
   if (p.live_next) {
     const int n = sum_words(lane < p.W ? live_in_word(skipped | fired, lane, p.Tk) : 0, p.W);
     if (lane == 0) p.live_next[row] = (uint32_t)n;
@@ -1492,8 +1495,8 @@ __global__ __launch_bounds__(Geo<QB>::kThreads * (PAIR ? 2 : 1), 2 / QB) void li
     if (FEW && p.cut_rows > 0) {
       cut = !p.scheduled || p.slots[(size_t)(xcd + 1) * p.per_xcd - kTableTail] ? p.cut_rows : 0;
       // (a table made by an earlier call, for an empty mask: whether any call since has marked a tile)
-      for (int x = 1; cut > 0 && x <= p.table_calls; ++x)
-        if (p.stat_newly[-3 * x]) cut = 0;
+      for (int x = 0; cut > 0 && x < p.table_calls; ++x)
+        if (p.marked[x]) cut = 0;
     }
     if (slot < p.resident) row = row_at_place<FEW>(p, xcd, slot, cut);
     if (row < 0) {
@@ -2338,8 +2341,9 @@ hipError_t prepare_fwd() {
 }
 
 hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int Tk, int W, int per_xcd, uint32_t* slots,
-                                uint32_t* xcd_rows, hipStream_t st) {
-  hipLaunchKernelGGL(schedule_rows_kernel, dim3(8), dim3(kSchedThreads), 0, st, bits, rows, Tk, W, per_xcd, slots, xcd_rows);
+                                uint32_t* xcd_rows, uint32_t* marked, hipStream_t st) {
+  hipLaunchKernelGGL(schedule_rows_kernel, dim3(8), dim3(kSchedThreads), 0, st, bits, rows, Tk, W, per_xcd, slots, xcd_rows,
+                     marked);
   return hipGetLastError();
 }
 

@@ -136,9 +136,11 @@ hipError_t launch_prepare_rows(const RowSchedule& p, const uint16_t*, uint16_t* 
   return launch(st, [=] { return prepare_rows(p, vt, BH, Tk, tickets, ticket_stride); });
 }
 
-static hipError_t schedule_rows(const uint64_t* bits, int rows, int W, int per_xcd, uint32_t* slots, uint32_t* xcd_rows) {
+static hipError_t schedule_rows(const uint64_t* bits, int rows, int W, int per_xcd, uint32_t* slots, uint32_t* xcd_rows,
+                                uint32_t* marked) {
   if (!before(slots + 8 * (size_t)per_xcd, xcd_rows)) return hipErrorInvalidValue;
   deal(slots, per_xcd, xcd_rows, rows);
+  memset(marked, 0, sizeof(uint32_t) * kTableCalls);
   for (int x = 1; x <= 8; ++x) {  // flag, arrivals, ticket
     memset(slots + (size_t)x * per_xcd - kTableTail, 0, sizeof(uint32_t) * kTableTail);
     slots[(size_t)x * per_xcd - kTableTail] = all_zero(bits, (size_t)rows * W);
@@ -146,8 +148,8 @@ static hipError_t schedule_rows(const uint64_t* bits, int rows, int W, int per_x
   return hipSuccess;
 }
 hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int, int W, int per_xcd, uint32_t* slots,
-                                uint32_t* xcd_rows, hipStream_t st) {
-  return launch(st, [=] { return schedule_rows(bits, rows, W, per_xcd, slots, xcd_rows); });
+                                uint32_t* xcd_rows, uint32_t* marked, hipStream_t st) {
+  return launch(st, [=] { return schedule_rows(bits, rows, W, per_xcd, slots, xcd_rows, marked); });
 }
 
 namespace {
@@ -179,6 +181,11 @@ hipError_t fwd_without_lists(const FwdParams& p) {
       if (p.arrive[r] != 0 || (int)p.live_rows[r] > p.Tk) return hipErrorInvalidValue;
   }
   if (p.cut_rows > 0) {
+    if (p.scheduled) {  // rows are cut if, and only if, the mask is empty, which the table and its calls' marks tell
+      bool empty = p.slots[(size_t)p.per_xcd - kTableTail] != 0;
+      for (int x = 0; x < p.table_calls; ++x) empty = empty && !p.marked[x];
+      if (empty != all_zero(p.bits, rows * p.W)) return hipErrorInvalidValue;
+    }
     const size_t cut = 8 * (size_t)p.cut_rows;
     if (!partials(p, cut * p.cut_pieces, cut)) return hipErrorInvalidValue;
     for (int x = 0; x < 8; ++x)
@@ -226,6 +233,7 @@ static hipError_t fwd(const FwdParams& p) {
   }
   for (size_t r = 0; p.thr > -INFINITY && r < rows; ++r) {
     *p.stat_newly += !(p.bits[r * p.W] & 1);
+    if (p.marked && !(p.bits[r * p.W] & 1)) p.marked[p.table_calls] = 1;
     p.bits[r * p.W] |= 1;
   }
   *p.stat_skipped_in += 0;

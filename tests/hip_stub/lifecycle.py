@@ -108,6 +108,22 @@ def exercise(h, heads, n, steps):
     assert (cnt == tk).all() and (idx == np.arange(tk, dtype=np.uint16)).all()
 
 
+def imports(heads, n, flags):
+    """An empty mask imported where earlier calls have marked: later calls find it empty, whatever the counters say."""
+    h, d, none, mark = H(), desc(heads, n, steps=4, flags=flags), ctypes.c_float(-float("inf")), ctypes.c_float(-1.5)
+    assert lib.lite_attn_init_mask(ctypes.byref(d), ctypes.byref(h)) == 0
+    words = lib.lite_attn_mask_words(h)
+    buf = (ctypes.c_uint8 * (heads * n * 128 * 2 + 16))()
+    p = (ctypes.addressof(buf) + 15) & ~15
+    bits = np.zeros(words, dtype=np.uint64)
+    assert lib.lite_attn_fwd(p, p, p, p, h, mark, 0) == 0
+    for steps in (((mark, 1),), ((none, 1), (none, 2), (mark, 3)), ((none, 1), (mark, 2), (mark, 3))):
+        assert lib.lite_attn_mask_import(h, bits.ctypes.data, words, 1) == 0
+        for thr, t in steps:
+            assert lib.lite_attn_fwd(p, p, p, p, h, thr, t) == 0, (heads, n, flags, t)
+    lib.lite_attn_free_mask(h)
+
+
 def replays(heads, n, flags):
     """Recorded calls run later, between calls that the host knows nothing of when it records them: each has to find what it
     reads in place, a schedule that names every row above all (the attention launch checks it)."""
@@ -170,6 +186,7 @@ for heads, n, way in ((1, 1, "in order"), (2, 300, None), (3, 128 * 65 + 7, "in 
         assert lib.lite_attn_set_stream(h, None) == 0
         exercise(h, heads, n, 3)
         lib.lite_attn_free_mask(h)
+        imports(heads, n, flags)
         replays(heads, n, flags)
 
 ctx = H()

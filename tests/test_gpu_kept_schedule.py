@@ -70,6 +70,32 @@ def test_cut_rows_while_a_kept_schedule_says_that_the_mask_is_empty(heads, token
         assert np.array_equal(masks[t], ref_masks[t]) and torch.equal(outs[t], ref_outs[t]), t
 
 
+@pytest.mark.parametrize("heads,tokens", [(12, 128 * 110), (18, 128 * 29)])
+def test_cut_rows_where_an_empty_mask_was_imported(heads, tokens):
+    """Steps whose counters tell of marks that an import has taken back: the rows are cut as where no call has marked."""
+    from paper_2511_11062_amd import lite_attn as la
+    assert parity.path_of(1, heads, tokens).rows % 512 in range(1, 321)
+    q, k, v = layer(heads, tokens)
+    out = torch.full((2,) + tuple(q.shape[1:]), float("nan"), dtype=q.dtype, device="cuda")
+    masks = []
+    for x, steps in enumerate(([(-1.5, 0), (-1.5, 1), None, (-60.0, 1), (-1.5, 2)],
+                               [(-60.0, 0), (-60.0, 1), None, (-60.0, 1), (-1.5, 2)])):
+        h = la.lite_attn_init_mask(1, heads, tokens, max_steps=3)
+        try:
+            la.lite_attn_set_stream(h, torch.cuda.current_stream().cuda_stream)
+            for step in steps:
+                if step is None:
+                    la.lite_attn_mask_import(h, np.zeros(la.lite_attn_mask_words(h), dtype=np.uint64), 1)
+                else:
+                    la.lite_attn_fwd(q[:1].data_ptr(), k[:1].data_ptr(), v[:1].data_ptr(), out[x:].data_ptr(), h, *step)
+            torch.cuda.synchronize()
+            masks.append(la.lite_attn_mask_export(h))
+        finally:
+            la.lite_attn_free_mask(h)
+    assert masks[0].any() and np.array_equal(masks[0], masks[1])
+    assert torch.equal(out[0].view(torch.int16), out[1].view(torch.int16))
+
+
 @pytest.mark.parametrize("heads,tokens,flags", SHAPES[1:4])
 def test_kept_schedule_in_a_graph(heads, tokens, flags):
     """Four steps recorded at once, the last two on the second's schedule, replayed with eager work between the replays."""
