@@ -2235,6 +2235,8 @@ __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const Fwd
         for (int u = 0; u < kAhead; ++u) {
           j[u] = u > 0 ? j[u - 1] : 0;
           walk.next(j[u]);
+          // (unknown: seen as the tile before where the row has ended, its load became a copy that the others waited for)
+          asm volatile("" : "+s"(j[u]));
           m[u] = mloc[(size_t)j[u] * kTile];
         }
 #pragma unroll
