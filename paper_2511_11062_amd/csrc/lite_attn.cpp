@@ -70,7 +70,6 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
   uint32_t* slots = reinterpret_cast<uint32_t*>(lists + ll.slots);
   uint32_t* xcd_rows = reinterpret_cast<uint32_t*>(lists + ll.xcd_rows);
   uint32_t* heads_ranked = reinterpret_cast<uint32_t*>(lists + ll.heads_ranked);
-  uint32_t* marked = reinterpret_cast<uint32_t*>(lists + ll.marked);
   uint32_t* own_tickets = reinterpret_cast<uint32_t*>(lists + ll.tickets);
   uint16_t* vt = reinterpret_cast<uint16_t*>(scratch);
   const int diagonal_first = (d.flags & LITE_ATTN_ORDER_DIAGONAL_FIRST) ? 1 : 0;
@@ -157,9 +156,9 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     if (cut_rows(g) > 0) {
       p.cut_rows = cut_rows(g);
       p.cut_pieces = cut_pieces(g);
-      p.arrive = table ? slots + g.per_xcd - kTableTail + 1 : own_tickets + 8 * kTicketWords;
+      p.arrive = table ? slots + g.per_xcd - 1 - kArrivals : own_tickets + 8 * kTicketWords;
       p.arrive_stride = table ? g.per_xcd : kArrivals;
-      p.marked = table ? marked : nullptr;
+      p.marked = table ? slots + g.per_xcd - kTableTail + 1 : nullptr;
     }
     if (p.nseg > 1 || p.piece_units > 0 || p.cut_rows > 0) {
       const ScratchLayout sl = scratch_layout(g, p.nseg);
@@ -181,7 +180,7 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
     if (table) {
       p.scheduled = 1;
       if (a.table_calls == 0)
-        e = launch_schedule_rows(a.bits, (int)g.rows, g.Tk, g.W, g.per_xcd, slots, xcd_rows, marked, stream);
+        e = launch_schedule_rows(a.bits, (int)g.rows, g.Tk, g.W, g.per_xcd, slots, xcd_rows, stream);
       else if (draws)
         e = launch_clear_tickets(p.tickets, p.ticket_stride, stream);
       if (e != hipSuccess) return e;

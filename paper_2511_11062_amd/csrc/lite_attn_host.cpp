@@ -195,8 +195,7 @@ ListLayout list_layout(const Geometry& g) {
   at += up256(sizeof(uint32_t) * 8 * (size_t)g.per_xcd);
   l.xcd_rows = at;
   l.heads_ranked = at + sizeof(uint32_t) * 8;
-  l.marked = l.heads_ranked + sizeof(uint32_t);
-  at += up256(sizeof(uint32_t) * (9 + kTableCalls));
+  at += up256(sizeof(uint32_t) * 9);
   l.tickets = l.slots;
   if (g.nseg > 0 && keeps_table(g)) {
     l.tickets = at;

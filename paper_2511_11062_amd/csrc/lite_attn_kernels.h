@@ -33,7 +33,9 @@ constexpr int kNoDraws = 1 << 30;
 constexpr int kDrawTiles = 16;
 constexpr int kTicketWords = 32;  // distance of the counters of an unscheduled call, a cache line
 constexpr int kArrivals = 64;     // arrival counters per XCD, of rows cut alike (cut_rows)
-constexpr int kTableTail = 2 + kArrivals;  // end of an XCD's share of a short rows' table: a flag, those, the ticket
+constexpr int kTableCalls = 8;    // calls that a row schedule serves (keeps_table)
+// End of an XCD's share of a short rows' table: a flag, marks of the table's calls (XCD 0's are used), arrivals, the ticket.
+constexpr int kTableTail = 2 + kTableCalls + kArrivals;
 constexpr int kPairWorkgroups = 256;
 constexpr int kClearWords = 64;   // us, 3 rows x 1 tile, 64 for each thread 9.6 (a launch: 8.9), 4096 for each 174 (12.1)
 constexpr int kMaxSegments = 16;
@@ -42,7 +44,6 @@ constexpr int kMaxSegments = 16;
 // rows alone are long, 155 x 31 192 / 169 / 157 / 152, 126 x 63 329 / 275 / 251 / 242.
 constexpr int kMaxPieces = 4;
 constexpr size_t kMaxSegmentBytes = (size_t)104 << 20;
-constexpr int kTableCalls = 8;  // calls that a row schedule serves (keeps_table)
 
 // The chunk of rows that XCD `xcd` takes of the `group`-th eight chunks.  The assignment turns from group to group, in
 // three periods, so that heads that differ with a period of their own (the heads of a layer, batch entry after batch entry)
@@ -133,8 +134,7 @@ struct Geometry {
   int nseg;        // > 0: few or short rows, each cut into this many segments (one workgroup each; 1 beyond kFewRows rows);
                    // 0: Skip-Lists, row ranking and V^T
   int per_xcd;     // entries per XCD in the schedule table: row slots, with lists (ceil(chunks / 8) + 1) chunks, short rows
-                   // 1.5 shares and kArrivals counters, and the ticket counter; where there is no table, the workgroups
-                   // of an XCD
+                   // 1.5 shares and kTableTail words; where there is no table, the workgroups of an XCD
 };
 
 // More than kFewRows rows: rows of each eighth, by number, that are cut, and into how many pieces each.
@@ -151,7 +151,6 @@ struct ListLayout {
   size_t slots;     // [8][per_xcd] uint32 schedule table
   size_t xcd_rows;  // [8] uint32
   size_t heads_ranked;  // uint32, a counter of prepare_rows_kernel, zero between launches
-  size_t marked;    // [kTableCalls] uint32 (FwdParams::marked)
   size_t tickets;   // [8] tickets at kTicketWords, [8][kArrivals] arrival counters, of calls that make no table: behind the
                     //   table of layers that also make one, else where it would be
   size_t runs;      // [rows][run_stride] uint32 Skip-List
@@ -223,7 +222,7 @@ hipError_t launch_prepare_rows(const RowSchedule& sched, const uint16_t* v, uint
                                hipStream_t st);
 hipError_t launch_clear_tickets(uint32_t* tickets, int stride, hipStream_t st);
 hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int Tk, int W, int per_xcd, uint32_t* slots,
-                                uint32_t* xcd_rows, uint32_t* marked, hipStream_t st);
+                                uint32_t* xcd_rows, hipStream_t st);
 hipError_t launch_fwd(const FwdParams& p, bool immediate, hipStream_t st);
 
 }  // namespace la

@@ -355,8 +355,7 @@ constexpr int kSchedThreads = 1024;
 __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint64_t* __restrict__ bits, int rows,
                                                                        int Tk, int W, int per_xcd,
                                                                        uint32_t* __restrict__ slots,
-                                                                       uint32_t* __restrict__ xcd_rows,
-                                                                       uint32_t* __restrict__ marked) {
+                                                                       uint32_t* __restrict__ xcd_rows) {
   constexpr int kWaves = kSchedThreads / 64;
   // before each thread's piece of the rows: work of the long rows | work of the others << 24 | number of the others << 48
   __shared__ uint64_t part[kSchedThreads];
@@ -492,11 +491,10 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
     }
     xcd_rows[xcd] = run;
   }
-  // this XCD's ticket and arrival counters; before them, whether all rows are of full length, so that some are to be cut
+  // this XCD's ticket and arrival counters, the marks of the table's calls; before them, whether all rows are of full length, so that some are to be cut
   if (tid < kTableTail)
     slots[(size_t)xcd * per_xcd + per_xcd - 1 - tid] =
         tid == kTableTail - 1 && total == (uint32_t)rows * (uint32_t)(Tk + kRowOverhead) ? 1u : 0u;
-  if (xcd == 0 && tid < kTableCalls) marked[tid] = 0;
   __syncthreads();
   // positions inside the classes, in row order: kSchedThreads rows at a time
   for (int x0 = 0; x0 < n; x0 += kSchedThreads) {
@@ -2343,9 +2341,8 @@ hipError_t prepare_fwd() {
 }
 
 hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int Tk, int W, int per_xcd, uint32_t* slots,
-                                uint32_t* xcd_rows, uint32_t* marked, hipStream_t st) {
-  hipLaunchKernelGGL(schedule_rows_kernel, dim3(8), dim3(kSchedThreads), 0, st, bits, rows, Tk, W, per_xcd, slots, xcd_rows,
-                     marked);
+                                uint32_t* xcd_rows, hipStream_t st) {
+  hipLaunchKernelGGL(schedule_rows_kernel, dim3(8), dim3(kSchedThreads), 0, st, bits, rows, Tk, W, per_xcd, slots, xcd_rows);
   return hipGetLastError();
 }
 

@@ -136,20 +136,18 @@ hipError_t launch_prepare_rows(const RowSchedule& p, const uint16_t*, uint16_t* 
   return launch(st, [=] { return prepare_rows(p, vt, BH, Tk, tickets, ticket_stride); });
 }
 
-static hipError_t schedule_rows(const uint64_t* bits, int rows, int W, int per_xcd, uint32_t* slots, uint32_t* xcd_rows,
-                                uint32_t* marked) {
+static hipError_t schedule_rows(const uint64_t* bits, int rows, int W, int per_xcd, uint32_t* slots, uint32_t* xcd_rows) {
   if (!before(slots + 8 * (size_t)per_xcd, xcd_rows)) return hipErrorInvalidValue;
   deal(slots, per_xcd, xcd_rows, rows);
-  memset(marked, 0, sizeof(uint32_t) * kTableCalls);
-  for (int x = 1; x <= 8; ++x) {  // flag, arrivals, ticket
+  for (int x = 1; x <= 8; ++x) {  // flag, marks, arrivals, ticket
     memset(slots + (size_t)x * per_xcd - kTableTail, 0, sizeof(uint32_t) * kTableTail);
     slots[(size_t)x * per_xcd - kTableTail] = all_zero(bits, (size_t)rows * W);
   }
   return hipSuccess;
 }
 hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int, int W, int per_xcd, uint32_t* slots,
-                                uint32_t* xcd_rows, uint32_t* marked, hipStream_t st) {
-  return launch(st, [=] { return schedule_rows(bits, rows, W, per_xcd, slots, xcd_rows, marked); });
+                                uint32_t* xcd_rows, hipStream_t st) {
+  return launch(st, [=] { return schedule_rows(bits, rows, W, per_xcd, slots, xcd_rows); });
 }
 
 namespace {
