@@ -94,10 +94,10 @@ hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListL
                          heads_ranked, stream);
       if (e != hipSuccess) return e;
     }
-    const RowSchedule sched = {live_cnt, order, chunk_work, slots, xcd_rows, heads_ranked, g.Tq, g.Tk,
-                               a.table_calls == 0 ? g.BH : 0, g.chunks, g.per_xcd};
-    e = launch_prepare_rows(sched, static_cast<const uint16_t*>(a.v), vt, d.stride_b, d.stride_h, d.stride_n, g.BH, d.heads,
-                            d.seqlen, g.Tq, g.Tk, a.table_calls > 0 ? slots + g.per_xcd - 1 : nullptr, g.per_xcd, stream);
+    const RowSchedule sched = {live_cnt, order, chunk_work, slots, xcd_rows, heads_ranked, g.Tq, g.Tk, g.BH, g.chunks,
+                               g.per_xcd};
+    e = launch_prepare_rows(sched, static_cast<const uint16_t*>(a.v), vt, d.stride_b, d.stride_h, d.stride_n, d.heads,
+                            d.seqlen, stream);
     if (e != hipSuccess) return e;
   }
   FwdParams p;
@@ -392,8 +392,8 @@ int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_a
   // The row schedule serves up to kTableCalls calls of a trajectory, as long as no call has marked with a looser threshold
   // than the mask that it was made for has seen: what a threshold marks, it marks nearly all at once.
   if (step == 0) m->loosest = -INFINITY;
-  const bool keeps = la::keeps_table(m->geo) && (m->geo.nseg == 0 || !a.empty);
-  const bool ready_table = keeps && known && step != 0 && m->table_calls < la::kTableCalls && m->table_loosest == m->loosest;
+  const bool keeps = la::keeps_table(m->geo) && !a.empty;
+  const bool ready_table = keeps && known && m->table_calls < la::kTableCalls && m->table_loosest == m->loosest;
   a.table_calls = ready_table ? m->table_calls : 0;
   const int served = keeps ? a.table_calls + 1 : 0;
   m->table_calls = 0;

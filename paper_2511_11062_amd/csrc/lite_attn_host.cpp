@@ -178,7 +178,7 @@ Geometry geometry(const lite_attn_desc_t& d) {
 
 // A row schedule is an order of the rows, good for any mask; when later calls have marked some more tiles, the lengths it
 // was made for are a little off, and rows are drawn.
-bool keeps_table(const Geometry& g) { return g.nseg == 0 || (g.rows > kFewRows && g.rows <= kSchedRows); }
+bool keeps_table(const Geometry& g) { return g.nseg > 0 && g.rows > kFewRows && g.rows <= kSchedRows; }
 
 ListLayout list_layout(const Geometry& g) {
   ListLayout l;
@@ -197,7 +197,7 @@ ListLayout list_layout(const Geometry& g) {
   l.heads_ranked = at + sizeof(uint32_t) * 8;
   at += up256(sizeof(uint32_t) * 9);
   l.tickets = l.slots;
-  if (g.nseg > 0 && keeps_table(g)) {
+  if (keeps_table(g)) {
     l.tickets = at;
     at += up256(sizeof(uint32_t) * 8 * (kTicketWords + kArrivals));
   }

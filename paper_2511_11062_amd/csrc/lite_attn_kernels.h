@@ -171,7 +171,7 @@ struct ScratchLayout {
 };
 ScratchLayout scratch_layout(const Geometry& g, int nseg = 1);
 
-// The row schedule of rows with Skip-Lists, made beside V^T; BH 0: an earlier call's serves.
+// The row schedule of rows with Skip-Lists, made beside V^T.
 struct RowSchedule {
   const uint32_t* live_cnt;
   uint32_t *order, *chunk_work, *slots, *xcd_rows, *heads_ranked;
@@ -201,10 +201,13 @@ struct CallArgs {
   bool lists_ready, build_next;
   int table_calls;             // calls of the trajectory that the row schedule in place has served; 0: to be made
 };
-// A row schedule made once and used by several calls: an order of the rows is good for any mask.  us, made for every call ->
-// for up to eight (a launch of 10 us, or two of 17, less; where rows are drawn, one of 3 more): six steps of 640 rows of
-// 8 tiles 340 -> 308, three of 888 x 37 666 -> 660, four of 1200 x 40 979 -> 966, six of 600 x 200 3682 -> 3645, ten of
-// 3072 x 256 27523 -> 27342.
+// A row schedule of short rows made once and used by several calls: an order of the rows is good for any mask.  us, sixteen
+// steps, made by every call / for 4 calls / for 8 / for 16 / once: 888 rows x 37 tiles 3241 / 3168 / 3159 / 3149 / 3149, 640 x
+// 16 1223 / 1141 / 1130 / 1123 / 1123, 1320 x 110 6020 / 5979 / 5973 / 5967 / 5985, 2440 x 61 11671 / 11613 / 11602 / 11602 /
+// 11613, rows that go by place, 640 x 8 878 / 793 / 781 / 773 / 773, 742 x 14 1277 / 1197 / 1178 / 1167 / 1166; eight steps
+// whose inputs have nothing to do with each other, every call / 8, 888 x 37 1613 / 1576, 640 x 16 619 / 581, 1320 x 110 3120 /
+// 3065, 2440 x 61 5807 / 5808, 640 x 8 446 / 399, 742 x 14 641 / 597.  The table of rows with lists is made beside V^T and costs
+// nothing (600 x 200 and 3072 x 256 0.1 % apart): every call makes its own.
 bool keeps_table(const Geometry& g);  // layers that make one
 
 hipError_t launch_call(const lite_attn_desc_t& d, const Geometry& g, const ListLayout& ll, char* lists, char* scratch,
@@ -218,8 +221,7 @@ hipError_t launch_count_rows(const uint64_t* bits, int rows, int Tk, int W, uint
 hipError_t launch_compact(const uint64_t* bits, int rows, int Tq, int Tk, int W, int diagonal_first, int run_stride,
                           uint32_t* runs, uint32_t* nruns, uint32_t* live_cnt, uint32_t* heads_ranked, hipStream_t st);
 hipError_t launch_prepare_rows(const RowSchedule& sched, const uint16_t* v, uint16_t* vt, int64_t stride_b, int64_t stride_h,
-                               int64_t stride_n, int BH, int H, int N, int Tq, int Tk, uint32_t* tickets, int ticket_stride,
-                               hipStream_t st);
+                               int64_t stride_n, int H, int N, hipStream_t st);
 hipError_t launch_clear_tickets(uint32_t* tickets, int stride, hipStream_t st);
 hipError_t launch_schedule_rows(const uint64_t* bits, int rows, int Tk, int W, int per_xcd, uint32_t* slots,
                                 uint32_t* xcd_rows, hipStream_t st);

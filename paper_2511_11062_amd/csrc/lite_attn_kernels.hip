@@ -533,15 +533,13 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
 // transposing reads, once to regroup, because a wave that stores the transposed pieces as it reads them writes 64
 // separate 16-byte pieces.  Bound by memory: 55 -> 39 us for 12 heads x 32760 tokens (3.7 -> 5.1 TB/s; a large copy
 // reaches 4.9).
-// The first workgroups, one per head, make the row schedule (none where an earlier call's serves): a chain of latencies on a
-// few CUs, hidden behind the transposing ones.  As launches of their own its halves took 17 us and two gaps: a late step of
-// 12 heads x 256 tiles 2250 -> 2236 us, a dense one 5553 -> 5536.  `tickets`, if not null, are cleared on the way: those of
-// a table that serves another call.
+// The first workgroups, one per head, make the row schedule: a chain of latencies on a few CUs, hidden behind the
+// transposing ones.  As launches of their own its halves took 17 us and two gaps: a late step of 12 heads x 256 tiles 2250 ->
+// 2236 us, a dense one 5553 -> 5536.
 constexpr int kVtRow = 256 + 16;  // padded LDS row (bytes)
 __global__ __launch_bounds__(256) void prepare_rows_kernel(const RowSchedule sched, const uint16_t* __restrict__ v,
                                                             uint16_t* __restrict__ vt, int64_t stride_b, int64_t stride_h,
-                                                            int64_t stride_n, int H, int N, int Tk,
-                                                            uint32_t* __restrict__ tickets, int ticket_stride) {
+                                                            int64_t stride_n, int H, int N, int Tk) {
   extern __shared__ __attribute__((aligned(16))) char tile[];
   constexpr int kRow = kVtRow;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -558,7 +556,6 @@ __global__ __launch_bounds__(256) void prepare_rows_kernel(const RowSchedule sch
     return;
   }
   const int block = blockIdx.x - sched.BH;
-  if (tickets && block == 0 && tid < 8) tickets[(size_t)tid * ticket_stride] = 0;
   const int j = block % Tk, bh = block / Tk;
   const uint16_t* vb = v + (int64_t)(bh / H) * stride_b + (int64_t)(bh % H) * stride_h;
 #pragma unroll
@@ -2314,11 +2311,9 @@ static size_t prepare_lds_bytes(int Tq, int Tk) {
 }
 
 hipError_t launch_prepare_rows(const RowSchedule& sched, const uint16_t* v, uint16_t* vt, int64_t stride_b, int64_t stride_h,
-                               int64_t stride_n, int BH, int H, int N, int Tq, int Tk, uint32_t* tickets, int ticket_stride,
-                               hipStream_t st) {
-  hipLaunchKernelGGL(prepare_rows_kernel, dim3((unsigned)(sched.BH + BH * Tk)), dim3(256),
-                     sched.BH > 0 ? prepare_lds_bytes(Tq, Tk) : 128 * kVtRow, st, sched, v, vt, stride_b, stride_h, stride_n,
-                     H, N, Tk, tickets, ticket_stride);
+                               int64_t stride_n, int H, int N, hipStream_t st) {
+  hipLaunchKernelGGL(prepare_rows_kernel, dim3((unsigned)(sched.BH * (1 + sched.Tk))), dim3(256),
+                     prepare_lds_bytes(sched.Tq, sched.Tk), st, sched, v, vt, stride_b, stride_h, stride_n, H, N, sched.Tk);
   return hipGetLastError();
 }
 

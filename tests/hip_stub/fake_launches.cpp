@@ -119,21 +119,19 @@ hipError_t launch_clear_tickets(uint32_t* tickets, int stride, hipStream_t st) {
   return launch(st, [=] { return clear_tickets(tickets, stride); });
 }
 
-static hipError_t prepare_rows(const RowSchedule& p, uint16_t* vt, int BH, int Tk, uint32_t* tickets, int ticket_stride) {
-  if (p.BH > 0) {
-    if (*p.heads_ranked != 0) return hipErrorInvalidValue;  // zero between launches
-    for (int x = 0; x < p.BH * p.Tq; ++x) p.order[x] = p.live_cnt[x] ? (uint32_t)(x % p.Tq) : 0u;
-    for (int u = 0; u < p.chunks; ++u) p.chunk_work[u] = 1;
-    if (!before(p.slots + 8 * (size_t)p.per_xcd, p.xcd_rows)) return hipErrorInvalidValue;
-    deal(p.slots, p.per_xcd, p.xcd_rows, p.BH * p.Tq);
-    clear_tickets(p.slots + p.per_xcd - 1, p.per_xcd);
-  }
-  memset(vt, 0, sizeof(uint16_t) * (size_t)BH * 128 * ((size_t)Tk * 128));
-  return tickets ? clear_tickets(tickets, ticket_stride) : hipSuccess;
+static hipError_t prepare_rows(const RowSchedule& p, uint16_t* vt) {
+  if (*p.heads_ranked != 0) return hipErrorInvalidValue;  // zero between launches
+  for (int x = 0; x < p.BH * p.Tq; ++x) p.order[x] = p.live_cnt[x] ? (uint32_t)(x % p.Tq) : 0u;
+  for (int u = 0; u < p.chunks; ++u) p.chunk_work[u] = 1;
+  if (!before(p.slots + 8 * (size_t)p.per_xcd, p.xcd_rows)) return hipErrorInvalidValue;
+  deal(p.slots, p.per_xcd, p.xcd_rows, p.BH * p.Tq);
+  clear_tickets(p.slots + p.per_xcd - 1, p.per_xcd);
+  memset(vt, 0, sizeof(uint16_t) * (size_t)p.BH * 128 * ((size_t)p.Tk * 128));
+  return hipSuccess;
 }
-hipError_t launch_prepare_rows(const RowSchedule& p, const uint16_t*, uint16_t* vt, int64_t, int64_t, int64_t, int BH, int,
-                               int, int, int Tk, uint32_t* tickets, int ticket_stride, hipStream_t st) {
-  return launch(st, [=] { return prepare_rows(p, vt, BH, Tk, tickets, ticket_stride); });
+hipError_t launch_prepare_rows(const RowSchedule& p, const uint16_t*, uint16_t* vt, int64_t, int64_t, int64_t, int, int,
+                               hipStream_t st) {
+  return launch(st, [=] { return prepare_rows(p, vt); });
 }
 
 static hipError_t schedule_rows(const uint64_t* bits, int rows, int W, int per_xcd, uint32_t* slots, uint32_t* xcd_rows) {
