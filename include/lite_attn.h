@@ -130,8 +130,9 @@ int lite_attn_ctx_free(lite_attn_ctx_t* ctx);
                previous call's step + 1
    Asynchronous on the handle's stream; allocates nothing.  With profiling off (lite_attn_profile) the call only
    launches kernels -- no memset, memcpy or event nodes -- so a sequence of calls may be captured in a HIP graph; a
-   replay repeats the captured steps (same step numbers, thresholds and pointers); the statistics counters of a
-   replayed step keep adding up unless the replay includes step 0, which clears them. */
+   replay repeats the captured steps (same step numbers, thresholds and pointers) on the mask as it stands then,
+   whatever calls, replays and imports have come between, so calls may be recorded together or one by one; the
+   statistics counters of a replayed step keep adding up unless the replay includes step 0, which clears them. */
 int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_attn_mask_t* skip_mask,
                   float threshold, int step);
 

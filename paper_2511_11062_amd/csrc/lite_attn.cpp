@@ -35,7 +35,7 @@ struct lite_attn_mask {
   float table_loosest;  // what it was when the row schedule was made
   unsigned long long capture;  // the capture that the last call was recorded in; 0: it ran
   bool recorded;               // a call has been recorded: it may run again whenever its graph is replayed
-  bool lists_valid;   // the lists describe the mask as it stands (left by the previous call's epilogue)
+  bool lists_valid;   // the lists describe the mask as it stands (left by the previous call's epilogue, or an import)
   unsigned long long* d_stats;  // [max_steps][3]: skipped on entry, newly marked, Skip-List runs
   uint32_t* d_newly;            // few rows, behind them: [kFewRows] tiles that step 0 marked, per row (part of step
                                 //   0's newly marked)
@@ -229,6 +229,16 @@ hipError_t capture_on(hipStream_t stream, unsigned long long* capture) {
   return e;
 }
 
+// The Skip-Lists of the mask as it stands.  A handle of a layer that has them keeps them in line with its mask from the first,
+// as a recorded later call reads them whatever has happened since it was recorded.
+hipError_t make_lists(const lite_attn_mask* m, hipStream_t stream) {
+  const la::Geometry& g = m->geo;
+  const la::ListLayout& l = m->ll;
+  auto at = [&](size_t offset) { return reinterpret_cast<uint32_t*>(m->d_lists + offset); };
+  return la::launch_compact(m->d_bits, (int)g.rows, g.Tq, g.Tk, g.W, m->desc.flags & LITE_ATTN_ORDER_DIAGONAL_FIRST,
+                            g.run_stride, at(l.runs), at(l.nruns), at(l.live_cnt), at(l.heads_ranked), stream);
+}
+
 int grow(la_scratch* s, size_t bytes) {
   if (bytes <= s->bytes) return LITE_ATTN_OK;
   if (s->base) LA_HIP(hipFree(s->base));
@@ -287,6 +297,7 @@ int init_common(const lite_attn_desc_t* desc, lite_attn_ctx* ctx, lite_attn_mask
       m->d_newly = reinterpret_cast<uint32_t*>(m->d_stats + nstats);
       m->d_arrive = m->d_newly + la::kFewRows;
     }
+    if (e == hipSuccess && m->geo.nseg == 0) e = make_lists(m, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) rc = hip_fail(e);
   }
@@ -362,8 +373,8 @@ int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_a
   hipEvent_t* ev = (m->profile && m->events) ? m->events + 3 * (size_t)step : nullptr;
   if (m->timed) m->timed[step] = ev != nullptr;
   if (ev) LA_HIP(hipEventRecord(ev[0], stream));
-  // Lists left by the previous call's epilogue are used when they still describe the mask: not at step 0 (the mask
-  // was just cleared) and not after an import.  This call's epilogue then leaves the lists of the next call.
+  // Lists left by the previous call's epilogue, or an import, are used: not at step 0 (the mask was just cleared).  This call's
+  // epilogue then leaves the lists of the next call.
   const bool ready = m->lists_valid && step != 0;
   m->lists_valid = false;
   // A recorded call runs when its graph is replayed, of which the host hears nothing: what it knows of the device's state (an
@@ -478,11 +489,12 @@ int lite_attn_mask_import(lite_attn_mask_t* m, const uint64_t* host_bits, size_t
   LA_HIP(hipMemcpyAsync(m->d_bits, host_bits, words * sizeof(uint64_t), hipMemcpyHostToDevice, stream_of(m)));
   if (uint32_t* live = live_rows(m, next_step))
     LA_HIP(la::launch_count_rows(m->d_bits, (int)m->geo.rows, m->geo.Tk, m->geo.W, live, nullptr, stream_of(m)));
+  if (m->geo.nseg == 0) LA_HIP(make_lists(m, stream_of(m)));
   LA_HIP(hipStreamSynchronize(stream_of(m)));
   m->next_step = next_step;
   m->empty = false;
   m->table_calls = 0;
-  m->lists_valid = false;  // the next call rebuilds its Skip-Lists from the imported mask
+  m->lists_valid = m->geo.nseg == 0;
   return LITE_ATTN_OK;
 }
 
@@ -493,9 +505,7 @@ int lite_attn_skipruns_export(lite_attn_mask_t* m, uint32_t* host_runs, uint32_t
   uint32_t* nruns = reinterpret_cast<uint32_t*>(m->d_lists + m->ll.nruns);
   hipStream_t stream = stream_of(m);
   // (if the lists were already in place -- left by the last call's epilogue -- this writes the same values again)
-  LA_HIP(la::launch_compact(m->d_bits, (int)g.rows, g.Tq, g.Tk, g.W, m->desc.flags & LITE_ATTN_ORDER_DIAGONAL_FIRST,
-                            g.run_stride, runs, nruns, reinterpret_cast<uint32_t*>(m->d_lists + m->ll.live_cnt),
-                            reinterpret_cast<uint32_t*>(m->d_lists + m->ll.heads_ranked), stream));
+  LA_HIP(make_lists(m, stream));
   LA_HIP(hipMemcpyAsync(host_runs, runs, sizeof(uint32_t) * (size_t)g.rows * g.run_stride, hipMemcpyDeviceToHost,
                         stream));
   LA_HIP(hipMemcpyAsync(host_nruns, nruns, sizeof(uint32_t) * (size_t)g.rows, hipMemcpyDeviceToHost, stream));

@@ -50,6 +50,18 @@ bool every_row_once(const uint32_t* slots, int per_xcd, const uint32_t* xcd_rows
   return std::count(seen.begin(), seen.end(), 1) == rows;
 }
 
+// Lists: one run covering the row, [0, Tk), whatever the mask; the live tiles tell whether its first tile is marked.
+uint32_t live_tiles(const uint64_t* bits, int r, int Tk, int W) { return (uint32_t)Tk - (uint32_t)(bits[(size_t)r * W] & 1); }
+void lists_of(const uint64_t* bits, int rows, int Tk, int W, int run_stride, uint32_t* runs, uint32_t* nruns,
+              uint32_t* live_cnt) {
+  for (int r = 0; r < rows; ++r) {
+    memset(runs + (size_t)r * run_stride, 0, sizeof(uint32_t) * run_stride);
+    runs[(size_t)r * run_stride] = (uint32_t)Tk << 16;
+    nruns[r] = 1;
+    live_cnt[r] = live_tiles(bits, r, Tk, W);
+  }
+}
+
 bool all_zero(const uint64_t* bits, size_t words) { return std::count(bits, bits + words, 0) == (long)words; }
 
 }  // namespace
@@ -96,14 +108,7 @@ hipError_t launch_count_rows(const uint64_t* bits, int rows, int, int W, uint32_
 static hipError_t compact(const uint64_t* bits, int rows, int Tk, int W, int run_stride, uint32_t* runs, uint32_t* nruns,
                           uint32_t* live_cnt, uint32_t* heads_ranked) {
   *heads_ranked = 0;
-  volatile bool sink = all_zero(bits, (size_t)rows * W);  // reads the whole mask
-  (void)sink;
-  for (int r = 0; r < rows; ++r) {  // one run covering the row: [0, Tk)
-    memset(runs + (size_t)r * run_stride, 0, sizeof(uint32_t) * run_stride);
-    runs[(size_t)r * run_stride] = (uint32_t)Tk << 16;
-    nruns[r] = 1;
-    live_cnt[r] = (uint32_t)Tk;
-  }
+  lists_of(bits, rows, Tk, W, run_stride, runs, nruns, live_cnt);
   return hipSuccess;
 }
 hipError_t launch_compact(const uint64_t* bits, int rows, int, int Tk, int W, int, int run_stride, uint32_t* runs,
@@ -218,20 +223,16 @@ static hipError_t fwd(const FwdParams& p) {
     if (!every_row_once(p.slots, p.per_xcd, p.xcd_rows, p.rows_total)) return hipErrorInvalidValue;
     for (int x = 0; x < 8; ++x)
       if (p.tickets && p.tickets[x * p.ticket_stride]++ != 0) return hipErrorInvalidValue;
-    if (p.build_next) {  // the epilogue rewrites the lists in full
-      memset(p.runs, 0, sizeof(uint32_t) * rows * p.run_stride);
-      for (size_t r = 0; r < rows; ++r) {
-        p.runs[r * p.run_stride] = (uint32_t)p.Tk << 16;
-        p.nruns[r] = 1;
-        p.live_cnt[r] = (uint32_t)p.Tk;
-      }
-    }
+    for (size_t r = 0; r < rows; ++r)  // the lists are those of the mask
+      if (p.nruns[r] != 1 || p.live_cnt[r] != live_tiles(p.bits, (int)r, p.Tk, p.W)) return hipErrorInvalidValue;
   }
   for (size_t r = 0; p.thr > -INFINITY && r < rows; ++r) {
     *p.stat_newly += !(p.bits[r * p.W] & 1);
     if (p.marked && !(p.bits[r * p.W] & 1)) p.marked[p.table_calls] = 1;
     p.bits[r * p.W] |= 1;
   }
+  if (p.build_next && p.nseg == 0)  // the epilogue rewrites the lists in full
+    lists_of(p.bits, p.rows_total, p.Tk, p.W, p.run_stride, p.runs, p.nruns, p.live_cnt);
   *p.stat_skipped_in += 0;
   *p.stat_runs += (unsigned long long)rows;
   return hipSuccess;

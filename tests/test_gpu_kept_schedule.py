@@ -130,8 +130,8 @@ def test_kept_schedule_in_a_graph(heads, tokens, flags):
         la.lite_attn_free_mask(h)
 
 
-# (short rows of every kind, few rows in pieces and in segments)
-@pytest.mark.parametrize("heads,tokens,flags", SHAPES[:4] + [(18, 128 * 29, 3), (5, 128 * 31, 0), (2, 128 * 16, 2)])
+# (short rows of every kind, rows with lists, few rows in pieces and in segments)
+@pytest.mark.parametrize("heads,tokens,flags", SHAPES + [(18, 128 * 29, 3), (5, 128 * 31, 0), (2, 128 * 16, 2)])
 def test_later_call_recorded_alone(heads, tokens, flags):
     """Step 2 by itself in a graph, replayed between calls of which the host knew nothing when it was recorded: output and
     mask, bit for bit, are those of an eager call on a handle that has imported the mask."""
