@@ -53,14 +53,15 @@ size_t segment_bytes(const Geometry& g, int nseg) {
 // the other: 2050 cycles for a stage of 1024 matrix cycles), a pair 1.36 us and 2.7 us more per row for its merge in
 // LDS, two workgroups on a CU 2.7 us for a tile each, a further round of workgroups 5 us.  Cutting a row costs a second
 // launch, 64 KB of fp32 partials per segment written and read again, and the walk over the tiles' row maxima in the merge
-// pass (3 us, 0.8 us per four segments, 18 ns per segment, 30 ns per row and 0.15 us per tile of a segment fit calls of
-// 3..300 rows).  Minimum of a cost in units of 10 ns made of these measurements.  They were taken while the exponents'
-// reference trailed the maximum; since it follows it again a tile takes 1.88 us, in a pair 1.53, at the same ratio, and the
-// choices made with the new values are no better: over eighteen shapes between 3 x 3 and 450 x 15 the choice is the best of
-// all that were timed or within 7 % of it.  us per call, whole rows -> segments: 32 rows of 16 tiles 35.4 -> 19.6 (8
-// segments), 72 x 12 29.4 -> 24.4 (3), 128 x 128 236 -> 126 (4); -> pairs: 200 x 10 28.9 -> 27.0, 256 x 32 71.6 -> 65.4;
-// -> both: 64 x 64 122 -> 45.8 (4).  The immediate variant needs a tile's verdict before its PV product, which a segment
-// cannot know: never cut.
+// pass (3 us, 0.8 us per four segments, 18 ns per segment, 30 ns per row and 0.15 us per tile of a segment).  Minimum of a
+// cost in units of 10 ns made of these measurements.  They fit calls of 3..300 rows with an earlier, slower merge pass and
+// while the exponents' reference trailed the maximum (since it follows it again a tile takes 1.88 us, in a pair 1.53, at the
+// same ratio).  With both as they are, every number of segments, with and without pairs, of 27 shapes between 3 x 1 and
+// 300 x 60 timed on a dense step: the choice is the best of all or within 5 % of it, and within 7 % at 155 x 31 (54.0 in
+// pairs, 50.6 in 3 segments).  us per call, whole rows -> segments: 32 rows of 16 tiles 33.0 -> 18.1 (8 segments; 6 17.5),
+// 72 x 12 26.6 -> 22.1 (3), 100 x 100 180 -> 84.9 (5); -> pairs: 256 x 64 130 -> 121, 135 x 15 32.8 -> 30.3; -> both: 64 x 64
+// 117 -> 44.6 (4; 8 single groups 43.5), 128 x 128 228 -> 129 (2).  The immediate variant needs a tile's verdict before its PV
+// product, which a segment cannot know: never cut.
 void share_chip(Geometry& g, int flags) {
   const int most = (flags & LITE_ATTN_PV_SKIP_IMMEDIATE) ? 1 : std::min(kMaxSegments, g.Tk);
   int64_t best = -1;
@@ -137,8 +138,9 @@ void allow_pieces(Geometry& g, const lite_attn_desc_t& d) {
 // share_chip() finds, if that is for the same kind of workgroups; else as many as fill one round of pairs, or, with
 // more than half as many rows as that, three in two rounds.  us, step 0, share_chip()'s single groups -> pairs: 80 x 20
 // 27.9 -> 27.3, 100 x 25 39.4 -> 36.3, 105 x 35 46.4 -> 46.1, 128 x 64 80.4 -> 80.8, 99 x 99 96.3 -> 102.1, 130 x 65
-// 90.4 -> 101.8, 150 x 150 199.8 -> 211.3: what it costs that a mask's pieces are pairs, and that a call's result
-// depends on its inputs and its mask, not on how the caller came by them.
+// 90.4 -> 101.8, 150 x 150 199.8 -> 211.3 (with today's merge pass, 100 x 100 89.5 -> 97.2, 130 x 65 82.3 -> 92.7): what it
+// costs that a mask's pieces are pairs, and that a call's result depends on its inputs and its mask, not on how the caller
+// came by them.
 int equal_pieces(const Geometry& g) {
   if (g.rows > kFewRows) return 1;
   if (g.nseg == 1 || (g.pieces == kPairWorkgroups) == (g.pair != 0)) return g.nseg;
@@ -177,7 +179,7 @@ Geometry geometry(const lite_attn_desc_t& d) {
 }
 
 // A row schedule is an order of the rows, good for any mask; when later calls have marked some more tiles, the lengths it
-// was made for are a little off, and rows are drawn.
+// was made for are a little off.
 bool keeps_table(const Geometry& g) { return g.nseg > 0 && g.rows > kFewRows && g.rows <= kSchedRows; }
 
 ListLayout list_layout(const Geometry& g) {

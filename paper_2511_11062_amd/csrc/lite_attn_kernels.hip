@@ -116,7 +116,7 @@ __device__ __forceinline__ void touch_arguments(size_t bytes) {
   asm volatile("" ::"s"(x0), "s"(x1), "s"(x2), "s"(x3), "s"(x4), "s"(x5));
 }
 
-// Tickets of a table that serves another call (a launch of 3 us; the table 10).
+// Tickets of a table that serves another call (in a trace 5 us, most of it the launch; schedule_rows_kernel 9).
 __global__ void clear_tickets_kernel(uint32_t* tickets, int stride) {
   if (threadIdx.x < 8) tickets[(size_t)threadIdx.x * stride] = 0;
 }
@@ -491,7 +491,8 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_rows_kernel(const uint
     }
     xcd_rows[xcd] = run;
   }
-  // this XCD's ticket and arrival counters, the marks of the table's calls; before them, whether all rows are of full length, so that some are to be cut
+  // this XCD's ticket and arrival counters, the marks of the table's calls; before them, whether all rows are of full length,
+  // so that some are to be cut
   if (tid < kTableTail)
     slots[(size_t)xcd * per_xcd + per_xcd - 1 - tid] =
         tid == kTableTail - 1 && total == (uint32_t)rows * (uint32_t)(Tk + kRowOverhead) ? 1u : 0u;
@@ -972,9 +973,10 @@ __device__ __forceinline__ void stage(State<QB, IMM>& st, const Lane<QB>& ln, ch
     // ---- vector ALU: slice k of the online softmax of stage s (raw dot products; 1/sqrt(d) folded into c) ----
     {
       if (k < 4) {
-        // m_local: this lane's 32 scores in one chain, two more per instruction.  With four chains of eight, which take two
-        // more to join, and the predicate below in lane masks: 12 heads x 256 tiles 5639 -> 5573 us, 40 x 591, two steps,
-        // 162.0 -> 161.0 ms, 24 x 931 239.7 -> 238.9 (three rounds of both sides: 0.1-1.2 %, 0.4-0.6, 0.3-0.4)
+        // m_local: this lane's 32 scores in one chain, two more per instruction; four chains of eight take two instructions
+        // more to join (vector instructions besides the MFMAs, per MFMA, 40 heads x 591 tiles: 4.38 -> 4.31).  With that and
+        // the predicate below in lane masks 12 heads x 256 tiles 5639 -> 5573 us, 40 x 591, two steps, 162.0 -> 161.0 ms, 24 x
+        // 931 239.7 -> 238.9: every long layer a little faster, none by more than two runs of one side differ
         const int e0 = k == 0 ? 1 : 8 * k + 1, e1 = k == 3 ? 32 : 8 * k + 9;
         float v = k == 0 ? cur[qb][0][0] : pm[qb];
 #pragma unroll
@@ -2230,7 +2232,8 @@ __global__ __launch_bounds__(kMergeThreads) void merge_segments_kernel(const Fwd
         for (int u = 0; u < kAhead; ++u) {
           j[u] = u > 0 ? j[u - 1] : 0;
           walk.next(j[u]);
-          // (unknown: seen as the tile before where the row has ended, its load became a copy that the others waited for)
+          // (unknown: seen as the tile before where the row has ended, its load became a copy that the others waited for; a
+          // step that marks, 100 x 100 110 -> 99 us, 200 x 200 338 -> 316)
           asm volatile("" : "+s"(j[u]));
           m[u] = mloc[(size_t)j[u] * kTile];
         }

@@ -1,5 +1,6 @@
 """A row schedule that serves several calls of a trajectory: the tickets are at zero again behind every call, all rows are
-computed whatever the mask has become, and nothing of a result depends on the order of the rows."""
+computed whatever the mask has become, and nothing of a result depends on the order of the rows.  Recorded calls, of any path:
+what a replay gives depends on its inputs and on the mask as it stands then."""
 import numpy as np
 import pytest
 import torch
@@ -145,8 +146,8 @@ def test_later_call_recorded_alone(heads, tokens, flags):
     side = torch.cuda.Stream()
 
     def call(handle, o, threshold, step, s):
-        la.lite_attn_fwd(q[s:s + 1].data_ptr(), k[s:s + 1].data_ptr(), v[s:s + 1].data_ptr(), o[:1].data_ptr(), handle, threshold,
-                         step)
+        la.lite_attn_fwd(q[s:s + 1].data_ptr(), k[s:s + 1].data_ptr(), v[s:s + 1].data_ptr(), o[:1].data_ptr(), handle,
+                         threshold, step)
 
     def check(what, run, step, s):
         mask = la.lite_attn_mask_export(h)

@@ -73,4 +73,4 @@ def test_partial_results_fit_for_every_layer(lib, first, last, flags):
     assert m.with_lists <= lib.array()               # the allocation-free entry point takes every layer that a handle cuts
     assert m.equal <= 15                             # four bits of the word that the kernel keeps them in
     assert m.parts_end <= 0                          # nothing runs into what lies behind it
-    assert m.tiles < 1 << 15                         # the bit beside a row's live tiles that says that it has all of them
+    assert m.tiles < 1 << 15                         # tiles of a row in 16 bits of a Skip-List entry
