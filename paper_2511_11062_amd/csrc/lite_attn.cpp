@@ -218,15 +218,19 @@ uint32_t* live_rows(const lite_attn_mask* m, int step) {
   return m->d_arrive + (1 + (step & 1)) * la::kFewRows;
 }
 
-// The capture under way on a stream, 0 if there is none (the null stream cannot be captured).
-hipError_t capture_on(hipStream_t stream, unsigned long long* capture) {
+// The capture under way on a stream, 0 if there is none (the null stream cannot be captured, and may not be asked while
+// another stream is).  False if the runtime does not tell: no reason to refuse a call.
+bool capture_on(hipStream_t stream, unsigned long long* capture) {
   *capture = 0;
-  if (!stream) return hipSuccess;
+  if (!stream || stream == hipStreamLegacy) return true;
   hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
   unsigned long long id = 0;
-  const hipError_t e = hipStreamGetCaptureInfo(stream, &status, &id);
-  if (e == hipSuccess && status != hipStreamCaptureStatusNone) *capture = id + 1;
-  return e;
+  if (hipStreamGetCaptureInfo(stream, &status, &id) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (status != hipStreamCaptureStatusNone) *capture = id + 1;
+  return true;
 }
 
 // The Skip-Lists of the mask as it stands.  A handle of a layer that has them keeps them in line with its mask from the first,
@@ -381,10 +385,10 @@ int lite_attn_fwd(const void* q, const void* k, const void* v, void* out, lite_a
   // empty mask, a row schedule that fits) holds among the calls of one capture, and among eager ones while no call has been
   // recorded.  Elsewhere a call finds out for itself, with the same bits.
   unsigned long long capture;
-  LA_HIP(capture_on(stream, &capture));
-  const bool known = capture == m->capture && (capture != 0 || !m->recorded);
+  const bool told = capture_on(stream, &capture);
+  const bool known = told && capture == m->capture && (capture != 0 || !m->recorded);
   m->capture = capture;
-  m->recorded = m->recorded || capture != 0;
+  m->recorded = m->recorded || !told || capture != 0;
   la::CallArgs a;
   a.q = q; a.k = k; a.v = v; a.out = out;
   a.threshold = threshold;

@@ -32,8 +32,10 @@ inline hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 // be captured.
 enum hipStreamCaptureStatus { hipStreamCaptureStatusNone, hipStreamCaptureStatusActive };
 extern unsigned long long fake_capture;  // its number, 0 if none is under way
+#define hipStreamLegacy ((hipStream_t)1)
 inline hipError_t hipStreamGetCaptureInfo(hipStream_t st, hipStreamCaptureStatus* status, unsigned long long* id) {
-  *status = st && fake_capture ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  if (!st || st == hipStreamLegacy || st == (hipStream_t)192) return hipErrorInvalidValue;  // (192: one that does not tell)
+  *status = fake_capture ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
   *id = fake_capture;
   return hipSuccess;
 }
